@@ -64,9 +64,9 @@ __global__ __launch_bounds__(256) void k_prune_prep(PruneFusedArgs a, int64_t U)
     clear = true;
   }
   if (!clear) return;
-  if (lane == 0) a.arrived[u] = 0;
+  if (lane == 0) a.arrived[u * kCtrStep<int>] = 0;
   if (a.GS > 0) {
-    if (lane < kMaxGroups) a.arrived_g[(size_t)u * kMaxGroups + lane] = 0;
+    if (lane < kMaxGroups) a.arrived_g[((size_t)u * kMaxGroups + lane) * kCtrStep<int>] = 0;
     for (int i = lane; i < kMaxGroups * kD; i += kWave) a.gpartial[(size_t)u * kMaxGroups * kD + i] = 0.0;
   }
   a.idx_pub[(size_t)u * kWave + lane] = 0u;
@@ -93,7 +93,7 @@ __device__ __forceinline__ bool unit_index_list(const PruneFusedArgs &a, int64_t
     const int g = blk / a.GS;
     const int gsize = min(a.GS, a.NB - g * a.GS);
     double *gp = a.gpartial + (size_t)u * kMaxGroups * kD;
-    if (arrive(a.arrived_g + (size_t)u * kMaxGroups + g, gsize, s_flag)) {
+    if (arrive(a.arrived_g + ((size_t)u * kMaxGroups + g) * kCtrStep<int>, gsize, s_flag)) {
       const double gs = merge_partials(src + (size_t)g * a.GS * kD, gsize, s_part);
       if (tid < kD) pub_store_marked(gp + (size_t)g * kD + tid, gs);
     }
@@ -129,7 +129,7 @@ __device__ __forceinline__ bool unit_index_list(const PruneFusedArgs &a, int64_t
     return true;
   }
 
-  if (arrive(a.arrived + u, a.NB, s_flag)) {
+  if (arrive(a.arrived + u * kCtrStep<int>, a.NB, s_flag)) {
     const double kss = merge_partials(src, a.NB, s_part);   // s_part: its sums are published already
     score_and_select(a, u, qn_c, kss, s_sc, s_idx, true);
     if (tid < kWave) {
@@ -372,10 +372,10 @@ size_t prune_fused_ws_bytes(int64_t U, int NB) {
   size_t b = (size_t)U * NB * kD * sizeof(double);   // partial
   if (group_size(NB) > 0) {
     b += (size_t)U * kMaxGroups * kD * sizeof(double);   // gpartial
-    b += (size_t)U * kMaxGroups * sizeof(int);           // arrived_g
+    b += (size_t)U * kMaxGroups * kCtrBytes;             // arrived_g
   }
   b += (size_t)U * kD * sizeof(double);              // qn
-  b += (size_t)U * sizeof(int);                      // arrived
+  b += (size_t)U * kCtrBytes;                        // arrived
   b = (b + 15) & ~(size_t)15;
   b += (size_t)U * kWave * sizeof(uint32_t);         // idx_pub
   b += ((size_t)U * NB + 15) & ~(size_t)15;          // done
@@ -416,10 +416,10 @@ hipError_t launch_prune_fused(int dtype, const void *q_obs, const void *k, float
   a.gpartial = nullptr; a.arrived_g = nullptr;
   if (a.GS > 0) {
     a.gpartial = (double *)w; w += (size_t)U * kMaxGroups * kD * sizeof(double);
-    a.arrived_g = (int *)w;   w += (size_t)U * kMaxGroups * sizeof(int);
+    a.arrived_g = (int *)w;   w += (size_t)U * kMaxGroups * kCtrBytes;
   }
   a.qn = (double *)w;      w += (size_t)U * kD * sizeof(double);
-  a.arrived = (int *)w;    w += (size_t)U * sizeof(int);
+  a.arrived = (int *)w;    w += (size_t)U * kCtrBytes;
   w = (char *)(((uintptr_t)w + 15) & ~(uintptr_t)15);
   a.idx_pub = (uint32_t *)w; w += (size_t)U * kWave * sizeof(uint32_t);
   a.done = (unsigned char *)w;

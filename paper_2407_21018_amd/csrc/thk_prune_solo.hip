@@ -59,8 +59,8 @@ __device__ __forceinline__ void solo_prologue(const PruneFusedArgs &a, int64_t u
   for (int i = tid; i < a.NB; i += 256)
     __hip_atomic_store(a.undone + (size_t)u * a.NB + i, (unsigned char)0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   if (tid == 0) {
-    __hip_atomic_store(a.gaveup + u, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __hip_atomic_store(a.arrived + u, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(a.gaveup + u * kCtrStep<int>, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(a.arrived + u * kCtrStep<int>, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
   if (a.GS > 0)
     for (int i = tid; i < kMaxGroups * kD; i += 256) pub_store_f64(a.gpartial + (size_t)u * kMaxGroups * kD + i, 0.0);
@@ -72,9 +72,10 @@ __device__ __forceinline__ void solo_prologue(const PruneFusedArgs &a, int64_t u
   if (a.GS > 0) {
     const int n_grp = (a.NB + a.GS - 1) / a.GS;
     if (tid < n_grp)
-      __hip_atomic_store(a.tctr_g + (size_t)u * kMaxGroups + tid, a.nonce << 16, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      __hip_atomic_store(a.tctr_g + ((size_t)u * kMaxGroups + tid) * kCtrStep<unsigned long long>, a.nonce << 16,
+                         __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   } else if (tid == 0) {
-    __hip_atomic_store(a.tctr + u, a.nonce << 16, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(a.tctr + u * kCtrStep<unsigned long long>, a.nonce << 16, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
 }
 
@@ -188,14 +189,14 @@ __device__ __forceinline__ int solo_index_list(const PruneFusedArgs &a, int64_t 
     const int n_grp = (a.NB + a.GS - 1) / a.GS;
     double *gp = a.gpartial + (size_t)u * kMaxGroups * kD;
     bool finisher = false;
-    const bool group_last = arrive_tagged(a.tctr_g + (size_t)u * kMaxGroups + g, a.nonce, gsize, s_flag);
+    const bool group_last = arrive_tagged(a.tctr_g + ((size_t)u * kMaxGroups + g) * kCtrStep<unsigned long long>, a.nonce, gsize, s_flag);
     // from here on the prologue's work is visible: the query norms travel with whatever comes next
     const double qn_c = tid < kD ? pub_load_f64(a.qn + (size_t)u * kD + tid) : 0.0;
     if (group_last) {
       const double gs = merge_partials(src + (size_t)g * a.GS * kD, gsize, s_part);
       if (tid < kD) pub_store_marked(gp + (size_t)g * kD + tid, gs);
       block_stores_done();
-      finisher = arrive(a.arrived + u, n_grp, s_flag);
+      finisher = arrive(a.arrived + u * kCtrStep<int>, n_grp, s_flag);
     }
     double kss;
     if (!read_group_sums(a, u, s_part, s_flag, finisher ? kSurePolls : a.spin_limit, kss)) return kGaveUp;
@@ -203,7 +204,7 @@ __device__ __forceinline__ int solo_index_list(const PruneFusedArgs &a, int64_t 
     return finisher ? kFinisher : kHaveList;
   }
 
-  if (arrive_tagged(a.tctr + u, a.nonce, a.NB, s_flag)) {
+  if (arrive_tagged(a.tctr + u * kCtrStep<unsigned long long>, a.nonce, a.NB, s_flag)) {
     const double qn_c = tid < kD ? pub_load_f64(a.qn + (size_t)u * kD + tid) : 0.0;
     const double kss = merge_partials(src, a.NB, s_part);   // s_part: its sums are published already
     score_and_select(a, u, qn_c, kss, s_sc, s_idx, true);
@@ -229,7 +230,7 @@ __device__ __forceinline__ bool hand_over_rows(const PruneFusedArgs &a, int64_t 
   if (tid == 0)
     __hip_atomic_store(a.undone + item, (unsigned char)1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   block_stores_done();
-  if (tid == 0) *s_flag = atomicAdd(a.gaveup + u, 1) >= kFinisherDone;
+  if (tid == 0) *s_flag = atomicAdd(a.gaveup + u * kCtrStep<int>, 1) >= kFinisherDone;
   __syncthreads();
   const bool late = *s_flag != 0;
   __syncthreads();
@@ -253,7 +254,7 @@ __device__ __forceinline__ bool hand_over_rows(const PruneFusedArgs &a, int64_t 
 // itself.  (Drawing the ticket after the finisher's own rows instead, behind a wait for the
 // acknowledgement of everything it had published, measured the same on every shape.)
 __device__ __forceinline__ int close_unit(const PruneFusedArgs &a, int64_t u, int *s_flag) {
-  if (threadIdx.x == 0) *s_flag = atomicAdd(a.gaveup + u, kFinisherDone);
+  if (threadIdx.x == 0) *s_flag = atomicAdd(a.gaveup + u * kCtrStep<int>, kFinisherDone);
   __syncthreads();
   const int n = *s_flag;
   __syncthreads();
@@ -430,11 +431,10 @@ size_t prune_solo_ws_bytes(int64_t U, int NB) {
   size_t b = (size_t)U * NB * kD * sizeof(double);                                   // partial
   if (solo_group_size(NB) > 0) {
     b += (size_t)U * kMaxGroups * kD * sizeof(double);                               // gpartial
-    b += (size_t)U * kMaxGroups * sizeof(unsigned long long);                        // tctr_g
+    b += (size_t)U * kMaxGroups * kCtrBytes;                                         // tctr_g
   }
   b += (size_t)U * kD * sizeof(double);                                              // qn
-  b += (size_t)U * sizeof(unsigned long long);                                       // tctr
-  b += 2 * (size_t)U * sizeof(int);                                                  // arrived, gaveup
+  b += 3 * (size_t)U * kCtrBytes;                                                    // tctr, arrived, gaveup
   b = (b + 15) & ~(size_t)15;
   b += (size_t)U * kWave * sizeof(uint32_t);                                         // idx_pub
   b += ((size_t)U * NB + 15) & ~(size_t)15;                                          // undone
@@ -454,12 +454,12 @@ hipError_t launch_prune_solo(int dtype, const void *q_obs, const void *k, float 
   a.partial = (double *)w; w += (size_t)U * NB * kD * sizeof(double);
   if (a.GS > 0) {
     a.gpartial = (double *)w;            w += (size_t)U * kMaxGroups * kD * sizeof(double);
-    a.tctr_g = (unsigned long long *)w;  w += (size_t)U * kMaxGroups * sizeof(unsigned long long);
+    a.tctr_g = (unsigned long long *)w;  w += (size_t)U * kMaxGroups * kCtrBytes;
   }
   a.qn = (double *)w;                w += (size_t)U * kD * sizeof(double);
-  a.tctr = (unsigned long long *)w;  w += (size_t)U * sizeof(unsigned long long);
-  a.arrived = (int *)w;              w += (size_t)U * sizeof(int);
-  a.gaveup = (int *)w;               w += (size_t)U * sizeof(int);
+  a.tctr = (unsigned long long *)w;  w += (size_t)U * kCtrBytes;
+  a.arrived = (int *)w;              w += (size_t)U * kCtrBytes;
+  a.gaveup = (int *)w;               w += (size_t)U * kCtrBytes;
   w = (char *)(((uintptr_t)w + 15) & ~(uintptr_t)15);
   a.idx_pub = (uint32_t *)w;         w += (size_t)U * kWave * sizeof(uint32_t);
   a.undone = (unsigned char *)w;
