@@ -174,8 +174,8 @@ __global__ __launch_bounds__(256) void k_prune_fused(PruneFusedArgs a) {
   __shared__ int s_flag;
   const int tid = threadIdx.x;
   const int64_t item = blockIdx.x;
-  const int64_t u = item / a.NB;
-  const int blk = (int)(item % a.NB);
+  const int64_t u = (uint32_t)item / (uint32_t)a.NB;   // the grid has fewer than 2^31 blocks
+  const int blk = (int)((uint32_t)item % (uint32_t)a.NB);
   const int64_t s0 = (int64_t)blk * a.RB;
   const int64_t s1 = min(a.S, s0 + a.RB);
   const u32x4 *src = (const u32x4 *)((const char *)a.k + (size_t)u * a.S * kD * E::EB);
@@ -216,8 +216,8 @@ void k_prune_onepass(PruneFusedArgs a) {
   __shared__ int s_flag;
   const int tid = threadIdx.x, wave = tid / kWave, lane = tid % kWave;
   const int64_t item = blockIdx.x;
-  const int64_t u = item / a.NB;
-  const int blk = (int)(item % a.NB);
+  const int64_t u = (uint32_t)item / (uint32_t)a.NB;   // the grid has fewer than 2^31 blocks
+  const int blk = (int)((uint32_t)item % (uint32_t)a.NB);
   const int64_t s0 = (int64_t)blk * a.RB;   // a.RB == 128 * NTW
   const int64_t s1 = min(a.S, s0 + a.RB);
   const u32x4 *src = (const u32x4 *)((const char *)a.k + (size_t)u * a.S * kD * E::EB);

@@ -47,6 +47,7 @@ struct PruneFusedArgs {
   unsigned long long nonce;    // 48 bits, never 0, different for every call
   unsigned char *undone;       // [U * NB] raised by a block that gave up waiting: its rows are the finisher's
   int *gaveup;                 // [U] tickets: +1 per block that gave up, + kFinisherDone by the finisher
+  int32_t poll_ticks;          // 64-cycle ticks between two looks of a waiting block
   int32_t prologue_delay;      // test hook: 64-cycle ticks the prologue block sleeps before it starts
   int64_t U;                   // units of the call: blocks 0 .. U-1 are the prologue blocks, the row blocks follow
   int64_t S, RB;          // rows per unit, rows per block
@@ -94,6 +95,36 @@ __device__ __forceinline__ double merge_partials(const double *base, int n, doub
     for (int j = 0; j < 8; ++j) x[j] = pub_load_f64(p + (size_t)min(b + j, b1 - 1) * kD);
 #pragma unroll
     for (int j = 0; j < 8; ++j) sum += (b + j < b1) ? x[j] : 0.0;
+  }
+  if (half) xch[c] = sum;
+  __syncthreads();
+  if (!half) sum += xch[c];
+  return sum;
+}
+
+// The same sum (the same order, the same bits) with UN loads in flight and little code: the loads
+// go through a buffer resource that ends where the thread group's vectors end, so that those of
+// a short last batch return 0 instead of being clamped and masked one by one.  Every batch is a
+// trip to the coherence point, and code that a launch runs once is fetched as it runs (about 45 ns
+// per 64 bytes: clamping 24 loads cost more than the trips it saved).
+template <int UN>
+__device__ __forceinline__ double merge_partials_once(const double *base, int n, double *xch) {
+  const int tid = threadIdx.x;
+  const int c = tid & (kD - 1);
+  const int half = __builtin_amdgcn_readfirstlane(tid >> 7);   // whole waves
+  const int b_mid = (n + 1) / 2;
+  const int b0 = half ? b_mid : 0, m = (half ? n : b_mid) - b0;
+  constexpr int kRow = kD * (int)sizeof(double), kDeviceScope = 16;   // sc1, as pub_load_f64
+  const auto rsrc = __builtin_amdgcn_make_buffer_rsrc((void *)(base + (size_t)b0 * kD), (short)0, m * kRow, 0x00027000);
+  double sum = 0.0;
+  for (int b = 0; b < m; b += UN) {
+    double x[UN];
+    const int off = b * kRow + c * (int)sizeof(double);
+#pragma unroll
+    for (int j = 0; j < UN; ++j)
+      x[j] = __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(rsrc, off + j * kRow, 0, kDeviceScope));
+#pragma unroll
+    for (int j = 0; j < UN; ++j) sum += x[j];
   }
   if (half) xch[c] = sum;
   __syncthreads();

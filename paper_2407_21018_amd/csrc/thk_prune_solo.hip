@@ -8,16 +8,18 @@
 //
 //   * Blocks 0 .. U-1 of the grid are PROLOGUE blocks, one per unit, the U * NB row blocks of
 //     k_prune_onepass follow.  A prologue block has no rows; it clears its unit's hand-off state
-//     (index-list words, group vectors, give-up flags and tickets), computes the query norms,
-//     waits until all of that has been acknowledged, and only then initialises the unit's
-//     arrival counters.  (A unit's prologue block directly in front of its row blocks, the
+//     (index-list words, query-norm words, group vectors, give-up flags and tickets), waits until
+//     all of that has been acknowledged, initialises the unit's arrival counters, and only then
+//     computes the query norms, whose words carry a validity mark: they are wanted last, and with
+//     them in front of the counters (4.5 us into the launch) every row block of a short call
+//     waited for the prologue.  (A unit's prologue block directly in front of its row blocks, the
 //     first layout, put NB + 1 blocks per unit into a chip that holds a whole number of NB-block
 //     units: units straddled the rounds of resident blocks and long launches ran 6-12 % slower.)
 //   * The arrival counters are the first shared thing a row block touches, and they are TAGGED:
 //     the upper 48 bits hold the call's nonce.  A block whose atomic add returns a word with
 //     another tag has arrived before the prologue's initialisation (which will overwrite what
 //     it added): it waits for the tag and adds again.  A block that has arrived under the right
-//     tag is thereby ordered after everything the prologue published.  Nothing has to be clean
+//     tag is thereby ordered after everything the prologue cleared.  Nothing has to be clean
 //     when the kernel starts.  The block that completes a counter stores 0 into it, so that a
 //     replay of the same launch from a graph, which carries the same nonce, does not mistake
 //     the previous replay's count for its own.
@@ -62,11 +64,9 @@ __device__ __forceinline__ void solo_prologue(const PruneFusedArgs &a, int64_t u
     __hip_atomic_store(a.gaveup + u * kCtrStep<int>, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     __hip_atomic_store(a.arrived + u * kCtrStep<int>, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
+  if (tid < kD) pub_store_f64(a.qn + (size_t)u * kD + tid, 0.0);
   if (a.GS > 0)
     for (int i = tid; i < kMaxGroups * kD; i += 256) pub_store_f64(a.gpartial + (size_t)u * kMaxGroups * kD + i, 0.0);
-  block_query_norm<DT, 4>(a.q_obs, u, a.G, a.S_obs, qn_l, hn);
-  __syncthreads();
-  if (tid < kD) pub_store_f64(a.qn + (size_t)u * kD + tid, qn_l[tid]);
   block_stores_done();
   // everything above has landed: the counters may now be found initialised
   if (a.GS > 0) {
@@ -77,6 +77,25 @@ __device__ __forceinline__ void solo_prologue(const PruneFusedArgs &a, int64_t u
   } else if (tid == 0) {
     __hip_atomic_store(a.tctr + u * kCtrStep<unsigned long long>, a.nonce << 16, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
+  block_query_norm<DT, 4>(a.q_obs, u, a.G, a.S_obs, qn_l, hn);
+  __syncthreads();
+  // the norms carry their own validity mark: a row block may want them before they are there
+  if (tid < kD) pub_store_marked(a.qn + (size_t)u * kD + tid, qn_l[tid]);
+}
+
+// The unit's query norm of channel tid (threads < 128) from `w`, the word loaded earlier (behind a
+// counter whose tag was there, i.e. after the prologue had cleared the words).
+__device__ __forceinline__ double query_norm_of(const PruneFusedArgs &a, int64_t u, unsigned long long w) {
+  if (threadIdx.x >= kD) return 0.0;
+  const double *p = a.qn + (size_t)u * kD + threadIdx.x;
+  for (int n = 0; (w & 1ull) == 0 && n < kSurePolls; ++n) {
+    __builtin_amdgcn_s_sleep(2);
+    w = pub_load_bits(p);
+  }
+  return __longlong_as_double((long long)(w & ~1ull));
+}
+__device__ __forceinline__ unsigned long long query_norm_word(const PruneFusedArgs &a, int64_t u) {
+  return threadIdx.x < kD ? pub_load_bits(a.qn + (size_t)u * kD + threadIdx.x) : 0ull;
 }
 
 // One arrival on a tagged counter: true in every thread of the block that makes the count `full`.
@@ -112,7 +131,7 @@ __device__ __forceinline__ bool read_list_words(const PruneFusedArgs &a, int64_t
     const uint32_t *p = a.idx_pub + (size_t)u * kWave + tid;
     uint32_t w = __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     for (int n = 0; __any((w & kPubValid) == 0) && n < limit; ++n) {
-      __builtin_amdgcn_s_sleep(16);
+      for (int t = a.poll_ticks; t > 0; t -= 4) __builtin_amdgcn_s_sleep(4);
       if ((w & kPubValid) == 0) w = __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     const bool ok = __all((w & kPubValid) != 0);
@@ -148,7 +167,7 @@ __device__ __forceinline__ bool read_group_sums(const PruneFusedArgs &a, int64_t
 #pragma unroll
     for (int j = 0; j < HG; ++j) miss |= (w[j] & 1ull) == 0;
     if (!__any(miss) || n >= limit) { ok = !miss; break; }
-    __builtin_amdgcn_s_sleep(16);
+    for (int t = a.poll_ticks; t > 0; t -= 4) __builtin_amdgcn_s_sleep(4);
 #pragma unroll
     for (int j = 0; j < HG; ++j)
       if ((w[j] & 1ull) == 0) w[j] = pub_load_bits(gp + (size_t)min(j0 + j, n_grp - 1) * kD + c);
@@ -167,12 +186,14 @@ __device__ __forceinline__ bool read_group_sums(const PruneFusedArgs &a, int64_t
   return all_ok;
 }
 
-// A row block's way from its column sums (s_part) to the unit's index list (s_idx).
-// item: u * NB + the block's number among the unit's row blocks.
-__device__ __forceinline__ int solo_index_list(const PruneFusedArgs &a, int64_t u, int64_t item, double *s_part,
-                                               float *s_sc, int16_t *s_idx, int *s_flag) {
+// A row block's way from its column sums (`part`: of channel tid, threads < 128) to the unit's index
+// list (s_idx).  item: u * NB + the block's number among the unit's row blocks.
+// UN: partial sums of other blocks in flight per thread while they are merged.
+template <int UN>
+__device__ __forceinline__ int solo_index_list(const PruneFusedArgs &a, int64_t u, int64_t item, double part,
+                                               double *s_part, float *s_sc, int16_t *s_idx, int *s_flag) {
   const int tid = threadIdx.x;
-  if (tid < kD) pub_store_f64(a.partial + (size_t)item * kD + tid, s_part[tid]);
+  if (tid < kD) pub_store_f64(a.partial + (size_t)item * kD + tid, part);
   block_stores_done();
 
   const double *src = a.partial + (size_t)u * a.NB * kD;
@@ -191,23 +212,23 @@ __device__ __forceinline__ int solo_index_list(const PruneFusedArgs &a, int64_t 
     bool finisher = false;
     const bool group_last = arrive_tagged(a.tctr_g + ((size_t)u * kMaxGroups + g) * kCtrStep<unsigned long long>, a.nonce, gsize, s_flag);
     // from here on the prologue's work is visible: the query norms travel with whatever comes next
-    const double qn_c = tid < kD ? pub_load_f64(a.qn + (size_t)u * kD + tid) : 0.0;
+    const unsigned long long qn_w = query_norm_word(a, u);
     if (group_last) {
-      const double gs = merge_partials(src + (size_t)g * a.GS * kD, gsize, s_part);
+      const double gs = merge_partials_once<UN>(src + (size_t)g * a.GS * kD, gsize, s_part);
       if (tid < kD) pub_store_marked(gp + (size_t)g * kD + tid, gs);
       block_stores_done();
       finisher = arrive(a.arrived + u * kCtrStep<int>, n_grp, s_flag);
     }
     double kss;
     if (!read_group_sums(a, u, s_part, s_flag, finisher ? kSurePolls : a.spin_limit, kss)) return kGaveUp;
-    score_and_select(a, u, qn_c, kss, s_sc, s_idx, finisher);
+    score_and_select(a, u, query_norm_of(a, u, qn_w), kss, s_sc, s_idx, finisher);
     return finisher ? kFinisher : kHaveList;
   }
 
   if (arrive_tagged(a.tctr + u * kCtrStep<unsigned long long>, a.nonce, a.NB, s_flag)) {
-    const double qn_c = tid < kD ? pub_load_f64(a.qn + (size_t)u * kD + tid) : 0.0;
-    const double kss = merge_partials(src, a.NB, s_part);   // s_part: its sums are published already
-    score_and_select(a, u, qn_c, kss, s_sc, s_idx, true);
+    const unsigned long long qn_w = query_norm_word(a, u);
+    const double kss = merge_partials_once<UN>(src, a.NB, s_part);
+    score_and_select(a, u, query_norm_of(a, u, qn_w), kss, s_sc, s_idx, true);
     if (tid < kWave) {
       const uint32_t lo = 2 * tid < a.T ? (uint16_t)s_idx[2 * tid] : 0u;
       const uint32_t hi = 2 * tid + 1 < a.T ? (uint16_t)s_idx[2 * tid + 1] : 0u;
@@ -236,10 +257,10 @@ __device__ __forceinline__ bool hand_over_rows(const PruneFusedArgs &a, int64_t 
   __syncthreads();
   if (!late) return false;
   if (a.GS > 0) {
-    const double qn_c = tid < kD ? pub_load_f64(a.qn + (size_t)u * kD + tid) : 0.0;
+    const unsigned long long qn_w = query_norm_word(a, u);
     double kss;
     read_group_sums(a, u, s_part, s_flag, kSurePolls, kss);
-    score_and_select(a, u, qn_c, kss, s_sc, s_idx, false);
+    score_and_select(a, u, query_norm_of(a, u, qn_w), kss, s_sc, s_idx, false);
   } else {
     read_list_words(a, u, s_idx, s_flag, kSurePolls);
   }
@@ -280,11 +301,12 @@ __device__ __forceinline__ void serve_gaveup(const PruneFusedArgs &a, int64_t u,
 // from the column sums until the index list arrives: the first NTW - NLT tiles of a wave in
 // registers, the last NLT in the wave's LDS tiles -- exactly as k_prune_onepass does.
 template <int DT, int NTW, int NLT>
-__global__ __launch_bounds__(256, (NTW - NLT) * 16 * Elem<DT>::EB <= 32 ? 4 : (NTW - NLT) * 16 * Elem<DT>::EB <= 96 ? 3 : 2)
+__global__ __launch_bounds__(256, Elem<DT>::EB == 4 ? 2 : (NTW - NLT) * 16 * Elem<DT>::EB <= 32 ? 4 : 3)
 void k_prune_solo(PruneFusedArgs a) {
   using E = Elem<DT>;
   constexpr int VEC = E::VEC, CPR = kD / VEC, TR = kCompactTileRows, NLD = TR * CPR / kWave;
-  constexpr int NRT = NTW - NLT;             // tiles per wave held in registers
+  constexpr int NRT = NTW - NLT;             // tiles per wave held in registers ...
+  constexpr int kHeld = NRT * 16 * E::EB;    // ... and the registers they take
   extern __shared__ u32x4 smem[];
   int16_t *tab = (int16_t *)smem;            // 2 KiB
   u32x4 *tiles = smem + 128;                 // [4 waves][NLT] x [32][128] elements
@@ -294,47 +316,53 @@ void k_prune_solo(PruneFusedArgs a) {
   __shared__ int16_t s_idx[kD];
   __shared__ int s_flag;
   const int tid = threadIdx.x, lane = tid % kWave;
-  const int wave = tid / kWave;
-  if ((int64_t)blockIdx.x < a.U) {
+  // A launch of this kernel is over in ten to a hundred microseconds and runs most of its code
+  // once, so what it executes is kept SHORT: instructions come from memory at about 45 ns per
+  // 64 bytes.  The wave index is uniform (row counts and their branches are scalar), rows are
+  // numbered in 32 bits (a unit held on chip has fewer than 2^19), every load takes the same
+  // form -- a byte offset, clamped to the unit's last chunk, on the unit's base -- and only a
+  // ragged tile pays for its raggedness.  8 units x 5003 rows: first load issued after 0.6
+  // instead of 1.8 us.
+  const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+  if (blockIdx.x < (uint32_t)a.U) {
     solo_prologue<DT>(a, blockIdx.x, (double *)tiles);   // the tiles are free in a block without rows
     return;
   }
-  const int64_t item = (int64_t)blockIdx.x - a.U;
-  const int64_t u = item / a.NB;
-  const int blk = (int)(item % a.NB);
-  const int64_t s0 = (int64_t)blk * a.RB;   // a.RB == 128 * NTW
-  const int64_t s1 = min(a.S, s0 + a.RB);
-  const u32x4 *src = (const u32x4 *)((const char *)a.k + (size_t)u * a.S * kD * E::EB);
+  const uint32_t item = blockIdx.x - (uint32_t)a.U;
+  const uint32_t u = item / (uint32_t)a.NB;
+  const int blk = (int)(item - u * (uint32_t)a.NB);
+  const int S = (int)a.S;
+  const int s0 = blk * (128 * NTW);          // a.RB == 128 * NTW
+  const int s1 = min(S, s0 + 128 * NTW);
+  const char *src = (const char *)a.k + (size_t)u * S * (kD * E::EB);
   u32x4 *wtile = tiles + (size_t)wave * NLT * Tile<DT>::CHUNKS;   // this wave's NLT tiles
-  if (a.ld != a.T)
-#pragma unroll
-    for (int n = 0; n < NLT; ++n) tile_clear_padding<DT>(wtile + (size_t)n * Tile<DT>::CHUNKS, lane);
 
   // tile n of this wave = rows s0 + (4 n + wave) * 32 .. + 32, nr of them inside [s0, hi)
-  auto tile_row0 = [&](int n) { return s0 + (int64_t)(4 * n + wave) * TR; };
-  auto tile_rows = [&](int n, int64_t hi) { return (int)max((int64_t)0, min((int64_t)TR, hi - tile_row0(n))); };
+  auto tile_row0 = [&](int n) { return s0 + (4 * n + wave) * TR; };
+  auto tile_rows = [&](int n, int hi) { return max(0, min(TR, hi - tile_row0(n))); };
 
   // the graded start of the launch's first round (see k_prune_onepass)
-  if (item < a.stagger_blocks) {
-    int ticks = (int)(u % a.stagger_units) * a.stagger_ticks;
+  if (item < (uint32_t)a.stagger_blocks) {
+    int ticks = (int)(u % (uint32_t)a.stagger_units) * a.stagger_ticks;
     for (; ticks >= 127; ticks -= 127) __builtin_amdgcn_s_sleep(127);
     for (; ticks >= 16; ticks -= 16) __builtin_amdgcn_s_sleep(16);
   }
 
   // ---- load: every chunk of the block's rows is in flight at once ----------------------------
   u32x4 r[NTW][NLD];
+  {
+    const uint32_t last = (uint32_t)S * CPR - 1;
 #pragma unroll
-  for (int n = 0; n < NTW; ++n) {
-    const int nr = tile_rows(n, s1);
-    const u32x4 *tsrc = src + (size_t)tile_row0(n) * CPR;
-    const int cmax = nr * CPR - 1;
+    for (int n = 0; n < NTW; ++n)
 #pragma unroll
-    for (int j = 0; j < NLD; ++j) {
-      const u32x4 zero = {0u, 0u, 0u, 0u};
-      // chunks past a ragged tile's end repeat its last chunk (in bounds; excluded below)
-      r[n][j] = nr > 0 ? ld_stream(tsrc + min(j * kWave + lane, cmax)) : zero;
-    }
+      for (int j = 0; j < NLD; ++j) {
+        const uint32_t c = (uint32_t)tile_row0(n) * CPR + (uint32_t)(j * kWave + lane);
+        r[n][j] = ld_stream((const u32x4 *)(src + min(c, last) * 16u));
+      }
   }
+  if (a.ld != a.T)
+#pragma unroll
+    for (int n = 0; n < NLT; ++n) tile_clear_padding<DT>(wtile + (size_t)n * Tile<DT>::CHUNKS, lane);
 
   // ---- column sums of squares; the last NLT tiles then move to LDS -----------------------------
   double dacc[VEC];
@@ -344,6 +372,11 @@ void k_prune_solo(PruneFusedArgs a) {
   for (int nn = 0; nn < NTW; ++nn) {
     const int n = (nn + NRT) % NTW;          // LDS-bound tiles first: their registers free up early
     const int nr = tile_rows(n, s1);
+    if (__builtin_expect(nr < TR, 0)) {      // rows past the block's end count nothing
+#pragma unroll
+      for (int j = 0; j < NLD; ++j)
+        if (j * kWave + lane >= nr * CPR) r[n][j] = u32x4{0u, 0u, 0u, 0u};
+    }
     float facc[VEC];
 #pragma unroll
     for (int v = 0; v < VEC; ++v) facc[v] = 0.f;
@@ -351,9 +384,8 @@ void k_prune_solo(PruneFusedArgs a) {
     for (int j = 0; j < NLD; ++j) {
       float f[VEC];
       E::unpack(r[n][j], f);
-      const bool valid = (j * kWave + lane) / CPR < nr;
 #pragma unroll
-      for (int v = 0; v < VEC; ++v) facc[v] = valid ? fmaf(f[v], f[v], facc[v]) : facc[v];
+      for (int v = 0; v < VEC; ++v) facc[v] = fmaf(f[v], f[v], facc[v]);
       if (n >= NRT) wtile[(size_t)(n - NRT) * Tile<DT>::CHUNKS + Tile<DT>::slot(j * kWave + lane)] = r[n][j];
     }
 #pragma unroll
@@ -365,10 +397,9 @@ void k_prune_solo(PruneFusedArgs a) {
 #pragma unroll
     for (int v = 0; v < VEC; ++v) red[wave][lane * VEC + v] = dacc[v];
   __syncthreads();
-  if (tid < kD) s_part[tid] = ((red[0][tid] + red[1][tid]) + red[2][tid]) + red[3][tid];
-  __syncthreads();
+  const double part = tid < kD ? ((red[0][tid] + red[1][tid]) + red[2][tid]) + red[3][tid] : 0.0;
 
-  int st = solo_index_list(a, u, item, s_part, s_sc, s_idx, &s_flag);
+  int st = solo_index_list<kHeld == 0 ? 24 : kHeld <= 32 ? 16 : 8>(a, u, item, part, s_part, s_sc, s_idx, &s_flag);
   if (st == kGaveUp) {
     if (!hand_over_rows(a, u, item, s_part, s_sc, s_idx, &s_flag)) return;
     st = kHaveList;
@@ -376,24 +407,18 @@ void k_prune_solo(PruneFusedArgs a) {
   const int n_gaveup = st == kFinisher ? close_unit(a, u, &s_flag) : 0;
 
   // ---- compaction: the LDS tiles first, then the register tiles through slot 0 ---------------
-  // (row numbers are formed again from an opaque copy of the wave index: kept alive from the
-  // load phase they would cost registers that this kernel does not have)
-  int wave_c = wave;
-  asm volatile("" : "+v"(wave_c));
-  auto tile_row0_c = [&](int n) { return s0 + (int64_t)(4 * n + wave_c) * TR; };
-  auto tile_rows_c = [&](int n, int64_t hi) { return (int)max((int64_t)0, min((int64_t)TR, hi - tile_row0_c(n))); };
   const FlatOut<DT> dst((char *)a.kp + (size_t)u * a.kp_unit_rows * a.ld * E::EB);
   compact_build_tab<DT>(tab, s_idx, a.T, a.ld, dst.sh);
   __syncthreads();
-  const int64_t s1c = min(s1, a.S_keep);
+  const int s1c = min(s1, (int)a.S_keep);
 #pragma unroll
   for (int n = NRT; n < NTW; ++n) {
-    const int nr = tile_rows_c(n, s1c);
-    if (nr > 0) compact_emit_tile<DT>(wtile + (size_t)(n - NRT) * Tile<DT>::CHUNKS, dst, tile_row0_c(n), nr, a.ld, tab, lane);
+    const int nr = tile_rows(n, s1c);
+    if (nr > 0) compact_emit_tile<DT>(wtile + (size_t)(n - NRT) * Tile<DT>::CHUNKS, dst, tile_row0(n), nr, a.ld, tab, lane);
   }
 #pragma unroll
   for (int n = 0; n < NRT; ++n) {
-    const int nr = tile_rows_c(n, s1c);
+    const int nr = tile_rows(n, s1c);
     if (nr > 0) {   // wave-uniform
       __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
       __builtin_amdgcn_wave_barrier();       // the slot's previous tile has been read
@@ -402,12 +427,12 @@ void k_prune_solo(PruneFusedArgs a) {
       __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
       __builtin_amdgcn_wave_barrier();
       __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-      compact_emit_tile<DT>(wtile, dst, tile_row0_c(n), nr, a.ld, tab, lane);
+      compact_emit_tile<DT>(wtile, dst, tile_row0(n), nr, a.ld, tab, lane);
     }
   }
   if (n_gaveup > 0) {   // block-uniform
     __syncthreads();   // every wave is done with the tiles, which the re-read uses
-    serve_gaveup<DT>(a, u, src, dst, tab, tiles);
+    serve_gaveup<DT>(a, u, (const u32x4 *)src, dst, tab, tiles);
   }
 }
 
@@ -468,6 +493,10 @@ hipError_t launch_prune_solo(int dtype, const void *q_obs, const void *k, float 
   a.prologue_delay = (int32_t)(std::min(std::max(env_switches().prologue_delay_us, 0L), 500L) * 2400 / 64);
   a.S = S; a.S_keep = S_keep; a.kp_unit_rows = kp_unit_rows; a.RB = RB; a.T = T; a.ld = ld; a.G = G;
   a.S_obs = S_obs; a.NB = NB; a.spin_limit = spin_limit;
+  // Pause between two looks: 4 ticks while all blocks are resident at once (8 units x 5003 rows: a
+  // quarter of a microsecond less from list to first store), 16 in longer launches, whose polls
+  // would queue among the streams.
+  a.poll_ticks = U * NB <= (int64_t)kCUs * (dtype == THK_BF16 ? 3 : 2) ? 4 : 16;
   a.stagger_blocks = 0; a.stagger_units = 1; a.stagger_ticks = 0;
   a.U = U;
   {

@@ -393,6 +393,34 @@ def test_prune_two_level_arrival(block_rows, S, spin_limit, thk_env, prune_launc
     np.testing.assert_array_equal(as_numpy(kp), O.compact_keys(as_numpy(k).reshape(U, S, D), idx.cpu().numpy(), "bf16"))
 
 
+@pytest.mark.parametrize("dtype,block_rows,n_blocks,short", [
+    ("bf16", 128, 1, 127), ("bf16", 128, 2, 1), ("bf16", 128, 47, 96), ("bf16", 128, 48, 0), ("bf16", 128, 49, 33),
+    ("bf16", 128, 64, 127), ("bf16", 128, 65, 31), ("bf16", 256, 33, 255), ("bf16", 512, 17, 129), ("f32", 128, 49, 65),
+    ("f32", 256, 18, 1)])
+def test_prune_single_launch_block_counts(dtype, block_rows, n_blocks, short, thk_env):
+    """The single-launch prune at the edges of its batches and tiles: the column sums of a unit's
+    blocks are merged 8, 16 or 24 vectors per thread group and batch (one block; exactly two groups
+    of 24; one more; the last one-level and the first two-level count), and the last block lacks
+    `short` rows (none; whole 32-row tiles; all but one row)."""
+    thk_env.setenv("THK_PRUNE_LAUNCH", "solo")
+    thk_env.setenv("THK_PRUNE_BLOCK_ROWS", str(block_rows))
+    L, B, N_kv, G, S_obs, T = 1, 1, 3, 2, 8, 77
+    S = block_rows * n_blocks - short
+    U = L * B * N_kv
+    S_obs = min(S_obs, S)
+    q_obs = _randn((L, B, N_kv * G, S_obs, D), dtype, 301, 1.0)
+    k = _randn((L, B, N_kv, S, D), dtype, 302, 1.0)
+    shape = thk.make_shape(L, B, N_kv * G, N_kv, D, S, S_obs, T, 0, DT[dtype], 0)
+    assert thk.thk_prune_launches(shape) == 1
+    for _ in range(2):      # the second call finds the first one's workspace state
+        score, idx, kp = gpu_prune(shape, q_obs, k)
+        o_sc, o_idx, _ = oracle_prune(q_obs, k, dtype, T)
+        rel = np.abs(score.cpu().numpy().astype(np.float64) - o_sc.reshape(U, D)) / o_sc.reshape(U, D)
+        assert rel.max() <= SCORE_TOL
+        check_idx_with_tie_rule(idx.cpu().numpy(), o_idx, o_sc, T)
+        np.testing.assert_array_equal(as_numpy(kp), O.compact_keys(as_numpy(k).reshape(U, S, D), idx.cpu().numpy(), dtype))
+
+
 @pytest.mark.parametrize("path", ["fused", "fused-small-blocks", "fused-no-wait", "hold-128", "hold-256", "hold-512",
                                   "hold-256-no-wait", "reread-256", "staged", "staged-groups"])
 @pytest.mark.parametrize("dtype,G,S,T,sigma", PRUNE_CASES)
