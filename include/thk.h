@@ -140,8 +140,10 @@ int32_t thk_prune_is_fused(const thk_shape *shape);
 int32_t thk_prune_launches(const thk_shape *shape);
 
 /* 1 if thk_decode_attn (T_v == 0) or thk_decode_attn_kv (value rows of T_v kept channels,
- * ld_v elements apart) would run `shape` on the matrix-core kernel k_decode_mq, 0 if on the
- * general kernel k_decode (or the shape is invalid).  Host-only; honours THK_DECODE_MFMA. */
+ * ld_v elements apart) would run `shape` on the matrix-core kernel k_decode_mq with key rows
+ * whose pitch is a multiple of 4 elements; 0 if on the general kernel k_decode, on k_decode_mq's
+ * variants for rows of other pitches, or if the shape is invalid.  Host-only; honours
+ * THK_DECODE_MFMA. */
 int32_t thk_decode_on_matrix_cores(const thk_shape *shape, int32_t T_v, int32_t ld_v);
 
 /*
@@ -275,13 +277,12 @@ thk_status thk_prune(const thk_shape *shape, const void *q_obs, const void *k,
  * through per-piece flag words in ws that carry a nonce drawn per call; no
  * read-modify-write, nothing in ws has to be cleared beforehand).
  * THK_DECODE_MERGE = kernel | fused in the environment overrides the choice.
- * bf16 caches with N_q / N_kv >= 3 and a key row pitch (ld_keep, or T when rows are
- * dense) that is a multiple of 4 elements run the two products on the matrix cores,
- * here and in thk_decode_attn_kv: four or eight query heads share every key and
- * value byte a block reads (probabilities as two bf16 terms, exact to 2^-16;
- * accumulation in fp32; elements of a padded row past T are masked, whatever they
- * hold).  For T that is not a multiple of 4 (51, 89, ...) a pitch rounded up to one
- * therefore pays with several query heads per KV head. THK_DECODE_MFMA=0 in the environment
+ * bf16 caches with N_q / N_kv >= 3 run the two products on the matrix cores, here and in
+ * thk_decode_attn_kv: four or eight query heads share every key and value byte a block
+ * reads (probabilities as two bf16 terms, exact to 2^-16; accumulation in fp32; elements of
+ * a padded row past T are masked, whatever they hold).  A key row pitch (ld_keep, or T when
+ * rows are dense) that is a multiple of 4 elements is read as it lies; other pitches put each
+ * operand together from two or three words, a few percent slower. THK_DECODE_MFMA=0 in the environment
  * (for experiments and tests) keeps them on the general kernel.
  *   ws : THK_OP_DECODE bytes.
  */

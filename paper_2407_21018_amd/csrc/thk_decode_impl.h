@@ -170,7 +170,8 @@ struct VPruned {
 // slots that no row read touches.
 // kr receives KB chunks per lane (the tile's K bytes staged in registers);
 // returns the byte distance between the widened start and the first row.
-template <int DT, int KB>
+// UNI: kbeg is wave-uniform for the compiler too; the offsets then stay 32-bit on a scalar base.
+template <int DT, int KB, bool UNI = false>
 __device__ __forceinline__ int k_issue(u32x4 (&kr)[KB], const char *__restrict__ kg, size_t kbeg,
                                        int nrows, int W, int ld, int lane) {
   constexpr int EB = Elem<DT>::EB;
@@ -179,7 +180,10 @@ __device__ __forceinline__ int k_issue(u32x4 (&kr)[KB], const char *__restrict__
   const int last = (int)((kend - a0 + 15) >> 4) - 1;
   const char *p = kg + a0;
 #pragma unroll
-  for (int j = 0; j < KB; ++j) kr[j] = ld_stream((const u32x4 *)(p + (size_t)min(j * kWave + lane, last) * 16));
+  for (int j = 0; j < KB; ++j) {
+    if constexpr (UNI) kr[j] = ld_stream((const u32x4 *)(p + min((uint32_t)(j * kWave + lane), (uint32_t)last) * 16u));
+    else kr[j] = ld_stream((const u32x4 *)(p + (size_t)min(j * kWave + lane, last) * 16));
+  }
   return (int)(kbeg - a0);
 }
 
@@ -187,6 +191,67 @@ template <int KB>
 __device__ __forceinline__ void k_commit(const u32x4 (&kr)[KB], char *kbuf, int lane) {
 #pragma unroll
   for (int j = 0; j < KB; ++j) ((u32x4 *)kbuf)[j * kWave + lane] = kr[j];   // kbuf holds KB * 64 chunks
+}
+
+// The first KBT chunks of kr from a full-width tail tile of `nrows` rows at `src` (whole 16-byte chunks):
+// the tail's key bytes travel in the registers the pruned tiles no longer need.
+template <int DT, int KBT, int KB>
+__device__ __forceinline__ void tail_k_issue(u32x4 (&kr)[KB], const u32x4 *__restrict__ src, int nrows, int lane) {
+  static_assert(KBT <= KB, "a tail tile's key bytes must fit the staging registers of a pruned tile");
+  const int last = nrows * (kD / Elem<DT>::VEC) - 1;
+#pragma unroll
+  for (int j = 0; j < KBT; ++j) kr[j] = ld_stream(src + min(j * kWave + lane, last));
+}
+template <int KBT, int KB>
+__device__ __forceinline__ void tail_k_commit(const u32x4 (&kr)[KB], char *kbuf, int lane) {
+#pragma unroll
+  for (int j = 0; j < KBT; ++j) ((u32x4 *)kbuf)[j * kWave + lane] = kr[j];
+}
+
+// The block's query rows and the unit's list of kept channels on their way to LDS: ONE trip to
+// memory, 16 bytes of a row (threads 0 .. 127) or one list entry (threads 128 .. 255) per
+// thread, issued before anything else so that waiting for them waits for nothing behind them.
+// (Gathering q[idx[c]] from memory instead is two dependent trips, and four where the packed and
+// the plain copy were made by two loops: 3-4 us at the start of every launch.)
+template <int DT, int GT>
+struct QueryStage {
+  static constexpr int LPR = kD / Elem<DT>::VEC;             // 16-byte chunks per row
+  static_assert(GT * LPR <= 128, "one chunk per thread of the first two waves");
+  static constexpr int kBytes = GT * kD * Elem<DT>::EB + kD * 2;   // rows, then the list
+  u32x4 row;
+  int16_t ch;
+  __device__ __forceinline__ void issue(const void *q, size_t bn0, int heads, const int16_t *uidx, int T) {
+    const int tid = threadIdx.x;
+    row = u32x4{0u, 0u, 0u, 0u};   // head slots that are not in use carry a zero query
+    ch = 0;
+    if (tid < heads * LPR) row = ((const u32x4 *)q)[bn0 * LPR + tid];
+    else if (tid >= 128 && tid - 128 < T) ch = uidx[tid - 128];
+  }
+  __device__ __forceinline__ void commit(char *lds) const {
+    const int tid = threadIdx.x;
+    if (tid < GT * LPR) ((u32x4 *)lds)[tid] = row;
+    if (tid >= 128) ((int16_t *)(lds + GT * kD * Elem<DT>::EB))[tid - 128] = ch;
+  }
+  static __device__ __forceinline__ const int16_t *list(const char *lds) {
+    return (const int16_t *)(lds + GT * kD * Elem<DT>::EB);
+  }
+};
+// The staged bf16 query rows as packed pairs: full [GT][kQS / 2] and gathered kept channels
+// (zero beyond T), both zero beyond channel 128.
+template <int GT>
+__device__ __forceinline__ void query_pack(const char *stage, int T, uint32_t *qfp, uint32_t *qkp) {
+  const uint16_t *raw = (const uint16_t *)stage;
+  const int16_t *list = QueryStage<THK_BF16, GT>::list(stage);
+  const int w = threadIdx.x & 127;
+  if (w < kQS / 2) {
+    const int c = 2 * w;
+    const int i0 = c < T ? list[c] : -1, i1 = c + 1 < T ? list[c + 1] : -1;
+    for (int g = threadIdx.x >> 7; g < GT; g += 2) {
+      const uint16_t *rg = raw + g * kD;
+      qfp[g * (kQS / 2) + w] = c < kD ? *(const uint32_t *)(rg + c) : 0u;
+      qkp[g * (kQS / 2) + w] = (i0 >= 0 ? (uint32_t)rg[i0] : 0u) | ((i1 >= 0 ? (uint32_t)rg[i1] : 0u) << 16);
+    }
+  }
 }
 
 // Shape of the value loads of one TR-row tile: NV wave-wide loads per batch.

@@ -43,6 +43,8 @@
 // (8 units x 131072 rows) 68.0 -> 65.0 us; with no arithmetic at all the same loads take 123 us.
 #include <stdlib.h>
 
+#include <type_traits>
+
 #include "thk_decode_impl.h"
 
 namespace thk {
@@ -98,65 +100,75 @@ __device__ __forceinline__ void mq_v_commit(const u32x4 (&vr)[kMqVChunks], char 
   for (int j = 0; j < kMqVChunks; ++j) *(u32x4 *)(slab + (4 * j + rsub) * 256 + col * 16) = vr[j];
 }
 
-// Logits of a tile whose key bytes are in the slab, for NH groups of four heads.  nch =
-// ceil(W / 4) 4-channel chunks per row; qrow: this lane's head of the first group as packed bf16, zero from
-// chunk nch on (the same head of the next group follows 4 * kQS / 2 words later).  d[g] receives,
+// Logits of a tile whose key bytes are in the slab, for NH groups of four heads.  qrow: this lane's
+// head of the first group as packed bf16, zero from channel W on (the same head of the next group
+// follows 4 * kQS / 2 words later).  d[g] receives,
 // in both halves of the wave, the dot products of rows 4 ((lane / 4) % 8) + r, r = 0 .. 3, with
 // head 4 g + lane % 4: the key operand is read once for all groups.
-// W: elements per key row; the elements the last chunk holds past W (row padding, or whatever
-// follows the tile) are masked off, so their bytes never matter.
-template <int NH>
+// W: elements per key row.
+// AL: alignment of the rows' start in bytes.  8: a chunk is one read.  4 (T = 70, 78, ...): two words.
+// 2 (dense rows of an odd T: 51 is lambda = 0.6): three words from the boundary below, of which a
+// lane takes the upper or the lower halves -- its row starts on a word or in the middle of
+// one, the same for every chunk of the row.
+template <int AL>
+__device__ __forceinline__ uint2 key_chunk(const char *p, uint32_t shift_bytes) {
+  if constexpr (AL == 8) {
+    return *(const uint2 *)p;
+  } else {
+    const uint32_t *w = (const uint32_t *)p;
+    if constexpr (AL == 4) return uint2{w[0], w[1]};
+    const uint32_t a = w[0], b = w[1], c = w[2];
+    return uint2{__builtin_amdgcn_alignbyte(b, a, shift_bytes), __builtin_amdgcn_alignbyte(c, b, shift_bytes)};
+  }
+}
+template <int NH, int AL>
 __device__ __forceinline__ void mq_logits(const char *slab, int shift, int nrows, int W, int pitch_bytes,
                                           const uint32_t *qrow, int lane, f32x4 (&d)[NH]) {
-  const int nch = (W + 3) >> 2;
-  const uint32_t m0 = (W & 3) == 1 ? 0x0000ffffu : 0xffffffffu;
-  const uint32_t m1 = (W & 3) == 0 ? 0xffffffffu : (W & 3) == 3 ? 0x0000ffffu : 0u;
   const int b = lane >> 2, x = lane & 3, half = b >> 3, bb = b & 7;
-  const char *rowp = slab + shift + min(4 * bb + x, nrows - 1) * pitch_bytes;
-  const int nst = (nch + 1) >> 1;          // chunks per half = matrix instructions per group
-  int rel = bb % nst;
+  int row_off = shift + min(4 * bb + x, nrows - 1) * pitch_bytes;
+  const uint32_t sb = AL == 2 ? (uint32_t)row_off & 2u : 0u;
+  if constexpr (AL == 2) row_off &= ~3;
+  const char *rowp = slab + row_off;
+  const char *qb = (const char *)qrow;
+  const int n_full = W >> 2;               // whole chunks; lanes of half 0 take the first h0 of them
+  const int h0 = (n_full + 1) >> 1, common = n_full - h0;
   f32x4 d0[NH], d1[NH];
 #pragma unroll
   for (int g = 0; g < NH; ++g) {
     d0[g] = f32x4{0.f, 0.f, 0.f, 0.f};
     d1[g] = f32x4{0.f, 0.f, 0.f, 0.f};
   }
-  auto step = [&](f32x4 (&acc)[NH]) {
-    const int c = half * nst + rel;
-    // a chunk past the row's end: the row's first chunk against the zero chunk of the query
-    const bool valid = c < nch;
-    const int ck = valid ? c : 0;
-    uint2 kw = *(const uint2 *)(rowp + ck * 8);
-    const bool last = ck == nch - 1;
-    kw.x &= last ? m0 : 0xffffffffu;
-    kw.y &= last ? m1 : 0xffffffffu;
-    const s16x4 ka = __builtin_bit_cast(s16x4, kw);
-    const char *qp = (const char *)qrow + (valid ? c : nch) * 8;
-#pragma unroll
-    for (int g = 0; g < NH; ++g) acc[g] = mfma4(ka, *(const s16x4 *)(qp + g * 4 * (kQS / 2) * 4), acc[g]);
-    rel = rel + 1 == nst ? 0 : rel + 1;
-  };
-  if ((W & 7) == 0) {
-    // Rows of whole chunks, an even number of them: every step of both halves is a real chunk
-    // and nothing is masked.  off walks this lane's chunks as a byte offset, wrapping inside
-    // the half's range.
-    const int lo = half * nst * 8, hi = lo + nst * 8;
-    int off = lo + rel * 8;
-    const char *qb = (const char *)qrow;
+  {
+    // The chunks both halves have, without masks or range checks: off walks this lane's chunks as
+    // a byte offset, wrapping inside the half's range.
+    const int lo = half * h0 * 8, hi = lo + common * 8;
+    int off = lo + (common > 0 ? bb % common : 0) * 8;
     auto pstep = [&](f32x4 (&acc)[NH]) {
-      const s16x4 ka = *(const s16x4 *)(rowp + off);
+      const s16x4 ka = __builtin_bit_cast(s16x4, key_chunk<AL>(rowp + off, sb));
 #pragma unroll
       for (int g = 0; g < NH; ++g) acc[g] = mfma4(ka, *(const s16x4 *)(qb + off + g * 4 * (kQS / 2) * 4), acc[g]);
       off = off + 8 == hi ? lo : off + 8;
     };
     int ks = 0;
-    for (; ks + 4 <= nst; ks += 4) { pstep(d0); pstep(d1); pstep(d0); pstep(d1); }
-    for (; ks + 2 <= nst; ks += 2) { pstep(d0); pstep(d1); }
-    if (ks < nst) pstep(d0);
-  } else {
-    int ks = 0;
-    for (; ks + 2 <= nst; ks += 2) { step(d0); step(d1); }
-    if (ks < nst) step(d0);
+    for (; ks + 4 <= common; ks += 4) { pstep(d0); pstep(d1); pstep(d0); pstep(d1); }
+    for (; ks + 2 <= common; ks += 2) { pstep(d0); pstep(d1); }
+    if (ks < common) pstep(d0);
+  }
+  if (h0 > common || (W & 3) != 0) {
+    // What is left over, one step: half 0 takes its odd chunk, half 1 the row's last, partial chunk,
+    // whose elements past W (row padding, or whatever follows the tile) are masked; a half with
+    // nothing left takes zeros.
+    const bool any = half == 0 ? h0 > common : (W & 3) != 0;
+    const int c = half == 0 ? common : n_full;
+    uint2 kw = key_chunk<AL>(rowp + (any ? c * 8 : 0), sb);
+    // elements this lane's chunk has: 4, the partial chunk's W & 3, or none
+    const int ne = !any ? 0 : half == 0 ? 4 : W & 3;
+    kw.x &= ne >= 2 ? 0xffffffffu : ne == 1 ? 0x0000ffffu : 0u;
+    kw.y &= ne == 4 ? 0xffffffffu : ne == 3 ? 0x0000ffffu : 0u;
+    const s16x4 ka = __builtin_bit_cast(s16x4, kw);
+    const char *qp = qb + (any ? c * 8 : kD * 2);
+#pragma unroll
+    for (int g = 0; g < NH; ++g) d1[g] = mfma4(ka, *(const s16x4 *)(qp + g * 4 * (kQS / 2) * 4), d1[g]);
   }
 #pragma unroll
   for (int g = 0; g < NH; ++g)
@@ -264,35 +276,39 @@ __device__ __forceinline__ void mq_values_pruned(const char *slab, int shift, in
   const int x = lane & 3, grp = lane >> 4, j = lane & 15, r = j >> 2, seg = j & 3;
   const char *vb = slab + shift + (16 * grp + 4 * seg) * 2;
   const char *pa = pline + x * 8;
-  const int nks = (nrows + 3) >> 2;
-  const bool wide = T_v > 64;
-#pragma unroll
-  for (int ks = 0; ks < kMqRows / 4; ++ks) {
-    if (ks >= nks) break;
-    const char *vrow = vb + min(4 * ks + r, nrows - 1) * pitch_bytes;
+  auto rows4 = [&](const int ks, const char *vrow, auto wide) {
     const s16x4 b0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4 *)(vrow));
+    s16x4 b1 = b0;
+    if constexpr (wide)
+      b1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4 *)(vrow + 128));
     s16x4 a_hi[NH], a_lo[NH];
 #pragma unroll
     for (int g = 0; g < NH; ++g) {
       a_hi[g] = *(const s16x4 *)(pa + g * 512 + ks * 32);
       a_lo[g] = *(const s16x4 *)(pa + g * 512 + 256 + ks * 32);
+    }
+#pragma unroll
+    for (int g = 0; g < NH; ++g) {
       st[g].accp[0] = mfma4(a_hi[g], b0, st[g].accp[0]);
+      if constexpr (wide) st[g].accp[1] = mfma4(a_hi[g], b1, st[g].accp[1]);
     }
-    if (wide) {
-      const s16x4 b1 =
-          __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4 *)(vrow + 128));
 #pragma unroll
-      for (int g = 0; g < NH; ++g) st[g].accp[1] = mfma4(a_hi[g], b1, st[g].accp[1]);
-#pragma unroll
-      for (int g = 0; g < NH; ++g) {
-        st[g].accp[0] = mfma4(a_lo[g], b0, st[g].accp[0]);
-        st[g].accp[1] = mfma4(a_lo[g], b1, st[g].accp[1]);
-      }
-    } else {
-#pragma unroll
-      for (int g = 0; g < NH; ++g) st[g].accp[0] = mfma4(a_lo[g], b0, st[g].accp[0]);
+    for (int g = 0; g < NH; ++g) {
+      st[g].accp[0] = mfma4(a_lo[g], b0, st[g].accp[0]);
+      if constexpr (wide) st[g].accp[1] = mfma4(a_lo[g], b1, st[g].accp[1]);
     }
-  }
+  };
+  auto tile = [&](auto wide) {
+    if (nrows == kMqRows) {   // straight-line code, the reads of later rows overlap the products
+#pragma unroll
+      for (int ks = 0; ks < kMqRows / 4; ++ks) rows4(ks, vb + (4 * ks + r) * pitch_bytes, wide);
+      return;
+    }
+    const int nks = (nrows + 3) >> 2;
+    for (int ks = 0; ks < nks; ++ks) rows4(ks, vb + min(4 * ks + r, nrows - 1) * pitch_bytes, wide);
+  };
+  if (T_v > 64) tile(std::true_type{});
+  else tile(std::false_type{});
 }
 
 // KB: 16-byte key chunks a lane may have to stage for one tile.  slab_bytes: the wave's LDS slab,
@@ -300,7 +316,8 @@ __device__ __forceinline__ void mq_values_pruned(const char *slab, int shift, in
 // VP = 1: the value rows of the pruned segment are channel-pruned (a.v = V_pruned, a.ld_v, a.idx_v).
 // NH: groups of four query heads served by one block (1, or 2 when N_q / N_kv is a multiple of 8:
 // the key and value operands are then read from LDS once for eight heads).
-template <int KB, int WPE, int VP, int NH>
+// AL: alignment of the key rows in bytes (mq_logits).
+template <int KB, int WPE, int VP, int NH, int AL>
 __global__ __launch_bounds__(256, WPE) void k_decode_mq(DecodeArgs a, int groups, int slab_bytes) {
   constexpr int DT = THK_BF16, GT = 4 * NH, EB = 2, TR = kMqRows, LPR = 16;
   constexpr int KBT = kTailRows * kD * EB / 16 / kWave;   // chunks per lane of a tail tile
@@ -314,52 +331,53 @@ __global__ __launch_bounds__(256, WPE) void k_decode_mq(DecodeArgs a, int groups
   char *pline = slab + slab_bytes;               // 512 bytes of probabilities per head group
   __shared__ int s_last;
 
-  const int sp = (int)(blockIdx.x % a.n_split);
-  const int64_t ug = blockIdx.x / a.n_split;
-  const int gi = (int)(ug % groups);
-  const int64_t u = ug / groups;             // (layer, batch, KV head)
-  const int G = a.N_q / a.N_kv;
+  // (the grid has fewer than 2^31 blocks: 32-bit divisions)
+  const uint32_t ug = blockIdx.x / (uint32_t)a.n_split;
+  const int sp = (int)(blockIdx.x - ug * (uint32_t)a.n_split);
+  const int64_t u = groups == 1 ? ug : ug / (uint32_t)groups;   // (layer, batch, KV head)
+  const int gi = (int)(ug - (uint32_t)u * (uint32_t)groups);
+  const int G = (int)((uint32_t)a.N_q / (uint32_t)a.N_kv);
   const int64_t bn0 = u * G + (int64_t)gi * GT;
   const int hb = min(GT, G - gi * GT);   // head slots in use; the others carry a zero query
 
   const int64_t s0 = min(a.S, (int64_t)sp * a.rows_per_split);
   const int64_t s1 = min(a.S, s0 + a.rows_per_split);
   const int nt_p = (int)((s1 - s0 + TR - 1) / TR);
+  const int nr_last = (int)(s1 - s0 - (int64_t)(nt_p - 1) * TR);   // rows of the piece's last tile
   const int nt_t = (a.s_tail + kTailRows - 1) / kTailRows;   // tail tiles of the unit: tile j goes to split j % n_split
+  const int tt0 = sp + wave * a.n_split;                     // this wave's first tail tile
   const char *kpg = (const char *)a.kp;
+  auto tile_rows = [&](int ti) { return ti == nt_p - 1 ? nr_last : TR; };
+  auto tail_rows = [&](int ti) { return min(kTailRows, a.s_tail - ti * kTailRows); };
+  const u32x4 *ktail = (const u32x4 *)a.kt + (size_t)u * a.s_tail_cap * LPR;   // this unit's tail keys
+
+  QueryStage<DT, GT> qs;
+  qs.issue(a.q, (size_t)bn0, hb, a.idx + (size_t)u * a.T, a.T);
   const size_t krow0 = (size_t)u * a.unit_rows + s0;     // first K_pruned / V row of this block
   const u32x4 *vbase = (const u32x4 *)a.v + krow0 * LPR;
 
-  // the first tile's key and value bytes start moving before anything else happens
+  // the first tile's key and value bytes start moving before anything is waited for
   u32x4 kr[KB];
   u32x4 vr[kMqVChunks];
   u32x4 vrp[VP ? KB : 1];
   int shift_next = 0, vshift = 0;
   if (wave < nt_p) {
-    const int nr = (int)min((int64_t)TR, s1 - s0 - (int64_t)wave * TR);
-    shift_next = k_issue<DT, KB>(kr, kpg, (krow0 + (size_t)wave * TR) * a.ldk * EB, nr, a.T, a.ldk, lane);
+    const int nr = tile_rows(wave);
+    shift_next = k_issue<DT, KB, true>(kr, kpg, (krow0 + (size_t)wave * TR) * a.ldk * EB, nr, a.T, a.ldk, lane);
     if constexpr (VP)
-      vshift = k_issue<DT, KB>(vrp, (const char *)a.v, (krow0 + (size_t)wave * TR) * a.ld_v * EB, nr, a.T_v, a.ld_v,
+      vshift = k_issue<DT, KB, true>(vrp, (const char *)a.v, (krow0 + (size_t)wave * TR) * a.ld_v * EB, nr, a.T_v, a.ld_v,
                                lane);
     else
       mq_v_issue(vr, vbase + (size_t)wave * TR * LPR, nr, lane);
+  } else if (tt0 < nt_t) {
+    tail_k_issue<DT, KBT>(kr, ktail + (size_t)tt0 * kTailRows * LPR, tail_rows(tt0), lane);
   }
 
-  // query: gather the kept channels (Sec. 3.3: the query is pruned with the stored mask)
-  {
-    const int16_t *uidx = a.idx + (size_t)u * a.T;
-    const uint16_t *q16 = (const uint16_t *)a.q;
-    for (int o = tid; o < GT * (kQS / 2); o += 256) {
-      const int g = o / (kQS / 2), c = 2 * (o % (kQS / 2));
-      const size_t qb = (size_t)(bn0 + g) * kD;
-      const bool used = g < hb;
-      const uint32_t f0 = used && c < kD ? q16[qb + c] : 0u, f1 = used && c + 1 < kD ? q16[qb + c + 1] : 0u;
-      const uint32_t k0 = used && c < a.T ? q16[qb + uidx[c]] : 0u;
-      const uint32_t k1 = used && c + 1 < a.T ? q16[qb + uidx[c + 1]] : 0u;
-      qfp[o] = f0 | (f1 << 16);
-      qkp[o] = k0 | (k1 << 16);
-    }
-  }
+  // query: gather the kept channels (Sec. 3.3: the query is pruned with the stored mask), out of
+  // LDS (the slabs are idle until the barrier below)
+  qs.commit(wbase);
+  __syncthreads();
+  query_pack<GT>(wbase, a.T, qfp, qkp);
   __syncthreads();
 
   MqState st[NH];
@@ -379,16 +397,18 @@ __global__ __launch_bounds__(256, WPE) void k_decode_mq(DecodeArgs a, int groups
   // ---- pruned segment: the bytes of this wave's next tile are in flight while the current
   // one is computed
   for (int ti = wave; ti < nt_p; ti += 4) {
-    const int nrows = (int)min((int64_t)TR, s1 - s0 - (int64_t)ti * TR);
+    const int nrows = tile_rows(ti);
     const bool more = ti + 4 < nt_p;
-    const int nr4 = more ? (int)min((int64_t)TR, s1 - s0 - (int64_t)(ti + 4) * TR) : 0;
+    const int nr4 = more ? tile_rows(ti + 4) : 0;
     const int shift = shift_next;
     k_commit<KB>(kr, slab, lane);
     if (more)
-      shift_next = k_issue<DT, KB>(kr, kpg, (krow0 + (size_t)(ti + 4) * TR) * a.ldk * EB, nr4, a.T, a.ldk, lane);
+      shift_next = k_issue<DT, KB, true>(kr, kpg, (krow0 + (size_t)(ti + 4) * TR) * a.ldk * EB, nr4, a.T, a.ldk, lane);
+    else if (tt0 < nt_t)   // the wave's last pruned tile: its first tail tile's keys are next
+      tail_k_issue<DT, KBT>(kr, ktail + (size_t)tt0 * kTailRows * LPR, tail_rows(tt0), lane);
     wave_sync_lds();
     f32x4 d[NH];
-    mq_logits<NH>(slab, shift, nrows, a.T, pitch_bytes, qkp + x * (kQS / 2), lane, d);
+    mq_logits<NH, AL>(slab, shift, nrows, a.T, pitch_bytes, qkp + x * (kQS / 2), lane, d);
 #pragma unroll
     for (int g = 0; g < NH; ++g) mq_softmax<VP>(d[g], nrows, a.scale_log2, st[g], pline + 512 * g, lane);
     wave_sync_lds();   // the key bytes are consumed: the slab takes the value rows
@@ -396,7 +416,7 @@ __global__ __launch_bounds__(256, WPE) void k_decode_mq(DecodeArgs a, int groups
       const int vs = vshift;
       k_commit<KB>(vrp, slab, lane);
       if (more)
-        vshift = k_issue<DT, KB>(vrp, (const char *)a.v, (krow0 + (size_t)(ti + 4) * TR) * a.ld_v * EB, nr4, a.T_v,
+        vshift = k_issue<DT, KB, true>(vrp, (const char *)a.v, (krow0 + (size_t)(ti + 4) * TR) * a.ld_v * EB, nr4, a.T_v,
                                  a.ld_v, lane);
       wave_sync_lds();
       mq_values_pruned<NH>(slab, vs, a.ld_v * EB, a.T_v, pline, nrows, st, lane);
@@ -410,20 +430,19 @@ __global__ __launch_bounds__(256, WPE) void k_decode_mq(DecodeArgs a, int groups
   }
 
   // ---- unpruned tail segment (full-width keys, full query) ------------------
-  for (int ti = sp + wave * a.n_split; ti < nt_t; ti += 4 * a.n_split) {
+  for (int ti = tt0; ti < nt_t; ti += 4 * a.n_split) {
     const int j0 = ti * kTailRows;
-    const int nrows = min(kTailRows, a.s_tail - j0);
+    const int nrows = tail_rows(ti);
     const size_t row0 = (size_t)u * a.s_tail_cap + j0;
-    u32x4 kt[KBT];
-    k_issue<DT, KBT>(kt, (const char *)a.kt, row0 * kD * EB, nrows, kD, kD, lane);
+    if (ti != tt0) tail_k_issue<DT, KBT>(kr, ktail + (size_t)j0 * LPR, nrows, lane);
     // the tail's value rows: a buffer of their own, or the rows that follow row S in v
     const u32x4 *vg = a.unified_v ? (const u32x4 *)a.v + ((size_t)u * a.unit_rows + a.S + j0) * LPR
                                   : (const u32x4 *)a.vt + row0 * LPR;
     mq_v_issue(vr, vg, nrows, lane);
-    k_commit<KBT>(kt, slab, lane);
+    tail_k_commit<KBT>(kr, slab, lane);
     wave_sync_lds();
     f32x4 d[NH];
-    mq_logits<NH>(slab, 0, nrows, kD, kD * EB, qfp + x * (kQS / 2), lane, d);
+    mq_logits<NH, 8>(slab, 0, nrows, kD, kD * EB, qfp + x * (kQS / 2), lane, d);
 #pragma unroll
     for (int g = 0; g < NH; ++g) mq_softmax<VP>(d[g], nrows, a.scale_log2, st[g], pline + 512 * g, lane);
     wave_sync_lds();
@@ -475,7 +494,7 @@ __global__ __launch_bounds__(256, WPE) void k_decode_mq(DecodeArgs a, int groups
 // Four blocks per compute unit with the narrow staging class and four heads per block (37 KB of
 // LDS and at most 128 registers per lane each), two with the wide class and eight heads, three
 // otherwise.
-template <int KB, int VP, int NH>
+template <int KB, int VP, int NH, int AL>
 static hipError_t mq_launch(const DecodeArgs &a, int groups, hipStream_t st) {
   constexpr int WPE = (KB <= 5 && NH == 1) ? 4 : (KB > 5 && NH == 2) ? 2 : 3;
   const int slab = KB * kWave * 16 > kMqVBytes ? KB * kWave * 16 : kMqVBytes;
@@ -483,11 +502,11 @@ static hipError_t mq_launch(const DecodeArgs &a, int groups, hipStream_t st) {
   const dim3 grid((unsigned)(a.units * groups * a.n_split)), block(256);
   {
     static DynLds set;   // one per instantiation
-    const hipError_t e = ensure_dyn_lds((const void *)k_decode_mq<KB, WPE, VP, NH>, lds, set);
+    const hipError_t e = ensure_dyn_lds((const void *)k_decode_mq<KB, WPE, VP, NH, AL>, lds, set);
     if (e != hipSuccess) return e;
   }
   void *kargs[] = {(void *)&a, (void *)&groups, (void *)&slab};
-  const hipError_t e = launch_main_kernel((const void *)k_decode_mq<KB, WPE, VP, NH>, grid, block, kargs, lds, st);
+  const hipError_t e = launch_main_kernel((const void *)k_decode_mq<KB, WPE, VP, NH, AL>, grid, block, kargs, lds, st);
   return e != hipSuccess ? e : hipGetLastError();
 }
 
@@ -502,15 +521,17 @@ static int mq_chunks(const DecodeArgs &a) {
   return kb;
 }
 
-// True when the shape is one this kernel serves: bf16, at least three query heads per KV head
-// (one or two share a key row cheaply enough on the vector units), and rows (keys, and values
-// when they are channel-pruned) whose pitch is a multiple of four elements, so that every operand
-// is an aligned 8 bytes (T itself is free: dense rows qualify when T is a multiple of 4, other T
-// with a padded pitch).  THK_DECODE_MFMA=0 in the environment keeps such shapes on k_decode.
+// True when the shape is one this kernel serves: bf16 and at least three query heads per KV head
+// (one or two share a key row cheaply enough on the vector units).  Key rows of any pitch: where it
+// is not a multiple of four elements an operand is put together from two or three words
+// (AL = 4, 2), which leaves the general kernel (four heads per block, vector arithmetic) far behind:
+// T = 51 dense, G = 4, 64 units x 32768 rows 149.6 -> 126.8 us, G = 8 244.8 -> 127.1 us; G = 7, 216
+// units x 1700 rows 72.7 -> 34.9 us; T = 70, G = 4, 144 units x 6847 rows 90.7 -> 80.0 us.
+// THK_DECODE_MFMA=0 in the environment keeps all shapes on k_decode.
 bool decode_mq_serves(const DecodeArgs &a) {
   if (a.dtype != THK_BF16 || a.N_kv <= 0) return false;
   const int G = a.N_q / a.N_kv;
-  if (G < 3 || a.ldk % 4 != 0) return false;
+  if (G < 3) return false;
   if (a.T_v > 0 && a.ld_v % 4 != 0) return false;
   if (mq_chunks(a) > 9) return false;
   return !env_switches().decode_mfma_off;
@@ -522,22 +543,28 @@ int decode_mq_heads(const DecodeArgs &a) { return (a.N_q / a.N_kv) <= 4 ? 4 : 8;
 
 // Staging classes: 4 chunks per lane (a 32-row tile of at most 4 KB: T <= 64 with 16-byte rows),
 // 5 (T <= 79) and 9 (up to 128 kept channels).
-template <int VP, int NH>
+template <int VP, int NH, int AL>
 static hipError_t mq_launch_class(const DecodeArgs &a, int groups, hipStream_t st) {
   const int kb = mq_chunks(a);
-  if (kb <= 4) return mq_launch<4, VP, NH>(a, groups, st);
-  if (kb <= 5) return mq_launch<5, VP, NH>(a, groups, st);
-  return mq_launch<9, VP, NH>(a, groups, st);
+  if constexpr (AL == 8)   // rows of other pitches: one class for the narrow ones
+    if (kb <= 4) return mq_launch<4, VP, NH, AL>(a, groups, st);
+  if (kb <= 5) return mq_launch<5, VP, NH, AL>(a, groups, st);
+  return mq_launch<9, VP, NH, AL>(a, groups, st);
+}
+template <int VP, int NH>
+static hipError_t mq_launch_aligned(const DecodeArgs &a, int groups, hipStream_t st) {
+  if (a.ldk % 4 == 0) return mq_launch_class<VP, NH, 8>(a, groups, st);
+  return a.ldk % 2 == 0 ? mq_launch_class<VP, NH, 4>(a, groups, st) : mq_launch_class<VP, NH, 2>(a, groups, st);
 }
 
 hipError_t decode_mq_launch(const DecodeArgs &a, hipStream_t st) {
   const int G = a.N_q / a.N_kv;
   if (decode_mq_heads(a) == 8) {
     const int groups = (G + 7) / 8;
-    return a.T_v > 0 ? mq_launch_class<1, 2>(a, groups, st) : mq_launch_class<0, 2>(a, groups, st);
+    return a.T_v > 0 ? mq_launch_aligned<1, 2>(a, groups, st) : mq_launch_aligned<0, 2>(a, groups, st);
   }
   const int groups = (G + 3) / 4;
-  return a.T_v > 0 ? mq_launch_class<1, 1>(a, groups, st) : mq_launch_class<0, 1>(a, groups, st);
+  return a.T_v > 0 ? mq_launch_aligned<1, 1>(a, groups, st) : mq_launch_aligned<0, 1>(a, groups, st);
 }
 
 }  // namespace thk

@@ -225,6 +225,18 @@ def test_decode_ignores_whatever_sits_in_the_row_padding(G, T, ld):
     assert err.max() <= ATTN_TOL["bf16"]
 
 
+@pytest.mark.parametrize("G", [4, 7])
+@pytest.mark.parametrize("T,ld", [(1, 0), (2, 0), (3, 0), (4, 5), (5, 0), (7, 0), (8, 9), (9, 10), (50, 51), (51, 0), (62, 0),
+                                  (66, 0), (77, 0), (79, 0), (81, 0), (126, 0), (127, 0), (51, 127)])
+def test_decode_matrix_cores_any_row_pitch(T, ld, G):
+    """Key rows that are not a multiple of 4 elements apart: rows start on a word or in the middle of
+    one, a row has fewer chunks than halves (T < 8), an odd chunk, a partial chunk, both or
+    neither, and the rows of a ragged last tile and of the tail follow."""
+    err, out = _decode_case("bf16", 1, 3, G, 161, T, ld, 0, 19, 32, 1.0, 4000 + 7 * T + ld)
+    assert np.isfinite(out.float().cpu().numpy()).all()
+    assert err.max() <= ATTN_TOL["bf16"]
+
+
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 def test_decode_split_invariance_and_determinism(dtype, decode_merge):
     outs = {}
