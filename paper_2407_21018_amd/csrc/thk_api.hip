@@ -348,6 +348,20 @@ Split value_split(const thk_shape *s) {
     const int64_t cap = ceil_div(s->S, s->dtype == THK_F32 ? 128 : 512);
     if (n > cap) n = (int)cap;
     if (n < 1) n = 1;
+    if (s->dtype == THK_BF16 && QT == 4) {
+      // The 8-wave kernel for grouped heads, one block per compute unit: the pieces that give the
+      // shortest sum of rounds x (rows of a piece + 256 for its start, end and share of the merge).
+      // 64 units x 32768 rows: 4 pieces instead of 8, 278 -> 268 us; 96 units: 5 instead of 3
+      // (288 blocks would be a round of 256 and one of 32).
+      const int64_t tiles = value_wide_tiles(G, s->S_obs);
+      const int64_t b1 = units_of(s) * ceil_div(nqt, tiles);
+      int64_t best = INT64_MAX;
+      for (int64_t c = 1; c <= std::min<int64_t>(cap, std::max<int64_t>(ceil_div((int64_t)kCUs * 2, b1), 1)); ++c) {
+        const int64_t piece = ceil_div(ceil_div(s->S, c), 128) * 128;
+        const int64_t cost = ceil_div(b1 * c, kCUs) * (piece + 256);
+        if (cost < best) { best = cost; n = (int)c; }
+      }
+    }
   }
   if (n > 256) n = 256;
   int64_t rows = ceil_div(s->S, n);
@@ -664,8 +678,10 @@ thk_status thk_prune(const thk_shape *s, const void *q_obs, const void *k, float
   return THK_OK;
 }
 
-thk_status thk_score_value(const thk_shape *s, const void *q_obs, const void *k, const void *v,
-                           int32_t causal, float *score_v, void *ws, size_t ws_bytes, void *stream) {
+// thk_score_value; with idx the selection too (the kernel that finishes a unit's score selects)
+static thk_status score_value_common(const thk_shape *s, const void *q_obs, const void *k, const void *v,
+                                     int32_t causal, float *score_v, int16_t *idx, void *ws, size_t ws_bytes,
+                                     void *stream) {
   thk_status st = check_shape(s, true);
   if (st != THK_OK) return st;
   if (q_obs == nullptr || k == nullptr || v == nullptr || score_v == nullptr) return THK_ERR_NULL;
@@ -680,10 +696,15 @@ thk_status thk_score_value(const thk_shape *s, const void *q_obs, const void *k,
   if (grid > kMaxGrid) return THK_ERR_SHAPE;
   if (ws == nullptr || !aligned16(ws) || ws_bytes < thk_workspace_bytes(s, THK_OP_SCORE_VALUE))
     return THK_ERR_WORKSPACE;
-  if (failed(launch_value_score(s->dtype, q_obs, k, v, (float *)ws, score_v, units_of(s), s->S, G, s->S_obs, causal,
-                         sp.n, sp.rows, (hipStream_t)stream)))
+  if (failed(launch_value_score(s->dtype, q_obs, k, v, (float *)ws, score_v, idx, s->T, units_of(s), s->S, G, s->S_obs,
+                         causal, sp.n, sp.rows, (hipStream_t)stream)))
     return THK_ERR_HIP;
   return THK_OK;
+}
+
+thk_status thk_score_value(const thk_shape *s, const void *q_obs, const void *k, const void *v,
+                           int32_t causal, float *score_v, void *ws, size_t ws_bytes, void *stream) {
+  return score_value_common(s, q_obs, k, v, causal, score_v, nullptr, ws, ws_bytes, stream);
 }
 
 thk_status thk_prune_value(const thk_shape *s, const void *q_obs, const void *k, const void *v,
@@ -698,9 +719,7 @@ thk_status thk_prune_value(const thk_shape *s, const void *q_obs, const void *k,
   if (ws == nullptr || !aligned16(ws) || ws_bytes < need) return THK_ERR_WORKSPACE;
   // the score array sits behind the value score's own scratch unless the caller wants it
   float *sc = score_v != nullptr ? score_v : (float *)((char *)ws + need - (size_t)units_of(s) * kD * sizeof(float));
-  st = thk_score_value(s, q_obs, k, v, causal, sc, ws, thk_workspace_bytes(s, THK_OP_SCORE_VALUE), stream);
-  if (st != THK_OK) return st;
-  st = thk_select_topk(s, sc, idx_v, stream);
+  st = score_value_common(s, q_obs, k, v, causal, sc, idx_v, ws, thk_workspace_bytes(s, THK_OP_SCORE_VALUE), stream);
   if (st != THK_OK) return st;
   // Long calls compact through the one-pass prune kernels with the list given: their hand-off
   // makes the blocks of a unit store together, and the memory takes a unit's rows in one burst

@@ -249,9 +249,12 @@ struct ValueAttnArgs {
   float scale_log2;            // log2(e) / sqrt(D)
 };
 int value_attn_qt(int G, int S_obs);   // query tiles of 32 rows carried by one block: 1, 2 or 4
+// ... and by a block of the 8-wave kernel (bf16, four tiles or more) in a call that fills the chip
+int value_wide_tiles(int G, int S_obs);
 size_t value_part_bytes(int64_t U, int G, int S_obs, int n_split);
+// idx (may be null): the Top_T of every unit's score
 hipError_t launch_value_score(int dtype, const void *q_obs, const void *k, const void *v, float *part,
-                              float *score, int64_t U, int64_t S, int G, int S_obs, int causal,
+                              float *score, int16_t *idx, int T, int64_t U, int64_t S, int G, int S_obs, int causal,
                               int n_split, int64_t rows_per_split, hipStream_t st);
 
 }  // namespace thk

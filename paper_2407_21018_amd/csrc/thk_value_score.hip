@@ -7,7 +7,8 @@
 // column norms.
 //
 // k_value_attn (bf16): 4 waves per block.  The G * S_obs query rows of one KV head are cut into
-// tiles of 32 rows; a block carries QT of them (1, 2 or 4) and streams the keys in chunks of
+// tiles of 32 rows; a block carries QT of them (1 or 2; units with four or more go to
+// k_value_attn_wide below) and streams the keys in chunks of
 // 128 rows; wave w works on query tile w % QT and on the QT consecutive 32-key sub-tiles
 // number w / QT of every chunk.  Per 32-key sub-tile a wave computes
 //   S^T = K_sub Q^T        8 x v_mfma_f32_32x32x16_bf16 (A = keys from LDS, B = queries in VGPRs)
@@ -16,7 +17,7 @@
 //                          transposed) comes from row-major LDS through ds_read_b64_tr_b16
 // so neither the softmax maximum (a query is a lane column: 16 registers and one cross-half
 // exchange) nor the probabilities ever move between lanes.
-#include "thk_internal.h"
+#include "thk_prune_device.h"
 
 namespace thk {
 
@@ -30,12 +31,16 @@ namespace {
 constexpr int kRec = 32 * kD + 64;   // floats per partial record: O^T [128][32], m [32], l [32]
 constexpr float kNegBig = -1.0e30f;  // finite stand-in for "no key seen yet"
 
-// One 32-key sub-tile of the running-maximum softmax in the MFMA accumulator layout: lane
-// (n, h) holds, for query column n, the 16 keys kb + (r / 4) * 8 + h * 4 + r % 4.  Hides keys
-// past `lim`, updates the running maximum (rescaling the row sum and the output accumulators
-// when some query's maximum moved) and leaves the probabilities exp2(s * scale_log2 - m) in s.
-__device__ __forceinline__ void softmax_step(f32x16 &s, int64_t kb, int h, int64_t lim, int64_t lim_min,
-                                             float scale_log2, float &m_run, float &l_run, f32x16 (&o)[4]) {
+// One 32-key sub-tile of the running softmax in the MFMA accumulator layout: lane (n, h) holds, for
+// query column n, the 16 keys kb + (r / 4) * 8 + h * 4 + r % 4.  Hides keys past `lim`, moves the
+// reference m (rescaling the row sum and the output accumulators) and leaves the weights
+// exp2(s * scale_log2 - m) in s.  m follows the running maximum only when some query's maximum has
+// left it behind by more than kSlack: weights up to 2^kSlack are as exact in floating point as
+// weights up to 1, and among 32 queries SOME maximum still moves in most sub-tiles of a piece (60 %
+// of the 128 of an 8192-row piece), 65 multiplications each time.
+constexpr float kSlack = 8.f;
+__device__ __forceinline__ void softmax_max(f32x16 &s, int64_t kb, int h, int64_t lim, int64_t lim_min,
+                                            float scale_log2, float &m_run, float &l_run, f32x16 (&o)[4]) {
   if (kb + 31 > lim_min) {   // wave-uniform: only the sub-tiles that reach the window or the end
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
@@ -46,10 +51,10 @@ __device__ __forceinline__ void softmax_step(f32x16 &s, int64_t kb, int h, int64
   float mt = s[0];
 #pragma unroll
   for (int r = 1; r < 16; ++r) mt = fmaxf(mt, s[r]);
-  mt = fmaxf(mt, __shfl_xor(mt, 32));
-  // the running maximum lives in the log2 domain (scale_log2 > 0 keeps the order)
-  const float m_new = fmaxf(m_run, mt * scale_log2);
-  if (__any(m_new > m_run)) {
+  const LanePair pr = pair32(mt);
+  // the reference lives in the log2 domain (scale_log2 > 0 keeps the order)
+  const float m_new = fmaxf(m_run, fmaxf(pr.a, pr.b) * scale_log2);
+  if (__any(m_new > m_run + kSlack)) {
     const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
     l_run *= alpha;
 #pragma unroll
@@ -58,8 +63,15 @@ __device__ __forceinline__ void softmax_step(f32x16 &s, int64_t kb, int h, int64
       for (int r = 0; r < 16; ++r) o[dt][r] *= alpha;
     m_run = m_new;
   }
+}
+__device__ __forceinline__ void softmax_exp(f32x16 &s, float scale_log2, float m_run) {
 #pragma unroll
   for (int r = 0; r < 16; ++r) s[r] = __builtin_amdgcn_exp2f(fmaf(s[r], scale_log2, -m_run));
+}
+__device__ __forceinline__ void softmax_step(f32x16 &s, int64_t kb, int h, int64_t lim, int64_t lim_min,
+                                             float scale_log2, float &m_run, float &l_run, f32x16 (&o)[4]) {
+  softmax_max(s, kb, h, lim, lim_min, scale_log2, m_run, l_run, o);
+  softmax_exp(s, scale_log2, m_run);
 }
 
 constexpr int kXcds = 8;   // workgroup i of a launch runs on XCD i % 8, each XCD behind an L2 of its own
@@ -291,6 +303,199 @@ __global__ __launch_bounds__(256, 2) void k_value_attn_bf16(ValueAttnArgs a) {
   write_record(a.part + (((size_t)u * a.n_split + sp) * nqt + qtile) * kRec, o, m_run, l_tot, n, h);
 }
 
+// Units with four or more query tiles (G * S_obs > 96 rows: grouped heads): 8 waves, one block per
+// compute unit, QT = 4 or 8 query tiles, so that a key / value row is fetched for 128 or 256 query rows
+// at once.  Against the kernel above:
+//   * rows go from memory to LDS without passing through registers (global_load_lds, 16 bytes per
+//     lane): the 64 staging registers and the copy through them are gone, the next chunk is in
+//     flight during all of a chunk's work, and there is one barrier per chunk;
+//   * that transfer writes LDS in lane order, so bank conflicts are avoided by permuting the SOURCE:
+//     16-byte chunk c of key row r lies at chunk c ^ (r & 15) (a b128 read takes one chunk of 16
+//     rows), of value row r at c ^ ((r & 3) << 2) (a transposing read takes 64 bytes of 4 rows);
+//   * the next sub-tile's logits are computed in front of this one's softmax, in straight-line code,
+//     so that matrix and vector instructions of one wave run side by side.
+// What bounds it: without any transfer it takes 195 us for 64 units x 32768 rows x 128 query rows,
+// 1.05 PFLOP/s of issued matrix work (the same card's 8192^3 library product: 1.2) at a clock that
+// the matrix load holds at 1.8 GHz; the transfers alone take 172 us.  (Two phases per sub-tile with
+// waves 4 .. 7 half a step behind, so that one wave of a SIMD feeds the matrix pipe while the other
+// computes weights, measured the same: the pipe is not short of work, the card is of power.)
+// 64 units x 32768 rows, G = 4, S_obs = 32: 295 -> 278 us; 8 units x 131072 rows, S_obs = 64: 278 -> 235;
+// 32 units x 16384 rows, G = 8: 151 -> 128 us (score calls).
+constexpr int kWideRows = 128;                    // rows per chunk
+constexpr int kWideBytes = kWideRows * kD * 2;    // one tensor's chunk in LDS
+
+// One chunk of one tensor, 4 rows (1024 bytes) per instruction, KEYS: the key permutation.
+template <bool KEYS>
+__device__ __forceinline__ void wide_fetch(const unsigned char *g, int64_t last, unsigned char *lds, int wave,
+                                           int lane) {
+  constexpr int NI = kWideRows / 4 / 8;           // instructions per wave
+  const int rsub = lane >> 4, slot = lane & 15;
+#pragma unroll
+  for (int i = 0; i < NI; ++i) {
+    const int inst = wave * NI + i;
+    const int row = inst * 4 + rsub;
+    const int chunk = KEYS ? slot ^ ((inst & 3) * 4 + rsub) : slot ^ (rsub << 2);
+    // rows past the end repeat the last one; their weights are zero
+    const uint32_t off = (uint32_t)(row < last ? row : (int)last) * (kD * 2) + chunk * 16;
+    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(g + off),
+                                     (__attribute__((address_space(3))) void *)(lds + inst * 1024), 16, 0, 2 /* nt */);
+  }
+}
+
+template <int QT>
+__global__ __launch_bounds__(512, 2) void k_value_attn_wide(ValueAttnArgs a) {
+  constexpr int KW = 8 / QT;                      // waves that share a query tile, each on its own keys
+  constexpr int KT = kWideRows / 32 / KW;         // sub-tiles per wave and chunk
+  // a variable per buffer: reads of one are then known not to depend on transfers into another
+  __shared__ __attribute__((aligned(1024))) unsigned char kb0[kWideBytes], vb0[kWideBytes];
+  __shared__ __attribute__((aligned(1024))) unsigned char kb1[kWideBytes], vb1[kWideBytes];
+
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int qt = w % QT, ksub = w / QT;
+  const int n = lane & 31, h = lane >> 5;
+
+  int qb, sp;
+  int64_t u;
+  if (!value_block_work(a, qb, sp, u)) return;
+
+  const int rows_q = a.G * a.S_obs;
+  const int qtile = qb * QT + qt;
+  const int row = qtile * 32 + n;      // this lane's query row in the unit's (head, window row) list
+  const int64_t S = a.S;
+  const int64_t k0 = (int64_t)sp * a.rows_per_split;
+  const int64_t k1 = (k0 + a.rows_per_split < S) ? k0 + a.rows_per_split : S;
+  const int nchunks = (int)((k1 - k0 + kWideRows - 1) / kWideRows);
+  const unsigned char *kg = (const unsigned char *)a.k + ((size_t)u * S + k0) * (kD * 2);
+  const unsigned char *vg = (const unsigned char *)a.v + ((size_t)u * S + k0) * (kD * 2);
+
+  auto fetch = [&](int c, unsigned char *kb, unsigned char *vb) {
+    const int64_t r0 = (int64_t)c * kWideRows;
+    const int64_t last = S - 1 - k0 - r0;          // the unit's last row, seen from the chunk's first
+    const int64_t lc = last < kWideRows - 1 ? last : kWideRows - 1;
+    wide_fetch<true>(kg + r0 * (kD * 2), lc, kb, w, lane);
+    wide_fetch<false>(vg + r0 * (kD * 2), lc, vb, w, lane);
+  };
+  if (nchunks > 0) fetch(0, kb0, vb0);
+
+  // Query operand: 8 k-steps of 8 channels for this lane's (row, half).
+  bf16x8 qreg[8];
+  {
+    const uint16_t *qp = (const uint16_t *)a.q_obs + ((size_t)u * rows_q + (row < rows_q ? row : 0)) * kD + h * 8;
+#pragma unroll
+    for (int ks = 0; ks < 8; ++ks) {
+      u32x4 r = *(const u32x4 *)(qp + ks * 16);
+      if (row >= rows_q) r = u32x4{0u, 0u, 0u, 0u};
+      qreg[ks] = __builtin_bit_cast(bf16x8, r);
+    }
+  }
+  // Last key this lane's query may see, and the smallest such limit in the call.
+  const int64_t lim = a.causal ? S - a.S_obs + (row % a.S_obs) : S - 1;
+  const int64_t lim_min = a.causal ? S - a.S_obs : S - 1;
+
+  f32x16 o[4];
+#pragma unroll
+  for (int dt = 0; dt < 4; ++dt)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) o[dt][r] = 0.f;
+  float m_run = kNegBig, l_run = 0.f;
+
+  // this lane's operand offsets inside a sub-tile
+  const int j = lane & 15, gsub = (lane >> 4) & 1;
+  const int ka_off = (ksub * KT * 32 + n) * 256 + ((h ^ (n & 15)) << 4);       // chunk 2 ks + h: ^ ks * 32
+  const int va_row = (ksub * KT * 32 + h * 4 + (j >> 2)) * 256 + gsub * 32 + (j & 3) * 8;
+  int va_off[4];                                                               // 64-byte block dt
+#pragma unroll
+  for (int dt = 0; dt < 4; ++dt) va_off[dt] = va_row + ((dt ^ (j >> 2)) << 6);
+
+  auto logits = [&](const unsigned char *kb, int t) {
+    f32x16 s;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) s[r] = 0.f;
+#pragma unroll
+    for (int ks = 0; ks < 8; ++ks) {
+      const bf16x8 ka = *(const bf16x8 *)(kb + (ka_off ^ (ks * 32)) + t * 32 * 256);
+      s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka, qreg[ks], s, 0, 0, 0);
+    }
+    return s;
+  };
+  auto values = [&](f32x16 &s, const unsigned char *vb, int t) {
+    // two bf16 terms per probability (see k_value_attn_bf16)
+    bf16x8 ph[2], pl[2];
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const __bf16 hi = (__bf16)s[r];
+      ph[r >> 3][r & 7] = hi;
+      pl[r >> 3][r & 7] = (__bf16)(s[r] - (float)hi);
+      l_run += s[r];
+    }
+#pragma unroll
+    for (int k2 = 0; k2 < 2; ++k2)
+#pragma unroll
+      for (int dt = 0; dt < 4; ++dt) {
+        const unsigned char *vp = vb + va_off[dt] + (t * 32 + k2 * 16) * 256;
+        const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4 *)(vp));
+        const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4 *)(vp + 8 * 256));
+        const bf16x8 va = __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+        o[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va, ph[k2], o[dt], 0, 0, 0);
+        o[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va, pl[k2], o[dt], 0, 0, 0);
+      }
+  };
+  const bool active = qtile * 32 < rows_q;   // a unit's last block may have tiles without rows: they only help to load
+  auto chunk = [&](int c, const unsigned char *kb, const unsigned char *vb, unsigned char *kb_next, unsigned char *vb_next) {
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this wave's part of chunk c has landed
+    __syncthreads();                                   // ... everybody's, and chunk c - 1 is no longer read
+    if (c + 1 < nchunks) fetch(c + 1, kb_next, vb_next);
+    if (!active) return;
+    const int64_t kb0_row = k0 + (int64_t)c * kWideRows + ksub * KT * 32;
+    f32x16 s = logits(kb, 0);
+#pragma unroll
+    for (int t = 0; t < KT; ++t) {
+      softmax_max(s, kb0_row + t * 32, h, lim, lim_min, a.scale_log2, m_run, l_run, o);
+      f32x16 s_next;
+      if (t + 1 < KT) s_next = logits(kb, t + 1);
+      softmax_exp(s, a.scale_log2, m_run);
+      values(s, vb, t);
+      if (t + 1 < KT) s = s_next;
+    }
+  };
+  for (int c = 0; c < nchunks; c += 2) {
+    chunk(c, kb0, vb0, kb1, vb1);
+    if (c + 1 < nchunks) chunk(c + 1, kb1, vb1, kb0, vb0);
+  }
+
+  // The waves that carried the same query tile meet in LDS (as in k_value_attn_bf16).
+  float l_tot = l_run + __shfl_xor(l_run, 32);
+  if constexpr (KW == 2) {
+    __syncthreads();                           // the last chunk is no longer read
+    float *mx = (float *)kb1;                  // [2][QT][32] maxima, then the second group's sums
+    float *ox0 = (float *)kb0, *ox1 = (float *)vb0;   // two query tiles' [64 registers][64 lanes] in each
+    if (h == 0) mx[(ksub * QT + qt) * 32 + n] = m_run;
+    __syncthreads();
+    const float M = fmaxf(mx[qt * 32 + n], mx[(QT + qt) * 32 + n]);
+    const float alpha = __builtin_amdgcn_exp2f(m_run - M);
+    l_tot *= alpha;
+    m_run = M;
+    float *xch = (qt < 2 ? ox0 : ox1) + (size_t)(qt & 1) * 64 * 64 + lane;
+    if (ksub > 0) {
+#pragma unroll
+      for (int dt = 0; dt < 4; ++dt)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) xch[(dt * 16 + r) * 64] = o[dt][r] * alpha;
+      if (h == 0) mx[2 * QT * 32 + qt * 32 + n] = l_tot;
+    }
+    __syncthreads();
+    if (ksub > 0) return;
+#pragma unroll
+    for (int dt = 0; dt < 4; ++dt)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) o[dt][r] = o[dt][r] * alpha + xch[(dt * 16 + r) * 64];
+    l_tot += mx[2 * QT * 32 + qt * 32 + n];
+  }
+  const int nqt = a.n_qblk * QT;
+  write_record(a.part + (((size_t)u * a.n_split + sp) * nqt + qtile) * kRec, o, m_run, l_tot, n, h);
+}
+
 // ---------------------------------------------------------------- fp32 ----
 // The same streaming attention in full fp32 on v_mfma_f32_32x32x2_f32 (one 32-key tile per
 // step, one wave per query tile, QT waves per block).  The contraction index of an MFMA step is
@@ -405,19 +610,35 @@ __global__ __launch_bounds__(256) void k_value_merge(const float *part, float *s
   const int d = db * DQ + dl;
   const int rows_q = G * S_obs;
   const float *pu = part + (size_t)u * n_part * nqt * kRec;
-  if (threadIdx.x < 32) {
-    const int q = threadIdx.x;
+  // weights of the records, row q = tid % 32, records tid / 32, + 8, ... per thread (one thread per row
+  // walked all of them before: 128 records took 60 us)
+  __shared__ float red[8][32];
+  __shared__ float inv[32];
+  {
+    const int q = threadIdx.x & 31, rg = threadIdx.x >> 5;
+    const float *rec = pu + (size_t)t * kRec + 32 * kD + q;
     float M = kNegBig;
-    for (int p = 0; p < n_part; ++p) M = fmaxf(M, pu[((size_t)p * nqt + t) * kRec + 32 * kD + q]);
+    for (int p = rg; p < n_part; p += 8) M = fmaxf(M, rec[(size_t)p * nqt * kRec]);
+    red[rg][q] = M;
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < 8; ++i) M = fmaxf(M, red[i][q]);
+    __syncthreads();
     float L = 0.f;
-    for (int p = 0; p < n_part; ++p) {
-      const float *r = pu + ((size_t)p * nqt + t) * kRec + 32 * kD;
-      const float wv = __builtin_amdgcn_exp2f(r[q] - M);
+    for (int p = rg; p < n_part; p += 8) {
+      const float *r = rec + (size_t)p * nqt * kRec;
+      const float wv = __builtin_amdgcn_exp2f(r[0] - M);
       wts[p * 32 + q] = wv;
-      L += wv * r[32 + q];
+      L += wv * r[32];
     }
-    const float inv = L > 0.f ? 1.f / L : 0.f;
-    for (int p = 0; p < n_part; ++p) wts[p * 32 + q] *= inv;
+    red[rg][q] = L;
+    __syncthreads();
+    if (rg == 0) {
+      L = red[0][q];
+#pragma unroll
+      for (int i = 1; i < 8; ++i) L += red[i][q];
+      inv[q] = L > 0.f ? 1.f / L : 0.f;
+    }
   }
   __syncthreads();
   float acc[32];
@@ -447,6 +668,8 @@ __global__ __launch_bounds__(256) void k_value_merge(const float *part, float *s
   for (int g2 = 1; g2 < PG; ++g2)
 #pragma unroll
     for (int q = 0; q < 32; ++q) acc[q] += xch[((g2 - 1) * DQ + dl) * 33 + q];
+#pragma unroll
+  for (int q = 0; q < 32; ++q) acc[q] *= inv[q];
   if (nt == 1) {
     double ss = 0.0, total = 0.0;
 #pragma unroll
@@ -470,8 +693,11 @@ __global__ __launch_bounds__(256) void k_value_merge(const float *part, float *s
 // Column norms per query head from the squared outputs.  1024 threads = 128 channels x 8 head
 // groups: thread (d, hg) sums the squares of heads hg, hg + 8, ... (eight rows in flight), takes
 // the roots, and the groups are added in group order.
-__global__ __launch_bounds__(1024) void k_value_norms(const float *sq, float *score, int G, int S_obs, int nt) {
+// With idx the unit's Top_T follows in the same block.
+__global__ __launch_bounds__(1024) void k_value_norms(const float *sq, float *score, int16_t *idx, int T, int G,
+                                                      int S_obs, int nt) {
   __shared__ double tot[8][kD];
+  __shared__ float s_sc[kD];
   const int64_t u = blockIdx.x;
   const int d = threadIdx.x & (kD - 1), hg = threadIdx.x >> 7;
   const float *src = sq + (size_t)u * nt * 32 * kD + d;
@@ -495,7 +721,11 @@ __global__ __launch_bounds__(1024) void k_value_norms(const float *sq, float *sc
 #pragma unroll
     for (int g2 = 1; g2 < 8; ++g2) t += tot[g2][d];
     score[(size_t)u * kD + d] = (float)t;
+    s_sc[d] = (float)t;
   }
+  if (idx == nullptr) return;
+  __syncthreads();
+  if (threadIdx.x < kWave) select_wave(s_sc[threadIdx.x], s_sc[threadIdx.x + kWave], T, idx + (size_t)u * T, threadIdx.x);
 }
 
 }  // namespace
@@ -503,6 +733,12 @@ __global__ __launch_bounds__(1024) void k_value_norms(const float *sq, float *sc
 int value_attn_qt(int G, int S_obs) {
   const int nqt = (G * S_obs + 31) / 32;
   return nqt >= 4 ? 4 : nqt >= 2 ? 2 : 1;
+}
+
+// Eight where the records, which are laid out in fours, come out even.
+int value_wide_tiles(int G, int S_obs) {
+  const int nqt = (G * S_obs + 31) / 32;
+  return (nqt + 3) / 4 % 2 == 0 ? 8 : 4;
 }
 
 size_t value_part_bytes(int64_t U, int G, int S_obs, int n_split) {
@@ -514,7 +750,7 @@ size_t value_part_bytes(int64_t U, int G, int S_obs, int n_split) {
 }
 
 hipError_t launch_value_score(int dtype, const void *q_obs, const void *k, const void *v, float *part,
-                              float *score, int64_t U, int64_t S, int G, int S_obs, int causal,
+                              float *score, int16_t *idx, int T, int64_t U, int64_t S, int G, int S_obs, int causal,
                               int n_split, int64_t rows_per_split, hipStream_t st) {
   clear_stale_hip_error();
   const int QT = value_attn_qt(G, S_obs);
@@ -523,7 +759,12 @@ hipError_t launch_value_score(int dtype, const void *q_obs, const void *k, const
   a.q_obs = q_obs; a.k = k; a.v = v; a.part = part;
   a.S = S; a.rows_per_split = rows_per_split;
   a.G = G; a.S_obs = S_obs; a.n_split = n_split; a.causal = causal;
-  a.n_qblk = (nqt_real + QT - 1) / QT;
+  // bf16 with four or more query tiles: the 8-wave kernel, with eight tiles per block where that
+  // leaves a block for every compute unit, else with four and twice the blocks
+  const bool wide = dtype == THK_BF16 && QT == 4;
+  int QB = wide ? value_wide_tiles(G, S_obs) : QT;
+  if (QB == 8 && U * n_split * ((nqt_real + 7) / 8) < kCUs) QB = 4;
+  a.n_qblk = (nqt_real + QB - 1) / QB;
   a.scale_log2 = (float)(1.4426950408889634 / sqrt((double)kD));
   a.U = U;
   // several query blocks per (unit, piece): pieces rounded up to a multiple of the XCD count
@@ -533,17 +774,18 @@ hipError_t launch_value_score(int dtype, const void *q_obs, const void *k, const
   const void *fn;
   int threads = 256;
   if (dtype == THK_BF16) {
-    fn = QT == 4 ? (const void *)k_value_attn_bf16<4> : QT == 2 ? (const void *)k_value_attn_bf16<2> : (const void *)k_value_attn_bf16<1>;
+    fn = wide ? (QB == 8 ? (const void *)k_value_attn_wide<8> : (const void *)k_value_attn_wide<4>) : QT == 2 ? (const void *)k_value_attn_bf16<2> : (const void *)k_value_attn_bf16<1>;
   } else {
     fn = QT == 4 ? (const void *)k_value_attn_f32<4> : QT == 2 ? (const void *)k_value_attn_f32<2> : (const void *)k_value_attn_f32<1>;
     threads = QT == 4 ? 256 : QT == 2 ? 128 : 64;
   }
+  if (wide) threads = 512;
   void *kargs[] = {(void *)&a};
   hipError_t e = launch_main_kernel(fn, dim3(grid), dim3(threads), kargs, 0, st);
   if (e == hipSuccess) e = hipGetLastError();
   if (e != hipSuccess) return e;
   const int n_part = n_split;
-  const int nqt = a.n_qblk * QT;
+  const int nqt = a.n_qblk * QB;
   float *sq = part + (size_t)U * n_part * nqt * kRec;   // behind the partial records
   // few records: 2 groups x 128 channels per block; many: 8 groups x 32 channels, 4 blocks
   const int PG = n_part > 8 ? 8 : 2;
@@ -557,8 +799,9 @@ hipError_t launch_value_score(int dtype, const void *q_obs, const void *k, const
   else
     hipLaunchKernelGGL(k_value_merge<2>, mg, dim3(256), lds, st, part, sq, score, G, S_obs, n_part, nqt, nqt_real);
   e = hipGetLastError();
-  if (e != hipSuccess || nqt_real == 1) return e;
-  hipLaunchKernelGGL(k_value_norms, dim3((unsigned)U), dim3(1024), 0, st, sq, score, G, S_obs, nqt_real);
+  if (e != hipSuccess) return e;
+  if (nqt_real == 1) return idx != nullptr ? launch_select(score, idx, U, T, st) : hipSuccess;
+  hipLaunchKernelGGL(k_value_norms, dim3((unsigned)U), dim3(1024), 0, st, sq, score, idx, T, G, S_obs, nqt_real);
   return hipGetLastError();
 }
 

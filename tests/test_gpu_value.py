@@ -99,6 +99,30 @@ def test_value_score_matches_oracle(G, S_obs, S, n_split, causal, sigma, dtype):
     check_score(got, want.reshape(-1, D), v64, G, S_obs, f"G={G} S_obs={S_obs} S={S}", dtype)
 
 
+@pytest.mark.parametrize("B,N_kv,G,S_obs,S,n_split,causal", [
+    (1, 2, 4, 32, 1, 0, 1), (1, 2, 4, 32, 127, 0, 0), (1, 2, 4, 32, 128, 0, 1), (1, 2, 4, 32, 129, 0, 1),
+    (1, 2, 4, 32, 513, 2, 0),       # the second piece is one row
+    (1, 2, 5, 32, 300, 0, 1),       # 5 tiles: eight slots, the second four mostly idle
+    (1, 2, 7, 32, 260, 3, 1),       # 7 tiles, the last piece is four rows
+    (1, 2, 9, 32, 400, 0, 1),       # 9 tiles: three blocks of four
+    (1, 1, 4, 25, 391, 0, 1),       # tiles that straddle heads, the last one short
+    (8, 8, 8, 32, 500, 4, 1), (8, 8, 5, 32, 385, 4, 0),   # 256 blocks: eight tiles (three idle) per block
+])
+def test_value_score_eight_wave_kernel(B, N_kv, G, S_obs, S, n_split, causal):
+    """Four or more query tiles per unit (bf16): one row, the edges of a 128-row chunk and of a piece, tiles
+    without rows, four and eight tiles per block.  The keys grow along the sequence, so that every
+    query's maximum keeps rising: the softmax reference lags behind it by up to its slack."""
+    S_obs = min(S_obs, S)
+    q_obs = _randn((1, B, N_kv * G, S_obs, D), "bf16", 501, 0.5)
+    ramp = (0.2 + 2.0 * torch.arange(S, device="cuda") / S)[:, None]
+    k = (_randn((1, B, N_kv, S, D), "f32", 502, 0.5) * ramp).to(torch.bfloat16)
+    v = _randn((1, B, N_kv, S, D), "bf16", 503)
+    shape = thk.make_shape(1, B, N_kv * G, N_kv, D, S, S_obs, 64, 0, thk.THK_BF16, n_split)
+    got = gpu_score_value(shape, q_obs, k, v, causal).cpu().numpy().astype(np.float64)
+    want = O.score_value(as_numpy(q_obs), as_numpy(k), as_numpy(v), "bf16", causal).reshape(B * N_kv, D)
+    check_score(got, want, None, G, S_obs, f"B={B} G={G} S={S} n={n_split}")
+
+
 def test_value_score_split_count_changes_only_rounding():
     """Any cut of the key axis gives the same score up to fp32 merge rounding."""
     L, B, N_kv, G, S, S_obs = 1, 1, 2, 2, 3000, 32
