@@ -272,7 +272,7 @@ thk_status thk_prune(const thk_shape *shape, const void *q_obs, const void *k,
  * S_obs in the shape is ignored.  With n_split > 1 partial (max, sum, acc[D])
  * states go through ws and are merged in split order, so repeated calls give
  * identical bits: by a second kernel, or -- for small calls (at most 16 pieces, at
- * most two query heads per block, at most two blocks per compute unit) -- inside the
+ * most four query heads per block, at most two blocks per compute unit) -- inside the
  * one launch by the block that finishes last for a head group (the blocks signal
  * through per-piece flag words in ws that carry a nonce drawn per call; no
  * read-modify-write, nothing in ws has to be cleared beforehand).

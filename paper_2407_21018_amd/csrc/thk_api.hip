@@ -172,6 +172,10 @@ size_t decode_records_bytes(const thk_shape *s, int n_split) {
   return (b + 7) & ~(size_t)7;
 }
 
+size_t decode_ws_bytes(const thk_shape *s, int n_split) {
+  return decode_records_bytes(s, n_split) + (size_t)decode_groups(s) * n_split * sizeof(unsigned long long);
+}
+
 // A 64-bit number, never 0, different for every call of the process and spread over the whole
 // range (what an earlier call or other data left in a workspace will not look like it).
 unsigned long long next_nonce() {
@@ -188,29 +192,75 @@ unsigned long long next_nonce() {
 // a head group) where that saves more than it costs -- see decode_merge_in_launch below.
 bool decode_merge_in_launch(const thk_shape *s, int n_split);
 
+// The number of pieces with the least estimated time, if that is at least 8 % below the estimate for
+// n0.  With k = steps of a piece and L = blocks on the fullest compute unit, in us:
+//     max(k t_step, L k t_stream) + 0.5 L + merge
+// t_step: a step (128 rows by four waves) that waits for its own loads, 2.4, times 1.6 for fp32 and
+// 1.35 where a block serves eight heads; t_stream: a compute unit's share of the memory rate, 0.04 per KB
+// of a step's rows; 0.5: what a block costs whatever its length; merge: nothing for one piece, 1.5
+// inside the launch, 3 and 0.03 per piece by the merge kernel.  Fitted to 64 shapes (a third of them
+// fp32, 1-8 heads per KV head, 4-248 units, 258-125958 rows) measured at every piece count with
+// whole steps: the powers of two above took 8.9 % more than the best count on average, this takes
+// 2.3 %.  What they miss is rounds (136 units x 5184 rows: 4 pieces are 544 blocks, 3 on some compute
+// units and 2 on others; 7 pieces: 62.4 -> 54.5 us) and whole steps (16 units x 1815 rows, 15
+// pieces of one step instead of 8: 11.0 -> 9.5 us).
+int decode_pieces(const thk_shape *s, int hpb, int64_t wgs, int64_t steps, int n0) {
+  constexpr int kMaxPieces = 128;
+  // more pieces only while the records fit the scratch array of thk_decode_attn_static, which takes
+  // every call that n0 pieces fit
+  const int64_t heads = (int64_t)s->L * s->B * s->N_q;
+  const int64_t fit = (int64_t)THK_STATIC_SCRATCH_BYTES / ((kD + 2) * 4 + 8) / heads;
+  if (n0 > 1 && n0 > fit) return n0;
+  const double t_step = 2.4 * (s->dtype == THK_F32 ? 1.6 : 1.0) * (hpb == 8 ? 1.35 : 1.0);
+  const double t_stream = 0.04 * 128 * (ld_of(s) + kD) * elem_bytes(s->dtype) / 1024.0;
+  auto cost = [&](int64_t n, int64_t k) {
+    const int64_t blocks = wgs * n;
+    const double L = (double)((blocks + kCUs - 1) / kCUs);
+    const double merge = n == 1 ? 0.0 : n <= kDecodeFuseMaxSplit && blocks <= 2 * kCUs ? 1.5 : 3.0 + 0.03 * (double)n;
+    return std::max((double)k * t_step, L * (double)k * t_stream) + 0.5 * L + merge;
+  };
+  double best = 0.92 * cost(n0, ceil_div(ceil_div(s->S, n0), 128));
+  int64_t n_best = n0;
+  // more than eight blocks per compute unit never pay
+  const int64_t top = std::min<int64_t>({steps, kMaxPieces, std::max<int64_t>(n0, 8 * (int64_t)kCUs / wgs), std::max<int64_t>(fit, 1)});
+  int64_t k_last = 0;
+  for (int64_t i = 1; i <= top; ++i) {
+    const int64_t k = (steps + i - 1) / i;
+    if (k == k_last) continue;   // the same pieces, some of them empty
+    k_last = k;
+    const double c = cost(i, k);
+    if (c < best) { best = c; n_best = i; }
+  }
+  return (int)n_best;
+}
+
 Split decode_split(const thk_shape *s) {
   int n = s->n_split;
   const int G = s->N_q / s->N_kv;
   const int64_t wgs = units_of(s) * ceil_div(G, decode_heads_per_block(s));
   if (n == 0) {
     // About one resident set of blocks over the call (4 per compute unit, 3 where a block
-    // serves eight heads), a power of two pieces per unit.  A piece has at least 256 rows, or
-    // 128 while the launch stays within one block per compute unit; more than 64 pieces (the
-    // merge grows with n) only where even that leaves compute units idle.  Short sequences
+    // serves eight heads), a power of two pieces per unit.  The four waves of a block take 128 rows
+    // per step; a piece has at least two steps, or one while the launch stays within one block per
+    // compute unit (a started step counts: 8 units x 1000 rows take 8 pieces, not the 4 of at least
+    // 128 whole rows: 11.4 -> 9.0 us; 64 units x 2000 rows 8 instead of 4: 18.0 -> 16.0 us); more than
+    // 64 pieces (the merge grows with n) only where even that leaves compute units idle.  Short sequences
     // take one block per unit: below these lengths the second launch (the merge) costs more
     // than the split saves.  Big calls still get two pieces per unit so that the last blocks
     // to finish are short.
     const int hpb = decode_heads_per_block(s);
     const int per_cu = hpb == 8 ? 3 : 4;
     const int64_t one_block_rows = (hpb >= 4 ? 320 : 768) * 2 / elem_bytes(s->dtype);   // bf16 rows; half as many fp32 rows
+    const int64_t steps = ceil_div(s->S, 128);
     n = 1;
     while (s->S > one_block_rows && n < 128) {
       const int64_t blocks = (int64_t)n * 2 * wgs;
       if (blocks > (int64_t)kCUs * per_cu || (n >= 64 && blocks > kCUs)) break;
-      if (ceil_div(s->S, (int64_t)n * 2) < (blocks <= kCUs ? 128 : 256)) break;
+      if ((int64_t)n * 2 * (blocks <= kCUs ? 1 : 2) > steps) break;
       n *= 2;
     }
     if (n == 1 && s->S >= 2048) n = 2;
+    if (s->S > one_block_rows || units_of(s) > 8) n = decode_pieces(s, hpb, wgs, steps, n);
   }
   int64_t rows = ceil_div(s->S, n);
   rows = ceil_div(rows, 64) * 64;
@@ -219,20 +269,21 @@ Split decode_split(const thk_shape *s) {
 }
 
 // Small calls merge their split records inside the launch: the block that finishes last for a
-// head group does it, and the second launch goes away (fp32, 8 heads x 2048 rows: 11.8 -> 9.3 us;
-// one sequence of 32 heads x 1024 bf16 rows: 11.1 -> 9.4 us).  The hand-off costs three memory
-// round trips at the end of the kernel, a second launch about as much, so the gain fades as the
-// launch grows (nothing left at 1024 blocks; a launch that fills the chip four blocks deep --
-// 128 units x 8 pieces of 512 rows -- runs 1 us SLOWER: 38.4 -> 39.5 us) and a block that
-// serves four or eight heads needs two or four rounds of loads for its merge (+1.1 .. 1.6 us).
-// Hence: at most 16 pieces, at most two heads per block, at most two blocks per compute unit.
+// head group does it, and the second launch goes away.  The hand-off costs three memory round trips
+// at the end of the kernel and, per four heads, one for the records; a second launch costs about
+// as much and its dispatch.  Merged by the kernel / inside, us per call: 8 units x 1000 rows, four
+// heads, 8 pieces 10.0 / 9.0; 64 units x 2000 rows, 8 pieces, one head 14.5 / 14.0, four heads 16.2 /
+// 16.0; eight heads, 8 units x 2000 rows, 8 pieces 14.2 / 14.4, 64 units x 8191 rows 35.1 / 37.1.  From
+// 1024 blocks on the exchange ends a launch whose memory queues are full: 128 units x 8 pieces 37.8 /
+// 38.2, 64 x 16 pieces of 2048 rows 127.3 / 130.6.  Hence: at most 16 pieces, at most four heads per
+// block, at most two blocks per compute unit.
 // THK_DECODE_MERGE = kernel | fused overrides (fused only within the 16 pieces).
 bool decode_merge_in_launch(const thk_shape *s, int n_split) {
   if (n_split < 2 || n_split > kDecodeFuseMaxSplit) return false;
   const char sw = env_switches().decode_merge;
   if (sw == 'k') return false;
   if (sw == 'f') return true;
-  return decode_heads_per_block(s) <= 2 && decode_groups(s) * n_split <= 2 * (int64_t)kCUs;
+  return decode_heads_per_block(s) <= 4 && decode_groups(s) * n_split <= 2 * (int64_t)kCUs;
 }
 
 // Units per group in the staged form of thk_prune (three launches per group).
@@ -462,8 +513,7 @@ size_t thk_workspace_bytes(const thk_shape *s, int32_t op) {
       return score_ws_bytes(s, units_of(s));
     case THK_OP_DECODE: {
       const Split sp = decode_split(s);
-      if (sp.n == 1) return 16;
-      return decode_records_bytes(s, sp.n) + (size_t)decode_groups(s) * sp.n * sizeof(unsigned long long);
+      return sp.n == 1 ? 16 : decode_ws_bytes(s, sp.n);
     }
     case THK_OP_SCORE_VALUE:
       if (s->S_obs < 1 || (int64_t)s->S_obs > s->S) return 0;
@@ -762,7 +812,7 @@ static thk_status decode_common(const thk_shape *s, const void *q, const void *k
   const Split sp = decode_split(s);
   const int G = s->N_q / s->N_kv;
   if (units_of(s) * ceil_div(G, decode_heads_per_block(s)) * sp.n > kMaxGrid) return THK_ERR_SHAPE;
-  if (sp.n > 1 && (ws == nullptr || !aligned16(ws) || ws_bytes < thk_workspace_bytes(s, THK_OP_DECODE)))
+  if (sp.n > 1 && (ws == nullptr || !aligned16(ws) || ws_bytes < decode_ws_bytes(s, sp.n)))
     return THK_ERR_WORKSPACE;
   DecodeArgs a;
   a.q = q; a.kp = k_pruned; a.v = v; a.kt = k_tail; a.vt = v_tail; a.idx = idx; a.out = out;

@@ -580,29 +580,37 @@ __device__ __forceinline__ void block_merge_store(const float *mrg, int wstride,
   }
   __syncthreads();
   if (*s_last == 0) return;
-  for (int o = threadIdx.x; o < heads * kD; o += 256) {
-    const int g = o / kD, c = o % kD;
+  // A wave takes a head, a lane two of its channels; lane i also holds piece i's maximum and sum, whose
+  // weight reaches the others through v_readlane.  One trip to memory per head: the loads go
+  // through a buffer resource that ends with the last piece, so that those of absent pieces return 0
+  // (little code matters here as much as few trips: it is fetched as it runs).
+  constexpr int kRecB = (kD + 2) * 4, kDeviceScope = 16;   // bytes from piece to piece; sc1, as pub_load_f32
+  const int lane = threadIdx.x % kWave;
+  for (int g = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave); g < heads; g += 4) {
     const size_t bn = (size_t)(bn0 + g);
-    const float *rec0 = a.ws + bn * a.n_split * (kD + 2);
-    float mv[kFuseMaxSplit], lv[kFuseMaxSplit], av[kFuseMaxSplit];
+    const auto rsrc = __builtin_amdgcn_make_buffer_rsrc((void *)(a.ws + bn * a.n_split * (kD + 2)), (short)0,
+                                                        a.n_split * kRecB, 0x00027000);
+    typedef float f32x2 __attribute__((ext_vector_type(2)));
+    auto load2 = [&](int off) {
+      return __builtin_bit_cast(f32x2, __builtin_amdgcn_raw_buffer_load_b64(rsrc, off, 0, kDeviceScope));
+    };
+    const f32x2 ml = load2(lane * kRecB);
+    f32x2 av[kFuseMaxSplit];
 #pragma unroll
-    for (int i = 0; i < kFuseMaxSplit; ++i) {   // all loads in flight at once; entries past n_split repeat the last
-      const float *rec = rec0 + (size_t)min(i, a.n_split - 1) * (kD + 2);
-      mv[i] = pub_load_f32(rec);
-      lv[i] = pub_load_f32(rec + 1);
-      av[i] = pub_load_f32(rec + 2 + c);
-    }
-    float M = -INFINITY;
-#pragma unroll
-    for (int i = 0; i < kFuseMaxSplit; ++i) M = fmaxf(M, mv[i]);
-    float Lsum = 0.f, A = 0.f;
+    for (int i = 0; i < kFuseMaxSplit; ++i) av[i] = load2(i * kRecB + 8 + lane * 8);
+    const float m = lane < a.n_split ? ml[0] : -INFINITY;
+    const float M = wave_max(m);
+    const float wgt = m == -INFINITY ? 0.f : exp2f(m - M);
+    float Lsum = 0.f, A0 = 0.f, A1 = 0.f;
 #pragma unroll
     for (int i = 0; i < kFuseMaxSplit; ++i) {
-      const float wgt = (i >= a.n_split || mv[i] == -INFINITY) ? 0.f : exp2f(mv[i] - M);
-      Lsum = fmaf(lv[i], wgt, Lsum);
-      A = fmaf(av[i], wgt, A);
+      const float wi = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(wgt), i));
+      Lsum = fmaf(__int_as_float(__builtin_amdgcn_readlane(__float_as_int(ml[1]), i)), wi, Lsum);
+      A0 = fmaf(av[i][0], wi, A0);
+      A1 = fmaf(av[i][1], wi, A1);
     }
-    E::store1(a.out, bn * kD + c, A / Lsum);
+    E::store1(a.out, bn * kD + 2 * lane, A0 / Lsum);
+    E::store1(a.out, bn * kD + 2 * lane + 1, A1 / Lsum);
   }
   if ((int)threadIdx.x < a.n_split)
     __hip_atomic_store(flags + threadIdx.x, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);

@@ -284,6 +284,26 @@ def test_default_decode_split_follows_the_size_of_the_call(thk_env):
     assert split(32, 40, 40, 16384) == 2       # big calls: two pieces per unit
 
 
+def test_default_decode_split_balances_rounds_and_stays_within_the_static_scratch():
+    """Piece counts other than powers of two where those leave compute units idle or a step half
+    empty; never so many that thk_decode_attn_static would refuse a call that the powers of two fit."""
+    def split(B, N_q, N_kv, S, T=64, dtype=thk.THK_BF16):
+        return thk.thk_default_split(thk.make_shape(1, B, N_q, N_kv, 128, S, 1, T, 0, dtype, 0), thk.THK_OP_DECODE)
+    assert split(2, 32, 8, 1815) == 15                   # 16 units: 15 pieces of one step
+    n = split(17, 32, 8, 5184, 76)
+    assert -(-136 * n // 256) * -(-5184 // (128 * n)) < 3 * 11    # 136 units: less than 4 pieces' 3 rounds of 11 steps
+    for B in (1, 3, 8, 32, 100, 400):
+        for N_q, N_kv in ((8, 8), (32, 8), (64, 8), (64, 4), (40, 40)):
+            for S in (100, 257, 900, 2047, 2048, 5000, 40000, 131072):
+                for dtype in (thk.THK_BF16, thk.THK_F32):
+                    s = thk.make_shape(1, B, N_q, N_kv, 128, S, 1, 51, 0, dtype, 0)
+                    n = thk.thk_default_split(s, thk.THK_OP_DECODE)
+                    assert 1 <= n <= 128
+                    s1 = thk.make_shape(1, B, N_q, N_kv, 128, S, 1, 51, 0, dtype, 2)
+                    if thk.thk_workspace_bytes(s1, thk.THK_OP_DECODE) <= 8 << 20:
+                        assert thk.thk_workspace_bytes(s, thk.THK_OP_DECODE) <= 8 << 20
+
+
 def test_plain_c_program_uses_the_boundary(tmp_path):
     """thk.h is a C header and libthk.so a C library: a gcc-built program with no C++ and no
     Python in it includes the one and links the other."""
