@@ -656,6 +656,12 @@ thk_status thk_tail_flush(const thk_shape *s, const int16_t *idx, void *k_pruned
     return THK_ERR_ALIGN;
   hipStream_t hs = (hipStream_t)stream;
   const int64_t U = units_of(s);
+  if (v != nullptr && n_flush == s_tail) {   // nothing stays behind to be shifted
+    hipError_t e = hipSuccess;
+    if (launch_flush(s->dtype, k_tail, v_tail, s_tail_cap, idx, k_pruned, v, unit_rows, s->S, U, n_flush, s->T,
+                     ld_of(s), hs, &e))
+      return failed(e) ? THK_ERR_HIP : THK_OK;
+  }
   if (failed(launch_compact(s->dtype, k_tail, s_tail_cap, 0, idx, k_pruned, unit_rows, s->S, U, n_flush, s->T,
                      ld_of(s), hs)))
     return THK_ERR_HIP;

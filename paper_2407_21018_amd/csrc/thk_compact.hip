@@ -8,19 +8,85 @@ namespace thk {
 // A run of rows of K_pruned is a run of bytes (dense rows, or rows with padding behind them,
 // which is written as zeros); the unit may start and end anywhere (see compact_rows).
 template <int DT>
-__global__ __launch_bounds__(256) void k_compact_flat(CompactArgs a) {
+__device__ __forceinline__ void compact_flat_block(const CompactArgs &a, uint32_t block, u32x4 *smem) {
   using E = Elem<DT>;
-  extern __shared__ u32x4 smem[];
+  constexpr int CPR = kD / E::VEC, TR = kCompactTileRows, NLD = TR * CPR / kWave;
   int16_t *tab = (int16_t *)smem;                         // [8 * T], padded to 2 KiB
-  const int64_t u = blockIdx.x / a.blocks_per_unit;
-  const int blk = (int)(blockIdx.x % a.blocks_per_unit);
+  const uint32_t u = block / (uint32_t)a.blocks_per_unit;
+  const int blk = (int)(block - u * (uint32_t)a.blocks_per_unit);
   const int64_t s0 = (int64_t)blk * a.rows_per_block;
-  const int64_t s1 = min(a.n_rows, s0 + a.rows_per_block);
+  const int n_rows = (int)min(a.n_rows - s0, a.rows_per_block);
+  const int lane = threadIdx.x % kWave;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  const char *src = (const char *)a.src + ((size_t)u * a.src_unit_rows + a.src_row0 + s0) * kD * E::EB;
+  u32x4 *tile = smem + 128 + wave * Tile<DT>::CHUNKS;
+  // A tile's rows are requested before the tile in front of it is gathered, the first tile's before the
+  // table is built: a short call is a chain of trips (64 units x 487 bf16 rows, T = 51: 7.7 -> 4.6 us),
+  // a long one is bounded by memory (64 x 32768 rows, T = 64: 5.7 TB/s).
+  u32x4 r[NLD];
+  auto request = [&](int row) {   // rows past the end of a ragged tile repeat its last one (never gathered)
+    const uint32_t last = (uint32_t)min(TR, n_rows - row) * CPR - 1u;
+#pragma unroll
+    for (int j = 0; j < NLD; ++j)
+      r[j] = ld_stream((const u32x4 *)(src + (size_t)row * (kD * E::EB) + min((uint32_t)(j * kWave + lane), last) * 16u));
+  };
+  int row = wave * TR;
+  if (row < n_rows) request(row);
   const FlatOut<DT> out((char *)a.dst + ((size_t)u * a.dst_unit_rows + a.dst_row0) * a.ld * E::EB);
   compact_build_tab<DT>(tab, a.idx + (size_t)u * a.T, a.T, a.ld, out.sh);
+  if (a.ld != a.T) tile_clear_padding<DT>(tile, lane);
   __syncthreads();
-  compact_rows<DT>((const u32x4 *)((const char *)a.src + ((size_t)u * a.src_unit_rows + a.src_row0) * kD * E::EB),
-                   out, s0, s1, a.T, a.ld, tab, smem + 128);
+  for (; row < n_rows; row += 4 * TR) {
+#pragma unroll
+    for (int j = 0; j < NLD; ++j) tile[Tile<DT>::slot(j * kWave + lane)] = r[j];
+    if (row + 4 * TR < n_rows) request(row + 4 * TR);
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    compact_emit_tile<DT>(tile, out, s0 + row, min(TR, n_rows - row), a.ld, tab, lane);
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+  }
+}
+
+template <int DT>
+__global__ __launch_bounds__(256) void k_compact_flat(CompactArgs a) {
+  extern __shared__ u32x4 smem[];
+  compact_flat_block<DT>(a, blockIdx.x, smem);
+}
+
+// A whole tail leaves for the pruned cache: the first n_compact blocks compact the keys, the others
+// copy the values, kFlushRows rows of a unit each (the other order is 10 % slower: the longer blocks
+// would come last).  One launch instead of two: the second one's dispatch and ramp weigh most on
+// small tails: 192 units x 128 rows 10.2 -> 6.6 us, 64 x 32 rows 5.7 -> 4.3 us, 1024 x 128 rows
+// 24.4 -> 23.6 us (bounded by memory: 121 MB, 5.1 TB/s).
+constexpr int kFlushRows = 64;
+struct FlushCopy {
+  const void *src;
+  void *dst;
+  int64_t src_unit_rows, dst_unit_rows, dst_row0;
+  int32_t n_rows, blocks_per_unit;
+};
+template <int DT>
+__global__ __launch_bounds__(256) void k_flush(CompactArgs a, FlushCopy c, uint32_t n_compact) {
+  extern __shared__ u32x4 smem[];
+  if (blockIdx.x < n_compact) {
+    compact_flat_block<DT>(a, blockIdx.x, smem);
+    return;
+  }
+  constexpr int CPR = kD / Elem<DT>::VEC, PER = kFlushRows * CPR / 256;   // 16-byte chunks per row, per thread
+  const uint32_t block = blockIdx.x - n_compact;
+  const uint32_t u = block / (uint32_t)c.blocks_per_unit;
+  const int r0 = (int)(block - u * (uint32_t)c.blocks_per_unit) * kFlushRows;
+  const int total = min(kFlushRows, c.n_rows - r0) * CPR;
+  const u32x4 *s = (const u32x4 *)c.src + ((size_t)u * c.src_unit_rows + r0) * CPR;
+  u32x4 *d = (u32x4 *)c.dst + ((size_t)u * c.dst_unit_rows + c.dst_row0 + r0) * CPR;
+  u32x4 r[PER];
+#pragma unroll
+  for (int j = 0; j < PER; ++j) r[j] = ld_stream(s + min(j * 256 + (int)threadIdx.x, total - 1));
+#pragma unroll
+  for (int j = 0; j < PER; ++j)
+    if (j * 256 + (int)threadIdx.x < total) st_stream(d + j * 256 + threadIdx.x, r[j]);
 }
 
 // Full-width row copy dst[u][dst_row0 + r][:] = src[u][src_row0 + r][:], r < n_rows.
@@ -104,12 +170,8 @@ __global__ __launch_bounds__(256) void k_tail_append(const void *__restrict__ k_
   ((u32x4 *)v_dst)[((size_t)u * v_unit_rows + v_row) * CPR + c] = ((const u32x4 *)v_new)[i];
 }
 
-hipError_t launch_compact(int dtype, const void *src, int64_t src_unit_rows, int64_t src_row0,
-                          const int16_t *idx, void *dst, int64_t dst_unit_rows, int64_t dst_row0,
-                          int64_t U, int64_t n_rows, int T, int ld_keep, hipStream_t st) {
-  clear_stale_hip_error();
-  if (n_rows <= 0) return hipSuccess;
-  const int eb = dtype == THK_BF16 ? 2 : 4;
+static CompactArgs compact_args(const void *src, int64_t src_unit_rows, int64_t src_row0, const int16_t *idx, void *dst,
+                                int64_t dst_unit_rows, int64_t dst_row0, int64_t U, int64_t n_rows, int T, int ld_keep) {
   CompactArgs a;
   a.src = src; a.dst = dst; a.idx = idx;
   a.src_unit_rows = src_unit_rows; a.src_row0 = src_row0;
@@ -121,12 +183,57 @@ hipError_t launch_compact(int dtype, const void *src, int64_t src_unit_rows, int
   a.rows_per_block = 512;
   while (a.rows_per_block > 128 && U * ((n_rows + a.rows_per_block - 1) / a.rows_per_block) < 4 * kCUs) a.rows_per_block /= 2;
   a.blocks_per_unit = (int)((n_rows + a.rows_per_block - 1) / a.rows_per_block);
+  return a;
+}
+
+hipError_t launch_compact(int dtype, const void *src, int64_t src_unit_rows, int64_t src_row0,
+                          const int16_t *idx, void *dst, int64_t dst_unit_rows, int64_t dst_row0,
+                          int64_t U, int64_t n_rows, int T, int ld_keep, hipStream_t st) {
+  clear_stale_hip_error();
+  if (n_rows <= 0) return hipSuccess;
+  const int eb = dtype == THK_BF16 ? 2 : 4;
+  CompactArgs a = compact_args(src, src_unit_rows, src_row0, idx, dst, dst_unit_rows, dst_row0, U, n_rows, T, ld_keep);
   const dim3 grid((unsigned)(U * a.blocks_per_unit)), block(256);
   const size_t lds = 2048 + 4 * compact_tile_bytes(eb);
   void *kargs[] = {(void *)&a};
   const void *fn = dtype == THK_BF16 ? (const void *)k_compact_flat<THK_BF16> : (const void *)k_compact_flat<THK_F32>;
   const hipError_t e = launch_main_kernel(fn, grid, block, kargs, lds, st);
   return e != hipSuccess ? e : hipGetLastError();
+}
+
+// The whole key tail compacted and the whole value tail copied.  false: not a call for one launch
+// (ranges that may touch, more rows than the copy numbers, more blocks than a grid); nothing is done then.
+bool launch_flush(int dtype, const void *k_tail, const void *v_tail, int64_t tail_cap, const int16_t *idx, void *k_pruned,
+                  void *v, int64_t unit_rows, int64_t dst_row0, int64_t U, int64_t n_rows, int T, int ld_keep,
+                  hipStream_t st, hipError_t *err) {
+  const size_t eb = dtype == THK_BF16 ? 2 : 4;
+  const auto apart = [](const void *x, size_t nx, const void *y, size_t ny) {
+    return (const char *)x + nx <= (const char *)y || (const char *)y + ny <= (const char *)x;
+  };
+  const size_t n_tail = (size_t)U * tail_cap * kD * eb, n_v = (size_t)U * unit_rows * kD * eb;
+  const size_t n_k = (size_t)U * unit_rows * ld_keep * eb;
+  if (n_rows < 1 || n_rows > (1 << 20)) return false;
+  // one after the other, the two launches also serve buffers that share memory
+  if (!apart(v_tail, n_tail, v, n_v) || !apart(k_tail, n_tail, v, n_v) || !apart(v_tail, n_tail, k_pruned, n_k) ||
+      !apart(v, n_v, k_pruned, n_k))
+    return false;
+  CompactArgs a = compact_args(k_tail, tail_cap, 0, idx, k_pruned, unit_rows, dst_row0, U, n_rows, T, ld_keep);
+  FlushCopy c;
+  c.src = v_tail; c.dst = v; c.src_unit_rows = tail_cap; c.dst_unit_rows = unit_rows; c.dst_row0 = dst_row0;
+  c.n_rows = (int32_t)n_rows;
+  c.blocks_per_unit = (int)((n_rows + kFlushRows - 1) / kFlushRows);
+  const int64_t n_compact = U * a.blocks_per_unit, grid = n_compact + U * c.blocks_per_unit;
+  if (grid > 0x7fffffff) return false;
+  clear_stale_hip_error();
+  uint32_t nc = (uint32_t)n_compact;
+  void *kargs[] = {(void *)&a, (void *)&c, (void *)&nc};
+  const void *fn = dtype == THK_BF16 ? (const void *)k_flush<THK_BF16> : (const void *)k_flush<THK_F32>;
+  const size_t lds = 2048 + 4 * compact_tile_bytes((int)eb);
+  static DynLds set[2];
+  hipError_t e = ensure_dyn_lds(fn, lds, set[dtype == THK_BF16 ? 1 : 0]);
+  if (e == hipSuccess) e = launch_main_kernel(fn, dim3((unsigned)grid), dim3(256), kargs, lds, st);
+  *err = e != hipSuccess ? e : hipGetLastError();
+  return true;
 }
 
 hipError_t launch_copy_rows(int dtype, const void *src, int64_t src_unit_rows, int64_t src_row0, void *dst,

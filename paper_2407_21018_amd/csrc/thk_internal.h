@@ -180,6 +180,9 @@ struct CompactArgs {
 hipError_t launch_compact(int dtype, const void *src, int64_t src_unit_rows, int64_t src_row0,
                           const int16_t *idx, void *dst, int64_t dst_unit_rows, int64_t dst_row0,
                           int64_t U, int64_t n_rows, int T, int ld_keep, hipStream_t st);
+bool launch_flush(int dtype, const void *k_tail, const void *v_tail, int64_t tail_cap, const int16_t *idx, void *k_pruned,
+                  void *v, int64_t unit_rows, int64_t dst_row0, int64_t U, int64_t n_rows, int T, int ld_keep,
+                  hipStream_t st, hipError_t *err);
 hipError_t launch_copy_rows(int dtype, const void *src, int64_t src_unit_rows, int64_t src_row0, void *dst,
                             int64_t dst_unit_rows, int64_t dst_row0, int64_t U, int64_t n_rows,
                             hipStream_t st);

@@ -161,3 +161,28 @@ def test_decode_over_a_growing_cache(dtype, G, T, unified, decode_merge):
     # the value rows ended up in token order in the value cache (+ tail)
     got_v = as_numpy(vc)[:, :S_p] if not unified else as_numpy(vc)[:, :S_p + s_tail]
     np.testing.assert_array_equal(got_v, h_v[:, :got_v.shape[1]])
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("rows,cap,T,ld", [(1, 4, 51, 0), (63, 64, 76, 0), (64, 64, 64, 0), (65, 96, 51, 56), (128, 128, 77, 0),
+                                           (200, 200, 128, 0), (513, 520, 33, 0)])
+def test_flush_of_a_whole_tail(rows, cap, T, ld, dtype):
+    """All of a tail leaves at once (one launch compacts the keys and copies the values): the edges of
+    the copy's 64-row and the compaction's 32- and 128-row blocks; nothing else is written."""
+    tdt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    B, N, S, room = 1, 3, 37, rows + 5
+    g = torch.Generator(device="cuda"); g.manual_seed(rows + T)
+    rnd = lambda *d: torch.randn(*d, generator=g, device="cuda").to(tdt)
+    kt, vt = rnd(B, N, cap, 128), rnd(B, N, cap, 128)
+    pitch = ld or T
+    kp, v = rnd(B, N, S + room, pitch), rnd(B, N, S + room, 128)
+    idx = torch.rand(B, N, 128, generator=g, device="cuda").argsort(-1)[..., :T].sort(-1).values.to(torch.int16)
+    want_k, want_v = kp.clone(), v.clone()
+    want_k[:, :, S:S + rows] = 0
+    want_k[:, :, S:S + rows, :T] = kt[:, :, :rows].gather(3, idx.long()[:, :, None].expand(B, N, rows, T))
+    want_v[:, :, S:S + rows] = vt[:, :, :rows]
+    shape = thk.make_shape(1, B, N, N, 128, S, 1, T, ld, thk.THK_BF16 if dtype == "bf16" else thk.THK_F32, 0, 0, S + room)
+    thk.thk_tail_flush(shape, idx.contiguous(), kp, kt, v, vt, rows, cap, rows)
+    torch.cuda.synchronize()
+    assert torch.equal(kp, want_k)
+    assert torch.equal(v, want_v)
