@@ -617,6 +617,36 @@ __device__ __forceinline__ void block_merge_store(const float *mrg, int wstride,
 }
 
 // KB: 16-byte K chunks a lane may have to stage for one TR-row pruned tile.
+// Which (unit, piece, head group) a workgroup takes.  Where the heads of a KV head need several
+// groups, the blocks that read the SAME keys and values are 8 workgroup numbers apart: workgroup i
+// runs on XCD i % 8, so they share an L2 and are dispatched one after the other, and all but the
+// first find the rows there.  With the groups n_split numbers apart: bf16, 64 units x 16384 rows x 12
+// heads, 4 pieces, 136 -> 110 us; 28 units x 20000 rows x 16 heads, 9 pieces, 76.0 -> 59.2 us; where
+// n_split is a multiple of 8 the XCD was the same already and nothing changes (16 units x 32768 rows x
+// 16 heads 62 / 61 us, fp32 64 units x 9527 rows x 8 heads 137 / 135-143 us).
+// False: a surplus workgroup of the rounded-up grid.  (fewer than 2^31 blocks: 32-bit divisions)
+struct DecodeWork {
+  uint32_t u;   // (layer, batch, KV head)
+  int sp, gi;
+};
+template <bool MANY>   // a unit may have more than one head group
+__device__ __forceinline__ bool decode_block_work(const DecodeArgs &a, int groups, DecodeWork &w) {
+  uint32_t piece = blockIdx.x;   // (unit, piece of S)
+  w.gi = 0;
+  if (MANY && groups > 1) {
+    const uint32_t slot = piece / kXcds, round = slot / (uint32_t)groups;
+    w.gi = (int)(slot - round * (uint32_t)groups);
+    piece = round * kXcds + piece % kXcds;
+  }
+  w.u = piece / (uint32_t)a.n_split;
+  w.sp = (int)(piece - w.u * (uint32_t)a.n_split);
+  return !MANY || w.u < (uint32_t)a.units;
+}
+inline unsigned decode_grid(const DecodeArgs &a, int groups) {
+  const int64_t pieces = a.units * a.n_split;
+  return (unsigned)(groups == 1 ? pieces : (pieces + kXcds - 1) / kXcds * kXcds * groups);
+}
+
 // WPE: resident waves per SIMD the register budget is set for.
 // VP = 1: the value rows of the pruned segment hold only the T_v kept channels (a.v is
 // V_pruned with rows a.ld_v elements apart, a.idx_v lists the channels).  Their bytes are staged
@@ -654,10 +684,10 @@ __global__ __launch_bounds__(256, WPE) void k_decode(DecodeArgs a, int groups, i
     vpd.rsub = vpd.active ? lane / lprv : 0;   // idle lanes repeat row group 0; their sums are dropped
   }
 
-  const int sp = (int)(blockIdx.x % a.n_split);
-  const int64_t ug = blockIdx.x / a.n_split;
-  const int gi = (int)(ug % groups);
-  const int64_t u = ug / groups;             // (layer, batch, KV head)
+  DecodeWork work;
+  if (!decode_block_work<GT == 4>(a, groups, work)) return;   // fewer: all heads of a unit
+  const int sp = work.sp, gi = work.gi;
+  const int64_t u = work.u;
   const int G = a.N_q / a.N_kv;
   const int64_t bn0 = u * G + (int64_t)gi * GT;   // first query head served (heads of unit u: u*G ..)
   // the unit's last block may have fewer than GT heads left: the other slots carry a zero query
@@ -806,7 +836,7 @@ __global__ __launch_bounds__(256, WPE) void k_decode(DecodeArgs a, int groups, i
   }
   __syncthreads();
 
-  block_merge_store<DT, GT>(mrg, GT * (kD + 2), a, bn0, sp, hb, ug, &s_last);
+  block_merge_store<DT, GT>(mrg, GT * (kD + 2), a, bn0, sp, hb, u * groups + gi, &s_last);
 }
 
 // ---- host side: pick the instantiation for a shape --------------------------
@@ -835,7 +865,7 @@ inline hipError_t decode_launch_one(const DecodeArgs &a, int groups, hipStream_t
   const int tailbuf = kTailRows * kD * eb;
   if (kbuf < tailbuf) kbuf = tailbuf;
   const size_t lds = (size_t)(3 * GT * kQS + 4 * GT * (kD + 2)) * 4 + 4 * ((size_t)kbuf + GT * (TR + (VP ? kPsPad : 0)) * 4);
-  const dim3 grid((unsigned)(a.units * groups * a.n_split)), block(256);
+  const dim3 grid(decode_grid(a, groups)), block(256);
   {
     static DynLds set;   // one per instantiation
     const hipError_t e = ensure_dyn_lds((const void *)k_decode<DT, GT, RA, KB, TR, WPE, VP>, lds, set);

@@ -331,11 +331,10 @@ __global__ __launch_bounds__(256, WPE) void k_decode_mq(DecodeArgs a, int groups
   char *pline = slab + slab_bytes;               // 512 bytes of probabilities per head group
   __shared__ int s_last;
 
-  // (the grid has fewer than 2^31 blocks: 32-bit divisions)
-  const uint32_t ug = blockIdx.x / (uint32_t)a.n_split;
-  const int sp = (int)(blockIdx.x - ug * (uint32_t)a.n_split);
-  const int64_t u = groups == 1 ? ug : ug / (uint32_t)groups;   // (layer, batch, KV head)
-  const int gi = (int)(ug - (uint32_t)u * (uint32_t)groups);
+  DecodeWork work;
+  if (!decode_block_work<NH == 2>(a, groups, work)) return;   // four slots: all heads of a unit
+  const int sp = work.sp, gi = work.gi;
+  const int64_t u = work.u;
   const int G = (int)((uint32_t)a.N_q / (uint32_t)a.N_kv);
   const int64_t bn0 = u * G + (int64_t)gi * GT;
   const int hb = min(GT, G - gi * GT);   // head slots in use; the others carry a zero query
@@ -488,7 +487,7 @@ __global__ __launch_bounds__(256, WPE) void k_decode_mq(DecodeArgs a, int groups
     }
   }
   __syncthreads();
-  block_merge_store<DT, GT>((const float *)wbase, (slab_bytes + 512 * NH) / 4, a, bn0, sp, hb, ug, &s_last);
+  block_merge_store<DT, GT>((const float *)wbase, (slab_bytes + 512 * NH) / 4, a, bn0, sp, hb, u * groups + gi, &s_last);
 }
 
 // Four blocks per compute unit with the narrow staging class and four heads per block (37 KB of
@@ -499,7 +498,7 @@ static hipError_t mq_launch(const DecodeArgs &a, int groups, hipStream_t st) {
   constexpr int WPE = (KB <= 5 && NH == 1) ? 4 : (KB > 5 && NH == 2) ? 2 : 3;
   const int slab = KB * kWave * 16 > kMqVBytes ? KB * kWave * 16 : kMqVBytes;
   const size_t lds = (size_t)(2 * 4 * NH * (kQS / 2)) * 4 + 4 * ((size_t)slab + 512 * NH);
-  const dim3 grid((unsigned)(a.units * groups * a.n_split)), block(256);
+  const dim3 grid(decode_grid(a, groups)), block(256);
   {
     static DynLds set;   // one per instantiation
     const hipError_t e = ensure_dyn_lds((const void *)k_decode_mq<KB, WPE, VP, NH, AL>, lds, set);

@@ -13,6 +13,7 @@ namespace thk {
 constexpr int kD = 128;     // channels per head (the only size built)
 constexpr int kWave = 64;   // wavefront width on CDNA4
 constexpr int kCUs = 256;   // compute units of an MI355X
+constexpr int kXcds = 8;    // workgroup i of a launch runs on XCD i % 8, each XCD behind an L2 of its own
 
 // 16 bytes as a native vector: register arrays of this type are promoted to VGPRs reliably
 // (arrays of the uint4 class type are copied member-wise through memcpy and can end up in scratch).

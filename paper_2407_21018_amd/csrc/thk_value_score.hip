@@ -74,8 +74,6 @@ __device__ __forceinline__ void softmax_step(f32x16 &s, int64_t kb, int h, int64
   softmax_exp(s, scale_log2, m_run);
 }
 
-constexpr int kXcds = 8;   // workgroup i of a launch runs on XCD i % 8, each XCD behind an L2 of its own
-
 // Which (query block, S piece, unit) a workgroup takes.  With one query block per unit the
 // order is plain.  With several (more than 128 query rows per KV head) the blocks that stream
 // the SAME keys and values are placed 8 workgroup numbers apart: same XCD, dispatched one after

@@ -538,3 +538,28 @@ def test_device_is_the_one_the_kernels_are_written_for():
     assert p.multi_processor_count == 256 and p.warp_size == 64
     assert p.shared_memory_per_block == 160 * 1024
     assert p.total_memory >= 256 * 2**30
+
+
+@pytest.mark.parametrize("dtype,G,n_split,S", [("bf16", 9, 1, 300), ("bf16", 17, 3, 500), ("bf16", 24, 8, 1100), ("f32", 5, 1, 300),
+                                               ("f32", 9, 5, 700), ("f32", 12, 16, 2100)])
+def test_decode_several_head_groups(dtype, G, n_split, S, decode_merge):
+    """More heads per KV head than a block serves: the grid is laid out in eights and rounded up (numbers of
+    (unit, piece) pairs on both sides of a multiple of 8), every pair and group is served once."""
+    T, s_tail = 51, 5
+    for units in (1, 3, 8):
+        g = torch.Generator(device="cuda"); g.manual_seed(units * 100 + G)
+        rnd = lambda *d: torch.randn(*d, generator=g, device="cuda").to(TDT[dtype])
+        q, kp, v = rnd(1, units * G, 128), rnd(1, units, S, T), rnd(1, units, S, 128)
+        kt, vt = rnd(1, units, 16, 128), rnd(1, units, 16, 128)
+        idx = torch.rand(1, units, 128, generator=g, device="cuda").argsort(-1)[..., :T].sort(-1).values.to(torch.int16).contiguous()
+        out = torch.full_like(q, float("nan"))
+        shape = thk.make_shape(1, 1, units * G, units, 128, S, 1, T, 0, DT[dtype], n_split)
+        ws = ws_tensor(thk.thk_workspace_bytes(shape, thk.THK_OP_DECODE))
+        thk.thk_decode_attn(shape, q, kp, idx, v, kt, vt, s_tail, 16, out, ws)
+        qd, kd, vd = q.double()[0].view(units, G, 128), kp.double()[0], v.double()[0]
+        qk = qd.gather(2, idx.long()[0][:, None].expand(units, G, T))
+        logits = torch.cat([(qk[:, :, None] * kd[:, None]).sum(-1), (qd[:, :, None] * kt.double()[0, :, None, :s_tail]).sum(-1)], -1)
+        p = torch.softmax(logits / 128 ** 0.5, -1)
+        allv = torch.cat([vd, vt.double()[0, :, :s_tail]], 1)
+        ref = torch.stack([p[u] @ allv[u] for u in range(units)]).view(1, units * G, 128)
+        assert attn_rel_err(out, ref[0].cpu().numpy()).max() <= ATTN_TOL[dtype], units
