@@ -53,7 +53,7 @@ typedef enum {
   THK_ERR_SHAPE = 2,       /* a size is out of range or inconsistent           */
   THK_ERR_UNSUPPORTED = 3, /* valid in principle, not built (D != 128, dtype)  */
   THK_ERR_ALIGN = 4,       /* a pointer is not 16-byte aligned                 */
-  THK_ERR_WORKSPACE = 5,   /* ws is NULL or smaller than thk_workspace_bytes   */
+  THK_ERR_WORKSPACE = 5,   /* ws is NULL or smaller than the call needs        */
   THK_ERR_HIP = 6,         /* the HIP runtime refused a launch                 */
   THK_ERR_SCRATCH = 7      /* thk_decode_attn_static: the shape needs more than
                               THK_STATIC_SCRATCH_BYTES of scratch                */
@@ -119,6 +119,12 @@ int32_t thk_keep_count(int32_t D, double lambda);
  * Bytes of caller-provided scratch that `op` needs for `shape` (including the
  * shape's n_split; 0 there means the library's own choice, which this function
  * reproduces).  Returns 0 for an invalid shape.  Host-only arithmetic.
+ * The library's choice of pieces, and with it the size, may be larger for a shorter S.  A
+ * sequence that grows or a buffer for prompts of any length needs no more than the size
+ * at the largest S all the same: with n_split = 0 the decode and value-score calls
+ * (THK_OP_DECODE, THK_OP_SCORE_VALUE, and the score inside THK_OP_PRUNE_VALUE) take fewer pieces
+ * where the workspace holds no more of them -- the same result up to the rounding of the merge
+ * -- and only a workspace below what any longer S reports is refused.
  */
 size_t thk_workspace_bytes(const thk_shape *shape, int32_t op);
 

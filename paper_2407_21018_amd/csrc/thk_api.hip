@@ -1,6 +1,7 @@
 // C ABI of libthk: argument checks, workspace carving, launch sizing.
 // Everything here is host code; no entry point allocates or synchronises.
 #include <math.h>
+#include <stdint.h>
 #include <stdlib.h>
 
 #include <algorithm>
@@ -192,8 +193,8 @@ unsigned long long next_nonce() {
 // a head group) where that saves more than it costs -- see decode_merge_in_launch below.
 bool decode_merge_in_launch(const thk_shape *s, int n_split);
 
-// The number of pieces with the least estimated time, if that is at least 8 % below the estimate for
-// n0.  With k = steps of a piece and L = blocks on the fullest compute unit, in us:
+// The number of pieces (no fewer than least) with the least estimated time, if that is at least 8 %
+// below the estimate for n0.  With k = steps of a piece and L = blocks on the fullest compute unit, in us:
 //     max(k t_step, L k t_stream) + 0.5 L + merge
 // t_step: a step (128 rows by four waves) that waits for its own loads, 2.4, times 1.6 for fp32 and
 // 1.35 where a block serves eight heads; t_stream: a compute unit's share of the memory rate, 0.04 per KB
@@ -204,7 +205,7 @@ bool decode_merge_in_launch(const thk_shape *s, int n_split);
 // 2.3 %.  What they miss is rounds (136 units x 5184 rows: 4 pieces are 544 blocks, 3 on some compute
 // units and 2 on others; 7 pieces: 62.4 -> 54.5 us) and whole steps (16 units x 1815 rows, 15
 // pieces of one step instead of 8: 11.0 -> 9.5 us).
-int decode_pieces(const thk_shape *s, int hpb, int64_t wgs, int64_t steps, int n0) {
+int decode_pieces(const thk_shape *s, int hpb, int64_t wgs, int64_t steps, int n0, int least) {
   constexpr int kMaxPieces = 128;
   // more pieces only while the records fit the scratch array of thk_decode_attn_static, which takes
   // every call that n0 pieces fit
@@ -224,7 +225,7 @@ int decode_pieces(const thk_shape *s, int hpb, int64_t wgs, int64_t steps, int n
   // more than eight blocks per compute unit never pay
   const int64_t top = std::min<int64_t>({steps, kMaxPieces, std::max<int64_t>(n0, 8 * (int64_t)kCUs / wgs), std::max<int64_t>(fit, 1)});
   int64_t k_last = 0;
-  for (int64_t i = 1; i <= top; ++i) {
+  for (int64_t i = least; i <= top; ++i) {
     const int64_t k = (steps + i - 1) / i;
     if (k == k_last) continue;   // the same pieces, some of them empty
     k_last = k;
@@ -234,7 +235,17 @@ int decode_pieces(const thk_shape *s, int hpb, int64_t wgs, int64_t steps, int n
   return (int)n_best;
 }
 
-Split decode_split(const thk_shape *s) {
+// ws_bytes: what the caller's workspace holds.  The estimate's count goes up and down with S, so a
+// workspace asked for at a sequence's final length can hold fewer pieces than a shorter length
+// would take; a call then takes the pieces that fit, down to an eighth of the count n0 that the estimate
+// starts from, and to two.  n0 never falls with S, the estimate takes a quarter of it or more (of 12000
+// calls of one to eight heads over 256 .. 131072 rows 12 wanted less, 15 pieces instead of 16), and
+// cutting n pieces into whole 64-row runs leaves more than half of them (a piece has at least 127 rows):
+// the workspace of the final length serves every shorter one.  Less than that is refused.  One piece,
+// which needs no workspace, is taken only where n0 is 1 and by calls of at least 128 blocks per piece
+// under 4096 rows (beyond, the estimate wants it of calls of over 500 blocks, to save 2-4 %): those
+// are served with any workspace.
+Split decode_split(const thk_shape *s, size_t ws_bytes = SIZE_MAX) {
   int n = s->n_split;
   const int G = s->N_q / s->N_kv;
   const int64_t wgs = units_of(s) * ceil_div(G, decode_heads_per_block(s));
@@ -260,7 +271,11 @@ Split decode_split(const thk_shape *s) {
       n *= 2;
     }
     if (n == 1 && s->S >= 2048) n = 2;
-    if (s->S > one_block_rows || units_of(s) > 8) n = decode_pieces(s, hpb, wgs, steps, n);
+    const int n0 = n;
+    const bool one = n0 == 1 || (wgs >= kCUs / 2 && s->S < 4096);
+    if (s->S > one_block_rows || units_of(s) > 8) n = decode_pieces(s, hpb, wgs, steps, n0, one ? 1 : std::max(2, n0 / 4));
+    const int64_t fit = (int64_t)std::min<size_t>(ws_bytes / decode_ws_bytes(s, 1), (size_t)n);
+    if (fit < n && fit >= (one ? 0 : std::max(2, n0 / 8))) n = std::max((int)fit, 1);
   }
   int64_t rows = ceil_div(s->S, n);
   rows = ceil_div(rows, 64) * 64;
@@ -385,12 +400,20 @@ bool value_compact_in_bursts(const thk_shape *s, const FusedPlan &fp) {
 // each; more pieces only add merge work -- one layer of config 2: 65 us with 8 pieces per
 // unit, 54-55 us with 2-4), and few enough that the merge kernel's weight table (at most 256
 // pieces) fits.
-Split value_split(const thk_shape *s) {
+Split value_cut(const thk_shape *s, int n) {
+  int64_t rows = ceil_div(s->S, n);
+  rows = ceil_div(rows, 128) * 128;
+  return {(int)ceil_div(s->S, rows), rows};   // empty pieces dropped
+}
+// least (may be null): the fewest pieces a call with a smaller workspace is cut into
+// instead, never more for a shorter S than what any longer one reports (as in decode_split; half of
+// the count that is independent of rounds, for the runs are whole 128-row chunks).
+Split value_split(const thk_shape *s, int *least = nullptr) {
   const int G = s->N_q / s->N_kv;
   const int QT = value_attn_qt(G, s->S_obs);
   const int nqt = (G * s->S_obs + 31) / 32;
   const int64_t blocks1 = units_of(s) * ceil_div(nqt, QT);
-  int n = s->n_split;
+  int n = s->n_split, floor_n = kMaxSplit;
   if (n == 0) {
     n = (int)ceil_div((int64_t)kCUs * 2, blocks1);
     // fp32: pieces down to one 128-row chunk (a block is one to four wavefronts bound by the
@@ -399,6 +422,7 @@ Split value_split(const thk_shape *s) {
     const int64_t cap = ceil_div(s->S, s->dtype == THK_F32 ? 128 : 512);
     if (n > cap) n = (int)cap;
     if (n < 1) n = 1;
+    floor_n = n;
     if (s->dtype == THK_BF16 && QT == 4) {
       // The 8-wave kernel for grouped heads, one block per compute unit: the pieces that give the
       // shortest sum of rounds x (rows of a piece + 256 for its start, end and share of the merge).
@@ -412,13 +436,34 @@ Split value_split(const thk_shape *s) {
         const int64_t cost = ceil_div(b1 * c, kCUs) * (piece + 256);
         if (cost < best) { best = cost; n = (int)c; }
       }
+      floor_n = (int)std::min<int64_t>(cap, std::max<int64_t>(kCUs / b1, 1));   // the most that one round holds
     }
+    floor_n = std::max(std::min(floor_n, 256) / 2, 1);
   }
   if (n > 256) n = 256;
-  int64_t rows = ceil_div(s->S, n);
-  rows = ceil_div(rows, 128) * 128;
-  n = (int)ceil_div(s->S, rows);   // drop empty pieces
-  return {n, rows};
+  if (least != nullptr) *least = floor_n;
+  return value_cut(s, n);
+}
+
+// The value score's pieces in a workspace of ws_bytes, of which a call of n pieces takes bytes(s, n).
+Split value_split_in(const thk_shape *s, size_t ws_bytes, size_t (*bytes)(const thk_shape *, int)) {
+  int least = 1;
+  const Split want = value_split(s, &least);
+  for (int n = want.n; n >= least; --n) {
+    const Split sp = value_cut(s, n);
+    if (bytes(s, sp.n) <= ws_bytes) return sp;
+  }
+  return want;
+}
+
+size_t value_ws_bytes(const thk_shape *s, int n) {
+  return value_part_bytes(units_of(s), s->N_q / s->N_kv, s->S_obs, n);
+}
+size_t prune_value_ws_bytes(const thk_shape *s, int n) {
+  size_t a = value_ws_bytes(s, n);
+  const FusedPlan fp = fused_plan(s);
+  if (value_compact_in_bursts(s, fp)) a = std::max(a, prune_fused_ws_bytes(units_of(s), fp.NB));
+  return ((a + 15) & ~(size_t)15) + (size_t)units_of(s) * kD * sizeof(float);
 }
 
 size_t score_ws_bytes(const thk_shape *s, int64_t units) {
@@ -517,14 +562,10 @@ size_t thk_workspace_bytes(const thk_shape *s, int32_t op) {
     }
     case THK_OP_SCORE_VALUE:
       if (s->S_obs < 1 || (int64_t)s->S_obs > s->S) return 0;
-      return value_part_bytes(units_of(s), s->N_q / s->N_kv, s->S_obs, value_split(s).n);
-    case THK_OP_PRUNE_VALUE: {
+      return value_ws_bytes(s, value_split(s).n);
+    case THK_OP_PRUNE_VALUE:
       if (s->S_obs < 1 || (int64_t)s->S_obs > s->S) return 0;
-      size_t a = value_part_bytes(units_of(s), s->N_q / s->N_kv, s->S_obs, value_split(s).n);
-      const FusedPlan fp = fused_plan(s);
-      if (value_compact_in_bursts(s, fp)) a = std::max(a, prune_fused_ws_bytes(units_of(s), fp.NB));
-      return ((a + 15) & ~(size_t)15) + (size_t)units_of(s) * kD * sizeof(float);
-    }
+      return prune_value_ws_bytes(s, value_split(s).n);
     case THK_OP_PRUNE: {
       // a score array for the whole call + the larger of the two paths' scratch
       const FusedPlan fp = fused_plan(s);
@@ -734,24 +775,21 @@ thk_status thk_prune(const thk_shape *s, const void *q_obs, const void *k, float
   return THK_OK;
 }
 
-// thk_score_value; with idx the selection too (the kernel that finishes a unit's score selects)
+// thk_score_value for a checked shape; with idx the selection too (the kernel that finishes a unit's score selects)
 static thk_status score_value_common(const thk_shape *s, const void *q_obs, const void *k, const void *v,
                                      int32_t causal, float *score_v, int16_t *idx, void *ws, size_t ws_bytes,
-                                     void *stream) {
-  thk_status st = check_shape(s, true);
-  if (st != THK_OK) return st;
+                                     size_t (*bytes)(const thk_shape *, int), void *stream) {
   if (q_obs == nullptr || k == nullptr || v == nullptr || score_v == nullptr) return THK_ERR_NULL;
   if (!aligned16(q_obs) || !aligned16(k) || !aligned16(v) || !aligned16(score_v)) return THK_ERR_ALIGN;
   if (causal != 0 && causal != 1) return THK_ERR_SHAPE;
   const int G = s->N_q / s->N_kv;
   if ((int64_t)G * s->S_obs > 32 * 1024) return THK_ERR_SHAPE;
-  const Split sp = value_split(s);
+  const Split sp = value_split_in(s, ws_bytes, bytes);
   const int QT = value_attn_qt(G, s->S_obs);
   // (the launch rounds the pieces up to a multiple of 8 where a unit has several query blocks)
   const int64_t grid = (units_of(s) * sp.n + 7) * ceil_div((G * s->S_obs + 31) / 32, QT);
   if (grid > kMaxGrid) return THK_ERR_SHAPE;
-  if (ws == nullptr || !aligned16(ws) || ws_bytes < thk_workspace_bytes(s, THK_OP_SCORE_VALUE))
-    return THK_ERR_WORKSPACE;
+  if (ws == nullptr || !aligned16(ws) || ws_bytes < bytes(s, sp.n)) return THK_ERR_WORKSPACE;
   if (failed(launch_value_score(s->dtype, q_obs, k, v, (float *)ws, score_v, idx, s->T, units_of(s), s->S, G, s->S_obs,
                          causal, sp.n, sp.rows, (hipStream_t)stream)))
     return THK_ERR_HIP;
@@ -760,7 +798,9 @@ static thk_status score_value_common(const thk_shape *s, const void *q_obs, cons
 
 thk_status thk_score_value(const thk_shape *s, const void *q_obs, const void *k, const void *v,
                            int32_t causal, float *score_v, void *ws, size_t ws_bytes, void *stream) {
-  return score_value_common(s, q_obs, k, v, causal, score_v, nullptr, ws, ws_bytes, stream);
+  const thk_status st = check_shape(s, true);
+  if (st != THK_OK) return st;
+  return score_value_common(s, q_obs, k, v, causal, score_v, nullptr, ws, ws_bytes, value_ws_bytes, stream);
 }
 
 thk_status thk_prune_value(const thk_shape *s, const void *q_obs, const void *k, const void *v,
@@ -771,11 +811,11 @@ thk_status thk_prune_value(const thk_shape *s, const void *q_obs, const void *k,
   if (idx_v == nullptr || v_pruned == nullptr) return THK_ERR_NULL;
   if (!aligned16(idx_v) || !aligned16(v_pruned) || (score_v != nullptr && !aligned16(score_v)))
     return THK_ERR_ALIGN;
-  const size_t need = thk_workspace_bytes(s, THK_OP_PRUNE_VALUE);
+  const size_t need = prune_value_ws_bytes(s, value_split_in(s, ws_bytes, prune_value_ws_bytes).n);
   if (ws == nullptr || !aligned16(ws) || ws_bytes < need) return THK_ERR_WORKSPACE;
   // the score array sits behind the value score's own scratch unless the caller wants it
   float *sc = score_v != nullptr ? score_v : (float *)((char *)ws + need - (size_t)units_of(s) * kD * sizeof(float));
-  st = score_value_common(s, q_obs, k, v, causal, sc, idx_v, ws, thk_workspace_bytes(s, THK_OP_SCORE_VALUE), stream);
+  st = score_value_common(s, q_obs, k, v, causal, sc, idx_v, ws, need, prune_value_ws_bytes, stream);
   if (st != THK_OK) return st;
   // Long calls compact through the one-pass prune kernels with the list given: their hand-off
   // makes the blocks of a unit store together, and the memory takes a unit's rows in one burst
@@ -797,7 +837,7 @@ static thk_status decode_common(const thk_shape *s, const void *q, const void *k
                                 const int16_t *idx, const void *v, const int16_t *idx_v, int32_t T_v,
                                 int32_t ld_v, const void *k_tail, const void *v_tail, int32_t s_tail,
                                 int32_t s_tail_cap, void *out, void *ws, size_t ws_bytes, void *stream) {
-  thk_status st = check_shape(s, false);
+  const thk_status st = check_shape(s, false);
   if (st != THK_OK) return st;
   if (q == nullptr || k_pruned == nullptr || idx == nullptr || v == nullptr || out == nullptr) return THK_ERR_NULL;
   if (s_tail < 0 || s_tail_cap < 0 || s_tail > s_tail_cap) return THK_ERR_SHAPE;
@@ -815,11 +855,11 @@ static thk_status decode_common(const thk_shape *s, const void *q, const void *k
   if (!aligned16(q) || !aligned16(k_pruned) || !aligned16(idx) || !aligned16(v) || !aligned16(out) ||
       (s_tail > 0 && (!aligned16(k_tail) || (v_tail != nullptr && !aligned16(v_tail)))))
     return THK_ERR_ALIGN;
-  const Split sp = decode_split(s);
+  const bool ws_usable = ws != nullptr && aligned16(ws);
+  const Split sp = decode_split(s, ws_usable ? ws_bytes : 0);
   const int G = s->N_q / s->N_kv;
   if (units_of(s) * ceil_div(G, decode_heads_per_block(s)) * sp.n > kMaxGrid) return THK_ERR_SHAPE;
-  if (sp.n > 1 && (ws == nullptr || !aligned16(ws) || ws_bytes < decode_ws_bytes(s, sp.n)))
-    return THK_ERR_WORKSPACE;
+  if (sp.n > 1 && (!ws_usable || ws_bytes < decode_ws_bytes(s, sp.n))) return THK_ERR_WORKSPACE;
   DecodeArgs a;
   a.q = q; a.kp = k_pruned; a.v = v; a.kt = k_tail; a.vt = v_tail; a.idx = idx; a.out = out;
   a.ws = (float *)ws;

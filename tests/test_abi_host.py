@@ -304,6 +304,41 @@ def test_default_decode_split_balances_rounds_and_stays_within_the_static_scratc
                         assert thk.thk_workspace_bytes(s, thk.THK_OP_DECODE) <= 8 << 20
 
 
+def _shorter_lengths(S_max):
+    return [s for s in sorted({1, 64, 128, 300, 321, 500, 769, 1000, 1024, 1025, 1815, 2047, 2048, 2176, 2816, 3264, 4032, 4160,
+                               4928, 5000, 8000, 8064, 12345, 16257, 30000, 32768} | {S_max - d for d in (1, 63, 64, 65, 128, 640)})
+            if 1 <= s < S_max]
+
+
+_GROWING = [  # B, N_q, N_kv, T, dtype, longest S
+    (3, 32, 32, 76, thk.THK_BF16, 16384), (3, 28, 4, 64, thk.THK_BF16, 8192), (1, 32, 32, 64, thk.THK_F32, 8192),
+    (17, 32, 8, 64, thk.THK_BF16, 5184), (5, 48, 4, 64, thk.THK_BF16, 4096), (17, 28, 4, 51, thk.THK_BF16, 8192),
+    (3, 8, 8, 51, thk.THK_F32, 4096), (1, 8, 8, 64, thk.THK_BF16, 1025), (2, 40, 8, 64, thk.THK_BF16, 131072),
+    (400, 32, 8, 51, thk.THK_BF16, 40000)]
+
+
+@pytest.mark.skipif(os.path.exists("/dev/kfd"), reason="accepted calls carry made-up addresses: host without a GPU only")
+@pytest.mark.parametrize("B,N_q,N_kv,T,dtype,S_max", _GROWING)
+def test_workspace_of_the_longest_sequence_serves_every_shorter_one(B, N_q, N_kv, T, dtype, S_max):
+    """A buffer sized for a sequence's final length is accepted at every length before it (the call then
+    ends at the launch, with no device to launch on); without one, or with far less, it is refused."""
+    A = 1 << 20
+    mk = lambda S: thk.make_shape(1, B, N_q, N_kv, 128, S, min(S, 32), T, 0, dtype, 0)
+    dec = lambda s, ws: _status(thk.thk_decode_attn, s, A, A, A, A, None, None, 0, 0, A, ws, stream=0)
+    sv = lambda s, ws: _status(thk.thk_score_value, s, A, A, A, 1, A, ws, stream=0)
+    pv = lambda s, ws: _status(thk.thk_prune_value, s, A, A, A, 1, A, A, A, ws, stream=0)
+    for call, op in ((dec, thk.THK_OP_DECODE), (sv, thk.THK_OP_SCORE_VALUE), (pv, thk.THK_OP_PRUNE_VALUE)):
+        held = thk.thk_workspace_bytes(mk(S_max), op)
+        for S in _shorter_lengths(S_max):
+            assert call(mk(S), (A, held)) == 6, (op, S, held, thk.thk_workspace_bytes(mk(S), op))
+        s = mk(S_max)
+        if thk.thk_default_split(s, op) > 1 or op != thk.THK_OP_DECODE:
+            assert call(s, (A, 16)) == 5 and call(s, None) == 5
+            s.n_split = thk.thk_default_split(s, op)         # the caller's own count: exactly what it needs
+            need = thk.thk_workspace_bytes(s, op)
+            assert call(s, (A, need)) == 6 and call(s, (A, need - 16)) == 5
+
+
 def test_plain_c_program_uses_the_boundary(tmp_path):
     """thk.h is a C header and libthk.so a C library: a gcc-built program with no C++ and no
     Python in it includes the one and links the other."""

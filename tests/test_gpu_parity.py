@@ -563,3 +563,29 @@ def test_decode_several_head_groups(dtype, G, n_split, S, decode_merge):
         allv = torch.cat([vd, vt.double()[0, :, :s_tail]], 1)
         ref = torch.stack([p[u] @ allv[u] for u in range(units)]).view(1, units * G, 128)
         assert attn_rel_err(out, ref[0].cpu().numpy()).max() <= ATTN_TOL[dtype], units
+
+
+@pytest.mark.parametrize("dtype,B,N_q,N_kv,T,S,S_max", [
+    ("bf16", 3, 32, 32, 76, 3264, 16384), ("bf16", 3, 28, 4, 64, 8000, 8192), ("bf16", 17, 32, 8, 51, 4928, 5184),
+    ("f32", 1, 32, 32, 64, 4032, 8192)])
+def test_decode_in_the_workspace_of_a_longer_sequence(dtype, B, N_q, N_kv, T, S, S_max):
+    """A workspace asked for at the final length holds fewer pieces than this length would take: the call is cut
+    into those, writes nothing behind the workspace, and gives the result of the full-size one."""
+    mk = lambda S: thk.make_shape(1, B, N_q, N_kv, 128, S, 1, T, 0, DT[dtype], 0)
+    shape, held = mk(S), thk.thk_workspace_bytes(mk(S_max), thk.THK_OP_DECODE)
+    need = thk.thk_workspace_bytes(shape, thk.THK_OP_DECODE)
+    assert held < need
+    g = torch.Generator(device="cuda"); g.manual_seed(S + B)
+    rnd = lambda *d: torch.randn(*d, generator=g, device="cuda").to(TDT[dtype])
+    q, kp, v = rnd(B, N_q, 128), rnd(B, N_kv, S, T), rnd(B, N_kv, S, 128)
+    kt, vt = rnd(B, N_kv, 16, 128), rnd(B, N_kv, 16, 128)
+    idx = torch.rand(B, N_kv, 128, generator=g, device="cuda").argsort(-1)[..., :T].sort(-1).values.to(torch.int16).contiguous()
+    outs = []
+    for nbytes in (need, held):
+        ws = torch.full((need + 4096,), 0xA5, dtype=torch.uint8, device="cuda")
+        out = torch.full_like(q, float("nan"))
+        thk.thk_decode_attn(shape, q, kp, idx, v, kt, vt, 5, 16, out, (ws, nbytes))
+        torch.cuda.synchronize()
+        assert (ws[nbytes:] == 0xA5).all()
+        outs.append(out)
+    assert attn_rel_err(outs[1], outs[0].double().cpu().numpy()).max() <= ATTN_TOL[dtype]

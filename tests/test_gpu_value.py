@@ -390,3 +390,29 @@ def test_prune_keys_and_values_then_decode(dtype, G, S, lam_k, lam_v, causal):
                             want_idx_v.reshape(B, N_kv, T_v), dtype, as_numpy(kt).reshape(B, N_kv, cap, D),
                             as_numpy(vt).reshape(B, N_kv, cap, D), s_tail)
     assert attn_rel_err(out, want.reshape(-1, D)).max() <= ATTN_TOL[dtype]
+
+
+@pytest.mark.parametrize("prune", [False, True])
+@pytest.mark.parametrize("dtype,B,N_q,N_kv,S,S_max", [("bf16", 17, 28, 4, 6272, 6400), ("f32", 3, 8, 8, 2816, 2944)])
+def test_value_score_in_the_workspace_of_a_longer_sequence(dtype, B, N_q, N_kv, S, S_max, prune):
+    """The workspace of the longest prompt holds fewer pieces than this one would take: fewer are used, nothing is
+    written behind it, and the score is that of the full-size workspace up to the rounding of the merge."""
+    mk = lambda S: thk.make_shape(1, B, N_q, N_kv, D, S, 32, 64, 0, DT[dtype], 0)
+    op = thk.THK_OP_PRUNE_VALUE if prune else thk.THK_OP_SCORE_VALUE
+    shape, held, need = mk(S), thk.thk_workspace_bytes(mk(S_max), op), thk.thk_workspace_bytes(mk(S), op)
+    assert held < need
+    q_obs, k, v = (_randn(d, dtype, 600 + i) for i, d in enumerate([(1, B, N_q, 32, D), (1, B, N_kv, S, D), (1, B, N_kv, S, D)]))
+    scores = []
+    for nbytes in (need, held):
+        ws = torch.full((need + 4096,), 0xA5, dtype=torch.uint8, device="cuda")
+        score = torch.full((B * N_kv, D), float("nan"), device="cuda")
+        if prune:
+            idx = torch.empty(B * N_kv, 64, dtype=torch.int16, device="cuda")
+            vp = torch.empty(B * N_kv, S, 64, dtype=v.dtype, device="cuda")
+            thk.thk_prune_value(shape, q_obs, k, v, 1, score, idx, vp, (ws, nbytes))
+        else:
+            thk.thk_score_value(shape, q_obs, k, v, 1, score, (ws, nbytes))
+        torch.cuda.synchronize()
+        assert (ws[nbytes:] == 0xA5).all()
+        scores.append(score.cpu().numpy().astype(np.float64))
+    check_score(scores[1], scores[0], None, N_q // N_kv, 32, f"S={S}", dtype)
