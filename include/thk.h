@@ -285,10 +285,11 @@ thk_status thk_prune(const thk_shape *shape, const void *q_obs, const void *k,
  * THK_DECODE_MERGE = kernel | fused in the environment overrides the choice.
  * bf16 caches with N_q / N_kv >= 3 run the two products on the matrix cores, here and in
  * thk_decode_attn_kv: four or eight query heads share every key and value byte a block
- * reads (probabilities as two bf16 terms, exact to 2^-16; accumulation in fp32; elements of
- * a padded row past T are masked, whatever they hold).  A key row pitch (ld_keep, or T when
- * rows are dense) that is a multiple of 4 elements is read as it lies; other pitches put each
- * operand together from two or three words, a few percent slower. THK_DECODE_MFMA=0 in the environment
+ * reads (accumulation in fp32; elements of a padded row past T are masked, whatever they
+ * hold).  With a key row pitch (ld_keep, or T when rows are dense) that is a multiple of 4
+ * elements, rows are read as they lie and a probability enters the product with V as two bf16
+ * terms (exact to 2^-16); with other pitches an operand is put together from two or three words
+ * and a probability keeps its 24 bits (three terms), a few percent slower. THK_DECODE_MFMA=0 in the environment
  * (for experiments and tests) keeps them on the general kernel.
  *   ws : THK_OP_DECODE bytes.
  */

@@ -14,12 +14,16 @@
 //            in rotated order so that the row reads spread over the LDS banks; the two halves
 //            are added with one cross-half exchange.
 //   softmax  lane 4 b + j owns head j and four rows: the running maximum is a per-lane scalar,
-//            reduced over the lanes of equal j.  A probability is split into two bf16 terms
-//            (p = hi + lo, exact to 2^-16), so that the matrix product loses nothing against
-//            the fp32 arithmetic of the other kernels.
+//            reduced over the lanes of equal j.  A probability is split into bf16 terms of 8 bits
+//            each: two (p = hi + lo, exact to 2^-16) for key rows a multiple of 4 elements apart;
+//            three, which are all of p's 24 bits, for other pitches: those calls came from the
+//            general kernel, whose product with V is fp32.  The third term costs a half more
+//            matrix instructions and probability reads in the second product (64 units, T = 51:
+//            32768 rows, G = 4 123.4 -> 124.2 us, G = 8 122.7 -> 124.4; 8191 rows, G = 8, 76 value
+//            channels 32.2 -> 34.6).
 //   values   block b <-> output channels 4 b .. + 3 (two instructions cover 128 channels).
 //            A_b = the four heads' probabilities of four rows, the same for every block (read
-//            back from a 512-byte LDS line); B_b = four value rows x four channels, which is a
+//            back from an LDS line of 256 bytes per term); B_b = four value rows x four channels, which is a
 //            transposed read of the row-major value tile: ds_read_b64_tr_b16 out of LDS, where
 //            the tile is staged with the two 128-byte halves of odd rows swapped (the four rows
 //            of one read then cover all banks).  D_b[i][j] accumulates head i, channel 4 b + j:
@@ -179,10 +183,10 @@ __device__ __forceinline__ void mq_logits(const char *slab, int shift, int nrows
     }
 }
 
-// Running softmax over the tile's logits; the probabilities go to pline as two bf16 terms:
-// bytes [0, 256) the leading terms, [256, 512) the remainders, entry 4 ks + head holding the
-// four rows 4 ks .. 4 ks + 3.
-template <int VP>
+// Running softmax over the tile's logits; the probabilities go to pline as NT bf16 terms:
+// bytes [0, 256) the leading terms, [256, 512) the next, then the third, entry 4 ks + head holding
+// the four rows 4 ks .. 4 ks + 3.
+template <int VP, int NT>
 __device__ __forceinline__ void mq_softmax(const f32x4 &d, int nrows, float scale, MqState &st, char *pline,
                                            int lane) {
   const int bb = (lane >> 2) & 7;
@@ -206,13 +210,15 @@ __device__ __forceinline__ void mq_softmax(const f32x4 &d, int nrows, float scal
       }
     }
   }
-  uint32_t hi[4], lo[4];
+  uint32_t hi[4], lo[4], lo2[4];
 #pragma unroll
   for (int r = 0; r < 4; ++r) {
     const float p = __builtin_amdgcn_exp2f(zz[r] - m_new);
     st.l += p;
     hi[r] = __float_as_uint(p) & 0xffff0000u;
-    lo[r] = __float_as_uint(p - __uint_as_float(hi[r])) & 0xffff0000u;
+    const float rem = p - __uint_as_float(hi[r]);
+    lo[r] = __float_as_uint(rem) & 0xffff0000u;
+    if constexpr (NT == 3) lo2[r] = __float_as_uint(rem - __uint_as_float(lo[r]));   // 8 bits are left: exact
   }
   // the lower half of the wave writes the leading terms, the upper half the remainders
   const bool up = lane >= 32;
@@ -220,11 +226,14 @@ __device__ __forceinline__ void mq_softmax(const f32x4 &d, int nrows, float scal
   w.x = up ? ((lo[0] >> 16) | lo[1]) : ((hi[0] >> 16) | hi[1]);
   w.y = up ? ((lo[2] >> 16) | lo[3]) : ((hi[2] >> 16) | hi[3]);
   *(uint2 *)(pline + lane * 8) = w;
+  if constexpr (NT == 3)
+    if (!up) *(uint2 *)(pline + 512 + lane * 8) = uint2{(lo2[0] >> 16) | (lo2[1] & 0xffff0000u), (lo2[2] >> 16) | (lo2[3] & 0xffff0000u)};
 }
 
 // acc += P . V for the tile whose value rows are in the slab; the probabilities of head group g
-// are in the 512 bytes at pline + 512 g.  The value operand is read once for all groups.
-template <int NH>
+// are in the 256 NT bytes at pline + 256 NT g, term by term.  The value operand is read once for all
+// groups.
+template <int NH, int NT>
 __device__ __forceinline__ void mq_values(const char *slab, const char *pline, int nrows, MqState (&st)[NH],
                                           int lane) {
   const int x = lane & 3, grp = lane >> 4, j = lane & 15, r = j >> 2, seg = j & 3;
@@ -237,22 +246,18 @@ __device__ __forceinline__ void mq_values(const char *slab, const char *pline, i
         (__attribute__((address_space(3))) s16x4 *)(vb0 + ks * 1024));
     const s16x4 b1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
         (__attribute__((address_space(3))) s16x4 *)(vb1 + ks * 1024));
-    s16x4 a_hi[NH], a_lo[NH];
+    s16x4 a[NT][NH];
 #pragma unroll
-    for (int g = 0; g < NH; ++g) {
-      a_hi[g] = *(const s16x4 *)(pa + g * 512 + ks * 32);
-      a_lo[g] = *(const s16x4 *)(pa + g * 512 + 256 + ks * 32);
-    }
+    for (int g = 0; g < NH; ++g)
 #pragma unroll
-    for (int g = 0; g < NH; ++g) {
-      st[g].acc[0] = mfma4(a_hi[g], b0, st[g].acc[0]);
-      st[g].acc[1] = mfma4(a_hi[g], b1, st[g].acc[1]);
-    }
+      for (int i = 0; i < NT; ++i) a[i][g] = *(const s16x4 *)(pa + (g * NT + i) * 256 + ks * 32);
 #pragma unroll
-    for (int g = 0; g < NH; ++g) {
-      st[g].acc[0] = mfma4(a_lo[g], b0, st[g].acc[0]);
-      st[g].acc[1] = mfma4(a_lo[g], b1, st[g].acc[1]);
-    }
+    for (int i = 0; i < NT; ++i)
+#pragma unroll
+      for (int g = 0; g < NH; ++g) {
+        st[g].acc[0] = mfma4(a[i][g], b0, st[g].acc[0]);
+        st[g].acc[1] = mfma4(a[i][g], b1, st[g].acc[1]);
+      }
   };
   if (nrows == kMqRows) {   // a whole tile: straight-line code, the reads of later rows overlap the products
 #pragma unroll
@@ -270,7 +275,7 @@ __device__ __forceinline__ void mq_values(const char *slab, const char *pline, i
 // or within the bytes that follow every slab, and only feeds kept-channel numbers >= T_v,
 // which nobody collects; a row past a ragged tile's end is read as the tile's last row, with
 // probability 0.
-template <int NH>
+template <int NH, int NT>
 __device__ __forceinline__ void mq_values_pruned(const char *slab, int shift, int pitch_bytes, int T_v,
                                                  const char *pline, int nrows, MqState (&st)[NH], int lane) {
   const int x = lane & 3, grp = lane >> 4, j = lane & 15, r = j >> 2, seg = j & 3;
@@ -281,22 +286,20 @@ __device__ __forceinline__ void mq_values_pruned(const char *slab, int shift, in
     s16x4 b1 = b0;
     if constexpr (wide)
       b1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4 *)(vrow + 128));
-    s16x4 a_hi[NH], a_lo[NH];
+    s16x4 a[NT][NH];
 #pragma unroll
-    for (int g = 0; g < NH; ++g) {
-      a_hi[g] = *(const s16x4 *)(pa + g * 512 + ks * 32);
-      a_lo[g] = *(const s16x4 *)(pa + g * 512 + 256 + ks * 32);
-    }
+    for (int g = 0; g < NH; ++g)
 #pragma unroll
-    for (int g = 0; g < NH; ++g) {
-      st[g].accp[0] = mfma4(a_hi[g], b0, st[g].accp[0]);
-      if constexpr (wide) st[g].accp[1] = mfma4(a_hi[g], b1, st[g].accp[1]);
-    }
+      for (int i = 0; i < NT; ++i) a[i][g] = *(const s16x4 *)(pa + (g * NT + i) * 256 + ks * 32);
+    // (three terms of eight heads: a read that runs ahead of the step before would not find registers)
+    if constexpr (NT * NH == 6) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int g = 0; g < NH; ++g) {
-      st[g].accp[0] = mfma4(a_lo[g], b0, st[g].accp[0]);
-      if constexpr (wide) st[g].accp[1] = mfma4(a_lo[g], b1, st[g].accp[1]);
-    }
+    for (int i = 0; i < NT; ++i)
+#pragma unroll
+      for (int g = 0; g < NH; ++g) {
+        st[g].accp[0] = mfma4(a[i][g], b0, st[g].accp[0]);
+        if constexpr (wide) st[g].accp[1] = mfma4(a[i][g], b1, st[g].accp[1]);
+      }
   };
   auto tile = [&](auto wide) {
     if (nrows == kMqRows) {   // straight-line code, the reads of later rows overlap the products
@@ -311,6 +314,8 @@ __device__ __forceinline__ void mq_values_pruned(const char *slab, int shift, in
   else tile(std::false_type{});
 }
 
+constexpr int mq_terms(int AL) { return AL == 8 ? 2 : 3; }   // bf16 terms of a probability
+
 // KB: 16-byte key chunks a lane may have to stage for one tile.  slab_bytes: the wave's LDS slab,
 // which holds a tile's key bytes and, once the logits are done, its value rows.
 // VP = 1: the value rows of the pruned segment are channel-pruned (a.v = V_pruned, a.ld_v, a.idx_v).
@@ -320,6 +325,7 @@ __device__ __forceinline__ void mq_values_pruned(const char *slab, int shift, in
 template <int KB, int WPE, int VP, int NH, int AL>
 __global__ __launch_bounds__(256, WPE) void k_decode_mq(DecodeArgs a, int groups, int slab_bytes) {
   constexpr int DT = THK_BF16, GT = 4 * NH, EB = 2, TR = kMqRows, LPR = 16;
+  constexpr int NT = mq_terms(AL), PB = 256 * NT;
   constexpr int KBT = kTailRows * kD * EB / 16 / kWave;   // chunks per lane of a tail tile
   extern __shared__ uint4 smem[];
   uint32_t *qkp = (uint32_t *)smem;                 // [GT][kQS/2] kept query channels, packed bf16, 0 beyond T
@@ -327,8 +333,8 @@ __global__ __launch_bounds__(256, WPE) void k_decode_mq(DecodeArgs a, int groups
   char *wbase = (char *)(qfp + GT * (kQS / 2));
   const int tid = threadIdx.x, lane = tid % kWave;
   const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);   // uniform: tile counts and branches stay scalar
-  char *slab = wbase + (size_t)wave * (slab_bytes + 512 * NH);
-  char *pline = slab + slab_bytes;               // 512 bytes of probabilities per head group
+  char *slab = wbase + (size_t)wave * (slab_bytes + PB * NH);
+  char *pline = slab + slab_bytes;               // PB bytes of probabilities per head group
   __shared__ int s_last;
 
   DecodeWork work;
@@ -409,7 +415,7 @@ __global__ __launch_bounds__(256, WPE) void k_decode_mq(DecodeArgs a, int groups
     f32x4 d[NH];
     mq_logits<NH, AL>(slab, shift, nrows, a.T, pitch_bytes, qkp + x * (kQS / 2), lane, d);
 #pragma unroll
-    for (int g = 0; g < NH; ++g) mq_softmax<VP>(d[g], nrows, a.scale_log2, st[g], pline + 512 * g, lane);
+    for (int g = 0; g < NH; ++g) mq_softmax<VP, NT>(d[g], nrows, a.scale_log2, st[g], pline + PB * g, lane);
     wave_sync_lds();   // the key bytes are consumed: the slab takes the value rows
     if constexpr (VP) {
       const int vs = vshift;
@@ -418,12 +424,12 @@ __global__ __launch_bounds__(256, WPE) void k_decode_mq(DecodeArgs a, int groups
         vshift = k_issue<DT, KB, true>(vrp, (const char *)a.v, (krow0 + (size_t)(ti + 4) * TR) * a.ld_v * EB, nr4, a.T_v,
                                  a.ld_v, lane);
       wave_sync_lds();
-      mq_values_pruned<NH>(slab, vs, a.ld_v * EB, a.T_v, pline, nrows, st, lane);
+      mq_values_pruned<NH, NT>(slab, vs, a.ld_v * EB, a.T_v, pline, nrows, st, lane);
     } else {
       mq_v_commit(vr, slab, lane);
       if (more) mq_v_issue(vr, vbase + (size_t)(ti + 4) * TR * LPR, nr4, lane);
       wave_sync_lds();
-      mq_values<NH>(slab, pline, nrows, st, lane);
+      mq_values<NH, NT>(slab, pline, nrows, st, lane);
     }
     wave_sync_lds();   // slab and pline are rewritten by the next tile
   }
@@ -443,11 +449,11 @@ __global__ __launch_bounds__(256, WPE) void k_decode_mq(DecodeArgs a, int groups
     f32x4 d[NH];
     mq_logits<NH, 8>(slab, 0, nrows, kD, kD * EB, qfp + x * (kQS / 2), lane, d);
 #pragma unroll
-    for (int g = 0; g < NH; ++g) mq_softmax<VP>(d[g], nrows, a.scale_log2, st[g], pline + 512 * g, lane);
+    for (int g = 0; g < NH; ++g) mq_softmax<VP, NT>(d[g], nrows, a.scale_log2, st[g], pline + PB * g, lane);
     wave_sync_lds();
     mq_v_commit(vr, slab, lane);
     wave_sync_lds();
-    mq_values<NH>(slab, pline, nrows, st, lane);
+    mq_values<NH, NT>(slab, pline, nrows, st, lane);
     wave_sync_lds();
   }
 
@@ -487,7 +493,7 @@ __global__ __launch_bounds__(256, WPE) void k_decode_mq(DecodeArgs a, int groups
     }
   }
   __syncthreads();
-  block_merge_store<DT, GT>((const float *)wbase, (slab_bytes + 512 * NH) / 4, a, bn0, sp, hb, u * groups + gi, &s_last);
+  block_merge_store<DT, GT>((const float *)wbase, (slab_bytes + PB * NH) / 4, a, bn0, sp, hb, u * groups + gi, &s_last);
 }
 
 // Four blocks per compute unit with the narrow staging class and four heads per block (37 KB of
@@ -497,7 +503,7 @@ template <int KB, int VP, int NH, int AL>
 static hipError_t mq_launch(const DecodeArgs &a, int groups, hipStream_t st) {
   constexpr int WPE = (KB <= 5 && NH == 1) ? 4 : (KB > 5 && NH == 2) ? 2 : 3;
   const int slab = KB * kWave * 16 > kMqVBytes ? KB * kWave * 16 : kMqVBytes;
-  const size_t lds = (size_t)(2 * 4 * NH * (kQS / 2)) * 4 + 4 * ((size_t)slab + 512 * NH);
+  const size_t lds = (size_t)(2 * 4 * NH * (kQS / 2)) * 4 + 4 * ((size_t)slab + 256 * mq_terms(AL) * NH);
   const dim3 grid(decode_grid(a, groups)), block(256);
   {
     static DynLds set;   // one per instantiation
@@ -523,9 +529,10 @@ static int mq_chunks(const DecodeArgs &a) {
 // True when the shape is one this kernel serves: bf16 and at least three query heads per KV head
 // (one or two share a key row cheaply enough on the vector units).  Key rows of any pitch: where it
 // is not a multiple of four elements an operand is put together from two or three words
-// (AL = 4, 2), which leaves the general kernel (four heads per block, vector arithmetic) far behind:
-// T = 51 dense, G = 4, 64 units x 32768 rows 149.6 -> 126.8 us, G = 8 244.8 -> 127.1 us; G = 7, 216
-// units x 1700 rows 72.7 -> 34.9 us; T = 70, G = 4, 144 units x 6847 rows 90.7 -> 80.0 us.
+// (AL = 4, 2) and a probability kept in three terms, which leaves the general kernel (four heads per
+// block, vector arithmetic) far behind: T = 51 dense, 64 units x 32768 rows, G = 4 142.5 -> 124.2 us,
+// G = 8 233 -> 124.4 us; G = 7, 216 units x 1700 rows 68.0 -> 33.6 us; T = 70, G = 4, 144 units x 6847
+// rows 84.5 -> 69.3 us (the last with seven pieces instead of four).
 // THK_DECODE_MFMA=0 in the environment keeps all shapes on k_decode.
 bool decode_mq_serves(const DecodeArgs &a) {
   if (a.dtype != THK_BF16 || a.N_kv <= 0) return false;

@@ -589,3 +589,48 @@ def test_decode_in_the_workspace_of_a_longer_sequence(dtype, B, N_q, N_kv, T, S,
         assert (ws[nbytes:] == 0xA5).all()
         outs.append(out)
     assert attn_rel_err(outs[1], outs[0].double().cpu().numpy()).max() <= ATTN_TOL[dtype]
+
+
+@pytest.mark.parametrize("G", [4, 7])
+@pytest.mark.parametrize("T,ld", [(51, 0), (70, 0), (127, 0), (51, 53)])
+@pytest.mark.parametrize("second_row", ["pruned", "tail", "pruned values"])
+def test_decode_probabilities_keep_24_bits_at_any_row_pitch(second_row, T, ld, G):
+    """Two rows with nearly equal logits and opposite values: the output is the difference of the two
+    probabilities, about 2^-13 of them, so what the kernel drops of a probability shows.  Key rows that are
+    not a multiple of 4 elements apart (T = 128: the narrowest such pitch, T - 1 kept) are to keep all
+    24 bits.  Bound per element: the bf16 rounding of the result, 2^-8 |out|, and 2^-20 of sum(p |v|) for
+    fp32 logits (a few units of 2^-24 of at most 8 in the log2 domain) and an exp2 of one unit."""
+    U, pitch = 64, ld or T
+    g = torch.Generator(device="cuda"); g.manual_seed(T + G)
+    rnd = lambda *d: torch.randn(*d, generator=g, device="cuda").to(torch.bfloat16)
+    idx = torch.rand(U, 128, generator=g, device="cuda").argsort(-1)[:, :T].sort(-1).values.to(torch.int16).contiguous()
+    q, k1, x = rnd(U, G, 128), torch.zeros(U, 128, device="cuda", dtype=torch.bfloat16), rnd(U, 128)
+    k1.scatter_(1, idx.long(), rnd(U, T))
+    c0 = idx[:, :1].long()
+    k1.scatter_(1, c0, torch.ones_like(c0, dtype=torch.bfloat16))        # one kept channel: 1 in the first row,
+    k2 = k1.clone()
+    k2.scatter_(1, c0, torch.full_like(c0, 1 + 2**-7, dtype=torch.bfloat16))   # the next bf16 in the second
+    keys, vals = torch.stack([k1, k2], 1), torch.stack([x, -x], 1)       # [U, 2, 128]
+    S = 1 if second_row == "tail" else 2
+    kp = torch.full((U, S, pitch), float("nan"), device="cuda", dtype=torch.bfloat16)
+    kp[..., :T] = keys[:, :S].gather(2, idx.long()[:, None].expand(U, S, T))
+    kt, vt = keys[:, 1:].contiguous(), vals[:, 1:].contiguous()
+    shape = thk.make_shape(1, U, G, 1, 128, S, 1, T, ld, thk.THK_BF16, 1)
+    out = torch.full_like(q, float("nan"))
+    ws = ws_tensor(thk.thk_workspace_bytes(shape, thk.THK_OP_DECODE))
+    tail = (kt, vt, 1, 1) if second_row == "tail" else (None, None, 0, 0)
+    if second_row == "pruned values":
+        iv = torch.arange(128, device="cuda", dtype=torch.int16).repeat(U, 1)
+        thk.thk_decode_attn_kv(shape, q, kp, idx, vals, iv, 128, 128, None, None, 0, 0, out, ws)
+    else:
+        thk.thk_decode_attn(shape, q, kp, idx, vals[:, :S].contiguous(), *tail, out, ws)
+    qk = torch.zeros(U, G, 128, dtype=torch.float64, device="cuda")
+    il = idx.long()[:, None].expand(U, G, T)
+    qk.scatter_(2, il, q.double().gather(2, il))
+    qs = torch.stack([qk, q.double() if second_row == "tail" else qk], 2)          # the query each row meets
+    p = torch.softmax((qs * keys.double()[:, None]).sum(-1) / 128 ** 0.5, -1)      # [U, G, 2]
+    ref = (p[..., None] * vals.double()[:, None]).sum(2)
+    size = (p[..., None] * vals.double().abs()[:, None]).sum(2)
+    worst = ((out.double() - ref).abs() / (2**-8 * ref.abs() + 2**-20 * size)).max().item()
+    print(f"error over its bound: {worst:.3f}")
+    assert worst <= 1
