@@ -45,6 +45,7 @@ namespace thk {
 // What a block knows when solo_index_list returns.
 enum ListState { kGaveUp = 0, kHaveList = 1, kFinisher = 2 };
 constexpr int kFinisherDone = 1 << 24;   // the finisher's closing ticket on the give-up counter
+constexpr unsigned long long kNormValid = 1ull << 63;   // mark of a published query norm
 constexpr int kSurePolls = 1 << 20;      // polls for something that is known to be in place
 constexpr int kInitPolls = 1 << 22;      // polls for the prologue's initialisation (a block that was dispatched earlier)
 
@@ -79,8 +80,11 @@ __device__ __forceinline__ void solo_prologue(const PruneFusedArgs &a, int64_t u
   }
   block_query_norm<DT, 4>(a.q_obs, u, a.G, a.S_obs, qn_l, hn);
   __syncthreads();
-  // the norms carry their own validity mark: a row block may want them before they are there
-  if (tid < kD) pub_store_marked(a.qn + (size_t)u * kD + tid, qn_l[tid]);
+  // the norms carry their own validity mark, the sign bit, which a sum of norms leaves free: a row
+  // block may want them before they are there
+  if (tid < kD)
+    __hip_atomic_store((unsigned long long *)a.qn + (size_t)u * kD + tid, (unsigned long long)__double_as_longlong(qn_l[tid]) | kNormValid,
+                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // The unit's query norm of channel tid (threads < 128) from `w`, the word loaded earlier (behind a
@@ -88,11 +92,11 @@ __device__ __forceinline__ void solo_prologue(const PruneFusedArgs &a, int64_t u
 __device__ __forceinline__ double query_norm_of(const PruneFusedArgs &a, int64_t u, unsigned long long w) {
   if (threadIdx.x >= kD) return 0.0;
   const double *p = a.qn + (size_t)u * kD + threadIdx.x;
-  for (int n = 0; (w & 1ull) == 0 && n < kSurePolls; ++n) {
+  for (int n = 0; (w & kNormValid) == 0 && n < kSurePolls; ++n) {
     __builtin_amdgcn_s_sleep(2);
     w = pub_load_bits(p);
   }
-  return __longlong_as_double((long long)(w & ~1ull));
+  return __longlong_as_double((long long)(w & ~kNormValid));
 }
 __device__ __forceinline__ unsigned long long query_norm_word(const PruneFusedArgs &a, int64_t u) {
   return threadIdx.x < kD ? pub_load_bits(a.qn + (size_t)u * kD + threadIdx.x) : 0ull;

@@ -634,3 +634,18 @@ def test_decode_probabilities_keep_24_bits_at_any_row_pitch(second_row, T, ld, G
     worst = ((out.double() - ref).abs() / (2**-8 * ref.abs() + 2**-20 * size)).max().item()
     print(f"error over its bound: {worst:.3f}")
     assert worst <= 1
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("S", [100, 700, 9000])
+def test_prune_query_norms_keep_53_bits(S, dtype, prune_launch):
+    """Three heads whose norms are 1, 2^-24 and 2^-52: their sum needs the last bit of an fp64, and with it the
+    score lies just above the middle of two fp32 numbers (without it, on the middle, which rounds down)."""
+    U, G = 2, 3
+    q_obs = torch.tensor([1.0, 2.0**-24, 2.0**-52], device="cuda").repeat(U)[None, None, :, None, None].expand(1, 1, U * G, 1, D)
+    k = torch.zeros(1, 1, U, S, D, device="cuda")
+    k[:, :, :, S // 2] = 1.0
+    shape = thk.make_shape(1, 1, U * G, U, D, S, 1, 64, 0, DT[dtype], 0)
+    score, idx, _ = gpu_prune(shape, q_obs.to(TDT[dtype]).contiguous(), k.to(TDT[dtype]))
+    assert (score == 1 + 2.0**-23).all()
+    assert (idx.cpu() == torch.arange(64, dtype=torch.int16)).all()      # all tie: the lowest channels
