@@ -254,6 +254,8 @@ thk_status thk_compact_keys(const thk_shape *shape, const void *k,
  * before a waiting block leaves its rows to the repair kernel or to the unit's
  * finisher; 0 forces that path), THK_PRUNE_STAGGER_NS (spacing of the first round's unit starts; 0 =
  * none), THK_PRUNE_GROUP_MIB (bytes of K per group of units in the staged form),
+ * THK_PRUNE_NORM_DELAY_US, THK_PRUNE_NORM_POLLS (single-launch form: the query norms come that
+ * much later, at most 500 us; looks for them, after which the scores are NaN),
  * THK_PRUNE_PROLOGUE_DELAY_US (single-launch form: the unit's prologue block starts
  * that late, at most 500 us, so that the row blocks find their arrival counters not
  * yet initialised and have to wait for them -- a path that otherwise needs an

@@ -44,6 +44,8 @@ const EnvSwitches *read_env() {
   const char *pl = getenv("THK_PRUNE_LAUNCH");
   s->prune_launch = pl != nullptr ? pl[0] : 0;
   s->prologue_delay_us = env_long_raw("THK_PRUNE_PROLOGUE_DELAY_US", 0);
+  s->norm_delay_us = env_long_raw("THK_PRUNE_NORM_DELAY_US", 0);
+  s->norm_polls = env_long_raw("THK_PRUNE_NORM_POLLS", -1);
   const char *mk = getenv("THK_DECODE_MERGE");
   s->decode_merge = mk != nullptr ? mk[0] : 0;
   const char *vc = getenv("THK_VALUE_COMPACT");

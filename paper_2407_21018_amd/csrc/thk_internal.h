@@ -130,6 +130,8 @@ struct EnvSwitches {
   bool decode_mfma_off;   // THK_DECODE_MFMA=0
   char prune_launch;      // first letter of THK_PRUNE_LAUNCH ('c'lassic: three launches, 's'olo: one), 0 = unset
   long prologue_delay_us; // THK_PRUNE_PROLOGUE_DELAY_US (test hook of the single-launch prune), <= 0 = none
+  long norm_delay_us;     // THK_PRUNE_NORM_DELAY_US (the same, in front of the query norms), <= 0 = none
+  long norm_polls;        // THK_PRUNE_NORM_POLLS (test hook: looks for the query norms), < 0 = unset
   char decode_merge;      // first letter of THK_DECODE_MERGE ('k'ernel: a second launch merges the split
                           // records, 'f'used: the last block of a head group merges), 0 = unset
   char value_compact;     // first letter of THK_VALUE_COMPACT ('f'lat: the plain compaction kernel,

@@ -49,6 +49,8 @@ struct PruneFusedArgs {
   int *gaveup;                 // [U] tickets: +1 per block that gave up, + kFinisherDone by the finisher
   int32_t poll_ticks;          // 64-cycle ticks between two looks of a waiting block
   int32_t prologue_delay;      // test hook: 64-cycle ticks the prologue block sleeps before it starts
+  int32_t norm_delay;          // ... and between the arrival counters and the query norms
+  int32_t norm_polls;          // looks for a query norm before a block goes on without
   int64_t U;                   // units of the call: blocks 0 .. U-1 are the prologue blocks, the row blocks follow
   int64_t S, RB;          // rows per unit, rows per block
   int64_t S_keep;         // rows [0, S_keep) of every unit are compacted

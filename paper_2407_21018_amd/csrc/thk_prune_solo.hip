@@ -23,8 +23,9 @@
 //     when the kernel starts.  The block that completes a counter stores 0 into it, so that a
 //     replay of the same launch from a graph, which carries the same nonce, does not mistake
 //     the previous replay's count for its own.
-//   * One block of every unit never waits: the FINISHER, whose arrival completes the unit's
-//     sums.  A block that gives up waiting raises a flag for its rows and draws a ticket from
+//   * One block of every unit waits for no other row block: the FINISHER, whose arrival completes
+//     the unit's sums.  (It may wait for the query norms of the prologue block, which has started
+//     and itself waits for nobody.)  A block that gives up waiting raises a flag for its rows and draws a ticket from
 //     the unit's give-up counter; the finisher draws the closing ticket, learns from it how
 //     many blocks gave up before, and compacts their rows after its own (re-reading them).
 //     A block that gives up later than that finds the closing ticket in the counter: the list is
@@ -46,7 +47,7 @@ namespace thk {
 enum ListState { kGaveUp = 0, kHaveList = 1, kFinisher = 2 };
 constexpr int kFinisherDone = 1 << 24;   // the finisher's closing ticket on the give-up counter
 constexpr unsigned long long kNormValid = 1ull << 63;   // mark of a published query norm
-constexpr int kSurePolls = 1 << 20;      // polls for something that is known to be in place
+constexpr int kSurePolls = 1 << 20;      // polls for what is in place or a running block is about to publish
 constexpr int kInitPolls = 1 << 22;      // polls for the prologue's initialisation (a block that was dispatched earlier)
 
 // ---- the prologue block --------------------------------------------------------------------
@@ -78,6 +79,8 @@ __device__ __forceinline__ void solo_prologue(const PruneFusedArgs &a, int64_t u
   } else if (tid == 0) {
     __hip_atomic_store(a.tctr + u * kCtrStep<unsigned long long>, a.nonce << 16, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
+  // test hook (THK_PRUNE_NORM_DELAY_US): the unit's sums are complete before its norms are
+  for (int t = a.norm_delay; t > 0; t -= 127) __builtin_amdgcn_s_sleep(127);
   block_query_norm<DT, 4>(a.q_obs, u, a.G, a.S_obs, qn_l, hn);
   __syncthreads();
   // the norms carry their own validity mark, the sign bit, which a sum of norms leaves free: a row
@@ -88,15 +91,17 @@ __device__ __forceinline__ void solo_prologue(const PruneFusedArgs &a, int64_t u
 }
 
 // The unit's query norm of channel tid (threads < 128) from `w`, the word loaded earlier (behind a
-// counter whose tag was there, i.e. after the prologue had cleared the words).
+// counter whose tag was there, i.e. after the prologue had cleared the words).  The prologue block is
+// running then and waits for nobody, so the word comes; if the looks run out all the same the
+// norm is NaN, and so is the score: no list is made of sums that lack their norms without a sign.
 __device__ __forceinline__ double query_norm_of(const PruneFusedArgs &a, int64_t u, unsigned long long w) {
   if (threadIdx.x >= kD) return 0.0;
   const double *p = a.qn + (size_t)u * kD + threadIdx.x;
-  for (int n = 0; (w & kNormValid) == 0 && n < kSurePolls; ++n) {
+  for (int n = 0; (w & kNormValid) == 0 && n < a.norm_polls; ++n) {
     __builtin_amdgcn_s_sleep(2);
     w = pub_load_bits(p);
   }
-  return __longlong_as_double((long long)(w & ~kNormValid));
+  return (w & kNormValid) != 0 ? __longlong_as_double((long long)(w & ~kNormValid)) : __builtin_nan("");
 }
 __device__ __forceinline__ unsigned long long query_norm_word(const PruneFusedArgs &a, int64_t u) {
   return threadIdx.x < kD ? pub_load_bits(a.qn + (size_t)u * kD + threadIdx.x) : 0ull;
@@ -495,6 +500,8 @@ hipError_t launch_prune_solo(int dtype, const void *q_obs, const void *k, float 
   a.nonce = next_nonce48();
   // at most 500 us, in 64-cycle ticks at about 2.4 GHz
   a.prologue_delay = (int32_t)(std::min(std::max(env_switches().prologue_delay_us, 0L), 500L) * 2400 / 64);
+  a.norm_delay = (int32_t)(std::min(std::max(env_switches().norm_delay_us, 0L), 500L) * 2400 / 64);
+  a.norm_polls = env_switches().norm_polls >= 0 ? (int32_t)std::min(env_switches().norm_polls, (long)kSurePolls) : kSurePolls;
   a.S = S; a.S_keep = S_keep; a.kp_unit_rows = kp_unit_rows; a.RB = RB; a.T = T; a.ld = ld; a.G = G;
   a.S_obs = S_obs; a.NB = NB; a.spin_limit = spin_limit;
   // Pause between two looks: 4 ticks while all blocks are resident at once (8 units x 5003 rows: a

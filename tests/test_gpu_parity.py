@@ -636,6 +636,40 @@ def test_decode_probabilities_keep_24_bits_at_any_row_pitch(second_row, T, ld, G
     assert worst <= 1
 
 
+
+@pytest.mark.parametrize("levels", [1, 2])
+def test_prune_single_launch_with_late_query_norms(levels, thk_env):
+    """The prologue publishes the query norms after the arrival counters, so a unit's sums can be complete before
+    its norms are there: held back from the host here, once behind blocks that wait for the list and once behind
+    blocks that give up at once.  A block that finds no norms in all its looks (THK_PRUNE_NORM_POLLS=1) must
+    not score with zeros: the scores are NaN, the list is one of valid channels, and the next call is right."""
+    thk_env.setenv("THK_PRUNE_LAUNCH", "solo")
+    if levels == 2:                                # 102 blocks of 128 rows per unit
+        thk_env.setenv("THK_PRUNE_BLOCK_ROWS", "128")
+    L, B, N, G, S, S_obs, T = (2, 2, 4, 2, 3000, 32, 76) if levels == 1 else (1, 2, 2, 1, 13008, 32, 64)
+    U = L * B * N
+    shape = thk.make_shape(L, B, N * G, N, D, S, S_obs, T, 0, thk.THK_BF16, 0)
+    assert thk.thk_prune_launches(shape) == 1
+    for rep, (delay, spin, polls) in enumerate([(200, None, None), (200, "0", None), (500, None, "1"), (0, None, None)]):
+        thk_env.setenv("THK_PRUNE_NORM_DELAY_US", str(delay))
+        for name, value in (("THK_PRUNE_SPIN_LIMIT", spin), ("THK_PRUNE_NORM_POLLS", polls)):
+            if value is None:
+                thk_env.delenv(name, raising=False)
+            else:
+                thk_env.setenv(name, value)
+        q_obs = _randn((L, B, N * G, S_obs, D), "bf16", 271 + rep, 1.0)
+        k = _randn((L, B, N, S, D), "bf16", 281 + rep, 1.0)
+        score, idx, kp = gpu_prune(shape, q_obs, k)
+        if polls is not None:
+            assert score.isnan().all() and (idx >= 0).all() and (idx < D).all()
+            continue
+        o_sc, o_idx, _ = oracle_prune(q_obs, k, "bf16", T)
+        rel = np.abs(score.cpu().numpy().astype(np.float64) - o_sc.reshape(U, D)) / o_sc.reshape(U, D)
+        assert rel.max() <= SCORE_TOL
+        check_idx_with_tie_rule(idx.cpu().numpy(), o_idx, o_sc, T)
+        np.testing.assert_array_equal(as_numpy(kp), O.compact_keys(as_numpy(k).reshape(U, S, D), idx.cpu().numpy(), "bf16"))
+
+
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 @pytest.mark.parametrize("S", [100, 700, 9000])
 def test_prune_query_norms_keep_53_bits(S, dtype, prune_launch):
