@@ -146,10 +146,8 @@ int32_t thk_prune_is_fused(const thk_shape *shape);
 int32_t thk_prune_launches(const thk_shape *shape);
 
 /* 1 if thk_decode_attn (T_v == 0) or thk_decode_attn_kv (value rows of T_v kept channels,
- * ld_v elements apart) would run `shape` on the matrix-core kernel k_decode_mq with key rows
- * whose pitch is a multiple of 4 elements; 0 if on the general kernel k_decode, on k_decode_mq's
- * variants for rows of other pitches, or if the shape is invalid.  Host-only; honours
- * THK_DECODE_MFMA. */
+ * ld_v elements apart) would run `shape` on the matrix-core kernel k_decode_mq, 0 if on the
+ * general kernel k_decode (or the shape is invalid).  Host-only; honours THK_DECODE_MFMA. */
 int32_t thk_decode_on_matrix_cores(const thk_shape *shape, int32_t T_v, int32_t ld_v);
 
 /*

@@ -550,7 +550,7 @@ int32_t thk_decode_on_matrix_cores(const thk_shape *s, int32_t T_v, int32_t ld_v
   DecodeArgs a = {};
   a.T = s->T; a.ldk = ld_of(s); a.N_q = s->N_q; a.N_kv = s->N_kv; a.dtype = s->dtype;
   a.T_v = T_v; a.ld_v = T_v > 0 ? ld_v : 0;
-  return decode_mq_serves(a) && a.ldk % 4 == 0 ? 1 : 0;   // other pitches: operands put together from words
+  return decode_mq_serves(a) ? 1 : 0;
 }
 
 size_t thk_workspace_bytes(const thk_shape *s, int32_t op) {

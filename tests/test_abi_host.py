@@ -232,7 +232,7 @@ def test_prune_launch_count_by_shape(thk_env):
 
 
 def test_decode_kernel_choice_by_shape(thk_env):
-    """bf16, query heads in groups of four, T and the row pitches multiples of 4: the matrix-core kernel."""
+    """bf16 and three or more query heads per KV head: the matrix-core kernel, with key rows of any pitch."""
     thk_env.delenv("THK_DECODE_MFMA", raising=False)
     mk = lambda N_q, N_kv, T, ld, dt: thk.make_shape(1, 1, N_q, N_kv, 128, 4096, 1, T, ld, dt, 0)
     assert thk.thk_decode_on_matrix_cores(mk(32, 8, 64, 0, thk.THK_BF16)) == 1
@@ -242,9 +242,9 @@ def test_decode_kernel_choice_by_shape(thk_env):
     assert thk.thk_decode_on_matrix_cores(mk(16, 8, 64, 0, thk.THK_BF16)) == 0        # two heads per KV head
     assert thk.thk_decode_on_matrix_cores(mk(24, 8, 64, 0, thk.THK_BF16)) == 1        # three: 3 of 4 slots
     assert thk.thk_decode_on_matrix_cores(mk(28, 4, 64, 0, thk.THK_BF16)) == 1        # seven: 7 of 8 slots
-    assert thk.thk_decode_on_matrix_cores(mk(32, 8, 51, 0, thk.THK_BF16)) == 0        # dense rows of 51: pitch not a multiple of 4
+    assert thk.thk_decode_on_matrix_cores(mk(32, 8, 51, 0, thk.THK_BF16)) == 1        # dense rows of 51: pitch not a multiple of 4
     assert thk.thk_decode_on_matrix_cores(mk(32, 8, 51, 52, thk.THK_BF16)) == 1       # the same rows padded to 52
-    assert thk.thk_decode_on_matrix_cores(mk(32, 8, 64, 66, thk.THK_BF16)) == 0       # pitch not a multiple of 4
+    assert thk.thk_decode_on_matrix_cores(mk(32, 8, 64, 66, thk.THK_BF16)) == 1       # pitch not a multiple of 4
     assert thk.thk_decode_on_matrix_cores(mk(32, 8, 64, 0, thk.THK_F32)) == 0
     assert thk.thk_decode_on_matrix_cores(mk(32, 8, 64, 0, thk.THK_BF16), 51, 52) == 1  # channel-pruned values
     assert thk.thk_decode_on_matrix_cores(mk(32, 8, 64, 0, thk.THK_BF16), 51, 51) == 0  # invalid pitch (below the ABI's multiple of 4)

@@ -157,7 +157,7 @@ DECODE_CASES = [
     (1, 1, 8, 2100, 64, 0, 5, 33, 64, 0.0),    # two groups of four heads
     (1, 2, 4, 1, 64, 0, 0, 0, 0, 1.0),
     (1, 2, 4, 1, 64, 0, 0, 1, 1, 1.0),
-    (1, 2, 4, 500, 64, 66, 0, 3, 8, 1.0),      # pitch not a multiple of 4: the general kernel
+    (1, 2, 4, 500, 64, 66, 0, 3, 8, 1.0),      # pitch not a multiple of 4
     (1, 1, 4, 4096, 76, 0, 0, 64, 64, 2.0),
     (1, 1, 4, 200, 124, 0, 0, 2, 4, 1.0),      # 248-byte rows: 8-byte aligned only
     (1, 1, 4, 200, 124, 128, 2, 0, 0, 1.0),    # the widest padded rows: pitch D
@@ -172,7 +172,7 @@ DECODE_CASES = [
     (1, 2, 5, 1300, 76, 0, 0, 0, 0, 1.0),      # 5 of 8
     (1, 1, 7, 650, 128, 0, 3, 17, 32, 0.0),    # 7 of 8, the wide staging class
     (1, 1, 9, 500, 64, 0, 0, 0, 0, 1.0),       # 8 + 1
-    (1, 2, 6, 800, 51, 0, 2, 9, 16, 1.0),      # T not a multiple of 4: general kernel, 4 + 2
+    (1, 2, 6, 800, 51, 0, 2, 9, 16, 1.0),      # T not a multiple of 4
     (1, 2, 5, 300, 51, 56, 0, 0, 0, 1.0),
 ]
 
@@ -232,6 +232,7 @@ def test_decode_matrix_cores_any_row_pitch(T, ld, G):
     """Key rows that are not a multiple of 4 elements apart: rows start on a word or in the middle of
     one, a row has fewer chunks than halves (T < 8), an odd chunk, a partial chunk, both or
     neither, and the rows of a ragged last tile and of the tail follow."""
+    assert thk.thk_decode_on_matrix_cores(thk.make_shape(1, 1, 3 * G, 3, D, 161, 1, T, ld, thk.THK_BF16, 0)) == 1
     err, out = _decode_case("bf16", 1, 3, G, 161, T, ld, 0, 19, 32, 1.0, 4000 + 7 * T + ld)
     assert np.isfinite(out.float().cpu().numpy()).all()
     assert err.max() <= ATTN_TOL["bf16"]
@@ -616,6 +617,7 @@ def test_decode_probabilities_keep_24_bits_at_any_row_pitch(second_row, T, ld, G
     kp[..., :T] = keys[:, :S].gather(2, idx.long()[:, None].expand(U, S, T))
     kt, vt = keys[:, 1:].contiguous(), vals[:, 1:].contiguous()
     shape = thk.make_shape(1, U, G, 1, 128, S, 1, T, ld, thk.THK_BF16, 1)
+    assert thk.thk_decode_on_matrix_cores(shape) == 1
     out = torch.full_like(q, float("nan"))
     ws = ws_tensor(thk.thk_workspace_bytes(shape, thk.THK_OP_DECODE))
     tail = (kt, vt, 1, 1) if second_row == "tail" else (None, None, 0, 0)

@@ -204,7 +204,7 @@ DECODE_CASES = [
     ("bf16", 16, 900, 76, 51, 52, 0, 0, 3),
     ("bf16", 3, 700, 64, 40, 40, 4, 8, 0),      # partly filled head groups
     ("bf16", 7, 500, 76, 90, 92, 0, 0, 2),
-    ("bf16", 5, 400, 51, 64, 64, 3, 4, 0),      # ... on the general kernel (T not a multiple of 4)
+    ("bf16", 5, 400, 51, 64, 64, 3, 4, 0),      # ... with key rows that are not a multiple of 4 elements apart
     ("f32", 3, 300, 64, 32, 32, 0, 0, 1),
     ("f32", 1, 1037, 64, 64, 64, 0, 0, 0),
     ("f32", 4, 900, 76, 51, 52, 9, 16, 4),
