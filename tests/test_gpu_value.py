@@ -416,3 +416,23 @@ def test_value_score_in_the_workspace_of_a_longer_sequence(dtype, B, N_q, N_kv, 
         assert (ws[nbytes:] == 0xA5).all()
         scores.append(score.cpu().numpy().astype(np.float64))
     check_score(scores[1], scores[0], None, N_q // N_kv, 32, f"S={S}", dtype)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("G,S,n_split,rising,log2_v", [
+    (1, 600, 1, True, 118),       # 600 weights of at most 1: sums below 2^128
+    (2, 600, 1, True, 118),
+    (1, 4096, 8, False, 117),     # 512 rows of equal weight a piece: 2^126 each, 2^129 in all
+    (1, 600, 1, True, -116), (1, 4096, 8, False, -116)])
+def test_value_score_of_extreme_values(G, S, n_split, rising, log2_v, dtype):
+    """Values near both ends of the number range: no weight is larger than 1, and pieces are normalised before they
+    are added, so that sums which fit with a maximum subtracted exactly still fit.  Keys that grow along the
+    sequence keep the maximum rising."""
+    ramp = torch.linspace(0.0, 1.0, S, device="cuda")[:, None] if rising else torch.zeros(S, 1, device="cuda")
+    q_obs = torch.full((1, 1, 2 * G, 8, D), 0.25, device="cuda").to(TDT[dtype])
+    k = (ramp * 2.5 + 0 * _randn((1, 1, 2, S, D), "f32", 701)).to(TDT[dtype])       # logits 0 .. 7
+    v = ((1 + 0.25 * _randn((1, 1, 2, S, D), "f32", 702).clamp(-2, 2)) * 2.0**log2_v).to(TDT[dtype])
+    shape = thk.make_shape(1, 1, 2 * G, 2, D, S, 8, 64, 0, DT[dtype], n_split)
+    got = gpu_score_value(shape, q_obs, k, v, 0).cpu().numpy().astype(np.float64)
+    want = O.score_value(as_numpy(q_obs), as_numpy(k), as_numpy(v), dtype, 0).reshape(2, D)
+    check_score(got, want, None, G, 8, f"G={G} S={S} 2^{log2_v}", dtype)
