@@ -248,8 +248,8 @@ thk_status thk_compact_keys(const thk_shape *shape, const void *k,
  * staged | fused | reread (the one-kernel form with the rows read twice);
  * THK_PRUNE_BLOCK_ROWS (rows per block; 128, 256 and 512 are held on chip),
  * THK_PRUNE_HOLD_ROWS (largest default block), THK_PRUNE_MAX_BLOCKS (blocks
- * per unit beyond which the staged form is taken), THK_PRUNE_SPIN_LIMIT (polls
- * before a waiting block leaves its rows to the repair kernel or to the unit's
+ * per unit beyond which the staged form is taken), THK_PRUNE_SPIN_LIMIT (polls, about
+ * half a microsecond each, before a waiting block leaves its rows to the repair kernel or to the unit's
  * finisher; 0 forces that path), THK_PRUNE_STAGGER_NS (spacing of the first round's unit starts; 0 =
  * none), THK_PRUNE_GROUP_MIB (bytes of K per group of units in the staged form),
  * THK_PRUNE_NORM_DELAY_US, THK_PRUNE_NORM_POLLS (single-launch form: the query norms come that

@@ -506,8 +506,13 @@ hipError_t launch_prune_solo(int dtype, const void *q_obs, const void *k, float 
   a.S_obs = S_obs; a.NB = NB; a.spin_limit = spin_limit;
   // Pause between two looks: 4 ticks while all blocks are resident at once (8 units x 5003 rows: a
   // quarter of a microsecond less from list to first store), 16 in longer launches, whose polls
-  // would queue among the streams.
-  a.poll_ticks = U * NB <= (int64_t)kCUs * (dtype == THK_BF16 ? 3 : 2) ? 4 : 16;
+  // would queue among the streams.  A look takes 0.25 us then instead of 0.53: twice as many keep the
+  // time after which a block resigns (4096 looks: 2.1 ms).
+  a.poll_ticks = 16;
+  if (U * NB <= (int64_t)kCUs * (dtype == THK_BF16 ? 3 : 2)) {
+    a.poll_ticks = 4;
+    a.spin_limit = (int32_t)std::min<int64_t>(2 * (int64_t)spin_limit, 0x7fffffff);
+  }
   a.stagger_blocks = 0; a.stagger_units = 1; a.stagger_ticks = 0;
   a.U = U;
   {

@@ -672,6 +672,31 @@ def test_prune_single_launch_with_late_query_norms(levels, thk_env):
         np.testing.assert_array_equal(as_numpy(kp), O.compact_keys(as_numpy(k).reshape(U, S, D), idx.cpu().numpy(), "bf16"))
 
 
+
+def test_prune_blocks_of_short_calls_wait_as_long_as_those_of_long_calls(thk_env):
+    """A block resigns after THK_PRUNE_SPIN_LIMIT polls of about half a microsecond, in calls of one round too, where it
+    looks twice as often: 1800 of them outlast norms that come 500 us late.  The give-up counters lie behind the
+    partial sums, the norms and two other counters, 256 bytes a unit; the finisher's closing ticket is 2^24."""
+    thk_env.setenv("THK_PRUNE_LAUNCH", "solo")
+    thk_env.setenv("THK_PRUNE_BLOCK_ROWS", "128")
+    thk_env.setenv("THK_PRUNE_NORM_DELAY_US", "500")
+    U, S, NB = 2, 3000, 24
+    shape = thk.make_shape(1, 1, U, U, D, S, 32, 64, 0, thk.THK_BF16, 0)
+    q_obs, k = _randn((1, 1, U, 32, D), "bf16", 291, 1.0), _randn((1, 1, U, S, D), "bf16", 292, 1.0)
+    score = torch.empty(U, D, dtype=torch.float32, device="cuda")
+    idx = torch.empty(U, 64, dtype=torch.int16, device="cuda")
+    kp = torch.empty(U, S, 64, dtype=torch.bfloat16, device="cuda")
+    first = U * NB * D * 8 + U * D * 8 + 2 * U * 256
+    resigned = {}
+    for spin in ("1800", "0"):
+        thk_env.setenv("THK_PRUNE_SPIN_LIMIT", spin)
+        ws = ws_tensor(thk.thk_workspace_bytes(shape, thk.THK_OP_PRUNE))
+        thk.thk_prune(shape, q_obs, k, score, idx, kp, ws)
+        torch.cuda.synchronize()
+        resigned[spin] = (ws[first:first + U * 256].view(torch.int32)[::64] - (1 << 24)).tolist()
+    assert resigned == {"1800": [0] * U, "0": [NB - 1] * U}
+
+
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 @pytest.mark.parametrize("S", [100, 700, 9000])
 def test_prune_query_norms_keep_53_bits(S, dtype, prune_launch):
