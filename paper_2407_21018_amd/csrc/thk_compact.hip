@@ -202,7 +202,8 @@ hipError_t launch_compact(int dtype, const void *src, int64_t src_unit_rows, int
 }
 
 // The whole key tail compacted and the whole value tail copied.  false: not a call for one launch
-// (ranges that may touch, more rows than the copy numbers, more blocks than a grid); nothing is done then.
+// (ranges that may touch, more rows than the copy numbers, more blocks than a grid: a launch of 2^32
+// work-items or more is cut short without an error); nothing is done then.
 bool launch_flush(int dtype, const void *k_tail, const void *v_tail, int64_t tail_cap, const int16_t *idx, void *k_pruned,
                   void *v, int64_t unit_rows, int64_t dst_row0, int64_t U, int64_t n_rows, int T, int ld_keep,
                   hipStream_t st, hipError_t *err) {
@@ -223,7 +224,7 @@ bool launch_flush(int dtype, const void *k_tail, const void *v_tail, int64_t tai
   c.n_rows = (int32_t)n_rows;
   c.blocks_per_unit = (int)((n_rows + kFlushRows - 1) / kFlushRows);
   const int64_t n_compact = U * a.blocks_per_unit, grid = n_compact + U * c.blocks_per_unit;
-  if (grid > 0x7fffffff) return false;
+  if (grid * 256 > 0xffffffffll) return false;
   clear_stale_hip_error();
   uint32_t nc = (uint32_t)n_compact;
   void *kargs[] = {(void *)&a, (void *)&c, (void *)&nc};

@@ -186,3 +186,22 @@ def test_flush_of_a_whole_tail(rows, cap, T, ld, dtype):
     torch.cuda.synchronize()
     assert torch.equal(kp, want_k)
     assert torch.equal(v, want_v)
+
+
+def test_flush_of_more_units_than_one_grid_numbers():
+    """8.4 million units of one tail row: compaction and copy blocks together are more work-items than one launch
+    may have (2^32), each alone is not."""
+    U, T = 8_400_000, 2
+    kt = torch.arange(U, device="cuda", dtype=torch.int32)[:, None, None].expand(U, 1, 128).to(torch.bfloat16)
+    vt = (-kt).contiguous()
+    kt = kt.contiguous()
+    kt[..., 127] = 7
+    kp = torch.full((U, 2, T), 5, device="cuda", dtype=torch.bfloat16)
+    v = torch.full((U, 2, 128), 5, device="cuda", dtype=torch.bfloat16)
+    idx = torch.tensor([3, 127], device="cuda", dtype=torch.int16).repeat(U, 1)
+    shape = thk.make_shape(1, 1, U, U, 128, 1, 1, T, 0, thk.THK_BF16, 0, 0, 2)
+    thk.thk_tail_flush(shape, idx, kp, kt, v, vt, 1, 1, 1)
+    torch.cuda.synchronize()
+    assert (kp[:, 0] == 5).all() and (v[:, 0] == 5).all()
+    assert torch.equal(kp[:, 1, 0], kt[:, 0, 3]) and (kp[:, 1, 1] == 7).all()
+    assert torch.equal(v[:, 1], vt[:, 0])
