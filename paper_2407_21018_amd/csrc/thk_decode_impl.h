@@ -624,7 +624,8 @@ __device__ __forceinline__ void block_merge_store(const float *mrg, int wstride,
 // heads, 4 pieces, 136 -> 110 us; 28 units x 20000 rows x 16 heads, 9 pieces, 76.0 -> 59.2 us; where
 // n_split is a multiple of 8 the XCD was the same already and nothing changes (16 units x 32768 rows x
 // 16 heads 62 / 61 us, fp32 64 units x 9527 rows x 8 heads 137 / 135-143 us).
-// False: a surplus workgroup of the rounded-up grid.  (fewer than 2^31 blocks: 32-bit divisions)
+// False: a surplus workgroup of the last eight, of which the grid ends with the last one that has work (it
+// may have up to 2^24 workgroups, and calls just below that are served).  (fewer than 2^31 blocks: 32-bit divisions)
 struct DecodeWork {
   uint32_t u;   // (layer, batch, KV head)
   int sp, gi;
@@ -643,8 +644,8 @@ __device__ __forceinline__ bool decode_block_work(const DecodeArgs &a, int group
   return !MANY || w.u < (uint32_t)a.units;
 }
 inline unsigned decode_grid(const DecodeArgs &a, int groups) {
-  const int64_t pieces = a.units * a.n_split;
-  return (unsigned)(groups == 1 ? pieces : (pieces + kXcds - 1) / kXcds * kXcds * groups);
+  const int64_t pieces = a.units * a.n_split, last = pieces % kXcds;   // last: pieces of an eight that is not full
+  return (unsigned)(groups == 1 || last == 0 ? pieces * groups : (pieces - last) * groups + (groups - 1) * kXcds + last);
 }
 
 // WPE: resident waves per SIMD the register budget is set for.

@@ -710,3 +710,19 @@ def test_prune_query_norms_keep_53_bits(S, dtype, prune_launch):
     score, idx, _ = gpu_prune(shape, q_obs.to(TDT[dtype]).contiguous(), k.to(TDT[dtype]))
     assert (score == 1 + 2.0**-23).all()
     assert (idx.cpu() == torch.arange(64, dtype=torch.int16)).all()      # all tie: the lowest channels
+
+
+@pytest.mark.parametrize("U,G", [(8388601, 9), (8388607, 16)])
+def test_decode_grid_rounded_to_eights_stays_within_one_launch(U, G):
+    """Units whose head groups come to just under 2^24 blocks, the most that one launch may have: laid out in eights they
+    must not be more.  One row each, so every head's output is that row."""
+    q = torch.zeros(U, G, 128, device="cuda", dtype=torch.bfloat16)
+    kp = torch.ones(U, 1, 4, device="cuda", dtype=torch.bfloat16)
+    v = (torch.arange(U, device="cuda") % 251).to(torch.bfloat16)[:, None, None].expand(U, 1, 128).contiguous()
+    idx = torch.arange(4, device="cuda", dtype=torch.int16).repeat(U, 1)
+    out = torch.full_like(q, -1.0)
+    shape = thk.make_shape(1, 1, U * G, U, 128, 1, 1, 4, 0, thk.THK_BF16, 1)
+    thk.thk_decode_attn(shape, q, kp, idx, v, None, None, 0, 0, out, ws_tensor(16))
+    torch.cuda.synchronize()
+    assert (out[:, 0] == v[:, 0]).all() and (out[:, G - 1] == v[:, 0]).all()
+    assert (out[:, 1:, 0] == v[:, 0, :1]).all()
