@@ -68,6 +68,8 @@ const EnvSwitches &env_switches() {
 }
 
 hipError_t launch_main_kernel(const void *fn, dim3 grid, dim3 block, void **args, size_t lds, hipStream_t st) {
+  // the runtime reduces 2^32 work-items or more modulo 2^32 without an error
+  if ((uint64_t)grid.x * block.x > 0xffffffffull) return hipErrorInvalidConfiguration;
   if (g_prof_start == nullptr || g_prof_stop == nullptr) return hipLaunchKernel(fn, grid, block, args, lds, st);
   const hipEvent_t e0 = g_prof_start, e1 = g_prof_stop;
   g_prof_start = g_prof_stop = nullptr;

@@ -726,3 +726,14 @@ def test_decode_grid_rounded_to_eights_stays_within_one_launch(U, G):
     torch.cuda.synchronize()
     assert (out[:, 0] == v[:, 0]).all() and (out[:, G - 1] == v[:, 0]).all()
     assert (out[:, 1:, 0] == v[:, 0, :1]).all()
+
+
+def test_launch_of_more_work_items_than_the_runtime_counts_is_refused():
+    """2^24 + 8 units of one row would be launched as 8 blocks."""
+    U = (1 << 24) + 8
+    q = torch.zeros(U, 1, 128, device="cuda", dtype=torch.bfloat16)
+    kp = torch.ones(U, 1, 4, device="cuda", dtype=torch.bfloat16)
+    idx = torch.arange(4, device="cuda", dtype=torch.int16).repeat(U, 1)
+    shape = thk.make_shape(1, 1, U, U, 128, 1, 1, 4, 0, thk.THK_BF16, 1)
+    with pytest.raises(thk.ThkError, match="status 6"):
+        thk.thk_decode_attn(shape, q, kp, idx, torch.ones_like(q), None, None, 0, 0, torch.empty_like(q), ws_tensor(16))
