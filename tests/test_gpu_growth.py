@@ -205,3 +205,39 @@ def test_flush_of_more_units_than_one_grid_numbers():
     assert (kp[:, 0] == 5).all() and (v[:, 0] == 5).all()
     assert torch.equal(kp[:, 1, 0], kt[:, 0, 3]) and (kp[:, 1, 1] == 7).all()
     assert torch.equal(v[:, 1], vt[:, 0])
+
+
+@pytest.mark.parametrize("where", ["its place in v", "v", "k_pruned", "keys in v"])
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_flush_of_a_whole_tail_with_shared_memory(where, dtype):
+    """Buffers that share an allocation take the two launches: a value tail that is already where it goes, one that
+    lies in unused rows of v or of K_pruned, and a key tail in unused rows of v."""
+    tdt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    S, rows, T = 40, 70, 64
+    cap = S + 3 * rows
+    g = torch.Generator(device="cuda"); g.manual_seed(9)
+    rnd = lambda *d: torch.randn(*d, generator=g, device="cuda").to(tdt)
+    kt, vt, kp, v = rnd(1, rows, 128), rnd(1, rows, 128), rnd(1, cap, T), rnd(1, cap, 128)
+    idx = torch.randperm(128, generator=g, device="cuda")[:T].sort().values.to(torch.int16)
+    keys, values = kt.clone(), vt.clone()
+    if where == "its place in v":
+        v[:, S:S + rows] = vt
+        vt = v[:, S:S + rows]
+    elif where == "v":
+        v[:, S + rows:S + 2 * rows] = vt
+        vt = v[:, S + rows:S + 2 * rows]
+    elif where == "k_pruned":     # two pruned rows hold one full one
+        kp[:, S + rows:S + 3 * rows] = vt.reshape(1, 2 * rows, T)
+        vt = kp[:, S + rows:S + 3 * rows].reshape(1, rows, 128)
+        assert vt.data_ptr() == kp.data_ptr() + (S + rows) * T * kp.element_size()
+    else:
+        v[:, S + 2 * rows:] = kt
+        kt = v[:, S + 2 * rows:]
+    want_k, want_v = kp.clone(), v.clone()
+    want_k[:, S:S + rows] = keys[..., idx.long()]
+    want_v[:, S:S + rows] = values
+    shape = thk.make_shape(1, 1, 1, 1, 128, S, 1, T, 0, thk.THK_BF16 if dtype == "bf16" else thk.THK_F32, 0, 0, cap)
+    thk.thk_tail_flush(shape, idx, kp, kt, v, vt, rows, rows, rows)
+    torch.cuda.synchronize()
+    assert torch.equal(kp, want_k)
+    assert torch.equal(v, want_v)
