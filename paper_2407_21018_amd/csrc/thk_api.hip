@@ -197,18 +197,24 @@ unsigned long long next_nonce() {
 // a head group) where that saves more than it costs -- see decode_merge_in_launch below.
 bool decode_merge_in_launch(const thk_shape *s, int n_split);
 
-// The number of pieces (no fewer than least) with the least estimated time, if that is at least 8 %
-// below the estimate for n0.  With k = steps of a piece and L = blocks on the fullest compute unit, in us:
-//     max(k t_step, L k t_stream) + 0.5 L + merge
-// t_step: a step (128 rows by four waves) that waits for its own loads, 2.4, times 1.6 for fp32 and
-// 1.35 where a block serves eight heads; t_stream: a compute unit's share of the memory rate, 0.04 per KB
-// of a step's rows; 0.5: what a block costs whatever its length; merge: nothing for one piece, 1.5
-// inside the launch, 3 and 0.03 per piece by the merge kernel.  Fitted to 64 shapes (a third of them
-// fp32, 1-8 heads per KV head, 4-248 units, 258-125958 rows) measured at every piece count with
-// whole steps: the powers of two above took 8.9 % more than the best count on average, this takes
-// 2.3 %.  What they miss is rounds (136 units x 5184 rows: 4 pieces are 544 blocks, 3 on some compute
-// units and 2 on others; 7 pieces: 62.4 -> 54.5 us) and whole steps (16 units x 1815 rows, 15
-// pieces of one step instead of 8: 11.0 -> 9.5 us).
+// The number of pieces (no fewer than least) with the least estimated time, if that is at least 9 %
+// below the estimate for n0.  With k = steps of a piece (128 rows by four waves), R = blocks that are
+// resident on a compute unit and L = blocks on the fullest one, in us:
+//     sum over rounds of resident blocks of max(k t_step, l k t_stream), l = R, in the last round what is
+//     left,  +  t_block L  +  merge
+// t_step: a step that waits for its own loads, 2.4, 2.7 where a block serves eight heads, 4.8 in fp32;
+// t_stream: a compute unit's share of the memory rate, 0.036 per KB of a step's rows (full-width values;
+// pruned ones are narrower, which the shape does not tell); t_block: what a block costs whatever its length,
+// 0.8, in fp32 3.4; merge: nothing for one piece, 3.5 inside the launch, by the merge kernel 4, 0.015 per
+// piece and 0.2 per thousand records.  Fitted to 570 random shapes (1-16 heads per KV head, 1-400 units,
+// 256-51200 rows, a third fp32, a quarter with pruned values), each measured at its piece counts with
+// whole steps.  On 290 other shapes it takes 1.7 % more than the best count on average, 5 of them over 5 %
+// more than the powers of two above would (worst: fp32, 16 units x 8 heads x 3423 rows, 35.2 against
+// 27.6 us); the powers of two take 9.8 % more.  What they miss is rounds (136 units x 5184 rows: 4 pieces
+// are 544 blocks, 3 on some compute units and 2 on others; 7 pieces: 62.4 -> 54.5 us) and whole steps (16
+// units x 1815 rows, 15 pieces of one step instead of 8: 11.0 -> 9.5 us).  (An estimate without R, with
+// cheaper blocks and one merge cost cut short calls too often: 192 units x 5 heads x 797 rows, T = 96, 4
+// pieces instead of 2: 25.3 -> 30.6 us.)
 int decode_pieces(const thk_shape *s, int hpb, int64_t wgs, int64_t steps, int n0, int least) {
   constexpr int kMaxPieces = 128;
   // more pieces only while the records fit the scratch array of thk_decode_attn_static, which takes
@@ -216,15 +222,20 @@ int decode_pieces(const thk_shape *s, int hpb, int64_t wgs, int64_t steps, int n
   const int64_t heads = (int64_t)s->L * s->B * s->N_q;
   const int64_t fit = (int64_t)THK_STATIC_SCRATCH_BYTES / ((kD + 2) * 4 + 8) / heads;
   if (n0 > 1 && n0 > fit) return n0;
-  const double t_step = 2.4 * (s->dtype == THK_F32 ? 1.6 : 1.0) * (hpb == 8 ? 1.35 : 1.0);
-  const double t_stream = 0.04 * 128 * (ld_of(s) + kD) * elem_bytes(s->dtype) / 1024.0;
+  const bool f32 = s->dtype == THK_F32, wide = ld_of(s) > 79;   // wide: the staging class of long rows
+  const int resident = f32 ? (hpb == 4 || wide ? 2 : 3) : (hpb == 8 ? 3 : 4) - (wide ? 1 : 0);
+  const double t_step = f32 ? 4.8 : hpb == 8 ? 2.7 : 2.4;
+  const double t_stream = 0.036 * 128 * (ld_of(s) + kD) * elem_bytes(s->dtype) / 1024.0;
+  const double t_block = f32 ? 3.4 : 0.8;
   auto cost = [&](int64_t n, int64_t k) {
-    const int64_t blocks = wgs * n;
-    const double L = (double)((blocks + kCUs - 1) / kCUs);
-    const double merge = n == 1 ? 0.0 : n <= kDecodeFuseMaxSplit && blocks <= 2 * kCUs ? 1.5 : 3.0 + 0.03 * (double)n;
-    return std::max((double)k * t_step, L * (double)k * t_stream) + 0.5 * L + merge;
+    const int64_t blocks = wgs * n, rounds = ceil_div(blocks, (int64_t)kCUs * resident);
+    auto round = [&](int64_t l) { return (double)k * std::max(t_step, (double)l * t_stream); };
+    const int64_t last = ceil_div(blocks - (rounds - 1) * kCUs * resident, kCUs);
+    const bool in_launch = n <= kDecodeFuseMaxSplit && blocks <= 2 * kCUs && hpb <= 4;
+    const double merge = n == 1 ? 0.0 : in_launch ? 3.5 : 4.0 + 0.015 * (double)n + 0.0002 * (double)(heads * n);
+    return (double)(rounds - 1) * round(resident) + round(last) + t_block * (double)ceil_div(blocks, kCUs) + merge;
   };
-  double best = 0.92 * cost(n0, ceil_div(ceil_div(s->S, n0), 128));
+  double best = 0.91 * cost(n0, ceil_div(ceil_div(s->S, n0), 128));
   int64_t n_best = n0;
   // more than eight blocks per compute unit never pay
   const int64_t top = std::min<int64_t>({steps, kMaxPieces, std::max<int64_t>(n0, 8 * (int64_t)kCUs / wgs), std::max<int64_t>(fit, 1)});

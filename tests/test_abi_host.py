@@ -292,6 +292,12 @@ def test_default_decode_split_balances_rounds_and_stays_within_the_static_scratc
     assert split(2, 32, 8, 1815) == 15                   # 16 units: 15 pieces of one step
     n = split(17, 32, 8, 5184, 76)
     assert -(-136 * n // 256) * -(-5184 // (128 * n)) < 3 * 11    # 136 units: less than 4 pieces' 3 rounds of 11 steps
+    # calls that more pieces make slower: short rows of many units, blocks beyond what is resident
+    assert split(24, 40, 8, 797, 96) <= 2                # 192 units x 5 heads: 2 pieces 25.3 us, 4 pieces 30.6
+    assert split(20, 56, 8, 434, 76) == 1                # 160 units x 7 heads: 14.1 us, 2 pieces 16.4
+    assert split(32, 48, 8, 447, 111) == 1               # 256 units x 6 heads: 20.5 us, 2 pieces 23.1
+    assert split(32, 40, 8, 391, 64, thk.THK_F32) == 1   # 256 units x 5 heads: 27.6 us, 2 pieces 36.8
+    assert split(1, 160, 32, 3582, 64, thk.THK_F32) == 8     # 32 units x 5 heads: 30.5 us, 4 pieces 36.6
     for B in (1, 3, 8, 32, 100, 400):
         for N_q, N_kv in ((8, 8), (32, 8), (64, 8), (64, 4), (40, 40)):
             for S in (100, 257, 900, 2047, 2048, 5000, 40000, 131072):
