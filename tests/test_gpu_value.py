@@ -393,13 +393,15 @@ def test_prune_keys_and_values_then_decode(dtype, G, S, lam_k, lam_v, causal):
 
 
 @pytest.mark.parametrize("prune", [False, True])
-@pytest.mark.parametrize("dtype,B,N_q,N_kv,S,S_max", [("bf16", 17, 28, 4, 6272, 6400), ("f32", 3, 8, 8, 2816, 2944)])
-def test_value_score_in_the_workspace_of_a_longer_sequence(dtype, B, N_q, N_kv, S, S_max, prune):
-    """The workspace of the longest prompt holds fewer pieces than this one would take: fewer are used, nothing is
-    written behind it, and the score is that of the full-size workspace up to the rounding of the merge."""
-    mk = lambda S: thk.make_shape(1, B, N_q, N_kv, D, S, 32, 64, 0, DT[dtype], 0)
+@pytest.mark.parametrize("dtype,B,N_q,N_kv,S", [("bf16", 17, 28, 4, 6272), ("f32", 3, 8, 8, 2816)])
+def test_value_score_in_the_workspace_of_a_longer_sequence(dtype, B, N_q, N_kv, S, prune):
+    """The workspace of the longest prompt can hold fewer pieces than a shorter one would take (here: two thirds): fewer
+    are used, nothing is written behind it, and the score is that of the full-size workspace up to rounding."""
+    mk = lambda n: thk.make_shape(1, B, N_q, N_kv, D, S, 32, 64, 0, DT[dtype], n)
     op = thk.THK_OP_PRUNE_VALUE if prune else thk.THK_OP_SCORE_VALUE
-    shape, held, need = mk(S), thk.thk_workspace_bytes(mk(S_max), op), thk.thk_workspace_bytes(mk(S), op)
+    pieces = thk.thk_default_split(mk(0), op)
+    assert pieces >= 3
+    shape, need, held = mk(0), thk.thk_workspace_bytes(mk(0), op), thk.thk_workspace_bytes(mk(-(-2 * pieces // 3)), op)
     assert held < need
     q_obs, k, v = (_randn(d, dtype, 600 + i) for i, d in enumerate([(1, B, N_q, 32, D), (1, B, N_kv, S, D), (1, B, N_kv, S, D)]))
     scores = []
