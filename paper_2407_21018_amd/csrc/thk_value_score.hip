@@ -615,18 +615,16 @@ __global__ __launch_bounds__(256) void k_value_merge(const float *part, float *s
   const float *pu = part + (size_t)u * n_part * nqt * kRec;
   // weights of the records, row q = tid % 32, records tid / 32, + 8, ... per thread (one thread per row
   // walked all of them before: 128 records took 60 us)
-  __shared__ float red[8][32];
-  __shared__ float inv[32];
+  __shared__ float red_m[8][32], red_l[8][32];
   {
     const int q = threadIdx.x & 31, rg = threadIdx.x >> 5;
     const float *rec = pu + (size_t)t * kRec + 32 * kD + q;
     float M = kNegBig;
     for (int p = rg; p < n_part; p += 8) M = fmaxf(M, rec[(size_t)p * nqt * kRec]);
-    red[rg][q] = M;
+    red_m[rg][q] = M;
     __syncthreads();
 #pragma unroll
-    for (int i = 0; i < 8; ++i) M = fmaxf(M, red[i][q]);
-    __syncthreads();
+    for (int i = 0; i < 8; ++i) M = fmaxf(M, red_m[i][q]);
     float L = 0.f;
     for (int p = rg; p < n_part; p += 8) {
       const float *r = rec + (size_t)p * nqt * kRec;
@@ -634,17 +632,14 @@ __global__ __launch_bounds__(256) void k_value_merge(const float *part, float *s
       wts[p * 32 + q] = wv;
       L += wv * r[32];
     }
-    red[rg][q] = L;
+    red_l[rg][q] = L;
     __syncthreads();
-    if (rg == 0) {
-      L = red[0][q];
+    L = red_l[0][q];
 #pragma unroll
-      for (int i = 1; i < 8; ++i) L += red[i][q];
-      inv[q] = L > 0.f ? 1.f / L : 0.f;
-    }
-    __syncthreads();
+    for (int i = 1; i < 8; ++i) L += red_l[i][q];
+    const float inv = L > 0.f ? 1.f / L : 0.f;
     // normalised before the records are added: a single record's sums may be near the end of the range
-    for (int p = rg; p < n_part; p += 8) wts[p * 32 + q] *= inv[q];
+    for (int p = rg; p < n_part; p += 8) wts[p * 32 + q] *= inv;
   }
   __syncthreads();
   float acc[32];
