@@ -7,6 +7,28 @@ namespace thk {
 
 // A run of rows of K_pruned is a run of bytes (dense rows, or rows with padding behind them,
 // which is written as zeros); the unit may start and end anywhere (see compact_rows).
+// A unit's list on its way to the gather table (compact_build_tab, with the loads apart from their use):
+// 32 threads per row of the table's period, entries thread % 32 + 32 n.
+struct ChannelList {
+  int ch[4];
+  __device__ __forceinline__ void request(const int16_t *uidx, int T) {
+#pragma unroll
+    for (int n = 0; n < 4; ++n) ch[n] = uidx[min((int)(threadIdx.x & 31) + 32 * n, T - 1)];
+  }
+  template <int DT>
+  __device__ __forceinline__ void build_tab(int16_t *tab, int T, int ld, int sh) const {
+    const int period = 8 * ld, row = threadIdx.x >> 5;
+#pragma unroll
+    for (int n = 0; n < 4; ++n) {
+      const int t = (int)(threadIdx.x & 31) + 32 * n;
+      if (t >= ld) break;
+      int i = row * ld + t + sh, back = 0;
+      if (i >= period) { i -= period; back = 8 * Tile<DT>::ROW_ELEMS; }
+      tab[i] = (int16_t)((row * Tile<DT>::ROW_ELEMS + (t < T ? ch[n] : kD) - back) * (int)sizeof(typename Elem<DT>::Bits));
+    }
+  }
+};
+
 template <int DT>
 __device__ __forceinline__ void compact_flat_block(const CompactArgs &a, uint32_t block, u32x4 *smem) {
   using E = Elem<DT>;
@@ -30,10 +52,15 @@ __device__ __forceinline__ void compact_flat_block(const CompactArgs &a, uint32_
     for (int j = 0; j < NLD; ++j)
       r[j] = ld_stream((const u32x4 *)(src + (size_t)row * (kD * E::EB) + min((uint32_t)(j * kWave + lane), last) * 16u));
   };
+  // The list goes first: loads return in order, and the table is to be built while the rows travel (with
+  // the list behind the rows 448 units x 512 fp32 rows took 31.9 us instead of 28.2, 224 x 896 bf16
+  // rows, T = 86, 18.4 instead of 16.7).
+  ChannelList list;
+  list.request(a.idx + (size_t)u * a.T, a.T);
   int row = wave * TR;
   if (row < n_rows) request(row);
   const FlatOut<DT> out((char *)a.dst + ((size_t)u * a.dst_unit_rows + a.dst_row0) * a.ld * E::EB);
-  compact_build_tab<DT>(tab, a.idx + (size_t)u * a.T, a.T, a.ld, out.sh);
+  list.build_tab<DT>(tab, a.T, a.ld, out.sh);
   if (a.ld != a.T) tile_clear_padding<DT>(tile, lane);
   __syncthreads();
   for (; row < n_rows; row += 4 * TR) {
