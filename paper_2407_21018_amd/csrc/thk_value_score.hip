@@ -616,7 +616,12 @@ __global__ __launch_bounds__(256) void k_value_merge(const float *part, float *s
   // weights of the records, row q = tid % 32, records tid / 32, + 8, ... per thread (one thread per row
   // walked all of them before: 128 records took 60 us)
   __shared__ float red_m[8][32], red_l[8][32];
-  {
+  if (n_part == 1) {   // short calls: one record, its weight is 1 over its sum
+    if (threadIdx.x < 32) {
+      const float L = pu[(size_t)t * kRec + 32 * kD + 32 + threadIdx.x];
+      wts[threadIdx.x] = L > 0.f ? 1.f / L : 0.f;
+    }
+  } else {
     const int q = threadIdx.x & 31, rg = threadIdx.x >> 5;
     const float *rec = pu + (size_t)t * kRec + 32 * kD + q;
     float M = kNegBig;
