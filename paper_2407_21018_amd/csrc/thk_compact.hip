@@ -14,6 +14,12 @@ struct ChannelList {
   __device__ __forceinline__ void request(const int16_t *uidx, int T) {
 #pragma unroll
     for (int n = 0; n < 4; ++n) ch[n] = uidx[min((int)(threadIdx.x & 31) + 32 * n, T - 1)];
+    __builtin_amdgcn_sched_barrier(0);   // what is requested next stays behind
+  }
+  // The entries are waited for here, all four at once (left alone, the compiler moves each load to its
+  // use, behind the rows: four trips one after the other).
+  __device__ __forceinline__ void arrived() {
+    asm volatile("" : "+v"(ch[0]), "+v"(ch[1]), "+v"(ch[2]), "+v"(ch[3]));
   }
   template <int DT>
   __device__ __forceinline__ void build_tab(int16_t *tab, int T, int ld, int sh) const {
@@ -46,19 +52,22 @@ __device__ __forceinline__ void compact_flat_block(const CompactArgs &a, uint32_
   // table is built: a short call is a chain of trips (64 units x 487 bf16 rows, T = 51: 7.7 -> 4.6 us),
   // a long one is bounded by memory (64 x 32768 rows, T = 64: 5.7 TB/s).
   u32x4 r[NLD];
-  auto request = [&](int row) {   // rows past the end of a ragged tile repeat its last one (never gathered)
-    const uint32_t last = (uint32_t)min(TR, n_rows - row) * CPR - 1u;
+  // (rows past the end of a ragged tile repeat its last chunk, never gathered; a wave without rows the block's first)
+  auto request = [&](int row) {
+    const uint32_t last = row < n_rows ? (uint32_t)min(TR, n_rows - row) * CPR - 1u : 0u;
+    row = row < n_rows ? row : 0;
 #pragma unroll
     for (int j = 0; j < NLD; ++j)
       r[j] = ld_stream((const u32x4 *)(src + (size_t)row * (kD * E::EB) + min((uint32_t)(j * kWave + lane), last) * 16u));
   };
-  // The list goes first: loads return in order, and the table is to be built while the rows travel (with
-  // the list behind the rows 448 units x 512 fp32 rows took 31.9 us instead of 28.2, 224 x 896 bf16
-  // rows, T = 86, 18.4 instead of 16.7).
+  // The list goes first: loads return in order, and the table is to be built while the rows travel (the
+  // other way round, calls of a few rounds of blocks lose: 448 units x 512 fp32 rows 31.6 instead of 28.0
+  // us, 224 x 896 bf16 rows, T = 86, 19.0 instead of 15.7).
   ChannelList list;
   list.request(a.idx + (size_t)u * a.T, a.T);
   int row = wave * TR;
-  if (row < n_rows) request(row);
+  request(row);   // no branch around it: how many loads are behind the list is known
+  list.arrived();
   const FlatOut<DT> out((char *)a.dst + ((size_t)u * a.dst_unit_rows + a.dst_row0) * a.ld * E::EB);
   list.build_tab<DT>(tab, a.T, a.ld, out.sh);
   if (a.ld != a.T) tile_clear_padding<DT>(tile, lane);
