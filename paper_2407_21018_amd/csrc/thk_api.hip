@@ -851,7 +851,8 @@ thk_status thk_prune_value(const thk_shape *s, const void *q_obs, const void *k,
 static thk_status decode_common(const thk_shape *s, const void *q, const void *k_pruned,
                                 const int16_t *idx, const void *v, const int16_t *idx_v, int32_t T_v,
                                 int32_t ld_v, const void *k_tail, const void *v_tail, int32_t s_tail,
-                                int32_t s_tail_cap, void *out, void *ws, size_t ws_bytes, void *stream) {
+                                int32_t s_tail_cap, void *out, void *ws, size_t ws_bytes, void *stream,
+                                const Split *split = nullptr) {
   const thk_status st = check_shape(s, false);
   if (st != THK_OK) return st;
   if (q == nullptr || k_pruned == nullptr || idx == nullptr || v == nullptr || out == nullptr) return THK_ERR_NULL;
@@ -871,7 +872,7 @@ static thk_status decode_common(const thk_shape *s, const void *q, const void *k
       (s_tail > 0 && (!aligned16(k_tail) || (v_tail != nullptr && !aligned16(v_tail)))))
     return THK_ERR_ALIGN;
   const bool ws_usable = ws != nullptr && aligned16(ws);
-  const Split sp = decode_split(s, ws_usable ? ws_bytes : 0);
+  const Split sp = split != nullptr ? *split : decode_split(s, ws_usable ? ws_bytes : 0);
   const int G = s->N_q / s->N_kv;
   if (units_of(s) * ceil_div(G, decode_heads_per_block(s)) * sp.n > kMaxGrid) return THK_ERR_SHAPE;
   if (sp.n > 1 && (!ws_usable || ws_bytes < decode_ws_bytes(s, sp.n))) return THK_ERR_WORKSPACE;
@@ -956,13 +957,13 @@ thk_status thk_decode_attn_static(const thk_shape *s, const void *q, const void 
   thk_status st = check_shape(s, false);
   if (st != THK_OK) return st;
   // the size check comes before anything touches the device
-  const size_t need = thk_workspace_bytes(s, THK_OP_DECODE);
-  if (need > (size_t)THK_STATIC_SCRATCH_BYTES) return THK_ERR_SCRATCH;
+  const Split sp = decode_split(s);
+  if (sp.n > 1 && decode_ws_bytes(s, sp.n) > (size_t)THK_STATIC_SCRATCH_BYTES) return THK_ERR_SCRATCH;
   void *ws = nullptr;
   st = static_scratch(&ws);
   if (st != THK_OK) return st;
   return decode_common(s, q, k_pruned, idx, v, nullptr, 0, 0, k_tail, v_tail, s_tail, s_tail_cap, out, ws,
-                       (size_t)THK_STATIC_SCRATCH_BYTES, stream);
+                       (size_t)THK_STATIC_SCRATCH_BYTES, stream, &sp);
 }
 
 thk_status thk_tail_append(const thk_shape *s, const void *k_new, const void *v_new, void *k_tail,
