@@ -212,12 +212,11 @@ __device__ __forceinline__ void tail_k_commit(const u32x4 (&kr)[KB], char *kbuf,
 // memory, 16 bytes of a row (threads 0 .. 127) or one list entry (threads 128 .. 255) per
 // thread, issued before anything else so that waiting for them waits for nothing behind them.
 // (Gathering q[idx[c]] from memory instead is two dependent trips, and four where the packed and
-// the plain copy were made by two loops: 3-4 us at the start of every launch.)
-template <int DT, int GT>
+// the plain copy were made by two loops: 3-4 us at the start of every launch.)  bf16: k_decode_mq's.
+template <int GT>
 struct QueryStage {
-  static constexpr int LPR = kD / Elem<DT>::VEC;             // 16-byte chunks per row
+  static constexpr int LPR = 16;                             // 16-byte chunks per row
   static_assert(GT * LPR <= 128, "one chunk per thread of the first two waves");
-  static constexpr int kBytes = GT * kD * Elem<DT>::EB + kD * 2;   // rows, then the list
   u32x4 row;
   int16_t ch;
   __device__ __forceinline__ void issue(const void *q, size_t bn0, int heads, const int16_t *uidx, int T) {
@@ -230,10 +229,10 @@ struct QueryStage {
   __device__ __forceinline__ void commit(char *lds) const {
     const int tid = threadIdx.x;
     if (tid < GT * LPR) ((u32x4 *)lds)[tid] = row;
-    if (tid >= 128) ((int16_t *)(lds + GT * kD * Elem<DT>::EB))[tid - 128] = ch;
+    if (tid >= 128) ((int16_t *)(lds + GT * kD * 2))[tid - 128] = ch;   // rows, then the list
   }
   static __device__ __forceinline__ const int16_t *list(const char *lds) {
-    return (const int16_t *)(lds + GT * kD * Elem<DT>::EB);
+    return (const int16_t *)(lds + GT * kD * 2);
   }
 };
 // The staged bf16 query rows as packed pairs: full [GT][kQS / 2] and gathered kept channels
@@ -241,7 +240,7 @@ struct QueryStage {
 template <int GT>
 __device__ __forceinline__ void query_pack(const char *stage, int T, uint32_t *qfp, uint32_t *qkp) {
   const uint16_t *raw = (const uint16_t *)stage;
-  const int16_t *list = QueryStage<THK_BF16, GT>::list(stage);
+  const int16_t *list = QueryStage<GT>::list(stage);
   const int w = threadIdx.x & 127;
   if (w < kQS / 2) {
     const int c = 2 * w;
@@ -616,7 +615,6 @@ __device__ __forceinline__ void block_merge_store(const float *mrg, int wstride,
     __hip_atomic_store(flags + threadIdx.x, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// KB: 16-byte K chunks a lane may have to stage for one TR-row pruned tile.
 // Which (unit, piece, head group) a workgroup takes.  Where the heads of a KV head need several
 // groups, the blocks that read the SAME keys and values are 8 workgroup numbers apart: workgroup i
 // runs on XCD i % 8, so they share an L2 and are dispatched one after the other, and all but the
@@ -648,6 +646,7 @@ inline unsigned decode_grid(const DecodeArgs &a, int groups) {
   return (unsigned)(groups == 1 || last == 0 ? pieces * groups : (pieces - last) * groups + (groups - 1) * kXcds + last);
 }
 
+// KB: 16-byte K chunks a lane may have to stage for one TR-row pruned tile.
 // WPE: resident waves per SIMD the register budget is set for.
 // VP = 1: the value rows of the pruned segment hold only the T_v kept channels (a.v is
 // V_pruned with rows a.ld_v elements apart, a.idx_v lists the channels).  Their bytes are staged

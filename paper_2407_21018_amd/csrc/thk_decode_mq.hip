@@ -41,8 +41,8 @@
 // branches live in scalar registers; a whole tile (32 rows, all but a block's last) takes
 // straight-line paths -- value loads at fixed offsets without per-row clamps, the eight 4-row
 // steps of the second product without a test between them so that later reads overlap earlier
-// products; rows of whole 8-channel groups (T a multiple of 8) take a logit loop without masks or
-// range checks; tiles of at most 4 KB of keys get a staging class of their own (no fifth,
+// products; the logit loop covers the chunks that both halves have without masks or range checks, and
+// what is left of a row (an odd chunk, a partial one) is one masked step behind it; tiles of at most 4 KB of keys get a staging class of their own (no fifth,
 // duplicate chunk).  Together: 805 MB (64 units x 32768 rows, G = 4) 130.4 -> 125.9 us, 403 MB
 // (8 units x 131072 rows) 68.0 -> 65.0 us; with no arithmetic at all the same loads take 123 us.
 #include <stdlib.h>
@@ -356,7 +356,7 @@ __global__ __launch_bounds__(256, WPE) void k_decode_mq(DecodeArgs a, int groups
   auto tail_rows = [&](int ti) { return min(kTailRows, a.s_tail - ti * kTailRows); };
   const u32x4 *ktail = (const u32x4 *)a.kt + (size_t)u * a.s_tail_cap * LPR;   // this unit's tail keys
 
-  QueryStage<DT, GT> qs;
+  QueryStage<GT> qs;
   qs.issue(a.q, (size_t)bn0, hb, a.idx + (size_t)u * a.T, a.T);
   const size_t krow0 = (size_t)u * a.unit_rows + s0;     // first K_pruned / V row of this block
   const u32x4 *vbase = (const u32x4 *)a.v + krow0 * LPR;

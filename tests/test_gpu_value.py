@@ -101,9 +101,10 @@ def test_value_score_matches_oracle(G, S_obs, S, n_split, causal, sigma, dtype):
 
 @pytest.mark.parametrize("B,N_kv,G,S_obs,S,n_split,causal", [
     (1, 2, 4, 32, 1, 0, 1), (1, 2, 4, 32, 127, 0, 0), (1, 2, 4, 32, 128, 0, 1), (1, 2, 4, 32, 129, 0, 1),
-    (1, 2, 4, 32, 513, 2, 0),       # the second piece is one row
+    (1, 2, 4, 32, 513, 2, 0),       # the second piece is one chunk and one row
     (1, 2, 5, 32, 300, 0, 1),       # 5 tiles: eight slots, the second four mostly idle
     (1, 2, 7, 32, 260, 3, 1),       # 7 tiles, the last piece is four rows
+    (1, 2, 4, 32, 129, 2, 0),       # the second piece is one row
     (1, 2, 9, 32, 400, 0, 1),       # 9 tiles: three blocks of four
     (1, 1, 4, 25, 391, 0, 1),       # tiles that straddle heads, the last one short
     (8, 8, 8, 32, 500, 4, 1), (8, 8, 5, 32, 385, 4, 0),   # 256 blocks: eight tiles (three idle) per block
