@@ -94,8 +94,8 @@ __global__ __launch_bounds__(256) void k_compact_flat(CompactArgs a) {
 // A whole tail leaves for the pruned cache: the first n_compact blocks compact the keys, the others
 // copy the values, kFlushRows rows of a unit each (the other order is 10 % slower: the longer blocks
 // would come last).  One launch instead of two: the second one's dispatch and ramp weigh most on
-// small tails: 192 units x 128 rows 10.2 -> 6.6 us, 64 x 32 rows 5.7 -> 4.3 us, 1024 x 128 rows
-// 24.4 -> 23.6 us (bounded by memory: 121 MB, 5.1 TB/s).
+// small tails (from a graph): 192 units x 128 rows 7.4 -> 5.3 us, 64 x 32 rows 5.4 -> 3.4 us; whole calls of
+// 1024 x 128 rows 24.4 -> 22.8 us (bounded by memory: 121 MB, 5.3 TB/s).
 constexpr int kFlushRows = 64;
 struct FlushCopy {
   const void *src;

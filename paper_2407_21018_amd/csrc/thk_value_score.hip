@@ -317,11 +317,12 @@ __global__ __launch_bounds__(256, 2) void k_value_attn_bf16(ValueAttnArgs a) {
 //     rows), of value row r at c ^ ((r & 3) << 2) (a transposing read takes 64 bytes of 4 rows);
 //   * the next sub-tile's logits are computed in front of this one's softmax, in straight-line code,
 //     so that matrix and vector instructions of one wave run side by side.
-// What bounds it: without any transfer it takes 195 us for 64 units x 32768 rows x 128 query rows,
-// 1.05 PFLOP/s of issued matrix work (the same card's 8192^3 library product: 1.2) at a clock that
-// the matrix load holds at 1.8 GHz; the transfers alone take 172 us.  (Two phases per sub-tile with
-// waves 4 .. 7 half a step behind, so that one wave of a SIMD feeds the matrix pipe while the other
-// computes weights, measured the same: the pipe is not short of work, the card is of power.)
+// Neither the memory nor the matrix pipes bound it alone: 64 units x 32768 rows x 128 query rows take 221
+// us in a run with counters, 4.9 TB/s and 0.93 PFLOP/s of issued matrix work; the matrix pipes are
+// busy 43 % of the cycles, no bank conflicts, and the clock is 2.0 GHz (2.4 in the copy kernel of
+// the same run), so the same instructions also take a fifth longer under this load.  (Two phases per
+// sub-tile with waves 4 .. 7 half a step behind, so that one wave of a SIMD feeds the matrix pipe while
+// the other computes weights, measured the same.)
 // 64 units x 32768 rows, G = 4, S_obs = 32: 300 -> 277 us; 8 units x 131072 rows, S_obs = 64: 279 -> 237;
 // 32 units x 16384 rows, G = 8: 150 -> 131 us (score calls, before: the kernel above with QT = 4).
 constexpr int kWideRows = 128;                    // rows per chunk
