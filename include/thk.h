@@ -119,12 +119,12 @@ int32_t thk_keep_count(int32_t D, double lambda);
  * Bytes of caller-provided scratch that `op` needs for `shape` (including the
  * shape's n_split; 0 there means the library's own choice, which this function
  * reproduces).  Returns 0 for an invalid shape.  Host-only arithmetic.
- * The library's choice of pieces, and with it the size, may be larger for a shorter S.  A
- * sequence that grows or a buffer for prompts of any length needs no more than the size
- * at the largest S all the same: with n_split = 0 the decode and value-score calls
- * (THK_OP_DECODE, THK_OP_SCORE_VALUE, and the score inside THK_OP_PRUNE_VALUE) take fewer pieces
+ * The library's choice of pieces, and with it the size, may be larger for a shorter S.  For
+ * THK_OP_DECODE and THK_OP_SCORE_VALUE with n_split = 0 the size at the largest S serves every
+ * shorter one all the same: the calls (and the score inside thk_prune_value) take fewer pieces
  * where the workspace holds no more of them -- the same result up to the rounding of the merge
- * -- and only a workspace below what any longer S reports is refused.
+ * -- and refuse only a workspace below what any longer S reports.  For the other operations
+ * take the largest size over the lengths in use.
  */
 size_t thk_workspace_bytes(const thk_shape *shape, int32_t op);
 
@@ -248,9 +248,9 @@ thk_status thk_compact_keys(const thk_shape *shape, const void *k,
  * staged | fused | reread (the one-kernel form with the rows read twice);
  * THK_PRUNE_BLOCK_ROWS (rows per block; 128, 256 and 512 are held on chip),
  * THK_PRUNE_HOLD_ROWS (largest default block), THK_PRUNE_MAX_BLOCKS (blocks
- * per unit beyond which the staged form is taken), THK_PRUNE_SPIN_LIMIT (polls, about
- * half a microsecond each, before a waiting block leaves its rows to the repair kernel or to the unit's
- * finisher; 0 forces that path), THK_PRUNE_STAGGER_NS (spacing of the first round's unit starts; 0 =
+ * per unit beyond which the staged form is taken), THK_PRUNE_SPIN_LIMIT (polls,
+ * about half a microsecond each, before a waiting block leaves its rows to the repair
+ * kernel or to the unit's finisher; 0 forces that path), THK_PRUNE_STAGGER_NS (spacing of the first round's unit starts; 0 =
  * none), THK_PRUNE_GROUP_MIB (bytes of K per group of units in the staged form),
  * THK_PRUNE_NORM_DELAY_US, THK_PRUNE_NORM_POLLS (single-launch form: the query norms come that
  * much later, at most 500 us; looks for them, after which the scores are NaN),
@@ -289,8 +289,9 @@ thk_status thk_prune(const thk_shape *shape, const void *q_obs, const void *k,
  * hold).  With a key row pitch (ld_keep, or T when rows are dense) that is a multiple of 4
  * elements, rows are read as they lie and a probability enters the product with V as two bf16
  * terms (exact to 2^-16); with other pitches an operand is put together from two or three words
- * and a probability keeps its 24 bits (three terms), a few percent slower. THK_DECODE_MFMA=0 in the environment
- * (for experiments and tests) keeps them on the general kernel.
+ * and a probability keeps its 24 bits (three terms), a few percent slower.
+ * THK_DECODE_MFMA=0 in the environment (for experiments and tests) keeps them on the general
+ * kernel.
  *   ws : THK_OP_DECODE bytes.
  */
 thk_status thk_decode_attn(const thk_shape *shape, const void *q,

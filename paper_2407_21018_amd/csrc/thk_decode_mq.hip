@@ -42,8 +42,8 @@
 // straight-line paths -- value loads at fixed offsets without per-row clamps, the eight 4-row
 // steps of the second product without a test between them so that later reads overlap earlier
 // products; the logit loop covers the chunks that both halves have without masks or range checks, and
-// what is left of a row (an odd chunk, a partial one) is one masked step behind it; tiles of at most 4 KB of keys get a staging class of their own (no fifth,
-// duplicate chunk).  Together: 805 MB (64 units x 32768 rows, G = 4) 130.4 -> 125.9 us, 403 MB
+// what is left of a row (an odd chunk, a partial one) is one masked step behind it; tiles of at
+// most 4 KB of keys get a staging class of their own (no fifth, duplicate chunk).  Together: 805 MB (64 units x 32768 rows, G = 4) 130.4 -> 125.9 us, 403 MB
 // (8 units x 131072 rows) 68.0 -> 65.0 us; with no arithmetic at all the same loads take 123 us.
 #include <stdlib.h>
 

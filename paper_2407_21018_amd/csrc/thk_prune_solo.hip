@@ -25,8 +25,8 @@
 //     the previous replay's count for its own.
 //   * One block of every unit waits for no other row block: the FINISHER, whose arrival completes
 //     the unit's sums.  (It may wait for the query norms of the prologue block, which has started
-//     and itself waits for nobody.)  A block that gives up waiting raises a flag for its rows and draws a ticket from
-//     the unit's give-up counter; the finisher draws the closing ticket, learns from it how
+//     and itself waits for nobody.)  A block that gives up waiting raises a flag for its rows and
+//     draws a ticket from the unit's give-up counter; the finisher draws the closing ticket, learns from it how
 //     many blocks gave up before, and compacts their rows after its own (re-reading them).
 //     A block that gives up later than that finds the closing ticket in the counter: the list is
 //     there by then, so it fetches it and carries on by itself.  Every block exits whatever the
