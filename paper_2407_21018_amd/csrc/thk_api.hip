@@ -883,6 +883,8 @@ static thk_status decode_common(const thk_shape *s, const void *q, const void *k
   a.T = s->T; a.ldk = ld_of(s); a.N_q = s->N_q; a.N_kv = s->N_kv;
   a.s_tail = s_tail; a.s_tail_cap = s_tail_cap; a.n_split = sp.n; a.dtype = s->dtype;
   a.units = units_of(s);
+  a.G = G;
+  a.split_inv = ((uint64_t)1 << kSplitShift) / (uint32_t)sp.n + 1;
   a.unit_rows = unit_rows;
   a.unified_v = unified_v ? 1 : 0;
   a.scale_log2_d = 1.4426950408889634 / sqrt((double)s->D);

@@ -30,6 +30,7 @@ namespace thk {
 
 constexpr int kTailRows = 16;   // rows per tile in the full-width tail segment
 constexpr int kQS = kD + 8;     // floats per query vector in LDS: 128 channels + 8 zeros
+constexpr int kBufferWord3 = 0x00027000, kNonTemporal = 2;   // raw buffer of bytes; the hint of ld_stream
 
 __device__ inline void wave_sync_lds() {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -159,133 +160,123 @@ struct VPruned {
   bool active;
 };
 
-// Issue the global loads of a tile of `nrows` rows, W elements wide with row
-// stride ld (elements), starting at byte kbeg of tensor kg.  The range is
-// widened to 16-byte boundaries, so up to 15 bytes before the first row and
-// after the last row are read as well: before is always inside the tensor (its
-// base is 16-byte aligned); after can pass the tensor's last element by less
-// than 16 bytes, inside the 16-byte granule that holds it (the API requires
-// that granule to be readable).  Chunk indices past the range are clamped to
-// its last chunk: no lane is predicated off, and the duplicates land in LDS
-// slots that no row read touches.
-// kr receives KB chunks per lane (the tile's K bytes staged in registers);
-// returns the byte distance between the widened start and the first row.
-// UNI: kbeg is wave-uniform for the compiler too; the offsets then stay 32-bit on a scalar base.
-template <int DT, int KB, bool UNI = false>
-__device__ __forceinline__ int k_issue(u32x4 (&kr)[KB], const char *__restrict__ kg, size_t kbeg,
-                                       int nrows, int W, int ld, int lane) {
-  constexpr int EB = Elem<DT>::EB;
-  const size_t kend = kbeg + ((size_t)(nrows - 1) * ld + W) * EB;
-  const size_t a0 = kbeg & ~(size_t)15;
-  const int last = (int)((kend - a0 + 15) >> 4) - 1;
-  const char *p = kg + a0;
+// ---- a tile's bytes through a buffer resource ------------------------------------------------
+// `bytes` (a multiple of 16, 0: no tile) from a 16-byte boundary on, chunk j * 64 + lane per lane and load.
+// The resource ends with the tile: chunks past it return 0 and move nothing, so no load is clamped and none
+// sits behind a branch.  A branch around loads is what costs here: where its paths meet the compiler no
+// longer knows how many loads are out and waits for ALL of them -- the first keys of a block were asked
+// for only after its query had arrived (1 us of a 9 us call), the query was packed only when the first tile
+// was there, and a tile's values waited for the next tile's keys.  Against clamped loads behind branches, whole
+// calls: bf16, 8 units x 314 rows x 2 heads 9.5 -> 7.6 us, 8 x 4439 rows 13.1 -> 10.5, 32 x 1536 rows x 8 heads 14.6
+// -> 11.5, 24 x 12801 rows 28.5 -> 26.6; fp32, 8 x 5160 rows x 7 heads 26.7 -> 22.2, 128 x 6080 rows x 5 heads 160
+// -> 145; pruned values, 128 x 2096 rows 44.0 -> 39.3.  Calls of several hundred MB: 0 to 4 %.
+struct ByteRange {   // wave-uniform
+  const char *base;
+  int bytes, shift;  // shift: from base to the first row
+};
+// nrows rows of W elements, ld apart, from byte beg of tensor t (16-byte aligned), widened to 16-byte
+// boundaries, so up to 15 bytes before the first row and after the last are read as well: before is
+// always inside the tensor; after can pass the tensor's last element by less than 16 bytes, inside the 16-byte
+// granule that holds it (the API requires that granule to be readable).
+template <int EB>
+__device__ __forceinline__ ByteRange flat_rows(const void *t, size_t beg, int nrows, int W, int ld) {
+  ByteRange r;
+  r.shift = (int)(beg & 15);
+  r.base = (const char *)t + (beg - r.shift);
+  r.bytes = (r.shift + ((nrows - 1) * ld + W) * EB + 15) & ~15;
+  return r;
+}
+// (stated for the compiler: a resource that it takes for divergent becomes a loop around every load)
+__device__ __forceinline__ int uniform(int x) { return __builtin_amdgcn_readfirstlane(x); }
+__device__ __forceinline__ const char *uniform_ptr(const char *p) {
+  const uint64_t b = (uint64_t)p;
+  return (const char *)((uint64_t)(uint32_t)uniform((int)(uint32_t)b) | (uint64_t)(uint32_t)uniform((int)(b >> 32)) << 32);
+}
+template <int N, int M>
+__device__ __forceinline__ void tile_issue(u32x4 (&r)[M], const char *base, int bytes, int lane) {
+  const auto rsrc = __builtin_amdgcn_make_buffer_rsrc((void *)uniform_ptr(base), (short)0, uniform(bytes), kBufferWord3);
 #pragma unroll
-  for (int j = 0; j < KB; ++j) {
-    if constexpr (UNI) kr[j] = ld_stream((const u32x4 *)(p + min((uint32_t)(j * kWave + lane), (uint32_t)last) * 16u));
-    else kr[j] = ld_stream((const u32x4 *)(p + (size_t)min(j * kWave + lane, last) * 16));
-  }
-  return (int)(kbeg - a0);
+  for (int j = 0; j < N; ++j)
+    r[j] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rsrc, lane * 16 + j * (kWave * 16), 0, kNonTemporal));
 }
 
-template <int KB>
-__device__ __forceinline__ void k_commit(const u32x4 (&kr)[KB], char *kbuf, int lane) {
+template <int N, int M>
+__device__ __forceinline__ void k_commit(const u32x4 (&kr)[M], char *kbuf, int lane) {
 #pragma unroll
-  for (int j = 0; j < KB; ++j) ((u32x4 *)kbuf)[j * kWave + lane] = kr[j];   // kbuf holds KB * 64 chunks
-}
-
-// The first KBT chunks of kr from a full-width tail tile of `nrows` rows at `src` (whole 16-byte chunks):
-// the tail's key bytes travel in the registers the pruned tiles no longer need.
-template <int DT, int KBT, int KB>
-__device__ __forceinline__ void tail_k_issue(u32x4 (&kr)[KB], const u32x4 *__restrict__ src, int nrows, int lane) {
-  static_assert(KBT <= KB, "a tail tile's key bytes must fit the staging registers of a pruned tile");
-  const int last = nrows * (kD / Elem<DT>::VEC) - 1;
-#pragma unroll
-  for (int j = 0; j < KBT; ++j) kr[j] = ld_stream(src + min(j * kWave + lane, last));
-}
-template <int KBT, int KB>
-__device__ __forceinline__ void tail_k_commit(const u32x4 (&kr)[KB], char *kbuf, int lane) {
-#pragma unroll
-  for (int j = 0; j < KBT; ++j) ((u32x4 *)kbuf)[j * kWave + lane] = kr[j];
+  for (int j = 0; j < N; ++j) ((u32x4 *)kbuf)[j * kWave + lane] = kr[j];   // kbuf holds M * 64 chunks
 }
 
 // The block's query rows and the unit's list of kept channels on their way to LDS: ONE trip to
-// memory, 16 bytes of a row (threads 0 .. 127) or one list entry (threads 128 .. 255) per
-// thread, issued before anything else so that waiting for them waits for nothing behind them.
+// memory, 16 bytes of a row (threads 0 .. 127) and one list entry (threads 128 .. 255 keep it) per
+// thread, issued before anything else and without a branch, so that waiting for them waits for nothing
+// behind them.
 // (Gathering q[idx[c]] from memory instead is two dependent trips, and four where the packed and
-// the plain copy were made by two loops: 3-4 us at the start of every launch.)  bf16: k_decode_mq's.
-template <int GT>
+// the plain copy were made by two loops: 3-4 us at the start of every launch.)
+template <int DT, int GT>
 struct QueryStage {
-  static constexpr int LPR = 16;                             // 16-byte chunks per row
+  using B = typename Elem<DT>::Bits;
+  static constexpr int LPR = kD / Elem<DT>::VEC;             // 16-byte chunks per row
   static_assert(GT * LPR <= 128, "one chunk per thread of the first two waves");
   u32x4 row;
   int16_t ch;
   __device__ __forceinline__ void issue(const void *q, size_t bn0, int heads, const int16_t *uidx, int T) {
     const int tid = threadIdx.x;
-    row = u32x4{0u, 0u, 0u, 0u};   // head slots that are not in use carry a zero query
-    ch = 0;
-    if (tid < heads * LPR) row = ((const u32x4 *)q)[bn0 * LPR + tid];
-    else if (tid >= 128 && tid - 128 < T) ch = uidx[tid - 128];
+    // head slots that are not in use are past the resource's end: a zero query
+    const auto rsrc = __builtin_amdgcn_make_buffer_rsrc((void *)((const char *)q + bn0 * (LPR * 16)), (short)0,
+                                                        heads * (LPR * 16), kBufferWord3);
+    row = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rsrc, tid * 16, 0, 0));
+    ch = uidx[min(tid & 127, T - 1)];
   }
   __device__ __forceinline__ void commit(char *lds) const {
     const int tid = threadIdx.x;
     if (tid < GT * LPR) ((u32x4 *)lds)[tid] = row;
-    if (tid >= 128) ((int16_t *)(lds + GT * kD * 2))[tid - 128] = ch;   // rows, then the list
+    if (tid >= 128) ((int16_t *)(lds + GT * LPR * 16))[tid - 128] = ch;   // rows, then the list
   }
-  static __device__ __forceinline__ const int16_t *list(const char *lds) {
-    return (const int16_t *)(lds + GT * kD * 2);
-  }
-};
-// The staged bf16 query rows as packed pairs: full [GT][kQS / 2] and gathered kept channels
-// (zero beyond T), both zero beyond channel 128.
-template <int GT>
-__device__ __forceinline__ void query_pack(const char *stage, int T, uint32_t *qfp, uint32_t *qkp) {
-  const uint16_t *raw = (const uint16_t *)stage;
-  const int16_t *list = QueryStage<GT>::list(stage);
-  const int w = threadIdx.x & 127;
-  if (w < kQS / 2) {
-    const int c = 2 * w;
-    const int i0 = c < T ? list[c] : -1, i1 = c + 1 < T ? list[c + 1] : -1;
-    for (int g = threadIdx.x >> 7; g < GT; g += 2) {
-      const uint16_t *rg = raw + g * kD;
-      qfp[g * (kQS / 2) + w] = c < kD ? *(const uint32_t *)(rg + c) : 0u;
-      qkp[g * (kQS / 2) + w] = (i0 >= 0 ? (uint32_t)rg[i0] : 0u) | ((i1 >= 0 ? (uint32_t)rg[i1] : 0u) << 16);
+  // The staged rows for the logits: full [GT][kQS] and gathered kept channels (zero beyond T), both zero beyond
+  // channel 128, as floats (qf, qk; may be null) and for bf16 as packed pairs (qfp, qkp, [GT][kQS / 2] words).
+  static __device__ __forceinline__ void pack(const char *lds, int T, float *qf, float *qk, uint32_t *qfp, uint32_t *qkp) {
+    const B *raw = (const B *)lds;
+    const int16_t *list = (const int16_t *)(lds + GT * LPR * 16);
+    const int w = threadIdx.x & 127, gh = threadIdx.x >> 7;
+    if (w >= kQS / 2) return;
+    const int c = min(2 * w, kD - 2);   // the zeros behind a vector: channels past T and past 128
+    const int i0 = list[c], i1 = list[c + 1];
+    const B m0 = 2 * w < T ? (B)~(B)0 : (B)0, m1 = 2 * w + 1 < T ? (B)~(B)0 : (B)0, mf = 2 * w < kD ? (B)~(B)0 : (B)0;
+#pragma unroll
+    for (int g0 = 0; g0 < GT; g0 += 2) {
+      const int g = g0 + gh;
+      if (GT % 2 != 0 && g >= GT) break;
+      const B *rg = raw + g * kD;
+      const uint32_t f0 = rg[c] & mf, f1 = rg[c + 1] & mf, k0 = rg[i0] & m0, k1 = rg[i1] & m1;
+      if constexpr (DT == THK_BF16) {
+        qfp[g * (kQS / 2) + w] = f0 | (f1 << 16);
+        qkp[g * (kQS / 2) + w] = k0 | (k1 << 16);
+      }
+      if (qf != nullptr) {
+        constexpr int SH = DT == THK_BF16 ? 16 : 0;
+        *(float2 *)(qf + g * kQS + 2 * w) = make_float2(__uint_as_float(f0 << SH), __uint_as_float(f1 << SH));
+        *(float2 *)(qk + g * kQS + 2 * w) = make_float2(__uint_as_float(k0 << SH), __uint_as_float(k1 << SH));
+      }
     }
   }
-}
+};
 
-// Shape of the value loads of one TR-row tile: NV wave-wide loads per batch.
+// Shape of the value loads of a tile of TR full-width rows: NL chunks per lane, chunk i of row i * RPL + lane / LPR.
 template <int DT, int TR>
 struct VShape {
   static constexpr int LPR = kD / Elem<DT>::VEC;     // lanes (16-byte chunks) per V row
   static constexpr int RPL = kWave / LPR;            // V rows per wave-wide load
   static constexpr int NL = TR / RPL;                // loads per lane per tile
-  static constexpr int NV = NL < 16 ? NL : 16;       // loads per lane per batch
-  static constexpr int NB = NL / NV;                 // batches per tile
 };
 
-// Batch b of a tile's value rows into registers.  Rows past a ragged tile's end
-// re-read its last row: their probability is 0.
-template <int DT, int TR, int NV>
-__device__ __forceinline__ void v_issue(u32x4 (&vr)[NV], const u32x4 *__restrict__ vg,
-                                        int nrows, int b, int lane) {
-  using VS = VShape<DT, TR>;
-  if (nrows == TR) {
-#pragma unroll
-    for (int i = 0; i < VS::NV; ++i) vr[i] = ld_stream(vg + (size_t)(b * VS::NV + i) * kWave + lane);
-  } else {
-    const int vrow = lane / VS::LPR, vcol = lane % VS::LPR;
-#pragma unroll
-    for (int i = 0; i < VS::NV; ++i)
-      vr[i] = ld_stream(vg + (size_t)min((b * VS::NV + i) * VS::RPL + vrow, nrows - 1) * VS::LPR + vcol);
-  }
-}
-
 // One tile whose K bytes are already in LDS (kbuf): logits, running softmax,
-// acc += p.V.  vg: the tile's value rows (16-byte chunks, 128 elements per row).
+// acc += p.V.  vr: the tile's value rows, chunk i of a lane as VShape says (rows past a ragged tile's end
+// hold zeros, as do their probabilities); vr_free is called when they have been used.
 // qs: [GT][kQS] floats, entries 128..135 of every vector are zero; qp: the same
 // vectors as packed bf16 pairs, [GT][kQS / 2] words (bf16 inputs only).
-// PV = 0: value rows are full width (vg, vr).  PV = 1: value rows are channel-pruned; their
-// bytes are in vrp (KBV staged chunks per lane) and are walked out of LDS as described by vp.
+// TV: rows of the tile that may hold values (a tail tile has 16).
+// PV = 0: value rows are full width.  PV = 1: value rows are channel-pruned; their
+// bytes are in vr as they lie in memory and are walked out of LDS as described by vp.
 // PV = 2: a full-width tile (the tail) of a kernel that also carries pruned-value sums, which
 // follow every change of the running maximum.
 // Precision of a logit.  bf16 inputs: products are exact in fp32 and the sum runs in fp32.  fp32
@@ -293,14 +284,13 @@ __device__ __forceinline__ void v_issue(u32x4 (&vr)[NV], const u32x4 *__restrict
 // before the result is rounded to fp32, so the error of exp2(z - m) does not grow with |z| (an
 // fp32 logit of a few thousand -- channel scales of sigma = 2 on query and keys -- is only
 // accurate to 1e-4 in absolute terms, which is the whole error budget of fp32 outputs).
-template <int DT, int GT, int RA, int TR, int NV, int PV = 0, int KBV = 1>
+template <int DT, int GT, int RA, int TR, int TV, int PV, int NV, class VrFree>
 __device__ __forceinline__ void tile_compute(int shift, int nrows, int W, int ld,
                                              const float *__restrict__ qs,
                                              const uint32_t *__restrict__ qp,
-                                             const u32x4 *__restrict__ vg,
                                              u32x4 (&vr)[NV], const char *kbuf,
                                              float *ps, TileState<DT, GT> &st, double scale_d, int lane,
-                                             const u32x4 (*vrp)[KBV] = nullptr, const VPruned *vp = nullptr) {
+                                             const VPruned *vp, VrFree vr_free) {
   using E = Elem<DT>;
   using ZT = typename LogitType<DT>::type;   // accumulator of a logit: float (bf16 inputs), double (fp32 inputs)
   const ZT scale = (ZT)scale_d;
@@ -419,7 +409,8 @@ __device__ __forceinline__ void tile_compute(int shift, int nrows, int W, int ld
   }
   if constexpr (PV == 1) {
     // ---- accp += p . V_pruned: value bytes to LDS, then 4 kept channels per lane ----------
-    k_commit<KBV>(*vrp, vp->vbuf, lane);
+    k_commit<NV>(vr, vp->vbuf, lane);
+    vr_free();
     wave_sync_lds();
     // Rows r0 + rsub, r0 = 0, rpw, 2 rpw, ...; NS steps are read before they are used.  Nothing
     // branches: a row past the tile's end takes the bytes of the tile's last row and a weight of 0
@@ -469,30 +460,27 @@ __device__ __forceinline__ void tile_compute(int shift, int nrows, int W, int ld
 
   // ---- acc += p . V --------------------------------------------------------
 #pragma unroll
-  for (int b = 0; b < VS::NB; ++b) {
+  for (int i = 0; i < VShape<DT, TV>::NL; ++i) {
+    const int row = i * VS::RPL + vrow;
+    float f[VEC];
+    E::unpack(vr[i], f);
+    float pv[GT];
+    if constexpr (GT == 4) {
+      const float4 t4 = *(const float4 *)(ps + row * 4);
+      pv[0] = t4.x; pv[1] = t4.y; pv[2] = t4.z; pv[3] = t4.w;
+    } else if constexpr (GT == 2) {
+      const float2 t2 = *(const float2 *)(ps + row * 2);
+      pv[0] = t2.x; pv[1] = t2.y;
+    } else {
 #pragma unroll
-    for (int i = 0; i < VS::NV; ++i) {
-      const int row = (b * VS::NV + i) * VS::RPL + vrow;
-      float f[VEC];
-      E::unpack(vr[i], f);
-      float pv[GT];
-      if constexpr (GT == 4) {
-        const float4 t4 = *(const float4 *)(ps + row * 4);
-        pv[0] = t4.x; pv[1] = t4.y; pv[2] = t4.z; pv[3] = t4.w;
-      } else if constexpr (GT == 2) {
-        const float2 t2 = *(const float2 *)(ps + row * 2);
-        pv[0] = t2.x; pv[1] = t2.y;
-      } else {
-#pragma unroll
-        for (int g = 0; g < GT; ++g) pv[g] = ps[row * GT + g];
-      }
-#pragma unroll
-      for (int g = 0; g < GT; ++g)
-#pragma unroll
-        for (int v = 0; v < VEC; ++v) st.acc[g][v] = fmaf(pv[g], f[v], st.acc[g][v]);
+      for (int g = 0; g < GT; ++g) pv[g] = ps[row * GT + g];
     }
-    if (b + 1 < VS::NB) v_issue<DT, TR, NV>(vr, vg, nrows, b + 1, lane);
+#pragma unroll
+    for (int g = 0; g < GT; ++g)
+#pragma unroll
+      for (int v = 0; v < VEC; ++v) st.acc[g][v] = fmaf(pv[g], f[v], st.acc[g][v]);
   }
+  vr_free();
   }
   wave_sync_lds();   // ps and kbuf are rewritten by the next tile
 }
@@ -588,7 +576,7 @@ __device__ __forceinline__ void block_merge_store(const float *mrg, int wstride,
   for (int g = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave); g < heads; g += 4) {
     const size_t bn = (size_t)(bn0 + g);
     const auto rsrc = __builtin_amdgcn_make_buffer_rsrc((void *)(a.ws + bn * a.n_split * (kD + 2)), (short)0,
-                                                        a.n_split * kRecB, 0x00027000);
+                                                        a.n_split * kRecB, kBufferWord3);
     typedef float f32x2 __attribute__((ext_vector_type(2)));
     auto load2 = [&](int off) {
       return __builtin_bit_cast(f32x2, __builtin_amdgcn_raw_buffer_load_b64(rsrc, off, 0, kDeviceScope));
@@ -637,7 +625,7 @@ __device__ __forceinline__ bool decode_block_work(const DecodeArgs &a, int group
     w.gi = (int)(slot - round * (uint32_t)groups);
     piece = round * kXcds + piece % kXcds;
   }
-  w.u = piece / (uint32_t)a.n_split;
+  w.u = (uint32_t)((piece * a.split_inv) >> kSplitShift);
   w.sp = (int)(piece - w.u * (uint32_t)a.n_split);
   return !MANY || w.u < (uint32_t)a.units;
 }
@@ -645,6 +633,73 @@ inline unsigned decode_grid(const DecodeArgs &a, int groups) {
   const int64_t pieces = a.units * a.n_split, last = pieces % kXcds;   // last: pieces of an eight that is not full
   return (unsigned)(groups == 1 || last == 0 ? pieces * groups : (pieces - last) * groups + (groups - 1) * kXcds + last);
 }
+
+// The tiles of one wave in the order it takes them: every fourth pruned tile of its piece, then its share
+// of the unit's tail tiles, which are dealt out from the last piece and the last wave on, for these have the
+// fewest rows.  All members are wave-uniform; a tile that is not there has no bytes.
+constexpr int kTileRows = 32;
+struct Tile {
+  enum { kPruned, kTail, kNone };
+  int kind, nrows;
+  ByteRange k, v;
+};
+template <int EB, int VP>
+struct WaveTiles {
+  static constexpr int TR = kTileRows, kRowB = kD * EB;
+  const char *tail_k, *tail_v;
+  ByteRange kt, vt;      // the next pruned tile (a wave's pruned tiles are 128 rows apart, a multiple of 16 bytes in any pitch: they share their shift)
+  size_t k_step, v_step;
+  int k_last, v_last, nr_last, nt_p, nt_t, ti, tj, tj_step, s_tail;
+  __device__ __forceinline__ WaveTiles(const DecodeArgs &a, int64_t u, int sp, int wave) {
+    const int64_t s0 = min(a.S, (int64_t)sp * a.rows_per_split);
+    const int64_t s1 = min(a.S, s0 + a.rows_per_split);
+    nt_p = (int)((s1 - s0 + TR - 1) / TR);
+    nr_last = (int)(s1 - s0 - (int64_t)(nt_p - 1) * TR);   // rows of the piece's last tile
+    s_tail = a.s_tail;
+    nt_t = (s_tail + kTailRows - 1) / kTailRows;
+    const size_t row = (size_t)u * a.unit_rows + s0 + (size_t)wave * TR;   // first K_pruned / V row of this wave
+    kt = flat_rows<EB>(a.kp, row * a.ldk * EB, TR, a.T, a.ldk);
+    k_last = (kt.shift + ((nr_last - 1) * a.ldk + a.T) * EB + 15) & ~15;
+    k_step = (size_t)a.ldk * (4 * TR * EB);
+    if constexpr (VP) {
+      vt = flat_rows<EB>(a.v, row * a.ld_v * EB, TR, a.T_v, a.ld_v);
+      v_last = (vt.shift + ((nr_last - 1) * a.ld_v + a.T_v) * EB + 15) & ~15;
+      v_step = (size_t)a.ld_v * (4 * TR * EB);
+    } else {
+      vt = ByteRange{(const char *)a.v + row * kRowB, TR * kRowB, 0};
+      v_last = nr_last * kRowB;
+      v_step = 4 * TR * kRowB;
+    }
+    // the tail's value rows: a buffer of their own, or the rows that follow row S in v
+    const size_t trow = (size_t)u * a.s_tail_cap;
+    tail_k = (const char *)a.kt + trow * kRowB;
+    tail_v = a.unified_v ? (const char *)a.v + ((size_t)u * a.unit_rows + a.S) * kRowB : (const char *)a.vt + trow * kRowB;
+    ti = wave;
+    tj = (a.n_split - 1 - sp) + (3 - wave) * a.n_split;
+    tj_step = 4 * a.n_split;
+  }
+  __device__ __forceinline__ Tile next() {
+    Tile t;
+    if (ti < nt_p) {
+      const bool last = ti == nt_p - 1;
+      t.kind = Tile::kPruned;
+      t.nrows = last ? nr_last : TR;
+      t.k = ByteRange{kt.base, last ? k_last : kt.bytes, kt.shift};
+      t.v = ByteRange{vt.base, last ? v_last : vt.bytes, vt.shift};
+      kt.base += k_step;
+      vt.base += v_step;
+      ti += 4;
+    } else {
+      const int j0 = min(tj, nt_t) * kTailRows, n = max(min(kTailRows, s_tail - j0), 0);
+      t.kind = tj < nt_t ? Tile::kTail : Tile::kNone;
+      t.nrows = n;
+      t.k = ByteRange{tail_k + (size_t)j0 * kRowB, n * kRowB, 0};
+      t.v = ByteRange{tail_v + (size_t)j0 * kRowB, n * kRowB, 0};
+      tj += tj_step;
+    }
+    return t;
+  }
+};
 
 // KB: 16-byte K chunks a lane may have to stage for one TR-row pruned tile.
 // WPE: resident waves per SIMD the register budget is set for.
@@ -659,7 +714,6 @@ __global__ __launch_bounds__(256, WPE) void k_decode(DecodeArgs a, int groups, i
   using E = Elem<DT>;
   using VS = VShape<DT, TR>;
   constexpr int VEC = E::VEC, EB = E::EB, LPR = VS::LPR, LPK = kWave / TR;
-  constexpr int KBT = kTailRows * kD * EB / 16 / kWave;   // chunks per lane of a tail tile
   extern __shared__ uint4 smem[];
   float *qk = (float *)smem;                 // [GT][kQS] gathered query channels, 0 beyond T
   float *qf = qk + GT * kQS;                 // [GT][kQS] full query
@@ -668,7 +722,8 @@ __global__ __launch_bounds__(256, WPE) void k_decode(DecodeArgs a, int groups, i
   float *mrg = (float *)(qfp + GT * (kQS / 2));  // [4][GT][130] per-wave states for the final merge
   char *wbase = (char *)(mrg + 4 * GT * (kD + 2));
   __shared__ int s_last;
-  const int tid = threadIdx.x, wave = tid / kWave, lane = tid % kWave;
+  const int lane = threadIdx.x % kWave;
+  const int wave = uniform(threadIdx.x / kWave);   // tile counts and branches stay scalar
   const int wstride = kbuf_bytes + GT * (TR + (VP ? kPsPad : 0)) * 4;
   char *kbuf = wbase + (size_t)wave * wstride;
   float *ps = (float *)(kbuf + kbuf_bytes);
@@ -688,58 +743,29 @@ __global__ __launch_bounds__(256, WPE) void k_decode(DecodeArgs a, int groups, i
   if (!decode_block_work<GT == 4>(a, groups, work)) return;   // fewer: all heads of a unit
   const int sp = work.sp, gi = work.gi;
   const int64_t u = work.u;
-  const int G = a.N_q / a.N_kv;
+  const int G = a.G;
   const int64_t bn0 = u * G + (int64_t)gi * GT;   // first query head served (heads of unit u: u*G ..)
   // the unit's last block may have fewer than GT heads left: the other slots carry a zero query
   // (their logits are 0, their output is never stored)
   const int hb = min(GT, G - gi * GT);
 
-  const int64_t s0 = min(a.S, (int64_t)sp * a.rows_per_split);
-  const int64_t s1 = min(a.S, s0 + a.rows_per_split);
-  const int nt_p = (int)((s1 - s0 + TR - 1) / TR);
-  const int nt_t = (a.s_tail + kTailRows - 1) / kTailRows;   // tail tiles of the unit: tile j goes to split j % n_split
-  const char *kpg = (const char *)a.kp;
+  QueryStage<DT, GT> qst;
+  qst.issue(a.q, (size_t)bn0, hb, a.idx + (size_t)u * a.T, a.T);
 
-  constexpr int NV = VS::NV;
-  const size_t krow0 = (size_t)u * a.unit_rows + s0;     // first K_pruned / V row of this block
-  const u32x4 *vbase = (const u32x4 *)a.v + krow0 * LPR;
-
-  // the first tile's key and value bytes start moving before anything else happens
-  u32x4 kr[KB];
-  u32x4 vr[NV];
-  u32x4 vrp[VP ? KB : 1];
-  int shift_next = 0;
-  if (wave < nt_p) {
-    const int nr = (int)min((int64_t)TR, s1 - s0 - (int64_t)wave * TR);
-    shift_next = k_issue<DT, KB>(kr, kpg, (krow0 + (size_t)wave * TR) * a.ldk * EB, nr, a.T, a.ldk, lane);
-    if constexpr (VP)
-      vpd.shift = k_issue<DT, KB>(vrp, (const char *)a.v, (krow0 + (size_t)wave * TR) * a.ld_v * EB, nr, a.T_v,
-                                  a.ld_v, lane);
-    else
-      v_issue<DT, TR, NV>(vr, vbase + (size_t)wave * TR * LPR, nr, 0, lane);
-  }
+  // the first tile's key and value bytes start moving before anything is waited for
+  WaveTiles<EB, VP> tiles(a, u, sp, wave);
+  constexpr int VB = VP ? KB : VS::NL;
+  constexpr int TB = kTailRows * kD * EB / (16 * kWave);   // chunks per lane of a tail tile's keys, and of its values
+  static_assert(TB <= KB && TB <= VB, "a tail tile fits the staging registers");
+  u32x4 kr[KB], vr[VB];
+  Tile nt = tiles.next();
+  tile_issue<KB>(kr, nt.k.base, nt.k.bytes, lane);
+  tile_issue<VB>(vr, nt.v.base, nt.v.bytes, lane);
 
   // query: gather the kept channels (Sec. 3.3: the query is pruned with the stored mask)
-  const int16_t *uidx = a.idx + (size_t)u * a.T;
-  for (int o = tid; o < GT * kQS; o += 256) {
-    const int g = o / kQS, c = o % kQS;
-    const size_t qb = (size_t)(bn0 + g) * kD;
-    qf[o] = (g < hb && c < kD) ? E::load1(a.q, qb + c) : 0.f;
-    qk[o] = (g < hb && c < a.T) ? E::load1(a.q, qb + uidx[c]) : 0.f;
-  }
-  if constexpr (DT == THK_BF16) {
-    const uint16_t *q16 = (const uint16_t *)a.q;
-    for (int o = tid; o < GT * (kQS / 2); o += 256) {
-      const int g = o / (kQS / 2), c = 2 * (o % (kQS / 2));
-      const size_t qb = (size_t)(bn0 + g) * kD;
-      const bool used = g < hb;
-      const uint32_t f0 = used && c < kD ? q16[qb + c] : 0u, f1 = used && c + 1 < kD ? q16[qb + c + 1] : 0u;
-      const uint32_t k0 = used && c < a.T ? q16[qb + uidx[c]] : 0u;
-      const uint32_t k1 = used && c + 1 < a.T ? q16[qb + uidx[c + 1]] : 0u;
-      qfp[o] = f0 | (f1 << 16);
-      qkp[o] = k0 | (k1 << 16);
-    }
-  }
+  qst.commit((char *)mrg);
+  __syncthreads();
+  QueryStage<DT, GT>::pack((const char *)mrg, a.T, qf, qk, qfp, qkp);
   if constexpr (VP) {
     for (int o = lane; o < GT * kPsPad; o += kWave) ps[GT * TR + o] = 0.f;
   }
@@ -755,47 +781,26 @@ __global__ __launch_bounds__(256, WPE) void k_decode(DecodeArgs a, int groups, i
     for (int e = 0; e < 4; ++e) st.accp[g][e] = 0.f;
   }
 
-  // ---- pruned segment: the K bytes of this wave's next tile are in flight while
-  // the current one is computed
-  for (int ti = wave; ti < nt_p; ti += 4) {
-    const int nrows = (int)min((int64_t)TR, s1 - s0 - (int64_t)ti * TR);
-    const u32x4 *vg = vbase + (size_t)ti * TR * LPR;
-    const int shift = shift_next;
+  // ---- the bytes of this wave's next tile are in flight while the current one is computed:
+  // pruned tiles, then the wave's share of the unpruned tail (full-width keys, full query)
+  while (nt.kind == Tile::kPruned) {
+    const Tile t = nt;
+    nt = tiles.next();
     k_commit<KB>(kr, kbuf, lane);
-    if (ti != wave) {
-      if constexpr (VP)
-        vpd.shift = k_issue<DT, KB>(vrp, (const char *)a.v, (krow0 + (size_t)ti * TR) * a.ld_v * EB, nrows,
-                                    a.T_v, a.ld_v, lane);
-      else
-        v_issue<DT, TR, NV>(vr, vg, nrows, 0, lane);
-    }
-    if (ti + 4 < nt_p) {
-      const int nr = (int)min((int64_t)TR, s1 - s0 - (int64_t)(ti + 4) * TR);
-      shift_next = k_issue<DT, KB>(kr, kpg, (krow0 + (size_t)(ti + 4) * TR) * a.ldk * EB, nr, a.T, a.ldk, lane);
-    }
+    tile_issue<KB>(kr, nt.k.base, nt.k.bytes, lane);
     wave_sync_lds();
-    if constexpr (VP)
-      tile_compute<DT, GT, RA, TR, NV, 1, KB>(shift, nrows, a.T, a.ldk, qk, qkp, vg, vr, kbuf, ps, st,
-                                              a.scale_log2_d, lane, &vrp, &vpd);
-    else
-      tile_compute<DT, GT, RA, TR, NV>(shift, nrows, a.T, a.ldk, qk, qkp, vg, vr, kbuf, ps, st, a.scale_log2_d, lane);
+    vpd.shift = t.v.shift;
+    tile_compute<DT, GT, RA, TR, TR, VP>(t.k.shift, t.nrows, a.T, a.ldk, qk, qkp, vr, kbuf, ps, st, a.scale_log2_d, lane, &vpd,
+                                         [&]() { tile_issue<VB>(vr, nt.v.base, nt.v.bytes, lane); });
   }
-
-  // ---- unpruned tail segment (full-width keys, full query) ------------------
-  for (int ti = sp + wave * a.n_split; ti < nt_t; ti += 4 * a.n_split) {
-    const int j0 = ti * kTailRows;
-    const int nrows = min(kTailRows, a.s_tail - j0);
-    const size_t row0 = (size_t)u * a.s_tail_cap + j0;
-    u32x4 kt[KBT];
-    k_issue<DT, KBT>(kt, (const char *)a.kt, row0 * kD * EB, nrows, kD, kD, lane);
-    // the tail's value rows: a buffer of their own, or the rows that follow row S in v
-    const u32x4 *vg = a.unified_v ? (const u32x4 *)a.v + ((size_t)u * a.unit_rows + a.S + j0) * LPR
-                                  : (const u32x4 *)a.vt + row0 * LPR;
-    v_issue<DT, TR, NV>(vr, vg, nrows, 0, lane);
-    k_commit<KBT>(kt, kbuf, lane);
+  while (nt.kind == Tile::kTail) {
+    const Tile t = nt;
+    nt = tiles.next();
+    k_commit<TB>(kr, kbuf, lane);
+    tile_issue<TB>(kr, nt.k.base, nt.k.bytes, lane);
     wave_sync_lds();
-    tile_compute<DT, GT, 16, TR, NV, (VP ? 2 : 0)>(0, nrows, kD, kD, qf, qfp, vg, vr, kbuf, ps, st, a.scale_log2_d,
-                                                    lane);
+    tile_compute<DT, GT, 16, TR, kTailRows, 2 * VP>(0, t.nrows, kD, kD, qf, qfp, vr, kbuf, ps, st, a.scale_log2_d, lane, &vpd,
+                                                    [&]() { tile_issue<TB>(vr, nt.v.base, nt.v.bytes, lane); });
   }
 
   // ---- wave state -> LDS ---------------------------------------------------

@@ -39,7 +39,7 @@
 // stream stays short (a wave64 instruction holds its SIMD for four cycles, and three or four
 // waves share one): the wave index is made uniform so that tile counts, row counts and their
 // branches live in scalar registers; a whole tile (32 rows, all but a block's last) takes
-// straight-line paths -- value loads at fixed offsets without per-row clamps, the eight 4-row
+// a straight-line path -- the eight 4-row
 // steps of the second product without a test between them so that later reads overlap earlier
 // products; the logit loop covers the chunks that both halves have without masks or range checks, and
 // what is left of a row (an odd chunk, a partial one) is one masked step behind it; tiles of at
@@ -56,7 +56,7 @@ namespace thk {
 typedef short s16x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
-constexpr int kMqRows = 32;                       // rows per tile
+constexpr int kMqRows = kTileRows;                // rows per tile
 constexpr int kMqVBytes = kMqRows * kD * 2;       // a value tile in LDS
 constexpr int kMqVChunks = kMqVBytes / 16 / kWave;   // 16-byte value chunks per lane and tile
 
@@ -83,25 +83,13 @@ __device__ __forceinline__ float quad_column_reduce(float x) {
   return MAX ? max_nn(p.a, p.b) : p.a + p.b;
 }
 
-// Value rows of a tile into registers: chunk j * 64 + lane is 16 bytes of row 4 j + lane / 16.
-// Rows past a ragged tile's end re-read its last row (their probability is 0).
-__device__ __forceinline__ void mq_v_issue(u32x4 (&vr)[kMqVChunks], const u32x4 *__restrict__ vg, int nrows,
-                                           int lane) {
-  if (nrows == kMqRows) {   // a whole tile is one contiguous run: chunk j * 64 + lane as it lies in memory
-#pragma unroll
-    for (int j = 0; j < kMqVChunks; ++j) vr[j] = ld_stream(vg + j * kWave + lane);
-    return;
-  }
-  const int rsub = lane >> 4, col = lane & 15;
-#pragma unroll
-  for (int j = 0; j < kMqVChunks; ++j) vr[j] = ld_stream(vg + (size_t)min(4 * j + rsub, nrows - 1) * 16 + col);
-}
-
-// ... and into the slab: rows 256 bytes apart, the two halves of odd rows swapped.
-__device__ __forceinline__ void mq_v_commit(const u32x4 (&vr)[kMqVChunks], char *slab, int lane) {
+// Value rows of a tile (chunk j * 64 + lane is 16 bytes of row 4 j + lane / 16) into the slab: rows 256 bytes
+// apart, the two halves of odd rows swapped.
+template <int N, int M>
+__device__ __forceinline__ void mq_v_commit(const u32x4 (&vr)[M], char *slab, int lane) {
   const int rsub = lane >> 4, col = (lane & 15) ^ ((rsub & 1) << 3);
 #pragma unroll
-  for (int j = 0; j < kMqVChunks; ++j) *(u32x4 *)(slab + (4 * j + rsub) * 256 + col * 16) = vr[j];
+  for (int j = 0; j < N; ++j) *(u32x4 *)(slab + (4 * j + rsub) * 256 + col * 16) = vr[j];
 }
 
 // Logits of a tile whose key bytes are in the slab, for NH groups of four heads.  qrow: this lane's
@@ -129,7 +117,7 @@ template <int NH, int AL>
 __device__ __forceinline__ void mq_logits(const char *slab, int shift, int nrows, int W, int pitch_bytes,
                                           const uint32_t *qrow, int lane, f32x4 (&d)[NH]) {
   const int b = lane >> 2, x = lane & 3, half = b >> 3, bb = b & 7;
-  int row_off = shift + min(4 * bb + x, nrows - 1) * pitch_bytes;
+  int row_off = shift + __umul24(min(4 * bb + x, nrows - 1), pitch_bytes);
   const uint32_t sb = AL == 2 ? (uint32_t)row_off & 2u : 0u;
   if constexpr (AL == 2) row_off &= ~3;
   const char *rowp = slab + row_off;
@@ -144,9 +132,9 @@ __device__ __forceinline__ void mq_logits(const char *slab, int shift, int nrows
   }
   {
     // The chunks both halves have, without masks or range checks: off walks this lane's chunks as
-    // a byte offset, wrapping inside the half's range.
-    const int lo = half * h0 * 8, hi = lo + common * 8;
-    int off = lo + (common > 0 ? bb % common : 0) * 8;
+    // a byte offset from its block's place on, wrapping inside the half's range.
+    const int lo = half ? h0 * 8 : 0, hi = lo + common * 8;
+    int off = lo + (common < 4 ? 0 : bb < common ? bb : bb - common) * 8;
     auto pstep = [&](f32x4 (&acc)[NH]) {
       const s16x4 ka = __builtin_bit_cast(s16x4, key_chunk<AL>(rowp + off, sb));
 #pragma unroll
@@ -233,7 +221,7 @@ __device__ __forceinline__ void mq_softmax(const f32x4 &d, int nrows, float scal
 // acc += P . V for the tile whose value rows are in the slab; the probabilities of head group g
 // are in the 256 NT bytes at pline + 256 NT g, term by term.  The value operand is read once for all
 // groups.
-template <int NH, int NT>
+template <int NH, int NT, bool RAGGED = false>
 __device__ __forceinline__ void mq_values(const char *slab, const char *pline, int nrows, MqState (&st)[NH],
                                           int lane) {
   const int x = lane & 3, grp = lane >> 4, j = lane & 15, r = j >> 2, seg = j & 3;
@@ -259,15 +247,14 @@ __device__ __forceinline__ void mq_values(const char *slab, const char *pline, i
         st[g].acc[1] = mfma4(a[i][g], b1, st[g].acc[1]);
       }
   };
-  if (nrows == kMqRows) {   // a whole tile: straight-line code, the reads of later rows overlap the products
+  // a whole tile: straight-line code, the reads of later rows overlap the products
+  if (RAGGED || nrows < kMqRows) {
+    const int nks = (nrows + 3) >> 2;
+    for (int ks = 0; ks < nks; ++ks) rows4(ks);
+  } else {
 #pragma unroll
     for (int ks = 0; ks < kMqRows / 4; ++ks) rows4(ks);
-    return;
   }
-  const int nks = (nrows + 3) >> 2;
-#pragma unroll
-  for (int ks = 0; ks < kMqRows / 4; ++ks)
-    if (ks < nks) rows4(ks);
 }
 
 // accp += P . V_pruned for the tile whose value bytes sit in the slab as staged (first row at
@@ -324,9 +311,8 @@ constexpr int mq_terms(int AL) { return AL == 8 ? 2 : 3; }   // bf16 terms of a 
 // AL: alignment of the key rows in bytes (mq_logits).
 template <int KB, int WPE, int VP, int NH, int AL>
 __global__ __launch_bounds__(256, WPE) void k_decode_mq(DecodeArgs a, int groups, int slab_bytes) {
-  constexpr int DT = THK_BF16, GT = 4 * NH, EB = 2, TR = kMqRows, LPR = 16;
+  constexpr int DT = THK_BF16, GT = 4 * NH, EB = 2, TR = kMqRows;
   constexpr int NT = mq_terms(AL), PB = 256 * NT;
-  constexpr int KBT = kTailRows * kD * EB / 16 / kWave;   // chunks per lane of a tail tile
   extern __shared__ uint4 smem[];
   uint32_t *qkp = (uint32_t *)smem;                 // [GT][kQS/2] kept query channels, packed bf16, 0 beyond T
   uint32_t *qfp = qkp + GT * (kQS / 2);             // [GT][kQS/2] full query
@@ -341,48 +327,27 @@ __global__ __launch_bounds__(256, WPE) void k_decode_mq(DecodeArgs a, int groups
   if (!decode_block_work<NH == 2>(a, groups, work)) return;   // four slots: all heads of a unit
   const int sp = work.sp, gi = work.gi;
   const int64_t u = work.u;
-  const int G = (int)((uint32_t)a.N_q / (uint32_t)a.N_kv);
+  const int G = a.G;
   const int64_t bn0 = u * G + (int64_t)gi * GT;
   const int hb = min(GT, G - gi * GT);   // head slots in use; the others carry a zero query
 
-  const int64_t s0 = min(a.S, (int64_t)sp * a.rows_per_split);
-  const int64_t s1 = min(a.S, s0 + a.rows_per_split);
-  const int nt_p = (int)((s1 - s0 + TR - 1) / TR);
-  const int nr_last = (int)(s1 - s0 - (int64_t)(nt_p - 1) * TR);   // rows of the piece's last tile
-  const int nt_t = (a.s_tail + kTailRows - 1) / kTailRows;   // tail tiles of the unit: tile j goes to split j % n_split
-  const int tt0 = sp + wave * a.n_split;                     // this wave's first tail tile
-  const char *kpg = (const char *)a.kp;
-  auto tile_rows = [&](int ti) { return ti == nt_p - 1 ? nr_last : TR; };
-  auto tail_rows = [&](int ti) { return min(kTailRows, a.s_tail - ti * kTailRows); };
-  const u32x4 *ktail = (const u32x4 *)a.kt + (size_t)u * a.s_tail_cap * LPR;   // this unit's tail keys
-
-  QueryStage<GT> qs;
+  QueryStage<DT, GT> qs;
   qs.issue(a.q, (size_t)bn0, hb, a.idx + (size_t)u * a.T, a.T);
-  const size_t krow0 = (size_t)u * a.unit_rows + s0;     // first K_pruned / V row of this block
-  const u32x4 *vbase = (const u32x4 *)a.v + krow0 * LPR;
 
   // the first tile's key and value bytes start moving before anything is waited for
-  u32x4 kr[KB];
-  u32x4 vr[kMqVChunks];
-  u32x4 vrp[VP ? KB : 1];
-  int shift_next = 0, vshift = 0;
-  if (wave < nt_p) {
-    const int nr = tile_rows(wave);
-    shift_next = k_issue<DT, KB, true>(kr, kpg, (krow0 + (size_t)wave * TR) * a.ldk * EB, nr, a.T, a.ldk, lane);
-    if constexpr (VP)
-      vshift = k_issue<DT, KB, true>(vrp, (const char *)a.v, (krow0 + (size_t)wave * TR) * a.ld_v * EB, nr, a.T_v, a.ld_v,
-                               lane);
-    else
-      mq_v_issue(vr, vbase + (size_t)wave * TR * LPR, nr, lane);
-  } else if (tt0 < nt_t) {
-    tail_k_issue<DT, KBT>(kr, ktail + (size_t)tt0 * kTailRows * LPR, tail_rows(tt0), lane);
-  }
+  constexpr int VB = VP ? KB : kMqVChunks;
+  static_assert(kTailRows * 16 <= 4 * kWave && KB >= 4, "a tail tile is four chunks per lane");
+  u32x4 kr[KB], vr[VB];
+  WaveTiles<EB, VP> tiles(a, u, sp, wave);
+  Tile nt = tiles.next();
+  tile_issue<KB>(kr, nt.k.base, nt.k.bytes, lane);
+  tile_issue<VB>(vr, nt.v.base, nt.v.bytes, lane);
 
   // query: gather the kept channels (Sec. 3.3: the query is pruned with the stored mask), out of
   // LDS (the slabs are idle until the barrier below)
   qs.commit(wbase);
   __syncthreads();
-  query_pack<GT>(wbase, a.T, qfp, qkp);
+  QueryStage<DT, GT>::pack(wbase, a.T, nullptr, nullptr, qfp, qkp);
   __syncthreads();
 
   MqState st[NH];
@@ -397,63 +362,43 @@ __global__ __launch_bounds__(256, WPE) void k_decode_mq(DecodeArgs a, int groups
     }
   }
   const int x = lane & 3;
-  const int pitch_bytes = a.ldk * EB;
 
-  // ---- pruned segment: the bytes of this wave's next tile are in flight while the current
-  // one is computed
-  for (int ti = wave; ti < nt_p; ti += 4) {
-    const int nrows = tile_rows(ti);
-    const bool more = ti + 4 < nt_p;
-    const int nr4 = more ? tile_rows(ti + 4) : 0;
-    const int shift = shift_next;
+  // ---- the bytes of this wave's next tile are in flight while the current one is computed:
+  // pruned tiles, then the wave's share of the unpruned tail (full-width keys, full query)
+  while (nt.kind == Tile::kPruned) {
+    const Tile t = nt;
+    nt = tiles.next();
     k_commit<KB>(kr, slab, lane);
-    if (more)
-      shift_next = k_issue<DT, KB, true>(kr, kpg, (krow0 + (size_t)(ti + 4) * TR) * a.ldk * EB, nr4, a.T, a.ldk, lane);
-    else if (tt0 < nt_t)   // the wave's last pruned tile: its first tail tile's keys are next
-      tail_k_issue<DT, KBT>(kr, ktail + (size_t)tt0 * kTailRows * LPR, tail_rows(tt0), lane);
+    tile_issue<KB>(kr, nt.k.base, nt.k.bytes, lane);
     wave_sync_lds();
     f32x4 d[NH];
-    mq_logits<NH, AL>(slab, shift, nrows, a.T, pitch_bytes, qkp + x * (kQS / 2), lane, d);
+    mq_logits<NH, AL>(slab, t.k.shift, t.nrows, a.T, a.ldk * EB, qkp + x * (kQS / 2), lane, d);
 #pragma unroll
-    for (int g = 0; g < NH; ++g) mq_softmax<VP, NT>(d[g], nrows, a.scale_log2, st[g], pline + PB * g, lane);
+    for (int g = 0; g < NH; ++g) mq_softmax<VP, NT>(d[g], t.nrows, a.scale_log2, st[g], pline + PB * g, lane);
     wave_sync_lds();   // the key bytes are consumed: the slab takes the value rows
-    if constexpr (VP) {
-      const int vs = vshift;
-      k_commit<KB>(vrp, slab, lane);
-      if (more)
-        vshift = k_issue<DT, KB, true>(vrp, (const char *)a.v, (krow0 + (size_t)(ti + 4) * TR) * a.ld_v * EB, nr4, a.T_v,
-                                 a.ld_v, lane);
-      wave_sync_lds();
-      mq_values_pruned<NH, NT>(slab, vs, a.ld_v * EB, a.T_v, pline, nrows, st, lane);
-    } else {
-      mq_v_commit(vr, slab, lane);
-      if (more) mq_v_issue(vr, vbase + (size_t)(ti + 4) * TR * LPR, nr4, lane);
-      wave_sync_lds();
-      mq_values<NH, NT>(slab, pline, nrows, st, lane);
-    }
+    if constexpr (VP) k_commit<KB>(vr, slab, lane);
+    else mq_v_commit<VB>(vr, slab, lane);
+    tile_issue<VB>(vr, nt.v.base, nt.v.bytes, lane);
+    wave_sync_lds();
+    if constexpr (VP) mq_values_pruned<NH, NT>(slab, t.v.shift, a.ld_v * EB, a.T_v, pline, t.nrows, st, lane);
+    else mq_values<NH, NT>(slab, pline, t.nrows, st, lane);
     wave_sync_lds();   // slab and pline are rewritten by the next tile
   }
-
-  // ---- unpruned tail segment (full-width keys, full query) ------------------
-  for (int ti = tt0; ti < nt_t; ti += 4 * a.n_split) {
-    const int j0 = ti * kTailRows;
-    const int nrows = tail_rows(ti);
-    const size_t row0 = (size_t)u * a.s_tail_cap + j0;
-    if (ti != tt0) tail_k_issue<DT, KBT>(kr, ktail + (size_t)j0 * LPR, nrows, lane);
-    // the tail's value rows: a buffer of their own, or the rows that follow row S in v
-    const u32x4 *vg = a.unified_v ? (const u32x4 *)a.v + ((size_t)u * a.unit_rows + a.S + j0) * LPR
-                                  : (const u32x4 *)a.vt + row0 * LPR;
-    mq_v_issue(vr, vg, nrows, lane);
-    tail_k_commit<KBT>(kr, slab, lane);
+  while (nt.kind == Tile::kTail) {
+    const Tile t = nt;
+    nt = tiles.next();
+    k_commit<4>(kr, slab, lane);
+    tile_issue<4>(kr, nt.k.base, nt.k.bytes, lane);
     wave_sync_lds();
     f32x4 d[NH];
-    mq_logits<NH, 8>(slab, 0, nrows, kD, kD * EB, qfp + x * (kQS / 2), lane, d);
+    mq_logits<NH, 8>(slab, 0, t.nrows, kD, kD * EB, qfp + x * (kQS / 2), lane, d);
 #pragma unroll
-    for (int g = 0; g < NH; ++g) mq_softmax<VP, NT>(d[g], nrows, a.scale_log2, st[g], pline + PB * g, lane);
+    for (int g = 0; g < NH; ++g) mq_softmax<VP, NT>(d[g], t.nrows, a.scale_log2, st[g], pline + PB * g, lane);
     wave_sync_lds();
-    mq_v_commit(vr, slab, lane);
+    mq_v_commit<4>(vr, slab, lane);
+    tile_issue<4>(vr, nt.v.base, nt.v.bytes, lane);
     wave_sync_lds();
-    mq_values<NH, NT>(slab, pline, nrows, st, lane);
+    mq_values<NH, NT, true>(slab, pline, t.nrows, st, lane);
     wave_sync_lds();
   }
 

@@ -212,6 +212,10 @@ hipError_t launch_prune_solo(int dtype, const void *q_obs, const void *k, float 
                              int64_t kp_unit_rows, int G, int S_obs, int T, int ld, int NB, int64_t RB,
                              int hold, int spin_limit, hipStream_t st);
 
+// piece / n_split as a multiplication: a grid has fewer than 2^24 blocks of 256 threads, and a call at most
+// 2^12 pieces per unit, so with 36 fractional bits the rounding up never reaches the next integer
+// (the product stays below 2^61).  A division costs a wave some 25 instructions in front of its first load.
+constexpr int kSplitShift = 36;
 struct DecodeArgs {
   const void *q, *kp, *v, *kt, *vt;
   const int16_t *idx;
@@ -222,6 +226,8 @@ struct DecodeArgs {
   int32_t unified_v;          // tail values continue in v after row S (no separate v_tail)
   int32_t T, ldk, N_q, N_kv, s_tail, s_tail_cap, n_split, dtype;
   int64_t units;              // L * B * N_kv
+  uint64_t split_inv;         // 2^kSplitShift / n_split, rounded up
+  int32_t G;                  // N_q / N_kv
   float scale_log2;           // log2(e) / sqrt(D)
   double scale_log2_d;        // the same, not rounded to float (logits of fp32 inputs)
   // merge inside the launch: one flag word per (unit, head group, split) behind the split

@@ -1,0 +1,54 @@
+"""The tiles a wavefront of the decode kernels takes: 32-row tiles of its piece, then 16-row tiles of the tail,
+each asked for through a range that ends with the tile.  Sequence lengths and tail lengths around the tiles'
+edges, pieces without rows and waves without tiles, with NaN in every row behind the sequence and
+behind the tail: what a tile reads past its last row must not count."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2407_21018_amd as thk
+from oracle import oracle as O
+from paper_2407_21018_amd.synth import as_numpy
+from helpers import ATTN_TOL, DT, TDT, attn_rel_err, ws_tensor
+
+pytestmark = pytest.mark.gpu
+D, CAP = 128, 112
+
+
+def _kept(rng, U, T):
+    return np.stack([np.sort(rng.permutation(D)[:T]) for _ in range(U)]).astype(np.int16)
+
+
+@pytest.mark.parametrize("tail", [0, 1, 16, 17, 112])
+@pytest.mark.parametrize("dtype,G,T,T_v", [("bf16", 1, 76, 0), ("bf16", 2, 51, 0), ("bf16", 1, 64, 68), ("bf16", 4, 64, 0), ("bf16", 3, 51, 0),
+                                           ("bf16", 8, 100, 0), ("bf16", 8, 76, 44), ("f32", 1, 64, 0), ("f32", 4, 51, 0), ("f32", 2, 76, 128)])
+def test_decode_tile_edges(dtype, G, T, T_v, tail, decode_merge):
+    B, N_kv = 1, 3
+    U, N_q = B * N_kv, N_kv * G
+    rng = np.random.default_rng(1000 * tail + 10 * T + G)
+    idx_np, idxv_np = _kept(rng, U, T), _kept(rng, U, max(T_v, 1))
+    for S, n_split in [(1, 1), (31, 2), (32, 1), (33, 1), (127, 1), (129, 3), (160, 2), (449, 4), (1000, 16)]:
+        S_cap = S + 40
+        g = torch.Generator(device="cuda"); g.manual_seed(S)
+        rnd = lambda *shape: torch.randn(*shape, generator=g, device="cuda").to(TDT[dtype])
+        q, kp, v = rnd(B, N_q, D), rnd(U, S_cap, T), rnd(U, S_cap, T_v or D)
+        kt, vt = rnd(U, CAP, D), rnd(U, CAP, D)
+        for x, n in ((kp, S), (v, S), (kt, tail), (vt, tail)):
+            x[:, n:] = float("nan")
+        idx, idxv = torch.from_numpy(idx_np).cuda(), torch.from_numpy(idxv_np).cuda()
+        shape = thk.make_shape(1, B, N_q, N_kv, D, S, 1, T, 0, DT[dtype], n_split, 0, S_cap)
+        out = torch.empty(B * N_q, D, dtype=q.dtype, device="cuda")
+        ws = ws_tensor(thk.thk_workspace_bytes(shape, thk.THK_OP_DECODE))
+        if T_v:
+            thk.thk_decode_attn_kv(shape, q, kp, idx, v, idxv, T_v, T_v, kt, vt, tail, CAP, out, ws)
+        else:
+            thk.thk_decode_attn(shape, q, kp, idx, v, kt, vt, tail, CAP, out, ws)
+        torch.cuda.synchronize()
+        h = lambda x, n: as_numpy(x[:, :n].contiguous()).reshape(B, N_kv, n, x.shape[-1])
+        tails = (h(kt, tail), h(vt, tail), tail) if tail else ()
+        if T_v:
+            ref = O.decode_attn_kv(as_numpy(q), h(kp, S), idx_np.reshape(B, N_kv, T), h(v, S), idxv_np.reshape(B, N_kv, T_v), dtype, *tails)
+        else:
+            ref = O.decode_attn(as_numpy(q), h(kp, S), idx_np.reshape(B, N_kv, T), h(v, S), dtype, *tails)
+        err = attn_rel_err(out, ref.reshape(-1, D)).max()
+        assert err <= ATTN_TOL[dtype], f"S={S} n_split={n_split}: {err}"
