@@ -298,22 +298,24 @@ Split decode_split(const thk_shape *s, size_t ws_bytes = SIZE_MAX) {
   return {n, rows};
 }
 
-// Small calls merge their split records inside the launch: the block that finishes last for a
-// head group does it, and the second launch goes away.  The hand-off costs three memory round trips
-// at the end of the kernel and, per four heads, one for the records; a second launch costs about
-// as much and its dispatch.  Merged by the kernel / inside, us per call: 8 units x 1000 rows, four
-// heads, 8 pieces 10.0 / 9.0; 64 units x 2000 rows, 8 pieces, one head 14.5 / 14.0, four heads 16.2 /
-// 16.0; eight heads, 8 units x 2000 rows, 8 pieces 14.2 / 14.4, 64 units x 8191 rows 35.1 / 37.1.  From
-// 1024 blocks on the exchange ends a launch whose memory queues are full: 128 units x 8 pieces 37.8 /
-// 38.2, 64 x 16 pieces of 2048 rows 127.3 / 130.6.  Hence: at most 16 pieces, at most four heads per
-// block, at most two blocks per compute unit.
+// Calls of at most 16 pieces merge their split records inside the launch: the block that finishes last for a
+// head group does it, and the second launch goes away.  The hand-off is three memory round trips
+// at the end of the kernel; a second launch costs about as much and its dispatch.  Merged by the kernel / inside,
+// us per call: one head, 32 units x 320 rows 8.9 / 7.2, 80 x 576 11.4 / 9.7, 160 x 2752 33.3 / 31.9, 256 x 9722 108.4 /
+// 106.4; four heads, 16 x 6494 rows 14.8 / 12.5, 128 x 2708 (512 blocks) 29.0 / 28.1, 96 x 5971 (768) 38.5 / 39.8, 128 x
+// 12777 (1024) 108.1 / 110.4; eight heads, 8 x 863 12.4 / 10.8, 40 x 2602 17.3 / 16.3, 80 x 12211 (480) 71.5 / 69.6, 64 x
+// 24512 (512) 106.4 / 109.1, 96 x 11824 (768) 71.1 / 78.0.  A block of four or eight heads exchanges four or eight records, and
+// with two such blocks per compute unit and more the exchange ends a launch whose memory queues are full.
+// Hence: up to two heads per block always, four up to two blocks per compute unit, eight below that.
 // THK_DECODE_MERGE = kernel | fused overrides (fused only within the 16 pieces).
 bool decode_merge_in_launch(const thk_shape *s, int n_split) {
   if (n_split < 2 || n_split > kDecodeFuseMaxSplit) return false;
   const char sw = env_switches().decode_merge;
   if (sw == 'k') return false;
   if (sw == 'f') return true;
-  return decode_heads_per_block(s) <= 4 && decode_groups(s) * n_split <= 2 * (int64_t)kCUs;
+  const int hpb = decode_heads_per_block(s);
+  const int64_t blocks = decode_groups(s) * n_split;
+  return hpb <= 2 || blocks < 2 * (int64_t)kCUs || (hpb == 4 && blocks == 2 * (int64_t)kCUs);
 }
 
 // Units per group in the staged form of thk_prune (three launches per group).

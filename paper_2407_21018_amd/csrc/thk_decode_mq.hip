@@ -239,6 +239,8 @@ __device__ __forceinline__ void mq_values(const char *slab, const char *pline, i
     for (int g = 0; g < NH; ++g)
 #pragma unroll
       for (int i = 0; i < NT; ++i) a[i][g] = *(const s16x4 *)(pa + (g * NT + i) * 256 + ks * 32);
+    // (three terms of eight heads: a read that runs ahead of the step before would not find registers)
+    if constexpr (NT * NH == 6) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int i = 0; i < NT; ++i)
 #pragma unroll
@@ -278,8 +280,7 @@ __device__ __forceinline__ void mq_values_pruned(const char *slab, int shift, in
     for (int g = 0; g < NH; ++g)
 #pragma unroll
       for (int i = 0; i < NT; ++i) a[i][g] = *(const s16x4 *)(pa + (g * NT + i) * 256 + ks * 32);
-    // (three terms of eight heads: a read that runs ahead of the step before would not find registers)
-    if constexpr (NT * NH == 6) __builtin_amdgcn_sched_barrier(0);
+    if constexpr (NT * NH == 6) __builtin_amdgcn_sched_barrier(0);   // as in mq_values
 #pragma unroll
     for (int i = 0; i < NT; ++i)
 #pragma unroll
@@ -323,6 +324,7 @@ __global__ __launch_bounds__(256, WPE) void k_decode_mq(DecodeArgs a, int groups
   char *pline = slab + slab_bytes;               // PB bytes of probabilities per head group
   __shared__ int s_last;
 
+  want_arguments(a, groups);
   DecodeWork work;
   if (!decode_block_work<NH == 2>(a, groups, work)) return;   // four slots: all heads of a unit
   const int sp = work.sp, gi = work.gi;

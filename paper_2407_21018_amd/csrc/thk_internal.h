@@ -82,6 +82,7 @@ template <> struct Elem<THK_F32> {
   }
   __device__ static inline float load1(const void *p, size_t i) { return ((const float *)p)[i]; }
   __device__ static inline void store1(void *p, size_t i, float x) { ((float *)p)[i] = x; }
+  __device__ static inline void store2(void *p, size_t i, float x, float y) { *(float2 *)((float *)p + i) = make_float2(x, y); }   // i even
 };
 template <> struct Elem<THK_BF16> {
   static constexpr int EB = 2, VEC = 8;
@@ -102,6 +103,9 @@ template <> struct Elem<THK_BF16> {
     return (uint16_t)(u >> 16);
   }
   __device__ static inline void store1(void *p, size_t i, float x) { ((uint16_t *)p)[i] = round_bf16(x); }
+  __device__ static inline void store2(void *p, size_t i, float x, float y) {   // i even
+    *(uint32_t *)((uint16_t *)p + i) = (uint32_t)round_bf16(x) | ((uint32_t)round_bf16(y) << 16);
+  }
 };
 
 // ---- one-shot timing hook (thk_profile_next) ----
