@@ -85,34 +85,15 @@ __device__ inline double lane_swap1(double x) {
   return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
 }
 
-// RA bytes of an LDS row at element offset t, widened to floats.
-template <int DT, int RA>
-__device__ inline void lds_row_read(const char *rowp, int t, float *f) {
-  using E = Elem<DT>;
-  const char *p = rowp + (size_t)t * E::EB;
-  if constexpr (DT == THK_BF16) {
-    if constexpr (RA == 16) {
-      float g[8]; E::unpack(*(const uint4 *)p, g);
-#pragma unroll
-      for (int i = 0; i < 8; ++i) f[i] = g[i];
-    } else if constexpr (RA == 8) {
-      const uint2 r = *(const uint2 *)p;
-      f[0] = __uint_as_float(r.x << 16); f[1] = __uint_as_float(r.x & 0xffff0000u);
-      f[2] = __uint_as_float(r.y << 16); f[3] = __uint_as_float(r.y & 0xffff0000u);
-    } else if constexpr (RA == 4) {
-      const uint32_t r = *(const uint32_t *)p;
-      f[0] = __uint_as_float(r << 16); f[1] = __uint_as_float(r & 0xffff0000u);
-    } else {
-      f[0] = __uint_as_float((uint32_t) * (const uint16_t *)p << 16);
-    }
+// RA bytes of an fp32 row in LDS.
+template <int RA>
+__device__ inline void lds_floats(const char *p, float *f) {
+  if constexpr (RA == 16) {
+    const float4 r = *(const float4 *)p; f[0] = r.x; f[1] = r.y; f[2] = r.z; f[3] = r.w;
+  } else if constexpr (RA == 8) {
+    const float2 r = *(const float2 *)p; f[0] = r.x; f[1] = r.y;
   } else {
-    if constexpr (RA == 16) {
-      const float4 r = *(const float4 *)p; f[0] = r.x; f[1] = r.y; f[2] = r.z; f[3] = r.w;
-    } else if constexpr (RA == 8) {
-      const float2 r = *(const float2 *)p; f[0] = r.x; f[1] = r.y;
-    } else {
-      f[0] = *(const float *)p;
-    }
+    f[0] = *(const float *)p;
   }
 }
 
@@ -125,6 +106,20 @@ __device__ inline void lds_words(const char *p, uint32_t (&w)[DW]) {
     const uint2 r = *(const uint2 *)p; w[0] = r.x; w[1] = r.y;
   } else {
     w[0] = *(const uint32_t *)p;
+  }
+}
+
+// DW words of a bf16 row in LDS whose rows start at multiples of RA bytes.  RA = 2 (dense rows of an odd T: 51 is
+// lambda = 0.6): p is the word below the row's place, of which a lane takes the upper or the lower halves -- its
+// row starts on a word or in the middle of one (shift_bytes 0, 2), the same for the whole row.
+template <int RA, int DW>
+__device__ __forceinline__ void bf16_words(const char *p, uint32_t shift_bytes, uint32_t (&w)[DW]) {
+  if constexpr (RA >= 4 * DW) {
+    lds_words<DW>(p, w);
+  } else {
+    const uint32_t *q = (const uint32_t *)p;
+#pragma unroll
+    for (int d = 0; d < DW; ++d) w[d] = RA == 2 ? __builtin_amdgcn_alignbyte(q[d + 1], q[d], shift_bytes) : q[d];
   }
 }
 
@@ -233,7 +228,7 @@ struct QueryStage {
     if (tid >= 128) ((int16_t *)(lds + GT * LPR * 16))[tid - 128] = ch;   // rows, then the list
   }
   // The staged rows for the logits: full [GT][kQS] and gathered kept channels (zero beyond T), both zero beyond
-  // channel 128, as floats (qf, qk; may be null) and for bf16 as packed pairs (qfp, qkp, [GT][kQS / 2] words).
+  // channel 128: fp32 inputs as floats (qf, qk), bf16 inputs as packed pairs (qfp, qkp, [GT][kQS / 2] words).
   static __device__ __forceinline__ void pack(const char *lds, int T, float *qf, float *qk, uint32_t *qfp, uint32_t *qkp) {
     const B *raw = (const B *)lds;
     const int16_t *list = (const int16_t *)(lds + GT * LPR * 16);
@@ -252,10 +247,9 @@ struct QueryStage {
         qfp[g * (kQS / 2) + w] = f0 | (f1 << 16);
         qkp[g * (kQS / 2) + w] = k0 | (k1 << 16);
       }
-      if (qf != nullptr) {
-        constexpr int SH = DT == THK_BF16 ? 16 : 0;
-        *(float2 *)(qf + g * kQS + 2 * w) = make_float2(__uint_as_float(f0 << SH), __uint_as_float(f1 << SH));
-        *(float2 *)(qk + g * kQS + 2 * w) = make_float2(__uint_as_float(k0 << SH), __uint_as_float(k1 << SH));
+      if constexpr (DT == THK_F32) {
+        *(uint2 *)(qf + g * kQS + 2 * w) = uint2{f0, f1};
+        *(uint2 *)(qk + g * kQS + 2 * w) = uint2{k0, k1};
       }
     }
   }
@@ -297,79 +291,90 @@ __device__ __forceinline__ void tile_compute(int shift, int nrows, int W, int ld
   using VS = VShape<DT, TR>;
   constexpr int VEC = E::VEC, EB = E::EB;
   constexpr int LPK = kWave / TR;            // lanes that share one K row (1 or 2)
-  constexpr int EPR = RA / EB;               // elements per LDS row read (one granule)
   const int vrow = lane / VS::LPR;
   const int r = lane / LPK, h = lane % LPK;
 
-  // ---- logits: LPK lanes per row, contiguous granule ranges ----------------
+  // ---- logits: two lanes per row, each a contiguous run of granules -----------
+  static_assert(LPK == 2, "two lanes share a row");
   const int rr = min(r, nrows - 1);
-  const char *rowp = kbuf + shift + (size_t)rr * ld * EB;
-  const int n_gran = W / EPR;
-  const int gran0 = (n_gran + LPK - 1) / LPK;              // granules of lane share 0 = trip count
-  const int my_first = h * gran0;
-  const int my_cnt = (LPK == 1 || h == 0) ? gran0 : n_gran - gran0;
+  int row_off = shift + rr * ld * EB;
   ZT z[GT];
 #pragma unroll
   for (int g = 0; g < GT; ++g) z[g] = (ZT)0;
-  if constexpr (DT == THK_BF16 && RA >= 4) {
+  if constexpr (DT == THK_BF16) {
     // bf16 pairs straight from LDS into v_dot2c_f32_bf16: products are exact, sums in fp32.
     // Keys and packed query share their byte offsets (two bytes per channel), so one offset
-    // walks both; the steps that every lane has run without a test, and where share 0 has one
-    // granule more, the lanes of share 1 take granule 0 against the zero slot of q in that step.
-    constexpr int DW = RA / 4;   // words per granule
-    const int common = LPK == 1 ? gran0 : n_gran - gran0;
-    const char *kw_p = rowp + my_first * RA;
-    const char *qw_p = (const char *)qp + my_first * RA;
-    constexpr int UNR = (GT == 4 && DW == 2) ? 1 : 2;   // the one shape that ran out of registers at 2
+    // walks both, in granules of DW words.  The steps that both lanes have run without a test; what is left is one
+    // masked step: lane 0 of a row takes its odd granule, lane 1 the row's last, partial one, whose elements past W
+    // (row padding, or whatever follows the tile) count as zero; a lane with nothing left takes zeros.
+    // (Rows of odd pitch used to be read channel by channel, four times the instructions: T = 51, 80 units x 4719
+    // rows 28.9 -> 25.2 us, 152 x 93039 807 -> 746; 40 x 39096 with pruned values 90.3 -> 73.8; T = 75, 2 heads, 96 x
+    // 53760 345 -> 309.)
+    constexpr int DW = RA == 16 ? 4 : 2, GB = 4 * DW, EPG = 2 * DW;
+    const int n_gran = W / EPG, rem = W % EPG;
+    const int gran0 = (n_gran + 1) / 2, common = n_gran - gran0;
+    const uint32_t sb = RA == 2 ? (uint32_t)row_off & 2u : 0u;
+    if constexpr (RA == 2) row_off &= ~3;
+    const char *rowp = kbuf + row_off, *qb = (const char *)qp;
+    const int first = h * gran0 * GB;
+    constexpr int UNR = GT == 1 ? 4 : (GT == 4 && DW == 2) ? 1 : 2;   // the widest reading ahead that registers allow
 #pragma unroll UNR
     for (int i = 0; i < common; ++i) {
       uint32_t kw[DW];
-      lds_words<DW>(kw_p + i * RA, kw);
+      bf16_words<RA, DW>(rowp + first + i * GB, sb, kw);
 #pragma unroll
       for (int g = 0; g < GT; ++g) {
         uint32_t qw[DW];
-        lds_words<DW>(qw_p + g * (kQS * 2) + i * RA, qw);
+        lds_words<DW>(qb + first + g * (kQS * 2) + i * GB, qw);
 #pragma unroll
         for (int d = 0; d < DW; ++d) z[g] = dot2_bf16(kw[d], qw[d], z[g]);
       }
     }
-    if (LPK == 2 && common < gran0) {
+    if (common < gran0 || rem != 0) {
+      const bool any = h == 0 ? common < gran0 : rem != 0;
+      const int ne = !any ? 0 : h == 0 ? EPG : rem;                 // elements that count
+      const int off = any ? (h == 0 ? common : n_gran) * GB : 0;
       uint32_t kw[DW];
-      lds_words<DW>(rowp + (h == 0 ? common * RA : 0), kw);
-      const char *qz = (const char *)qp + (h == 0 ? common * RA : kD * 2);
+      bf16_words<RA, DW>(rowp + off, sb, kw);
+#pragma unroll
+      for (int d = 0; d < DW; ++d) kw[d] &= ne >= 2 * d + 2 ? 0xffffffffu : ne == 2 * d + 1 ? 0x0000ffffu : 0u;
 #pragma unroll
       for (int g = 0; g < GT; ++g) {
         uint32_t qw[DW];
-        lds_words<DW>(qz + g * (kQS * 2), qw);
+        lds_words<DW>(qb + off + g * (kQS * 2), qw);
 #pragma unroll
         for (int d = 0; d < DW; ++d) z[g] = dot2_bf16(kw[d], qw[d], z[g]);
       }
     }
   } else {
+    constexpr int EPR = RA / EB;               // elements per LDS row read (one granule)
+    const char *rowp = kbuf + row_off;
+    const int n_gran = W / EPR;
+    const int gran0 = (n_gran + 1) / 2;                      // granules of lane share 0 = trip count
+    const int my_first = h * gran0;
+    const int my_cnt = h == 0 ? gran0 : n_gran - gran0;
 #pragma unroll 2
     for (int i = 0; i < gran0; ++i) {
       // a lane whose share is exhausted re-reads granule 0 against the zero slot of q
-      const bool valid = (LPK == 1) || i < my_cnt;
+      const bool valid = i < my_cnt;
       const int tk = valid ? (my_first + i) * EPR : 0;
       const int tq = valid ? tk : kD;
       float f[EPR];
-      lds_row_read<DT, RA>(rowp, tk, f);
+      lds_floats<RA>(rowp + tk * EB, f);
 #pragma unroll
       for (int g = 0; g < GT; ++g)
 #pragma unroll
         for (int e = 0; e < EPR; ++e) z[g] = fma_z((ZT)f[e], (ZT)qs[g * kQS + tq + e], z[g]);
     }
-  }
-  for (int t = n_gran * EPR; t < W; ++t) {   // elements past the last whole granule: share 0
-    const float f = E::load1(rowp, t);
-    const int tq = (LPK == 1 || h == 0) ? t : kD;
+    for (int t = n_gran * EPR; t < W; ++t) {   // elements past the last whole granule: share 0
+      const float f = E::load1(rowp, t);
+      const int tq = h == 0 ? t : kD;
 #pragma unroll
-    for (int g = 0; g < GT; ++g) z[g] = fma_z((ZT)f, (ZT)qs[g * kQS + tq], z[g]);
+      for (int g = 0; g < GT; ++g) z[g] = fma_z((ZT)f, (ZT)qs[g * kQS + tq], z[g]);
+    }
   }
-  if constexpr (LPK == 2) {
 #pragma unroll
-    for (int g = 0; g < GT; ++g) z[g] += lane_swap1(z[g]);
-  }
+  for (int g = 0; g < GT; ++g) z[g] += lane_swap1(z[g]);
 
   // ---- running softmax (base-2 exponent, scale folded in) ----------------
   // every row is held by LPK lanes, so l counts each probability LPK times
@@ -744,11 +749,14 @@ __global__ __launch_bounds__(256, WPE) void k_decode(DecodeArgs a, int groups, i
   using VS = VShape<DT, TR>;
   constexpr int VEC = E::VEC, EB = E::EB, LPR = VS::LPR, LPK = kWave / TR;
   extern __shared__ uint4 smem[];
-  float *qk = (float *)smem;                 // [GT][kQS] gathered query channels, 0 beyond T
-  float *qf = qk + GT * kQS;                 // [GT][kQS] full query
-  uint32_t *qkp = (uint32_t *)(qf + GT * kQS);   // [GT][kQS/2] qk as packed bf16 pairs (bf16 inputs)
-  uint32_t *qfp = qkp + GT * (kQS / 2);          // [GT][kQS/2] qf as packed bf16 pairs
-  float *mrg = (float *)(qfp + GT * (kQS / 2));  // [4][GT][130] per-wave states for the final merge
+  // the gathered query channels (0 beyond T) and the full query: [GT][kQS] floats each (fp32 inputs), or as
+  // packed pairs, [GT][kQS / 2] words each (bf16 inputs)
+  constexpr bool F32 = DT == THK_F32;
+  constexpr int QW = GT * kQS * EB / 4;          // words per copy
+  uint32_t *qkw = (uint32_t *)smem, *qfw = qkw + QW;
+  float *qk = F32 ? (float *)qkw : nullptr, *qf = F32 ? (float *)qfw : nullptr;
+  uint32_t *qkp = F32 ? nullptr : qkw, *qfp = F32 ? nullptr : qfw;
+  float *mrg = (float *)(qfw + QW);              // [4][GT][130] per-wave states for the final merge
   char *wbase = (char *)(mrg + 4 * GT * (kD + 2));
   __shared__ int s_last;
   const int lane = threadIdx.x % kWave;
@@ -899,7 +907,7 @@ inline hipError_t decode_launch_one(const DecodeArgs &a, int groups, hipStream_t
   int kbuf = KB * kWave * 16;                      // every staged chunk has an LDS slot
   const int tailbuf = kTailRows * kD * eb;
   if (kbuf < tailbuf) kbuf = tailbuf;
-  const size_t lds = (size_t)(3 * GT * kQS + 4 * GT * (kD + 2)) * 4 + 4 * ((size_t)kbuf + GT * (TR + (VP ? kPsPad : 0)) * 4);
+  const size_t lds = (size_t)2 * GT * kQS * eb + (size_t)4 * GT * (kD + 2) * 4 + 4 * ((size_t)kbuf + GT * (TR + (VP ? kPsPad : 0)) * 4);
   const dim3 grid(decode_grid(a, groups)), block(256);
   {
     static DynLds set;   // one per instantiation
