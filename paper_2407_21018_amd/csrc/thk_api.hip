@@ -196,27 +196,37 @@ unsigned long long next_nonce() {
 // The split records of a call are merged inside the launch (by the block that finishes last for
 // a head group) where that saves more than it costs -- see decode_merge_in_launch below.
 bool decode_merge_in_launch(const thk_shape *s, int n_split);
+bool merges_in_launch(int hpb, int64_t blocks);
 
-// The number of pieces (no fewer than least) with the least estimated time, if that is at least 9 %
-// below the estimate for n0.  With k = steps of a piece (128 rows by four waves), R = blocks that are
-// resident on a compute unit and L = blocks on the fullest one, in us:
-//     sum over rounds of resident blocks of max(k t_step, l k t_stream), l = R, in the last round what is
-//     left,  +  t_block L  +  merge
-// t_step: a step that waits for its own loads, 2.4, 2.7 where a block serves eight heads, 4.8 in fp32;
-// t_stream: a compute unit's share of the memory rate, 0.036 per KB of a step's rows (full-width values;
-// pruned ones are narrower, which the shape does not tell); t_block: what a block costs whatever its length,
-// 0.8, in fp32 3.4; merge: nothing for one piece, 3.5 inside the launch, by the merge kernel 4, 0.015 per
-// piece and 0.2 per thousand records.  Fitted to 570 random shapes (1-16 heads per KV head, 1-400 units,
-// 256-51200 rows, a third fp32, a quarter with pruned values), each measured at its piece counts with
-// whole steps.  On 290 other shapes it takes 1.7 % more than the best count on average, 5 of them over 5 %
-// more than the powers of two above would (worst: fp32, 16 units x 8 heads x 3423 rows, 35.2 against
-// 27.6 us); the powers of two take 9.8 % more.  What they miss is rounds (136 units x 5184 rows: 4 pieces
-// are 544 blocks, 3 on some compute units and 2 on others; 7 pieces: 62.4 -> 54.5 us) and whole steps (16
-// units x 1815 rows, 15 pieces of one step instead of 8: 11.0 -> 9.5 us).  (An estimate without R, with
-// cheaper blocks and one merge cost cut short calls too often: 192 units x 5 heads x 797 rows, T = 96, 4
-// pieces instead of 2: 25.3 -> 30.6 us.)
+// The number of pieces (no fewer than least) with the least estimated time, if that is at least 6 % (fp32: 9 %) below
+// the estimate for n0.  With k = steps of a piece (128 rows by
+// four waves, b KB of rows each), R = blocks that are resident on a compute unit, in us:
+//     sum over rounds of resident blocks  +  t_block * blocks on the fullest compute unit  +  merge  +  t0
+// A round's compute units hold q blocks each and some of them one more.  They move their rows at the least of what the memory
+// gives them (an equal share of 7.6 TB/s: 30 KB/us, more for the ones left over once the others are done), of what a compute
+// unit takes (c1 KB/us with one block, c2 with several), and of what waiting for its own loads lets a block take (k t_step).
+// t_block: what a block costs whatever its length; merge: nothing for one piece, m_in inside the launch, m_out + 0.01
+// per piece + 0.2 per thousand records by the merge kernel.  Rows whose pitch makes the kernels put words together (odd) and
+// long ones that take the wide staging class (wide) slow t_step, c1 and c2 by a factor.  The width of
+// the value rows is not known here (the workspace must not depend on it), so the estimate is the mean of those of 128
+// and of 64 channels.
+// Constants fitted per kernel to 1400 random bf16 shapes (1-8 heads per KV head, 1-1280 units, 256-131072 rows, a
+// quarter with pruned values), each measured at up to 29 piece counts; over these and 330 others the count taken costs 1.7 %
+// more than the best one on average (an estimate with the memory rate per block instead of per compute unit: 3.7 %),
+// 370 of them take 3 % and more less than with that, 55 more.
+// (fp32 keeps that one: fitted like this, calls of over 600 MB became up to 10 % slower.)  What it knows that a resident set of blocks (n0) misses: a few
+// blocks more than a multiple of 256 cost a round of few (64 units x 32768 rows, 4 heads: 4 pieces 121 us, 5 151); pieces of one
+// step that leave compute units idle (16 units x 1815 rows: 15 pieces instead of 8, 11.0 -> 9.5); that one
+// block per compute unit saturates the memory and fewer, longer streams use it better.
+struct DecodeCost { double t0, t_step, c1, c2, t_block, m_in, m_out, odd, wide; };
+const DecodeCost &decode_cost(int hpb) {
+  static constexpr DecodeCost h1 = {3.45, 1.0, 56.3, 44.7, 0.59, 2.04, 3.69, 1.05, 1.20}, h2 = {3.89, 1.12, 43.5, 44.3, 0.82, 2.33, 3.39, 1.18, 1.19},
+                              h4 = {3.69, 1.17, 38.8, 39.0, 0.50, 2.35, 3.59, 1.22, 1.0}, h8 = {3.9, 1.57, 30.5, 38.3, 0.98, 3.04, 3.82, 1.15, 1.13};
+  return hpb == 1 ? h1 : hpb == 2 ? h2 : hpb == 4 ? h4 : h8;
+}
 int decode_pieces(const thk_shape *s, int hpb, int64_t wgs, int64_t steps, int n0, int least) {
   constexpr int kMaxPieces = 128;
+  constexpr double kRate = 7600.0;   // KB per us
   // more pieces only while the records fit the scratch array of thk_decode_attn_static, which takes
   // every call that n0 pieces fit
   const int64_t heads = (int64_t)s->L * s->B * s->N_q;
@@ -224,28 +234,56 @@ int decode_pieces(const thk_shape *s, int hpb, int64_t wgs, int64_t steps, int n
   if (n0 > 1 && n0 > fit) return n0;
   const bool f32 = s->dtype == THK_F32, wide = ld_of(s) > 79;   // wide: the staging class of long rows
   const int resident = f32 ? (hpb == 4 || wide ? 2 : 3) : (hpb == 8 ? 3 : 4) - (wide ? 1 : 0);
-  const double t_step = f32 ? 4.8 : hpb == 8 ? 2.7 : 2.4;
-  const double t_stream = 0.036 * 128 * (ld_of(s) + kD) * elem_bytes(s->dtype) / 1024.0;
-  const double t_block = f32 ? 3.4 : 0.8;
-  auto cost = [&](int64_t n, int64_t k) {
+  // fp32: rounds x max(4.8 k, blocks per compute unit x k x share of the memory rate), 3.4 per block, and the merge
+  auto cost_f32 = [&](int64_t n, double k) {
     const int64_t blocks = wgs * n, rounds = ceil_div(blocks, (int64_t)kCUs * resident);
-    auto round = [&](int64_t l) { return (double)k * std::max(t_step, (double)l * t_stream); };
+    const double t_stream = 0.036 * 128 * (ld_of(s) + kD) * 4 / 1024.0;
+    auto round = [&](int64_t l) { return k * std::max(4.8, (double)l * t_stream); };
     const int64_t last = ceil_div(blocks - (rounds - 1) * kCUs * resident, kCUs);
-    const bool in_launch = n <= kDecodeFuseMaxSplit && blocks <= 2 * kCUs && hpb <= 4;
+    const bool in_launch = n <= kDecodeFuseMaxSplit && blocks <= 2 * kCUs;
     const double merge = n == 1 ? 0.0 : in_launch ? 3.5 : 4.0 + 0.015 * (double)n + 0.0002 * (double)(heads * n);
-    return (double)(rounds - 1) * round(resident) + round(last) + t_block * (double)ceil_div(blocks, kCUs) + merge;
+    return (double)(rounds - 1) * round(resident) + round(last) + 3.4 * (double)ceil_div(blocks, kCUs) + merge;
   };
-  double best = 0.91 * cost(n0, ceil_div(ceil_div(s->S, n0), 128));
+  const DecodeCost &c = decode_cost(hpb);
+  const double slow = (ld_of(s) % (hpb <= 2 ? 2 : 4) != 0 ? c.odd : 1.0) * (wide ? c.wide : 1.0);
+  const double t_step = c.t_step * slow;
+  auto cost = [&](int64_t n, double k, int width) {
+    const double b = 128.0 * 2 * (ld_of(s) + width) / 1024.0;
+    const int64_t blocks = wgs * n;
+    auto cu = [&](int64_t l) { return std::min((l == 1 ? c.c1 : c.c2) / slow, (double)l * b / t_step); };
+    auto round = [&](int64_t m) {
+      const int64_t q = m / kCUs, r = m % kCUs;
+      double t = 0.0;
+      if (q > 0) t += (double)q * k * b / std::min(kRate / kCUs, cu(q));
+      if (r > 0) t += k * b / std::min(kRate / (double)r, cu(q + 1));
+      return std::max(t, k * t_step);
+    };
+    const int64_t full = blocks / (kCUs * resident), rest = blocks % (kCUs * resident);
+    double t = c.t0 + c.t_block * (double)ceil_div(blocks, kCUs);
+    if (full > 0) t += (double)full * round(kCUs * resident);
+    if (rest > 0) t += round(rest);
+    if (n > 1) t += n <= kDecodeFuseMaxSplit && merges_in_launch(hpb, blocks) ? c.m_in : c.m_out + 0.01 * (double)n + 0.0002 * (double)(heads * n);
+    return t;
+  };
+  // (the estimate for rows of unknown value width)
+  auto estimate = [&](int64_t rows) {
+    const int64_t n = ceil_div(s->S, rows);
+    const double k = (double)((rows + 127) / 128);
+    if (f32) return cost_f32(n, k);
+    return cost(n, k, kD) * cost(n, k, kD / 2);
+  };
+  auto piece_rows = [&](int64_t n) { return (ceil_div(s->S, n) + 63) & ~(int64_t)63; };
+  double best = (f32 ? 0.91 : 0.94 * 0.94) * estimate(piece_rows(n0));
   int64_t n_best = n0;
   // more than eight blocks per compute unit never pay
   const int64_t top = std::min<int64_t>({steps, kMaxPieces, std::max<int64_t>(n0, 8 * (int64_t)kCUs / wgs), std::max<int64_t>(fit, 1)});
-  int64_t k_last = 0;
+  int64_t rows_last = 0;
   for (int64_t i = least; i <= top; ++i) {
-    const int64_t k = (steps + i - 1) / i;
-    if (k == k_last) continue;   // the same pieces, some of them empty
-    k_last = k;
-    const double c = cost(i, k);
-    if (c < best) { best = c; n_best = i; }
+    const int64_t rows = piece_rows(i);
+    if (rows == rows_last) continue;   // the same pieces, some of them empty
+    rows_last = rows;
+    const double e = estimate(rows);
+    if (e < best) { best = e; n_best = i; }
   }
   return (int)n_best;
 }
@@ -253,8 +291,7 @@ int decode_pieces(const thk_shape *s, int hpb, int64_t wgs, int64_t steps, int n
 // ws_bytes: what the caller's workspace holds.  The estimate's count goes up and down with S, so a
 // workspace asked for at a sequence's final length can hold fewer pieces than a shorter length
 // would take; a call then takes the pieces that fit, down to an eighth of the count n0 that the estimate
-// starts from, and to two.  n0 never falls with S, the estimate takes a quarter of it or more (of 12000
-// calls of one to eight heads over 256 .. 131072 rows 12 wanted less, 15 pieces instead of 16), and
+// starts from, and to two.  n0 never falls with S, the estimate takes a quarter of it or more, and
 // cutting n pieces into whole 64-row runs leaves more than half of them (a piece has at least 127 rows):
 // the workspace of the final length serves every shorter one.  Less than that is refused.  One piece,
 // which needs no workspace, is taken only where n0 is 1 and by calls of at least 128 blocks per piece
@@ -288,7 +325,7 @@ Split decode_split(const thk_shape *s, size_t ws_bytes = SIZE_MAX) {
     if (n == 1 && s->S >= 2048) n = 2;
     const int n0 = n;
     const bool one = n0 == 1 || (wgs >= kCUs / 2 && s->S < 4096);
-    if (s->S > one_block_rows || units_of(s) > 8) n = decode_pieces(s, hpb, wgs, steps, n0, one ? 1 : std::max(2, n0 / 4));
+    if (s->S > one_block_rows || units_of(s) > 8) n = decode_pieces(s, hpb, wgs, steps, n0, one ? 1 : std::max(n0 >= 8 ? 4 : 2, n0 / 4));
     const int64_t fit = (int64_t)std::min<size_t>(ws_bytes / decode_ws_bytes(s, 1), (size_t)n);
     if (fit < n && fit >= (one ? 0 : std::max(2, n0 / 8))) n = std::max((int)fit, 1);
   }
@@ -308,14 +345,15 @@ Split decode_split(const thk_shape *s, size_t ws_bytes = SIZE_MAX) {
 // with two such blocks per compute unit and more the exchange ends a launch whose memory queues are full.
 // Hence: up to two heads per block always, four up to two blocks per compute unit, eight below that.
 // THK_DECODE_MERGE = kernel | fused overrides (fused only within the 16 pieces).
+bool merges_in_launch(int hpb, int64_t blocks) {
+  return hpb <= 2 || blocks < 2 * (int64_t)kCUs || (hpb == 4 && blocks == 2 * (int64_t)kCUs);
+}
 bool decode_merge_in_launch(const thk_shape *s, int n_split) {
   if (n_split < 2 || n_split > kDecodeFuseMaxSplit) return false;
   const char sw = env_switches().decode_merge;
   if (sw == 'k') return false;
   if (sw == 'f') return true;
-  const int hpb = decode_heads_per_block(s);
-  const int64_t blocks = decode_groups(s) * n_split;
-  return hpb <= 2 || blocks < 2 * (int64_t)kCUs || (hpb == 4 && blocks == 2 * (int64_t)kCUs);
+  return merges_in_launch(decode_heads_per_block(s), decode_groups(s) * n_split);
 }
 
 // Units per group in the staged form of thk_prune (three launches per group).
