@@ -169,7 +169,11 @@ __global__ __launch_bounds__(256, 2) void k_value_attn_bf16(ValueAttnArgs a) {
 
   u32x4 pk[NP], pv[NP];
   // quarter q of the next chunk's loads: q = 0, 1 the two halves of the key rows, q = 2, 3 of
-  // the value rows
+  // the value rows.  Keys are not needed again; a value prune reads the values once more, for the copy, and
+  // values that were loaded without the non-temporal hint are still in the memory-side cache then, the last 256 MB
+  // of them (k_value_attn_wide: 64 units x 32768 rows, copy 139 -> 119 us, whole call 388 -> 370; this kernel: 88 x 858
+  // rows, 2 heads 28.9 -> 27.2, 12 x 17322, 4 heads 64.5 -> 63.0).  With one query tile the score itself is bound by memory and
+  // loses what the copy gains (24 units x 21938 rows 122.6 / 119.1, 32 x 4662 51.4 / 52.3): the hint stays.
   auto fetch_part = [&](int c, int q) {
     const unsigned char *g = q < 2 ? kg : vg;
 #pragma unroll
@@ -177,8 +181,9 @@ __global__ __launch_bounds__(256, 2) void k_value_attn_bf16(ValueAttnArgs a) {
       const int p = (q & 1) * (NP / 2) + pp;
       int64_t gr = k0 + (int64_t)c * CR + p * 16 + srow;
       gr = gr < S ? gr : S - 1;   // rows past the end repeat the last one; their weights are zero
-      const u32x4 x = ld_stream((const u32x4 *)(g + gr * (kD * 2) + scol));
-      if (q < 2) pk[p] = x; else pv[p] = x;
+      const u32x4 *src = (const u32x4 *)(g + gr * (kD * 2) + scol);
+      if (q < 2) pk[p] = ld_stream(src);
+      else pv[p] = QT == 1 ? ld_stream(src) : *src;
     }
   };
   auto stash = [&]() {
@@ -328,7 +333,8 @@ __global__ __launch_bounds__(256, 2) void k_value_attn_bf16(ValueAttnArgs a) {
 constexpr int kWideRows = 128;                    // rows per chunk
 constexpr int kWideBytes = kWideRows * kD * 2;    // one tensor's chunk in LDS
 
-// One chunk of one tensor, 4 rows (1024 bytes) per instruction, KEYS: the key permutation.
+// One chunk of one tensor, 4 rows (1024 bytes) per instruction, KEYS: the key permutation, and the non-temporal
+// hint, which values go without (see fetch_part above).
 template <bool KEYS>
 __device__ __forceinline__ void wide_fetch(const unsigned char *g, int64_t last, unsigned char *lds, int wave,
                                            int lane) {
@@ -342,7 +348,7 @@ __device__ __forceinline__ void wide_fetch(const unsigned char *g, int64_t last,
     // rows past the end repeat the last one; their weights are zero
     const uint32_t off = (uint32_t)(row < last ? row : (int)last) * (kD * 2) + chunk * 16;
     __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(g + off),
-                                     (__attribute__((address_space(3))) void *)(lds + inst * 1024), 16, 0, 2 /* nt */);
+                                     (__attribute__((address_space(3))) void *)(lds + inst * 1024), 16, 0, KEYS ? 2 /* nt */ : 0);
   }
 }
 
