@@ -606,9 +606,11 @@ __global__ __launch_bounds__(64 * QT) void k_value_attn_f32(ValueAttnArgs a) {
 // pg + PG, ... for channel d; the PG groups meet in LDS and are added in group order.  A unit
 // with a single tile gets its score here (each thread holds all of its rows); otherwise the
 // squared outputs go to sq[u][row][d] for k_value_norms.  PG = 2 for few records, 8 for many.
+// With idx (PG = 2 and a single tile: the block has the unit's whole score) the unit's Top_T follows here
+// instead of in a launch of its own: 40 units x 384 rows 25.0 -> 23.2 us.
 template <int PG>
-__global__ __launch_bounds__(256) void k_value_merge(const float *part, float *sq, float *score, int G, int S_obs,
-                                                     int n_part, int nqt, int nt) {
+__global__ __launch_bounds__(256) void k_value_merge(const float *part, float *sq, float *score, int16_t *idx, int T, int G,
+                                                     int S_obs, int n_part, int nqt, int nt) {
   constexpr int DQ = 256 / PG, NDB = kD / DQ;   // channels per block, blocks per (unit, tile)
   extern __shared__ float wts[];   // [n_part][32] merge weights, then [PG - 1][DQ][33] for the groups
   int64_t bid = blockIdx.x;
@@ -622,7 +624,7 @@ __global__ __launch_bounds__(256) void k_value_merge(const float *part, float *s
   const float *pu = part + (size_t)u * n_part * nqt * kRec;
   // weights of the records, row q = tid % 32, records tid / 32, + 8, ... per thread (one thread per row
   // walked all of them before: 128 records took 60 us)
-  __shared__ float red_m[8][32], red_l[8][32];
+  __shared__ float red_m[8][32], red_l[8][32], s_sc[kD];
   if (n_part == 1) {   // short calls: one record, its weight is 1 over its sum
     if (threadIdx.x < 32) {
       const float L = pu[(size_t)t * kRec + 32 * kD + 32 + threadIdx.x];
@@ -676,29 +678,35 @@ __global__ __launch_bounds__(256) void k_value_merge(const float *part, float *s
     for (int q = 0; q < 32; ++q) xch[((pg - 1) * DQ + dl) * 33 + q] = acc[q];
   }
   __syncthreads();
-  if (pg > 0) return;
+  if (pg > 0 && idx == nullptr) return;
+  if (pg == 0) {
 #pragma unroll
-  for (int g2 = 1; g2 < PG; ++g2)
+    for (int g2 = 1; g2 < PG; ++g2)
 #pragma unroll
-    for (int q = 0; q < 32; ++q) acc[q] += xch[((g2 - 1) * DQ + dl) * 33 + q];
-  if (nt == 1) {
-    double ss = 0.0, total = 0.0;
+      for (int q = 0; q < 32; ++q) acc[q] += xch[((g2 - 1) * DQ + dl) * 33 + q];
+    if (nt == 1) {
+      double ss = 0.0, total = 0.0;
 #pragma unroll
-    for (int q = 0; q < 32; ++q) {
-      if (q < rows_q) {
-        ss += (double)acc[q] * (double)acc[q];
-        if ((q + 1) % S_obs == 0) {   // last window row of a head
-          total += sqrt(ss);
-          ss = 0.0;
+      for (int q = 0; q < 32; ++q) {
+        if (q < rows_q) {
+          ss += (double)acc[q] * (double)acc[q];
+          if ((q + 1) % S_obs == 0) {   // last window row of a head
+            total += sqrt(ss);
+            ss = 0.0;
+          }
         }
       }
-    }
-    score[(size_t)u * kD + d] = (float)total;
-  } else {
-    float *dst = sq + ((size_t)u * nt + t) * 32 * kD;
+      score[(size_t)u * kD + d] = (float)total;
+      s_sc[d] = (float)total;
+    } else {
+      float *dst = sq + ((size_t)u * nt + t) * 32 * kD;
 #pragma unroll
-    for (int q = 0; q < 32; ++q) dst[q * kD + d] = acc[q] * acc[q];
+      for (int q = 0; q < 32; ++q) dst[q * kD + d] = acc[q] * acc[q];
+    }
   }
+  if (idx == nullptr) return;
+  __syncthreads();
+  if (threadIdx.x < kWave) select_wave(s_sc[threadIdx.x], s_sc[threadIdx.x + kWave], T, idx + (size_t)u * T, threadIdx.x);
 }
 
 // Column norms per query head from the squared outputs.  1024 threads = 128 channels x 8 head
@@ -805,12 +813,14 @@ hipError_t launch_value_score(int dtype, const void *q_obs, const void *k, const
   const size_t xch = (size_t)(PG - 1) * DQ * 33 * sizeof(float);
   if (lds < xch) lds = xch;
   const dim3 mg((unsigned)(U * nqt_real * (kD / DQ)));
+  const bool select_here = PG == 2 && nqt_real == 1;
+  int16_t *const midx = select_here ? idx : nullptr;
   if (PG == 8)
-    hipLaunchKernelGGL(k_value_merge<8>, mg, dim3(256), lds, st, part, sq, score, G, S_obs, n_part, nqt, nqt_real);
+    hipLaunchKernelGGL(k_value_merge<8>, mg, dim3(256), lds, st, part, sq, score, midx, T, G, S_obs, n_part, nqt, nqt_real);
   else
-    hipLaunchKernelGGL(k_value_merge<2>, mg, dim3(256), lds, st, part, sq, score, G, S_obs, n_part, nqt, nqt_real);
+    hipLaunchKernelGGL(k_value_merge<2>, mg, dim3(256), lds, st, part, sq, score, midx, T, G, S_obs, n_part, nqt, nqt_real);
   e = hipGetLastError();
-  if (e != hipSuccess) return e;
+  if (e != hipSuccess || select_here) return e;
   if (nqt_real == 1) return idx != nullptr ? launch_select(score, idx, U, T, st) : hipSuccess;
   hipLaunchKernelGGL(k_value_norms, dim3((unsigned)U), dim3(1024), 0, st, sq, score, idx, T, G, S_obs, nqt_real);
   return hipGetLastError();
