@@ -30,6 +30,7 @@ class thk_shape(ctypes.Structure):
 
 
 _lib = None
+_call = None   # the native issue of the per-token calls (csrc/thk_call.cpp), once the library is loaded
 
 
 def lib_path():
@@ -38,7 +39,7 @@ def lib_path():
 
 def load():
     """Load libthk.so; raises if it has not been built (no CPU fallback exists)."""
-    global _lib
+    global _lib, _call
     if _lib is not None:
         return _lib
     if not os.path.exists(_LIB_PATH):
@@ -105,6 +106,10 @@ def load():
     L.thk_profile_next.argtypes = [vp, vp]
     L.thk_tail_append.restype = ctypes.c_int
     L.thk_tail_append.argtypes = [sp, vp, vp, vp, vp, i32, i32, vp]
+    from . import _thk_call
+    addr = lambda f: ctypes.cast(f, vp).value
+    _thk_call.bind(addr(L.thk_decode_attn), addr(L.thk_decode_attn_kv), addr(L.thk_tail_append), addr(L.thk_prune))
+    _call = _thk_call
     _lib = L
     return L
 
@@ -117,8 +122,9 @@ def make_shape(L, B, N_q, N_kv, D, S, S_obs, T, ld_keep=0, dtype=THK_BF16, n_spl
 # them take less than ten microseconds: what a call costs the host decides there.  So a tensor is
 # looked at once (one helper checks it and returns its address as a plain int), the shape's
 # fields are read in one go, and the current stream's handle comes from torch's raw getter
-# (torch.cuda.current_stream() builds a Stream object first).  Per call, 32 layers of
-# thk_tail_append + thk_decode_attn: 10.1 -> 7.5 us of host time, of which the C call takes 5.0.
+# (torch.cuda.current_stream() builds a Stream object first).  Decode, append and prune go through
+# csrc/thk_call.cpp, which does the same natively for contiguous tensors and leaves everything else (returns
+# -1) to the code here.
 
 _FIELDS = struct.Struct("@iiiiiqiiiiiiq")
 assert _FIELDS.size == ctypes.sizeof(thk_shape)
@@ -146,6 +152,8 @@ _raw_stream = None   # torch's raw getters, once the runtime is up (see _current
 def _forget_runtime():
     global _raw_stream
     _raw_stream = None
+    if _call is not None:
+        _call.stream_getters(None, None)
 
 
 os.register_at_fork(after_in_child=_forget_runtime)   # a forked child must go through torch's own checks
@@ -162,6 +170,8 @@ def _current_stream():
     get_device = getattr(torch._C, "_cuda_getDevice", None)
     if get_stream is not None and get_device is not None:
         _raw_stream = (get_stream, get_device)
+        load()
+        _call.stream_getters(get_stream, get_device)
     return handle
 
 
@@ -195,6 +205,15 @@ def _dims(s):
 
 def thk_last_hip_error():
     return load().thk_last_hip_error().decode()
+
+
+def _issued(st, where):
+    """True when the native code took the call, whose status is then checked."""
+    if st == 0:
+        return True
+    if st < 0:
+        return False
+    _check(st, where)
 
 
 def _check(st, where):
@@ -289,6 +308,8 @@ def thk_compact_keys(shape, k, idx, k_pruned, stream=None):
 
 def thk_prune(shape, q_obs, k, score, idx, k_pruned, ws, stream=None):
     w = "thk_prune"
+    if _call is not None and _issued(_call.prune(shape, q_obs, k, score, idx, k_pruned, ws, stream), w):
+        return
     U, H, D, S, S_obs, T, ld, S_recent, S_cap = _dims(shape)
     _check(load().thk_prune(ctypes.byref(shape), _arg(q_obs, H * S_obs * D, "q_obs", w), _arg(k, U * S * D, "k", w),
                             _arg(score, U * D, "score", w), _arg(idx, U * T, "idx", w),
@@ -306,6 +327,9 @@ def _tail_args(k_tail, v_tail, n, s_tail, w):
 def thk_decode_attn(shape, q, k_pruned, idx, v, k_tail, v_tail, s_tail, s_tail_cap, out, ws,
                     stream=None):
     w = "thk_decode_attn"
+    if _call is not None and _issued(_call.decode_attn(shape, q, k_pruned, idx, v, k_tail, v_tail, s_tail, s_tail_cap, out, ws,
+                                                       stream), w):
+        return
     U, H, D, S, _, T, ld, _, S_cap = _dims(shape)
     n, rows = H * D, U * (S_cap or S)
     qp, op = _arg(q, n, "q", w), _arg(out, n, "out", w)
@@ -329,6 +353,9 @@ def thk_decode_attn_static(shape, q, k_pruned, idx, v, k_tail, v_tail, s_tail, s
 def thk_decode_attn_kv(shape, q, k_pruned, idx, v_pruned, idx_v, T_v, ld_v, k_tail, v_tail, s_tail,
                        s_tail_cap, out, ws, stream=None):
     w = "thk_decode_attn_kv"
+    if _call is not None and _issued(_call.decode_attn_kv(shape, q, k_pruned, idx, v_pruned, idx_v, T_v, ld_v, k_tail, v_tail,
+                                                          s_tail, s_tail_cap, out, ws, stream), w):
+        return
     U, H, D, S, _, T, ld, _, S_cap = _dims(shape)
     n, rows = H * D, U * (S_cap or S)
     qp, op = _arg(q, n, "q", w), _arg(out, n, "out", w)
@@ -341,6 +368,8 @@ def thk_decode_attn_kv(shape, q, k_pruned, idx, v_pruned, idx_v, T_v, ld_v, k_ta
 
 def thk_tail_append(shape, k_new, v_new, k_tail, v_tail, s_tail, s_tail_cap, stream=None):
     w = "thk_tail_append"
+    if _call is not None and _issued(_call.tail_append(shape, k_new, v_new, k_tail, v_tail, s_tail, s_tail_cap, stream), w):
+        return
     U, _, D, _, _, _, _, _, _ = _dims(shape)
     n, m = U * D, U * s_tail_cap * D
     _check(load().thk_tail_append(ctypes.byref(shape), _arg(k_new, n, "k_new", w), _arg(v_new, n, "v_new", w),
