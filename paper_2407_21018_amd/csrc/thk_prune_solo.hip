@@ -333,6 +333,10 @@ void k_prune_solo(PruneFusedArgs a) {
   // ragged tile pays for its raggedness.  8 units x 5003 rows: first load issued after 0.6
   // instead of 1.8 us.
   const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+  // What the block needs in front of its first loads, asked for at once: an argument loaded where it is
+  // first used is a trip of its own, and there were two.  8 units x 5003 rows 11.15 -> 11.0 us, fp32 8 x
+  // 2048 9.32 -> 9.24 us; calls above 100 us do not change.
+  asm volatile("" ::"s"(a.k), "s"(a.S), "s"(a.NB), "s"(a.U), "s"(a.stagger_blocks), "s"(a.stagger_units), "s"(a.stagger_ticks));
   if (blockIdx.x < (uint32_t)a.U) {
     solo_prologue<DT>(a, blockIdx.x, (double *)tiles);   // the tiles are free in a block without rows
     return;
