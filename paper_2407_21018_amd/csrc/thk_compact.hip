@@ -106,6 +106,11 @@ struct FlushCopy {
 template <int DT>
 __global__ __launch_bounds__(256) void k_flush(CompactArgs a, FlushCopy c, uint32_t n_compact) {
   extern __shared__ u32x4 smem[];
+  // all arguments at once, as the blocks of either kind need them: one trip instead of two (32 x 24 units,
+  // fp32, 31.7 -> 31.55 us; 32 x 32 units x 128 rows, bf16, 22.75 -> 22.6 us)
+  asm volatile("" ::"s"(a.src), "s"(a.dst), "s"(a.idx), "s"(a.src_unit_rows), "s"(a.src_row0), "s"(a.dst_unit_rows), "s"(a.dst_row0),
+               "s"(a.n_rows), "s"(a.rows_per_block), "s"(a.T), "s"(a.ld), "s"(a.blocks_per_unit), "s"(c.src), "s"(c.dst),
+               "s"(c.src_unit_rows), "s"(c.dst_unit_rows), "s"(c.dst_row0), "s"(c.n_rows), "s"(c.blocks_per_unit));
   if (blockIdx.x < n_compact) {
     compact_flat_block<DT>(a, blockIdx.x, smem);
     return;
@@ -198,6 +203,9 @@ __global__ __launch_bounds__(256) void k_tail_append(const void *__restrict__ k_
                                                      int64_t v_unit_rows, int64_t v_row) {
   using E = Elem<DT>;
   constexpr int CPR = kD / E::VEC;   // 16-byte chunks per row
+  // Every argument at once: behind the return below they were a second trip in front of the first load.
+  // 32 x (append + decode): bf16 5 x 8 units 345.5 -> 342.2 us, fp32 2 x 8 units 373.9 -> 370.1 us.
+  asm volatile("" ::"s"(k_new), "s"(v_new), "s"(k_dst), "s"(v_dst), "s"(k_unit_rows), "s"(k_row), "s"(v_unit_rows), "s"(v_row));
   const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (i >= U * CPR) return;
   const int64_t u = i / CPR;
