@@ -47,10 +47,10 @@ struct Args {
     if (t.layout() != at::kStrided || t.numel() < n || !t.is_contiguous()) return ok = false, nullptr;
     return t.data_ptr();
   }
-  // ... which is looked at only if `used`, and may be None otherwise
-  void *tensor_if(PyObject *x, int64_t n, bool used) {
+  // ... or of None
+  void *tensor_if(PyObject *x, int64_t n) {
     if (x == Py_None) return nullptr;
-    return tensor(x, used ? n : 0);
+    return tensor(x, n);
   }
   void *workspace(PyObject *x, size_t &bytes) {
     bytes = 0;
@@ -85,10 +85,23 @@ struct Args {
     if (PyErr_Occurred()) return PyErr_Clear(), ok = false, nullptr;
     return p;
   }
-  int64_t layers_units() const { return (int64_t)shape->L * shape->B * shape->N_kv; }
-  int64_t heads() const { return (int64_t)shape->L * shape->B * shape->N_q; }
+  // The product of a tensor's sizes.  A shape whose product does not fit 64 bits (a capacity that was never set)
+  // would wrap to a size that every tensor has; it is left to the Python code, which counts without a bound.
+  template <class... I>
+  int64_t count(I... sizes) {
+    int64_t n = 1;
+    for (const int64_t f : {(int64_t)sizes...}) ok = !__builtin_mul_overflow(n, f, &n) && ok;
+    return n;
+  }
+  int64_t less(int64_t a, int64_t b) {
+    int64_t n = 0;
+    ok = !__builtin_sub_overflow(a, b, &n) && ok;
+    return n;
+  }
+  int64_t layers_units() { return count(shape->L, shape->B, shape->N_kv); }
+  int64_t heads() { return count(shape->L, shape->B, shape->N_q); }
   int64_t ld() const { return shape->ld_keep ? shape->ld_keep : shape->T; }
-  int64_t rows(int64_t used) const { return layers_units() * (shape->S_cap ? shape->S_cap : used); }
+  int64_t rows(int64_t used) { return count(layers_units(), shape->S_cap ? shape->S_cap : used); }
 };
 
 // A call without the interpreter lock (a launch may have to wait for room in the queue).
@@ -119,10 +132,11 @@ PyObject *decode_attn(PyObject *, PyObject *const *a, Py_ssize_t n) {
     Args x(a[0]);
     if (!x.ok) return not_taken();
     const thk_shape *s = x.shape;
-    const int64_t U = x.layers_units(), hn = x.heads() * s->D, rows = x.rows(s->S);
+    const int64_t U = x.layers_units(), hn = x.count(x.heads(), s->D), rows = x.rows(s->S);
     const int32_t s_tail = x.integer(a[7]), cap = x.integer(a[8]);
-    void *q = x.tensor(a[1], hn), *kp = x.tensor(a[2], rows * x.ld()), *idx = x.tensor(a[3], U * s->T), *v = x.tensor(a[4], rows * s->D);
-    void *kt = x.tensor_if(a[5], U * cap * s->D, s_tail > 0), *vt = x.tensor_if(a[6], U * cap * s->D, s_tail > 0), *out = x.tensor(a[9], hn);
+    void *q = x.tensor(a[1], hn), *kp = x.tensor(a[2], x.count(rows, x.ld())), *idx = x.tensor(a[3], x.count(U, s->T)), *v = x.tensor(a[4], x.count(rows, s->D));
+    const int64_t tail = s_tail > 0 ? x.count(U, cap, s->D) : 0;
+    void *kt = x.tensor_if(a[5], tail), *vt = x.tensor_if(a[6], tail), *out = x.tensor(a[9], hn);
     size_t bytes = 0;
     void *ws = x.workspace(a[10], bytes), *st = x.stream(a[11]);
     if (!x.ok) return not_taken();
@@ -137,12 +151,13 @@ PyObject *decode_attn_kv(PyObject *, PyObject *const *a, Py_ssize_t n) {
     Args x(a[0]);
     if (!x.ok) return not_taken();
     const thk_shape *s = x.shape;
-    const int64_t U = x.layers_units(), hn = x.heads() * s->D, rows = x.rows(s->S);
+    const int64_t U = x.layers_units(), hn = x.count(x.heads(), s->D), rows = x.rows(s->S);
     const int32_t T_v = x.integer(a[6]), ld_v = x.integer(a[7]), s_tail = x.integer(a[10]), cap = x.integer(a[11]);
     if (T_v < 0 || ld_v < 0) return not_taken();
-    void *q = x.tensor(a[1], hn), *kp = x.tensor(a[2], rows * x.ld()), *idx = x.tensor(a[3], U * s->T);
-    void *v = x.tensor(a[4], rows * ld_v), *idxv = x.tensor(a[5], U * T_v);
-    void *kt = x.tensor_if(a[8], U * cap * s->D, s_tail > 0), *vt = x.tensor_if(a[9], U * cap * s->D, s_tail > 0), *out = x.tensor(a[12], hn);
+    void *q = x.tensor(a[1], hn), *kp = x.tensor(a[2], x.count(rows, x.ld())), *idx = x.tensor(a[3], x.count(U, s->T));
+    void *v = x.tensor(a[4], x.count(rows, ld_v)), *idxv = x.tensor(a[5], x.count(U, T_v));
+    const int64_t tail = s_tail > 0 ? x.count(U, cap, s->D) : 0;
+    void *kt = x.tensor_if(a[8], tail), *vt = x.tensor_if(a[9], tail), *out = x.tensor(a[12], hn);
     size_t bytes = 0;
     void *ws = x.workspace(a[13], bytes), *st = x.stream(a[14]);
     if (!x.ok) return not_taken();
@@ -160,8 +175,8 @@ PyObject *tail_append(PyObject *, PyObject *const *a, Py_ssize_t n) {
     if (!x.ok) return not_taken();
     const thk_shape *s = x.shape;
     const int32_t s_tail = x.integer(a[5]), cap = x.integer(a[6]);
-    const int64_t un = x.layers_units() * s->D;
-    void *kn = x.tensor(a[1], un), *vn = x.tensor(a[2], un), *kt = x.tensor(a[3], un * cap), *vt = x.tensor(a[4], un * cap);
+    const int64_t un = x.count(x.layers_units(), s->D), tail = x.count(un, cap);
+    void *kn = x.tensor(a[1], un), *vn = x.tensor(a[2], un), *kt = x.tensor(a[3], tail), *vt = x.tensor(a[4], tail);
     void *st = x.stream(a[7]);
     if (!x.ok) return not_taken();
     return issue([&] { return f_append(s, kn, vn, kt, vt, s_tail, cap, st); });
@@ -176,8 +191,9 @@ PyObject *prune(PyObject *, PyObject *const *a, Py_ssize_t n) {
     if (!x.ok) return not_taken();
     const thk_shape *s = x.shape;
     const int64_t U = x.layers_units();
-    void *q = x.tensor(a[1], x.heads() * s->S_obs * s->D), *k = x.tensor(a[2], U * s->S * s->D), *sc = x.tensor_if(a[3], U * s->D, true);
-    void *idx = x.tensor(a[4], U * s->T), *kp = x.tensor(a[5], x.rows(s->S - s->S_recent) * x.ld());
+    void *q = x.tensor(a[1], x.count(x.heads(), s->S_obs, s->D)), *k = x.tensor(a[2], x.count(U, s->S, s->D));
+    void *sc = x.tensor_if(a[3], x.count(U, s->D)), *idx = x.tensor(a[4], x.count(U, s->T));
+    void *kp = x.tensor(a[5], x.count(x.rows(x.less(s->S, s->S_recent)), x.ld()));
     size_t bytes = 0;
     void *ws = x.workspace(a[6], bytes), *st = x.stream(a[7]);
     if (!x.ok) return not_taken();

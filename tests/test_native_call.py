@@ -48,6 +48,34 @@ def test_checks_raise_as_before():
         thk.thk_tail_append(a["shape"], a["q"], a["q"], a["k_tail"], a["v_tail"], 16, 16, 0)
 
 
+def _four_calls(shape, device="cpu"):
+    """(native function, public function, arguments) of the four calls, every tensor of one size and large enough for _decode_args' shape."""
+    t = lambda: torch.zeros(1 << 15, dtype=torch.bfloat16, device=device)
+    idx, ws = torch.arange(64, dtype=torch.int16, device=device).repeat(2), torch.zeros(1 << 16, dtype=torch.uint8, device=device)
+    thk.load()
+    c = binding._call
+    return [(c.decode_attn, thk.thk_decode_attn, (shape, t(), t(), idx, t(), t(), t(), 3, 16, t(), ws, 0)),
+            (c.decode_attn_kv, thk.thk_decode_attn_kv, (shape, t(), t(), idx, t(), idx, 64, 64, t(), t(), 3, 16, t(), ws, 0)),
+            (c.tail_append, thk.thk_tail_append, (shape, t(), t(), t(), t(), 3, 16, 0)),
+            (c.prune, thk.thk_prune, (shape, t(), t(), None, idx, t(), ws, 0))]
+
+
+@pytest.mark.parametrize("fields", [dict(S_cap=1 << 56), dict(S_cap=(1 << 57) + 40), dict(S=1 << 56), dict(S_cap=1 << 62, T=128), dict(L=1 << 30, B=1 << 30, N_kv=8),
+                                    dict(S=(1 << 63) - 1, S_recent=-1), dict(L=1 << 30, B=1 << 29, N_q=16, N_kv=16)])
+def test_sizes_beyond_64_bits_are_no_small_sizes(fields):
+    """A product of sizes that does not fit 64 bits must not pass for a small one: such a call would read and
+    store behind its tensors."""
+    shape = _decode_args()["shape"]
+    for k, v in fields.items():
+        setattr(shape, k, v)
+    for native, public, args in _four_calls(shape):
+        if public is thk.thk_tail_append and not {"L", "B"} & set(fields):
+            continue   # its sizes do not depend on the sequence
+        assert native(*args) == -1
+        with pytest.raises(ValueError, match="the shape needs"):
+            public(*args)
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("side_stream", [False, True])
 def test_both_ways_of_issuing_a_call_agree(side_stream):
