@@ -108,7 +108,7 @@ def load():
     L.thk_tail_append.argtypes = [sp, vp, vp, vp, vp, i32, i32, vp]
     from . import _thk_call
     addr = lambda f: ctypes.cast(f, vp).value
-    _thk_call.bind(addr(L.thk_decode_attn), addr(L.thk_decode_attn_kv), addr(L.thk_tail_append), addr(L.thk_prune))
+    _thk_call.bind(addr(L.thk_decode_attn), addr(L.thk_decode_attn_kv), addr(L.thk_tail_append), addr(L.thk_prune), thk_shape)
     _call = _thk_call
     _lib = L
     return L

@@ -19,6 +19,7 @@ decltype(&thk_decode_attn) f_decode = nullptr;
 decltype(&thk_decode_attn_kv) f_decode_kv = nullptr;
 decltype(&thk_tail_append) f_append = nullptr;
 decltype(&thk_prune) f_prune = nullptr;
+PyTypeObject *g_shape = nullptr;   // thk_shape of the Python code
 PyObject *g_get_stream = nullptr, *g_get_device = nullptr;   // torch's raw getters, once the runtime is up
 
 // The arguments of one call; ok turns false at the first one that is not in the plain form.
@@ -28,6 +29,11 @@ struct Args {
   Py_buffer view{};
 
   explicit Args(PyObject *s) {
+    // (bytes of the same length are no shape, as for ctypes)
+    if (g_shape == nullptr || !PyObject_TypeCheck(s, g_shape)) {
+      ok = false;
+      return;
+    }
     if (PyObject_GetBuffer(s, &view, PyBUF_SIMPLE) != 0) {
       PyErr_Clear();
       ok = false;
@@ -201,9 +207,10 @@ PyObject *prune(PyObject *, PyObject *const *a, Py_ssize_t n) {
   });
 }
 
-// bind(decode_attn, decode_attn_kv, tail_append, prune): the library's entry points, as addresses
+// bind(decode_attn, decode_attn_kv, tail_append, prune, thk_shape): the library's entry points, as addresses, and
+// the type of a shape
 PyObject *bind(PyObject *, PyObject *const *a, Py_ssize_t n) {
-  if (n != 4) return PyErr_SetString(PyExc_TypeError, "bind: four addresses"), nullptr;
+  if (n != 5 || !PyType_Check(a[4])) return PyErr_SetString(PyExc_TypeError, "bind: four addresses and a type"), nullptr;
   void *p[4];
   for (int i = 0; i < 4; ++i) p[i] = PyLong_AsVoidPtr(a[i]);
   if (PyErr_Occurred()) return nullptr;
@@ -211,6 +218,9 @@ PyObject *bind(PyObject *, PyObject *const *a, Py_ssize_t n) {
   f_decode_kv = (decltype(f_decode_kv))p[1];
   f_append = (decltype(f_append))p[2];
   f_prune = (decltype(f_prune))p[3];
+  PyTypeObject *old = g_shape;
+  g_shape = (PyTypeObject *)Py_NewRef(a[4]);
+  Py_XDECREF((PyObject *)old);
   Py_RETURN_NONE;
 }
 

@@ -1,5 +1,7 @@
 """The native issue of the per-token calls (csrc/thk_call.cpp): what it takes, what it leaves to the Python
 code, and that both ways of issuing a call are the same call."""
+import ctypes
+
 import pytest
 import torch
 
@@ -73,6 +75,20 @@ def test_sizes_beyond_64_bits_are_no_small_sizes(fields):
             continue   # its sizes do not depend on the sequence
         assert native(*args) == -1
         with pytest.raises(ValueError, match="the shape needs"):
+            public(*args)
+
+
+class _OtherStruct(ctypes.Structure):
+    _fields_ = thk.thk_shape._fields_
+
+
+@pytest.mark.parametrize("other", [bytes, bytearray, lambda s: memoryview(bytes(s)), _OtherStruct.from_buffer_copy])
+def test_only_a_shape_is_a_shape(other):
+    """Whatever else holds as many bytes is refused, as ctypes does."""
+    bad = other(_decode_args()["shape"])
+    for native, public, args in _four_calls(bad):
+        assert native(*args) == -1
+        with pytest.raises((TypeError, ctypes.ArgumentError)):
             public(*args)
 
 
