@@ -7,6 +7,7 @@ if the library is missing, loading raises.
 import ctypes
 import os
 import struct
+import warnings
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 _LIB_PATH = os.path.join(_HERE, "libthk.so")
@@ -106,10 +107,14 @@ def load():
     L.thk_profile_next.argtypes = [vp, vp]
     L.thk_tail_append.restype = ctypes.c_int
     L.thk_tail_append.argtypes = [sp, vp, vp, vp, vp, i32, i32, vp]
-    from . import _thk_call
-    addr = lambda f: ctypes.cast(f, vp).value
-    _thk_call.bind(addr(L.thk_decode_attn), addr(L.thk_decode_attn_kv), addr(L.thk_tail_append), addr(L.thk_prune), thk_shape)
-    _call = _thk_call
+    try:   # built for one interpreter and one torch; the library needs neither, and ctypes issues every call
+        from . import _thk_call
+        addr = lambda f: ctypes.cast(f, vp).value
+        _thk_call.bind(addr(L.thk_decode_attn), addr(L.thk_decode_attn_kv), addr(L.thk_tail_append), addr(L.thk_prune), thk_shape)
+        _call = _thk_call
+    except ImportError as e:
+        warnings.warn(f"the native issue of the per-token calls cannot be loaded ({e}): calls go through ctypes, 2 us slower "
+                      "each; __graft_entry__.build() builds it", RuntimeWarning, stacklevel=2)
     _lib = L
     return L
 
@@ -171,7 +176,8 @@ def _current_stream():
     if get_stream is not None and get_device is not None:
         _raw_stream = (get_stream, get_device)
         load()
-        _call.stream_getters(get_stream, get_device)
+        if _call is not None:
+            _call.stream_getters(get_stream, get_device)
     return handle
 
 

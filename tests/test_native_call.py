@@ -1,6 +1,9 @@
 """The native issue of the per-token calls (csrc/thk_call.cpp): what it takes, what it leaves to the Python
 code, and that both ways of issuing a call are the same call."""
 import ctypes
+import os
+import subprocess
+import sys
 
 import pytest
 import torch
@@ -90,6 +93,36 @@ def test_only_a_shape_is_a_shape(other):
         assert native(*args) == -1
         with pytest.raises((TypeError, ctypes.ArgumentError)):
             public(*args)
+
+
+@pytest.mark.parametrize("found", [None, b"no library"])
+def test_the_library_works_without_the_native_issue(found, tmp_path):
+    """libthk.so needs neither an interpreter nor a torch of one version; what does may be missing or not load."""
+    pkg = tmp_path / "paper_2407_21018_amd"
+    pkg.mkdir()
+    src = os.path.dirname(binding.__file__)
+    for f in ("__init__.py", "binding.py", "libthk.so"):
+        os.symlink(os.path.join(src, f), pkg / f)
+    if found is not None:
+        (pkg / "_thk_call.so").write_bytes(found)
+    code = """if True:
+        import warnings, torch
+        import paper_2407_21018_amd as thk
+        from paper_2407_21018_amd import binding
+        with warnings.catch_warnings(record=True) as w:
+            warnings.simplefilter("always")
+            assert thk.thk_version() > 0 and thk.thk_version() > 0
+        assert [x.category for x in w] == [RuntimeWarning] and "ctypes" in str(w[0].message) and binding._call is None
+        t = torch.zeros(2048, dtype=torch.bfloat16)
+        try:
+            thk.thk_tail_append(thk.make_shape(1, 1, 8, 2, 128, 40, 1, 64), t, t, t, t, 8, 8, 0)   # refused by the library
+        except thk.ThkError as e:
+            assert e.status == 2
+        else:
+            raise AssertionError
+        binding._forget_runtime()
+    """
+    subprocess.run([sys.executable, "-c", code], check=True, cwd=tmp_path, env={**os.environ, "PYTHONPATH": str(tmp_path)}, timeout=300)
 
 
 @pytest.mark.gpu
