@@ -198,7 +198,50 @@ unsigned long long next_nonce() {
 bool decode_merge_in_launch(const thk_shape *s, int n_split);
 bool merges_in_launch(int hpb, int64_t blocks);
 
-// The number of pieces (no fewer than least) with the least estimated time, if that is at least 6 % (fp32: 9 %) below
+// The most pieces worth an estimate: more than eight blocks per compute unit never pay.
+int64_t most_pieces(int64_t wgs, int64_t steps, int n0) {
+  constexpr int64_t kMaxPieces = 128;
+  return std::min({steps, kMaxPieces, std::max<int64_t>(n0, 8 * (int64_t)kCUs / wgs)});
+}
+
+// fp32: the number of pieces (no fewer than least, no more than top) with the least estimated time, if that is at least 9 %
+// below the estimate for n0.  With k = steps of a piece (128 rows by four waves), R = blocks that are resident on a
+// compute unit and L = blocks on the fullest one, in us:
+//     sum over rounds of resident blocks of max(4.8 k, l k t_stream), l = R, in the last round what is left,
+//     +  3.4 L  +  merge
+// t_stream: a compute unit's share of the memory rate, 0.036 per KB of a step's rows (full-width values); merge:
+// nothing for one piece, 3.5 up to two blocks per compute unit, else 4, 0.015 per piece and 0.2 per thousand records.
+// Fitted to 190 random shapes whose calls above two blocks per compute unit merged in a launch of their own; with
+// the merge of one and two heads priced as it is now (merges_in_launch), 4 of 520 shapes take another count (0.92,
+// 0.95 and 1.08 of the time, one not measured), so the fitted price stays.  Pieces are told apart by their steps: by their
+// 64-row runs, pieces of half a step count as shorter ones (13 units x 28 heads of 4, 2304 rows: 9 pieces instead of 2, 53.1 -> 66.4 us;
+// 40 shapes that differed took 1.06x).  The estimate of bf16 calls fitted to fp32 made calls of over 600 MB up to 10 %
+// slower.
+int decode_pieces_f32(const thk_shape *s, int hpb, int64_t wgs, int64_t steps, int n0, int least, int64_t top) {
+  const int64_t heads = (int64_t)s->L * s->B * s->N_q;
+  const int resident = hpb == 4 || ld_of(s) > 79 ? 2 : 3;   // 79: the staging class of long rows
+  const double t_stream = 0.036 * 128 * (ld_of(s) + kD) * 4 / 1024.0;
+  auto cost = [&](int64_t n, int64_t k) {
+    const int64_t blocks = wgs * n, rounds = ceil_div(blocks, (int64_t)kCUs * resident);
+    auto round = [&](int64_t l) { return (double)k * std::max(4.8, (double)l * t_stream); };
+    const int64_t last = ceil_div(blocks - (rounds - 1) * kCUs * resident, kCUs);
+    const bool in_launch = n <= kDecodeFuseMaxSplit && blocks <= 2 * kCUs;
+    const double merge = n == 1 ? 0.0 : in_launch ? 3.5 : 4.0 + 0.015 * (double)n + 0.0002 * (double)(heads * n);
+    return (double)(rounds - 1) * round(resident) + round(last) + 3.4 * (double)ceil_div(blocks, kCUs) + merge;
+  };
+  double best = 0.91 * cost(n0, ceil_div(ceil_div(s->S, n0), 128));
+  int64_t n_best = n0, k_last = 0;
+  for (int64_t i = least; i <= top; ++i) {
+    const int64_t k = (steps + i - 1) / i;
+    if (k == k_last) continue;   // the same pieces, some of them empty
+    k_last = k;
+    const double c = cost(i, k);
+    if (c < best) { best = c; n_best = i; }
+  }
+  return (int)n_best;
+}
+
+// bf16: the number of pieces (no fewer than least) with the least estimated time, if that is at least 6 % below
 // the estimate for n0.  With k = steps of a piece (128 rows by
 // four waves, b KB of rows each), R = blocks that are resident on a compute unit, in us:
 //     sum over rounds of resident blocks  +  t_block * blocks on the fullest compute unit  +  merge  +  t0
@@ -214,7 +257,7 @@ bool merges_in_launch(int hpb, int64_t blocks);
 // quarter with pruned values), each measured at up to 29 piece counts; over these and 330 others the count taken costs 1.7 %
 // more than the best one on average (an estimate with the memory rate per block instead of per compute unit: 3.7 %),
 // 370 of them take 3 % and more less than with that, 55 more.
-// (fp32 keeps that one: fitted like this, calls of over 600 MB became up to 10 % slower.)  What it knows that a resident set of blocks (n0) misses: a few
+// What it knows that a resident set of blocks (n0) misses: a few
 // blocks more than a multiple of 256 cost a round of few (64 units x 32768 rows, 4 heads: 4 pieces 121 us, 5 151); pieces of one
 // step that leave compute units idle (16 units x 1815 rows: 15 pieces instead of 8, 11.0 -> 9.5); that one
 // block per compute unit saturates the memory and fewer, longer streams use it better.
@@ -225,25 +268,16 @@ const DecodeCost &decode_cost(int hpb) {
   return hpb == 1 ? h1 : hpb == 2 ? h2 : hpb == 4 ? h4 : h8;
 }
 int decode_pieces(const thk_shape *s, int hpb, int64_t wgs, int64_t steps, int n0, int least) {
-  constexpr int kMaxPieces = 128;
   constexpr double kRate = 7600.0;   // KB per us
   // more pieces only while the records fit the scratch array of thk_decode_attn_static, which takes
   // every call that n0 pieces fit
   const int64_t heads = (int64_t)s->L * s->B * s->N_q;
   const int64_t fit = (int64_t)THK_STATIC_SCRATCH_BYTES / ((kD + 2) * 4 + 8) / heads;
   if (n0 > 1 && n0 > fit) return n0;
-  const bool f32 = s->dtype == THK_F32, wide = ld_of(s) > 79;   // wide: the staging class of long rows
-  const int resident = f32 ? (hpb == 4 || wide ? 2 : 3) : (hpb == 8 ? 3 : 4) - (wide ? 1 : 0);
-  // fp32: rounds x max(4.8 k, blocks per compute unit x k x share of the memory rate), 3.4 per block, and the merge
-  auto cost_f32 = [&](int64_t n, double k) {
-    const int64_t blocks = wgs * n, rounds = ceil_div(blocks, (int64_t)kCUs * resident);
-    const double t_stream = 0.036 * 128 * (ld_of(s) + kD) * 4 / 1024.0;
-    auto round = [&](int64_t l) { return k * std::max(4.8, (double)l * t_stream); };
-    const int64_t last = ceil_div(blocks - (rounds - 1) * kCUs * resident, kCUs);
-    const bool in_launch = n <= kDecodeFuseMaxSplit && blocks <= 2 * kCUs;
-    const double merge = n == 1 ? 0.0 : in_launch ? 3.5 : 4.0 + 0.015 * (double)n + 0.0002 * (double)(heads * n);
-    return (double)(rounds - 1) * round(resident) + round(last) + 3.4 * (double)ceil_div(blocks, kCUs) + merge;
-  };
+  const int64_t top = std::min(most_pieces(wgs, steps, n0), std::max<int64_t>(fit, 1));
+  if (s->dtype == THK_F32) return decode_pieces_f32(s, hpb, wgs, steps, n0, least, top);
+  const bool wide = ld_of(s) > 79;   // the staging class of long rows
+  const int resident = (hpb == 8 ? 3 : 4) - (wide ? 1 : 0);
   const DecodeCost &c = decode_cost(hpb);
   const double slow = (ld_of(s) % (hpb <= 2 ? 2 : 4) != 0 ? c.odd : 1.0) * (wide ? c.wide : 1.0);
   const double t_step = c.t_step * slow;
@@ -269,15 +303,11 @@ int decode_pieces(const thk_shape *s, int hpb, int64_t wgs, int64_t steps, int n
   auto estimate = [&](int64_t rows) {
     const int64_t n = ceil_div(s->S, rows);
     const double k = (double)((rows + 127) / 128);
-    if (f32) return cost_f32(n, k);
     return cost(n, k, kD) * cost(n, k, kD / 2);
   };
   auto piece_rows = [&](int64_t n) { return (ceil_div(s->S, n) + 63) & ~(int64_t)63; };
-  double best = (f32 ? 0.91 : 0.94 * 0.94) * estimate(piece_rows(n0));
-  int64_t n_best = n0;
-  // more than eight blocks per compute unit never pay
-  const int64_t top = std::min<int64_t>({steps, kMaxPieces, std::max<int64_t>(n0, 8 * (int64_t)kCUs / wgs), std::max<int64_t>(fit, 1)});
-  int64_t rows_last = 0;
+  double best = 0.94 * 0.94 * estimate(piece_rows(n0));
+  int64_t n_best = n0, rows_last = 0;
   for (int64_t i = least; i <= top; ++i) {
     const int64_t rows = piece_rows(i);
     if (rows == rows_last) continue;   // the same pieces, some of them empty
@@ -325,7 +355,7 @@ Split decode_split(const thk_shape *s, size_t ws_bytes = SIZE_MAX) {
     if (n == 1 && s->S >= 2048) n = 2;
     const int n0 = n;
     const bool one = n0 == 1 || (wgs >= kCUs / 2 && s->S < 4096);
-    if (s->S > one_block_rows || units_of(s) > 8) n = decode_pieces(s, hpb, wgs, steps, n0, one ? 1 : std::max(n0 >= 8 ? 4 : 2, n0 / 4));
+    if (s->S > one_block_rows || units_of(s) > 8) n = decode_pieces(s, hpb, wgs, steps, n0, one ? 1 : std::max(n0 >= 8 && s->dtype == THK_BF16 ? 4 : 2, n0 / 4));
     const int64_t fit = (int64_t)std::min<size_t>(ws_bytes / decode_ws_bytes(s, 1), (size_t)n);
     if (fit < n && fit >= (one ? 0 : std::max(2, n0 / 8))) n = std::max((int)fit, 1);
   }

@@ -298,6 +298,10 @@ def test_default_decode_split_balances_rounds_and_stays_within_the_static_scratc
     assert split(32, 48, 8, 447, 111) == 1               # 256 units x 6 heads: 20.5 us, 2 pieces 23.1
     assert split(32, 40, 8, 391, 64, thk.THK_F32) == 1   # 256 units x 5 heads: 27.6 us, 2 pieces 36.8
     assert split(1, 160, 32, 3582, 64, thk.THK_F32) == 8     # 32 units x 5 heads: 30.5 us, 4 pieces 36.6
+    # fp32 pieces are told apart by their steps, not by runs of half a step
+    assert split(13, 28, 4, 2304, 111, thk.THK_F32) == 2     # 52 units x 7 heads: 53 us, 9 pieces 66
+    assert split(10, 32, 8, 2394, 124, thk.THK_F32) == 3     # 80 units x 4 heads: 46 us, 5 pieces 61
+    assert split(5, 64, 8, 2002, 125, thk.THK_F32) == 3      # 40 units x 8 heads: 40 us, 6 pieces 51
     for B in (1, 3, 8, 32, 100, 400):
         for N_q, N_kv in ((8, 8), (32, 8), (64, 8), (64, 4), (40, 40)):
             for S in (100, 257, 900, 2047, 2048, 5000, 40000, 131072):
