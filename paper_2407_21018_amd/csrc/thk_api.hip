@@ -204,30 +204,39 @@ int64_t most_pieces(int64_t wgs, int64_t steps, int n0) {
   return std::min({steps, kMaxPieces, std::max<int64_t>(n0, 8 * (int64_t)kCUs / wgs)});
 }
 
-// fp32: the number of pieces (no fewer than least, no more than top) with the least estimated time, if that is at least 9 %
-// below the estimate for n0.  With k = steps of a piece (128 rows by four waves), R = blocks that are resident on a
+// Blocks of the decode kernels that are resident on a compute unit.
+int decode_resident(const thk_shape *s, int hpb) {
+  const bool wide = ld_of(s) > 79;   // the staging class of long rows
+  return s->dtype == THK_F32 ? (hpb == 4 || wide ? 2 : 3) : (hpb == 8 ? 3 : 4) - (wide ? 1 : 0);
+}
+
+// The first estimate: the number of pieces (no fewer than least, no more than top) with the least estimated time, if that
+// is at least 9 % below the estimate for n0.  With k = steps of a piece (128 rows by four waves), R = resident blocks of a
 // compute unit and L = blocks on the fullest one, in us:
-//     sum over rounds of resident blocks of max(4.8 k, l k t_stream), l = R, in the last round what is left,
-//     +  3.4 L  +  merge
-// t_stream: a compute unit's share of the memory rate, 0.036 per KB of a step's rows (full-width values); merge:
-// nothing for one piece, 3.5 up to two blocks per compute unit, else 4, 0.015 per piece and 0.2 per thousand records.
-// Fitted to 190 random shapes whose calls above two blocks per compute unit merged in a launch of their own; with
-// the merge of one and two heads priced as it is now (merges_in_launch), 4 of 520 shapes take another count (0.92,
-// 0.95 and 1.08 of the time, one not measured), so the fitted price stays.  Pieces are told apart by their steps: by their
-// 64-row runs, pieces of half a step count as shorter ones (13 units x 28 heads of 4, 2304 rows: 9 pieces instead of 2, 53.1 -> 66.4 us;
-// 40 shapes that differed took 1.06x).  The estimate of bf16 calls fitted to fp32 made calls of over 600 MB up to 10 %
-// slower.
-int decode_pieces_f32(const thk_shape *s, int hpb, int64_t wgs, int64_t steps, int n0, int least, int64_t top) {
+//     sum over rounds of resident blocks of max(k t_step, l k t_stream), l = R, in the last round what is left,
+//     +  t_block L  +  merge
+// t_step: a step that waits for its own loads, 2.4, 2.7 where a block serves eight heads, 4.8 in fp32; t_stream: a compute
+// unit's share of the memory rate, 0.036 per KB of a step's rows (full-width values); t_block: what a block costs whatever
+// its length, 0.8, in fp32 3.4; merge: nothing for one piece, 3.5 up to two blocks of at most four heads per compute unit,
+// else 4, 0.015 per piece and 0.2 per thousand records.
+// Fitted to 570 random shapes, a third of them fp32, when calls above two blocks per compute unit merged in a launch of
+// their own; with the merge of fp32 calls of one and two heads priced as it is now (merges_in_launch), 4 of 520 shapes take
+// another count (0.92, 0.95, 1.00 and 1.08 of the time), so the fitted price stays.  Pieces are told apart by their
+// steps: by their 64-row runs, pieces of half a step count as shorter ones (fp32, 52 units x 7 heads, 2304 rows: 9 pieces
+// instead of 2, 53.1 -> 66.4 us; 40 shapes that differed took 1.06x).
+int pieces_by_rounds(const thk_shape *s, int hpb, int64_t wgs, int64_t steps, int n0, int least, int64_t top) {
+  const bool f32 = s->dtype == THK_F32;
   const int64_t heads = (int64_t)s->L * s->B * s->N_q;
-  const int resident = hpb == 4 || ld_of(s) > 79 ? 2 : 3;   // 79: the staging class of long rows
-  const double t_stream = 0.036 * 128 * (ld_of(s) + kD) * 4 / 1024.0;
+  const int resident = decode_resident(s, hpb);
+  const double t_step = f32 ? 4.8 : hpb == 8 ? 2.7 : 2.4, t_block = f32 ? 3.4 : 0.8;
+  const double t_stream = 0.036 * 128 * (ld_of(s) + kD) * elem_bytes(s->dtype) / 1024.0;
   auto cost = [&](int64_t n, int64_t k) {
     const int64_t blocks = wgs * n, rounds = ceil_div(blocks, (int64_t)kCUs * resident);
-    auto round = [&](int64_t l) { return (double)k * std::max(4.8, (double)l * t_stream); };
+    auto round = [&](int64_t l) { return (double)k * std::max(t_step, (double)l * t_stream); };
     const int64_t last = ceil_div(blocks - (rounds - 1) * kCUs * resident, kCUs);
-    const bool in_launch = n <= kDecodeFuseMaxSplit && blocks <= 2 * kCUs;
+    const bool in_launch = n <= kDecodeFuseMaxSplit && blocks <= 2 * kCUs && hpb <= 4;
     const double merge = n == 1 ? 0.0 : in_launch ? 3.5 : 4.0 + 0.015 * (double)n + 0.0002 * (double)(heads * n);
-    return (double)(rounds - 1) * round(resident) + round(last) + 3.4 * (double)ceil_div(blocks, kCUs) + merge;
+    return (double)(rounds - 1) * round(resident) + round(last) + t_block * (double)ceil_div(blocks, kCUs) + merge;
   };
   double best = 0.91 * cost(n0, ceil_div(ceil_div(s->S, n0), 128));
   int64_t n_best = n0, k_last = 0;
@@ -241,8 +250,10 @@ int decode_pieces_f32(const thk_shape *s, int hpb, int64_t wgs, int64_t steps, i
   return (int)n_best;
 }
 
-// bf16: the number of pieces (no fewer than least) with the least estimated time, if that is at least 6 % below
-// the estimate for n0.  With k = steps of a piece (128 rows by
+// bf16 calls have a second estimate, and take the number of pieces with the least time by it if that is at least 6 % below
+// its time for n0 and 2 % below that for the count of the first estimate, which they take otherwise: what both are wrong
+// about by a few percent is left as the first has it.  (fp32 has the first one only: the second one fitted to fp32 made calls
+// of over 600 MB up to 10 % slower.)  With k = steps of a piece (128 rows by
 // four waves, b KB of rows each), R = blocks that are resident on a compute unit, in us:
 //     sum over rounds of resident blocks  +  t_block * blocks on the fullest compute unit  +  merge  +  t0
 // A round's compute units hold q blocks each and some of them one more.  They move their rows at the least of what the memory
@@ -255,8 +266,10 @@ int decode_pieces_f32(const thk_shape *s, int hpb, int64_t wgs, int64_t steps, i
 // and of 64 channels.
 // Constants fitted per kernel to 1400 random bf16 shapes (1-8 heads per KV head, 1-1280 units, 256-131072 rows, a
 // quarter with pruned values), each measured at up to 29 piece counts; over these and 330 others the count taken costs 1.7 %
-// more than the best one on average (an estimate with the memory rate per block instead of per compute unit: 3.7 %),
-// 370 of them take 3 % and more less than with that, 55 more.
+// more than the best one on average (the first estimate alone: 3.7 %): 306 of 1728 bf16 shapes take 3 % and more less than with
+// that, 11 more.  (Without the look at the first estimate's count 355 less and 52 more, some of them slower than they had
+// been before this estimate: 8 units x 8 heads, T = 51, 71436 rows, pruned values, 94 pieces instead of 63, 39.4 -> 47.5 us; 56 x 5
+// heads x 13325 rows, 12 instead of 9, 50.3 -> 55.4.)
 // What it knows that a resident set of blocks (n0) misses: a few
 // blocks more than a multiple of 256 cost a round of few (64 units x 32768 rows, 4 heads: 4 pieces 121 us, 5 151); pieces of one
 // step that leave compute units idle (16 units x 1815 rows: 15 pieces instead of 8, 11.0 -> 9.5); that one
@@ -275,13 +288,16 @@ int decode_pieces(const thk_shape *s, int hpb, int64_t wgs, int64_t steps, int n
   const int64_t fit = (int64_t)THK_STATIC_SCRATCH_BYTES / ((kD + 2) * 4 + 8) / heads;
   if (n0 > 1 && n0 > fit) return n0;
   const int64_t top = std::min(most_pieces(wgs, steps, n0), std::max<int64_t>(fit, 1));
-  if (s->dtype == THK_F32) return decode_pieces_f32(s, hpb, wgs, steps, n0, least, top);
-  const bool wide = ld_of(s) > 79;   // the staging class of long rows
-  const int resident = (hpb == 8 ? 3 : 4) - (wide ? 1 : 0);
+  const int n1 = pieces_by_rounds(s, hpb, wgs, steps, n0, least, top);
+  if (s->dtype == THK_F32) return n1;
+  if (n0 >= 8) least = std::max(least, 4);
+  const bool wide = ld_of(s) > 79;
+  const int resident = decode_resident(s, hpb);
   const DecodeCost &c = decode_cost(hpb);
-  const double slow = (ld_of(s) % (hpb <= 2 ? 2 : 4) != 0 ? c.odd : 1.0) * (wide ? c.wide : 1.0);
+  const bool odd = ld_of(s) % (hpb <= 2 ? 2 : 4) != 0;
+  const double slow = (odd ? c.odd : 1.0) * (wide ? c.wide : 1.0);
   const double t_step = c.t_step * slow;
-  auto cost = [&](int64_t n, double k, int width) {
+  auto cost = [&](int64_t n, double k, int width, int resident) {
     const double b = 128.0 * 2 * (ld_of(s) + width) / 1024.0;
     const int64_t blocks = wgs * n;
     auto cu = [&](int64_t l) { return std::min((l == 1 ? c.c1 : c.c2) / slow, (double)l * b / t_step); };
@@ -300,22 +316,24 @@ int decode_pieces(const thk_shape *s, int hpb, int64_t wgs, int64_t steps, int n
     return t;
   };
   // (the estimate for rows of unknown value width)
-  auto estimate = [&](int64_t rows) {
-    const int64_t n = ceil_div(s->S, rows);
+  auto estimate = [&](int64_t i, int resident_full, int resident_half) {
+    const int64_t rows = (ceil_div(s->S, i) + 63) & ~(int64_t)63, n = ceil_div(s->S, rows);
     const double k = (double)((rows + 127) / 128);
-    return cost(n, k, kD) * cost(n, k, kD / 2);
+    return cost(n, k, kD, resident_full) * cost(n, k, kD / 2, resident_half);
   };
-  auto piece_rows = [&](int64_t n) { return (ceil_div(s->S, n) + 63) & ~(int64_t)63; };
-  double best = 0.94 * 0.94 * estimate(piece_rows(n0));
-  int64_t n_best = n0, rows_last = 0;
+  double best = 0.94 * 0.94 * estimate(n0, resident, resident);
+  int64_t n_best = n0, k_last = 0;
   for (int64_t i = least; i <= top; ++i) {
-    const int64_t rows = piece_rows(i);
-    if (rows == rows_last) continue;   // the same pieces, some of them empty
-    rows_last = rows;
-    const double e = estimate(rows);
+    const int64_t k = (steps + i - 1) / i;
+    if (k == k_last) continue;   // the same pieces, some of them empty
+    k_last = k;
+    const double e = estimate(i, resident, resident);
     if (e < best) { best = e; n_best = i; }
   }
-  return (int)n_best;
+  // (between the two counts, blocks of eight heads count as two to a compute unit with pruned value rows, whose wide staging
+  // class has two, and with key rows of odd pitch, where a third one does not help)
+  const int r_half = hpb == 8 ? 2 : resident, r_full = hpb == 8 && odd ? 2 : resident;
+  return estimate(n_best, r_full, r_half) < 0.98 * 0.98 * estimate(n1, r_full, r_half) ? (int)n_best : n1;
 }
 
 // ws_bytes: what the caller's workspace holds.  The estimate's count goes up and down with S, so a
@@ -355,7 +373,7 @@ Split decode_split(const thk_shape *s, size_t ws_bytes = SIZE_MAX) {
     if (n == 1 && s->S >= 2048) n = 2;
     const int n0 = n;
     const bool one = n0 == 1 || (wgs >= kCUs / 2 && s->S < 4096);
-    if (s->S > one_block_rows || units_of(s) > 8) n = decode_pieces(s, hpb, wgs, steps, n0, one ? 1 : std::max(n0 >= 8 && s->dtype == THK_BF16 ? 4 : 2, n0 / 4));
+    if (s->S > one_block_rows || units_of(s) > 8) n = decode_pieces(s, hpb, wgs, steps, n0, one ? 1 : std::max(2, n0 / 4));
     const int64_t fit = (int64_t)std::min<size_t>(ws_bytes / decode_ws_bytes(s, 1), (size_t)n);
     if (fit < n && fit >= (one ? 0 : std::max(2, n0 / 8))) n = std::max((int)fit, 1);
   }

@@ -298,6 +298,10 @@ def test_default_decode_split_balances_rounds_and_stays_within_the_static_scratc
     assert split(32, 48, 8, 447, 111) == 1               # 256 units x 6 heads: 20.5 us, 2 pieces 23.1
     assert split(32, 40, 8, 391, 64, thk.THK_F32) == 1   # 256 units x 5 heads: 27.6 us, 2 pieces 36.8
     assert split(1, 160, 32, 3582, 64, thk.THK_F32) == 8     # 32 units x 5 heads: 30.5 us, 4 pieces 36.6
+    # counts that the two estimates of bf16 calls do not agree on stay as the first one has them
+    assert split(2, 32, 4, 71436, 51) == 63                  # 8 units x 8 heads, pruned values 39.4 us, 94 pieces 47.5
+    assert split(7, 40, 8, 13325, 51) == 9                   # 56 units x 5 heads: 50.3 us, 12 pieces 55.4
+    assert split(31, 40, 8, 4287, 51) == 2                   # 248 units x 5 heads: 66.0 us, 3 pieces 69.4
     # fp32 pieces are told apart by their steps, not by runs of half a step
     assert split(13, 28, 4, 2304, 111, thk.THK_F32) == 2     # 52 units x 7 heads: 53 us, 9 pieces 66
     assert split(10, 32, 8, 2394, 124, thk.THK_F32) == 3     # 80 units x 4 heads: 46 us, 5 pieces 61
