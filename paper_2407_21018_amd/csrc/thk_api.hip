@@ -230,20 +230,25 @@ int pieces_by_rounds(const thk_shape *s, int hpb, int64_t wgs, int64_t steps, in
   const int resident = decode_resident(s, hpb);
   const double t_step = f32 ? 4.8 : hpb == 8 ? 2.7 : 2.4, t_block = f32 ? 3.4 : 0.8;
   const double t_stream = 0.036 * 128 * (ld_of(s) + kD) * elem_bytes(s->dtype) / 1024.0;
-  auto cost = [&](int64_t n, int64_t k) {
-    const int64_t blocks = wgs * n, rounds = ceil_div(blocks, (int64_t)kCUs * resident);
-    auto round = [&](int64_t l) { return (double)k * std::max(t_step, (double)l * t_stream); };
-    const int64_t last = ceil_div(blocks - (rounds - 1) * kCUs * resident, kCUs);
+  auto around = [&](int64_t n) {   // what the tiles do not pay for; grows with n
+    const int64_t blocks = wgs * n;
     const bool in_launch = n <= kDecodeFuseMaxSplit && blocks <= 2 * kCUs && hpb <= 4;
     const double merge = n == 1 ? 0.0 : in_launch ? 3.5 : 4.0 + 0.015 * (double)n + 0.0002 * (double)(heads * n);
-    return (double)(rounds - 1) * round(resident) + round(last) + t_block * (double)ceil_div(blocks, kCUs) + merge;
+    return t_block * (double)ceil_div(blocks, kCUs) + merge;
   };
+  auto cost = [&](int64_t n, int64_t k) {
+    const int64_t per_cu = ceil_div(wgs * n, kCUs), rounds = ceil_div(per_cu, resident);
+    auto round = [&](int64_t l) { return (double)k * std::max(t_step, (double)l * t_stream); };
+    return (double)(rounds - 1) * round(resident) + round(per_cu - (rounds - 1) * resident) + around(n);
+  };
+  const double least_time = (double)wgs * (double)steps / kCUs * t_stream;   // all rows at the memory rate
   double best = 0.91 * cost(n0, ceil_div(ceil_div(s->S, n0), 128));
   int64_t n_best = n0, k_last = 0;
   for (int64_t i = least; i <= top; ++i) {
     const int64_t k = (steps + i - 1) / i;
     if (k == k_last) continue;   // the same pieces, some of them empty
     k_last = k;
+    if (least_time + around(i) >= best) break;   // nor does any count from here on
     const double c = cost(i, k);
     if (c < best) { best = c; n_best = i; }
   }
@@ -297,43 +302,68 @@ int decode_pieces(const thk_shape *s, int hpb, int64_t wgs, int64_t steps, int n
   const bool odd = ld_of(s) % (hpb <= 2 ? 2 : 4) != 0;
   const double slow = (odd ? c.odd : 1.0) * (wide ? c.wide : 1.0);
   const double t_step = c.t_step * slow;
-  auto cost = [&](int64_t n, double k, int width, int resident) {
-    const double b = 128.0 * 2 * (ld_of(s) + width) / 1024.0;
+  // A call plans this before it can launch, over up to 113 counts: nothing is divided that can be multiplied, and the search
+  // ends where all rows at the memory rate and what a count adds to them reach the best time found.  Host time of
+  // thk_default_split, plain formula / so: 8 units x 8 heads x 131072 rows 1980 / 110 ns, 64 x 4 x 32768 1060 / 80, 8 x 4 x
+  // 1000 170 / 155.
+  // Value rows of one width.  us per step: a block at the memory rate (t_one) and one on every compute unit (t_mem), a
+  // block at the rate of a compute unit that it has alone (t1) or shares (t2), a whole round (t_round).
+  struct Width {
+    double t_one, t_mem, t1, t2, t_round;
+    int resident;
+  };
+  static constexpr double inv[] = {0.0, 1.0, 1.0 / 2, 1.0 / 3, 1.0 / 4, 1.0 / 5};
+  auto round = [&](const Width &w, int q, int r) {   // us per step: q blocks on every compute unit, one more on r of them
+    double t = 0.0;
+    if (q > 0) t += std::max({q * w.t_mem, q * (q == 1 ? w.t1 : w.t2), t_step});
+    if (r > 0) t += std::max({r * w.t_one, q == 0 ? w.t1 : w.t2, t_step * inv[q + 1]});
+    return std::max(t, t_step);
+  };
+  auto width = [&](int channels, int resident) {
+    const double b = 128.0 * 2 * (ld_of(s) + channels) / 1024.0;
+    Width w{b / kRate, b * (kCUs / kRate), b * slow / c.c1, b * slow / c.c2, 0.0, resident};
+    w.t_round = round(w, resident, 0);
+    return w;
+  };
+  const Width w_full = width(kD, resident), w_half = width(kD / 2, resident);
+  auto around = [&](int64_t n) {   // what the tiles do not pay for; grows with n
     const int64_t blocks = wgs * n;
-    auto cu = [&](int64_t l) { return std::min((l == 1 ? c.c1 : c.c2) / slow, (double)l * b / t_step); };
-    auto round = [&](int64_t m) {
-      const int64_t q = m / kCUs, r = m % kCUs;
-      double t = 0.0;
-      if (q > 0) t += (double)q * k * b / std::min(kRate / kCUs, cu(q));
-      if (r > 0) t += k * b / std::min(kRate / (double)r, cu(q + 1));
-      return std::max(t, k * t_step);
+    const double t = c.t0 + c.t_block * (double)ceil_div(blocks, kCUs);
+    if (n == 1) return t;
+    return t + (n <= kDecodeFuseMaxSplit && merges_in_launch(hpb, blocks) ? c.m_in : c.m_out + 0.01 * (double)n + 0.0002 * (double)(heads * n));
+  };
+  // (for rows of unknown value width)
+  auto estimate = [&](int64_t i, const Width &wide_rows, const Width &narrow_rows) {
+    const int64_t rows = (ceil_div(s->S, i) + 63) & ~(int64_t)63, n = ceil_div(s->S, rows), blocks = wgs * n, per_cu = blocks / kCUs;
+    const int r = (int)(blocks % kCUs);
+    const double fixed = around(n);
+    auto time = [&](const Width &w) {
+      const int64_t full = per_cu / w.resident;
+      const int q = (int)(per_cu - full * w.resident);
+      double t = (double)full * w.t_round;
+      if (q + r > 0) t += round(w, q, r);
+      return fixed + (double)((rows + 127) / 128) * t;
     };
-    const int64_t full = blocks / (kCUs * resident), rest = blocks % (kCUs * resident);
-    double t = c.t0 + c.t_block * (double)ceil_div(blocks, kCUs);
-    if (full > 0) t += (double)full * round(kCUs * resident);
-    if (rest > 0) t += round(rest);
-    if (n > 1) t += n <= kDecodeFuseMaxSplit && merges_in_launch(hpb, blocks) ? c.m_in : c.m_out + 0.01 * (double)n + 0.0002 * (double)(heads * n);
-    return t;
+    return time(wide_rows) * time(narrow_rows);
   };
-  // (the estimate for rows of unknown value width)
-  auto estimate = [&](int64_t i, int resident_full, int resident_half) {
-    const int64_t rows = (ceil_div(s->S, i) + 63) & ~(int64_t)63, n = ceil_div(s->S, rows);
-    const double k = (double)((rows + 127) / 128);
-    return cost(n, k, kD, resident_full) * cost(n, k, kD / 2, resident_half);
-  };
-  double best = 0.94 * 0.94 * estimate(n0, resident, resident);
+  const double least_full = (double)wgs * (double)steps * w_full.t_one, least_half = (double)wgs * (double)steps * w_half.t_one;
+  double best = 0.94 * 0.94 * estimate(n0, w_full, w_half);
   int64_t n_best = n0, k_last = 0;
   for (int64_t i = least; i <= top; ++i) {
     const int64_t k = (steps + i - 1) / i;
     if (k == k_last) continue;   // the same pieces, some of them empty
     k_last = k;
-    const double e = estimate(i, resident, resident);
+    const int64_t n = ceil_div(steps, k);   // pieces of k steps: at least this many
+    const double fixed = around(n);
+    if ((least_full + fixed) * (least_half + fixed) >= best) break;
+    const double e = estimate(i, w_full, w_half);
     if (e < best) { best = e; n_best = i; }
   }
+  if (n_best == n1) return n1;
   // (between the two counts, blocks of eight heads count as two to a compute unit with pruned value rows, whose wide staging
   // class has two, and with key rows of odd pitch, where a third one does not help)
-  const int r_half = hpb == 8 ? 2 : resident, r_full = hpb == 8 && odd ? 2 : resident;
-  return estimate(n_best, r_full, r_half) < 0.98 * 0.98 * estimate(n1, r_full, r_half) ? (int)n_best : n1;
+  const Width c_full = hpb == 8 && odd ? width(kD, 2) : w_full, c_half = hpb == 8 ? width(kD / 2, 2) : w_half;
+  return estimate(n_best, c_full, c_half) < 0.98 * 0.98 * estimate(n1, c_full, c_half) ? (int)n_best : n1;
 }
 
 // ws_bytes: what the caller's workspace holds.  The estimate's count goes up and down with S, so a
