@@ -122,7 +122,8 @@ constexpr int kKst = 272;  // LDS bytes per key row: 16-lane b128 reads of 16 ro
 constexpr int kVst = 320;  // LDS bytes per value row: the 4-row x 32-byte transposing reads of a
                            // half-wave cover all 64 banks once
 
-template <int QT>
+// KEEP: values without the non-temporal hint (see fetch_part).
+template <int QT, bool KEEP>
 __global__ __launch_bounds__(256, 2) void k_value_attn_bf16(ValueAttnArgs a) {
   constexpr int KW = 4 / QT;     // waves that share a query tile, each on its own key sub-tiles
   constexpr int KT = QT;         // 32-key sub-tiles per wave and chunk
@@ -169,11 +170,14 @@ __global__ __launch_bounds__(256, 2) void k_value_attn_bf16(ValueAttnArgs a) {
 
   u32x4 pk[NP], pv[NP];
   // quarter q of the next chunk's loads: q = 0, 1 the two halves of the key rows, q = 2, 3 of
-  // the value rows.  Keys are not needed again; a value prune reads the values once more, for the copy, and
-  // values that were loaded without the non-temporal hint are still in the memory-side cache then, the last 256 MB
-  // of them (k_value_attn_wide: 64 units x 32768 rows, copy 139 -> 119 us, whole call 388 -> 370; this kernel: 88 x 858
-  // rows, 2 heads 28.9 -> 27.2, 12 x 17322, 4 heads 64.5 -> 63.0).  With one query tile the score itself is bound by memory and
-  // loses what the copy gains (24 units x 21938 rows 122.6 / 119.1, 32 x 4662 51.4 / 52.3): the hint stays.
+  // the value rows.  Keys are not needed again, nor are the values of a score call.  A value prune reads the values
+  // once more, for the copy, and those loaded without the non-temporal hint are still in the memory-side cache then, the last
+  // 256 MB of them.  The score loses by it where it is bound by memory.  Whole prunes, with the hint / without: four query tiles
+  // and more (k_value_attn_wide) 64 units x 32768 rows 388 / 370 us, 184 x 15264 552 / 522, 24 x 2202, 8 heads 44.9 / 41.0, all of
+  // 14 calls 1 to 9 % shorter; two tiles, MB of values: 46 57.1 / 53.4, 220 185 / 174, 300 238 / 229, 380 300 / 295, 420 299 /
+  // 298, 460 305 / 310, 700 498 / 510, 850 518 / 539; one tile 24 units x 21938 rows 119.1 / 122.6, 32 x 4662 52.3 / 51.4.  Score calls
+  // of two tiles 32 units x 53870 rows 168 / 185, 40 x 12645 70 / 75.  Hence KEEP in prunes of four tiles and more, and
+  // of two up to 384 MiB of values.
   auto fetch_part = [&](int c, int q) {
     const unsigned char *g = q < 2 ? kg : vg;
 #pragma unroll
@@ -183,7 +187,7 @@ __global__ __launch_bounds__(256, 2) void k_value_attn_bf16(ValueAttnArgs a) {
       gr = gr < S ? gr : S - 1;   // rows past the end repeat the last one; their weights are zero
       const u32x4 *src = (const u32x4 *)(g + gr * (kD * 2) + scol);
       if (q < 2) pk[p] = ld_stream(src);
-      else pv[p] = QT == 1 ? ld_stream(src) : *src;
+      else pv[p] = KEEP ? *src : ld_stream(src);
     }
   };
   auto stash = [&]() {
@@ -333,9 +337,9 @@ __global__ __launch_bounds__(256, 2) void k_value_attn_bf16(ValueAttnArgs a) {
 constexpr int kWideRows = 128;                    // rows per chunk
 constexpr int kWideBytes = kWideRows * kD * 2;    // one tensor's chunk in LDS
 
-// One chunk of one tensor, 4 rows (1024 bytes) per instruction, KEYS: the key permutation, and the non-temporal
-// hint, which values go without (see fetch_part above).
-template <bool KEYS>
+// One chunk of one tensor, 4 rows (1024 bytes) per instruction, KEYS: the key permutation; KEEP: without the
+// non-temporal hint (see fetch_part above).
+template <bool KEYS, bool KEEP>
 __device__ __forceinline__ void wide_fetch(const unsigned char *g, int64_t last, unsigned char *lds, int wave,
                                            int lane) {
   constexpr int NI = kWideRows / 4 / 8;           // instructions per wave
@@ -348,11 +352,11 @@ __device__ __forceinline__ void wide_fetch(const unsigned char *g, int64_t last,
     // rows past the end repeat the last one; their weights are zero
     const uint32_t off = (uint32_t)(row < last ? row : (int)last) * (kD * 2) + chunk * 16;
     __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(g + off),
-                                     (__attribute__((address_space(3))) void *)(lds + inst * 1024), 16, 0, KEYS ? 2 /* nt */ : 0);
+                                     (__attribute__((address_space(3))) void *)(lds + inst * 1024), 16, 0, KEEP ? 0 : 2 /* nt */);
   }
 }
 
-template <int QT>
+template <int QT, bool KEEP>
 __global__ __launch_bounds__(512, 2) void k_value_attn_wide(ValueAttnArgs a) {
   constexpr int KW = 8 / QT;                      // waves that share a query tile, each on its own keys
   constexpr int KT = kWideRows / 32 / KW;         // sub-tiles per wave and chunk
@@ -383,8 +387,8 @@ __global__ __launch_bounds__(512, 2) void k_value_attn_wide(ValueAttnArgs a) {
     const int64_t r0 = (int64_t)c * kWideRows;
     const int64_t last = S - 1 - k0 - r0;          // the unit's last row, seen from the chunk's first
     const int64_t lc = last < kWideRows - 1 ? last : kWideRows - 1;
-    wide_fetch<true>(kg + r0 * (kD * 2), lc, kb, w, lane);
-    wide_fetch<false>(vg + r0 * (kD * 2), lc, vb, w, lane);
+    wide_fetch<true, false>(kg + r0 * (kD * 2), lc, kb, w, lane);
+    wide_fetch<false, KEEP>(vg + r0 * (kD * 2), lc, vb, w, lane);
   };
   if (nchunks > 0) fetch(0, kb0, vb0);
 
@@ -793,7 +797,15 @@ hipError_t launch_value_score(int dtype, const void *q_obs, const void *k, const
   const void *fn;
   int threads = 256;
   if (dtype == THK_BF16) {
-    fn = wide ? (QB == 8 ? (const void *)k_value_attn_wide<8> : (const void *)k_value_attn_wide<4>) : QT == 2 ? (const void *)k_value_attn_bf16<2> : (const void *)k_value_attn_bf16<1>;
+    // a copy of the values follows, and finds enough of them in the memory-side cache (fetch_part)
+    const bool keep = idx != nullptr && (wide || (size_t)U * S * (kD * 2) <= (size_t)384 << 20);
+    if (wide)
+      fn = keep ? (QB == 8 ? (const void *)k_value_attn_wide<8, true> : (const void *)k_value_attn_wide<4, true>)
+                : (QB == 8 ? (const void *)k_value_attn_wide<8, false> : (const void *)k_value_attn_wide<4, false>);
+    else if (QT == 2)
+      fn = keep ? (const void *)k_value_attn_bf16<2, true> : (const void *)k_value_attn_bf16<2, false>;
+    else
+      fn = (const void *)k_value_attn_bf16<1, false>;
   } else {
     fn = QT == 4 ? (const void *)k_value_attn_f32<4> : QT == 2 ? (const void *)k_value_attn_f32<2> : (const void *)k_value_attn_f32<1>;
     threads = QT == 4 ? 256 : QT == 2 ? 128 : 64;

@@ -162,6 +162,27 @@ def test_value_prune_select_and_compact():
     check_idx_against_oracle_ranking(idx.cpu().numpy(), ora, T_v)
 
 
+@pytest.mark.parametrize("B,N_kv,G,S_obs,S", [
+    (1, 2, 2, 32, 900), (2, 8, 2, 32, 98400),               # two query tiles, 16 * 98400 rows are 403 MB of values
+    (1, 2, 1, 32, 900), (1, 2, 4, 32, 900), (8, 8, 8, 32, 300)])   # one, four and eight tiles per block
+def test_value_score_alone_and_in_a_prune_are_the_same(B, N_kv, G, S_obs, S):
+    """A prune may load the values another way, for the copy behind the score: the same bits."""
+    U, T_v = B * N_kv, 64
+    q_obs = _randn((1, B, N_kv * G, S_obs, D), "bf16", 31, 0.5)
+    k = _randn((1, B, N_kv, S, D), "bf16", 32, 0.5)
+    v = _randn((1, B, N_kv, S, D), "bf16", 33, 0.7)
+    shape = thk.make_shape(1, B, N_kv * G, N_kv, D, S, S_obs, T_v, 0, thk.THK_BF16, 0)
+    score = gpu_score_value(shape, q_obs, k, v, 1)
+    score_p, idx = torch.empty_like(score), torch.empty(U, T_v, dtype=torch.int16, device="cuda")
+    vp = torch.empty(U, S, T_v, dtype=torch.bfloat16, device="cuda")
+    thk.thk_prune_value(shape, q_obs, k, v, 1, score_p, idx, vp, ws_tensor(thk.thk_workspace_bytes(shape, thk.THK_OP_PRUNE_VALUE)))
+    torch.cuda.synchronize()
+    assert torch.equal(score, score_p)
+    assert torch.equal(idx, gpu_select(shape, score))
+    for u in range(U):
+        assert torch.equal(vp[u], v.reshape(U, S, D)[u][:, idx[u].long()])
+
+
 def test_value_score_argument_errors():
     A = torch.zeros(1 << 16, dtype=torch.uint8, device="cuda")
     s = thk.make_shape(1, 1, 1, 1, D, 64, 32, 64, 0, thk.THK_BF16, 0)
