@@ -30,7 +30,7 @@ class _Sub(torch.Tensor):
     ("q", lambda x: x.data_ptr()), ("q", lambda x: x[:, :7]), ("q", lambda x: None), ("k_pruned", lambda x: x.transpose(0, 1)),
     ("v", lambda x: x.as_subclass(_Sub)), ("out", lambda x: x.to_sparse()), ("k_tail", lambda x: x[:, ::2]), ("k_tail", lambda x: x[:, :2]),
     ("idx", lambda x: [0]), ("s_tail", lambda x: True), ("s_tail", lambda x: 3.0), ("s_tail", lambda x: 1 << 40), ("ws", lambda x: (1, 2)),
-    ("stream", lambda x: "0"), ("shape", lambda x: b"short"), ("q", lambda x: torch.empty(8, D, device="meta")[:4])])
+    ("stream", lambda x: "0"), ("shape", lambda x: b"short")])
 def test_other_forms_are_left_to_the_python_code(name, make):
     thk.load()
     a = _decode_args()
@@ -39,6 +39,17 @@ def test_other_forms_are_left_to_the_python_code(name, make):
     a[name] = make(a[name])
     assert binding._call.decode_attn(*a.values()) == -1
     assert binding._call.decode_attn(*list(a.values())[:-1]) == -1
+
+
+def test_a_tensor_without_memory_is_a_null_pointer_both_ways():
+    a = _decode_args()
+    a["q"] = a["q"].to("meta")
+    thk.load()
+    assert binding._call.decode_attn(*a.values()) == 1
+    a["q"] = 0                                        # the same, as an address
+    with pytest.raises(thk.ThkError) as e:
+        thk.thk_decode_attn(*a.values())
+    assert e.value.status == 1
 
 
 def test_checks_raise_as_before():
@@ -63,6 +74,36 @@ def _four_calls(shape, device="cpu"):
             (c.decode_attn_kv, thk.thk_decode_attn_kv, (shape, t(), t(), idx, t(), idx, 64, 64, t(), t(), 3, 16, t(), ws, 0)),
             (c.tail_append, thk.thk_tail_append, (shape, t(), t(), t(), t(), 3, 16, 0)),
             (c.prune, thk.thk_prune, (shape, t(), t(), None, idx, t(), ws, 0))]
+
+
+def _refused(calls):
+    """The four calls with a value that the library refuses in front of any launch, and the status it gives."""
+    decode, decode_kv, append, prune = [list(args) for _, _, args in calls]
+    decode[7] = decode_kv[10] = 17                    # more rows than the tail holds
+    append[5] = 16                                    # no room for another one
+    prune[6] = None                                   # no workspace
+    return [(native, public, args, status) for (native, public, _), args, status in zip(calls, (decode, decode_kv, append, prune), (2, 2, 2, 5))]
+
+
+@pytest.mark.parametrize("stream", [0, None])
+def test_each_call_is_taken(stream):
+    """In the plain form every one of the four reaches the library: its status comes back, not -1."""
+    calls = _refused(_four_calls(_decode_args()["shape"]))
+    asked = []
+    binding._forget_runtime()                         # as at the start of a process
+    try:
+        if stream is None:
+            assert calls[0][0](*calls[0][2][:-1], None) == -1     # the current stream is not known before the runtime is up
+            binding._call.stream_getters(lambda device: asked.append(device) or 0, lambda: 3)
+        for native, public, args, status in calls:
+            args[-1] = stream
+            assert native(*args) == status
+            with pytest.raises(thk.ThkError) as e:
+                public(*args)
+            assert e.value.status == status
+    finally:
+        binding._forget_runtime()
+    assert asked == ([3] * 8 if stream is None else [])
 
 
 @pytest.mark.parametrize("fields", [dict(S_cap=1 << 56), dict(S_cap=(1 << 57) + 40), dict(S=1 << 56), dict(S_cap=1 << 62, T=128), dict(L=1 << 30, B=1 << 30, N_kv=8),
@@ -125,9 +166,25 @@ def test_the_library_works_without_the_native_issue(found, tmp_path):
     subprocess.run([sys.executable, "-c", code], check=True, cwd=tmp_path, env={**os.environ, "PYTHONPATH": str(tmp_path)}, timeout=300)
 
 
+class _Watched:
+    """The native module, and what its calls returned."""
+
+    def __init__(self, module):
+        self.module, self.returned = module, []
+
+    def __getattr__(self, name):
+        f = getattr(self.module, name)
+
+        def call(*a):
+            st = f(*a)
+            self.returned.append((name, st))
+            return st
+        return call
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("side_stream", [False, True])
-def test_both_ways_of_issuing_a_call_agree(side_stream):
+def test_both_ways_of_issuing_a_call_agree(side_stream, monkeypatch):
     g = torch.Generator(device="cuda"); g.manual_seed(5)
     rnd = lambda *d: torch.randn(*d, generator=g, device="cuda").to(torch.bfloat16)
     U, S, T, cap = 6, 700, 76, 32
@@ -154,6 +211,14 @@ def test_both_ways_of_issuing_a_call_agree(side_stream):
         torch.cuda.synchronize()
         return score, idx, kp, kt, vt, out, out_kv
 
-    for x, y in zip(run(None), run("addresses")):
+    run(None)                                         # the first call of a process sets the stream getters
+    watched = _Watched(binding._call)
+    monkeypatch.setattr(binding, "_call", watched)
+    native = run(None)
+    names = ["prune", "tail_append", "decode_attn", "decode_attn_kv"]
+    assert watched.returned == [(n, 0) for n in names]            # taken, and issued
+    watched.returned.clear()
+    for x, y in zip(native, run("addresses")):
         assert torch.equal(x, y)
-    assert run(None)[5].abs().max() > 0
+    assert watched.returned == [(n, -1) for n in names]           # addresses are left to the Python code
+    assert native[5].abs().max() > 0
