@@ -110,13 +110,19 @@ struct Args {
   int64_t rows(int64_t used) { return count(layers_units(), shape->S_cap ? shape->S_cap : used); }
 };
 
-// A call without the interpreter lock (a launch may have to wait for room in the queue).
+// A call without the interpreter lock (a launch may have to wait for room in the queue), which is taken again also
+// when f throws.
+struct Unlocked {
+  PyThreadState *state = PyEval_SaveThread();
+  ~Unlocked() { PyEval_RestoreThread(state); }
+};
 template <class F>
 PyObject *issue(F f) {
   thk_status st;
-  Py_BEGIN_ALLOW_THREADS
-  st = f();
-  Py_END_ALLOW_THREADS
+  {
+    Unlocked unlocked;
+    st = f();
+  }
   return PyLong_FromLong((long)st);
 }
 PyObject *not_taken() { return PyLong_FromLong(kNotTaken); }
