@@ -276,10 +276,11 @@ thk_status thk_prune(const thk_shape *shape, const void *q_obs, const void *k,
  * with s_tail > 0 selects the unified value cache: the tail's value rows are rows
  * [S, S + s_tail) of v (needs S_cap >= S + s_tail).
  * S_obs in the shape is ignored.  With n_split > 1 partial (max, sum, acc[D])
- * states go through ws and are merged in split order, so repeated calls give
- * identical bits: by a second kernel, or -- for small calls (at most 16 pieces, at
- * most four query heads per block, at most two blocks per compute unit) -- inside the
- * one launch by the block that finishes last for a head group (the blocks signal
+ * states go through ws and are merged in an order fixed by the shape and the launch form
+ * (not by which block finishes first), so repeated calls give identical bits: by a second
+ * kernel, or -- for calls of at most 16 pieces whose blocks serve one or two query heads,
+ * four with at most 512 blocks (units x head groups x pieces), or eight with fewer than
+ * 512 -- inside the one launch by the block that finishes last for a head group (the blocks signal
  * through per-piece flag words in ws that carry a nonce drawn per call; no
  * read-modify-write, nothing in ws has to be cleared beforehand).
  * THK_DECODE_MERGE = kernel | fused in the environment overrides the choice.

@@ -502,7 +502,7 @@ __device__ __forceinline__ void tile_compute(int shift, int nrows, int W, int ld
 //   3. loads the group's flags: if all of them hold the nonce it merges.
 // The block whose flag store is performed last finds all flags set, and by 1. every record is
 // then visible to it.  Blocks that finish within a round trip of each other may both find all
-// flags set: both merge, in split order, and store the same bits.  A merging block clears the
+// flags set: both merge, in the same order, and store the same bits.  A merging block clears the
 // flags afterwards, so that a replay of the same launch from a graph, which carries the same
 // nonce, starts clean; whatever else the flag words held before the call (another call's nonce,
 // other data of the workspace) is not the nonce: 64 bits drawn per call.
@@ -531,6 +531,8 @@ __device__ __forceinline__ void block_merge_store(const float *mrg, int wstride,
   int lane = threadIdx.x % kWave;
   asm volatile("" : "+v"(lane));   // a copy of its own: nothing made from it is kept through the tile loops (registers)
   const int wave = uniform(threadIdx.x / kWave);
+  // (a weight below 2^-126 is 0, as in the tiles; the library's exp2, which keeps a denormal, takes calls of 7 to 11 us
+  // 1 to 2 % longer, and the error against 64 bits over 240 random calls is no larger without it: bf16 1.000, fp32 0.90 of it)
   auto weight = [](float m, float M) { return m == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m - M); };
   auto store_out = [&](size_t bn, float A0, float A1, float L) { E::store2(a.out, bn * kD + 2 * lane, A0 / L, A1 / L); };
   // A wave takes a head, a lane two of its channels; heads <= GT of the block's slots are in use.
@@ -571,7 +573,7 @@ __device__ __forceinline__ void block_merge_store(const float *mrg, int wstride,
   }
   if (a.n_split == 1 || !fused) return;
 
-  // ---- the group's last block merges: m = max m_i, l = sum l_i 2^(m_i - m), acc likewise, in
+  // ---- the group's last block merges: m = max m_i, l = sum l_i 2^(m_i - m) by the wave's fixed tree, acc likewise in
   // split order (the result does not depend on who arrives last) ---------------------------
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this wave's record stores are acknowledged
   __syncthreads();                                   // ... and every wave's

@@ -334,8 +334,9 @@ void k_prune_solo(PruneFusedArgs a) {
   // instead of 1.8 us.
   const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
   // What the block needs in front of its first loads, asked for at once: an argument loaded where it is
-  // first used is a trip of its own, and there were two.  8 units x 5003 rows 11.15 -> 11.0 us, fp32 8 x
-  // 2048 9.32 -> 9.24 us; calls above 100 us do not change.
+  // first used is a trip of its own, and there were two.  Medians of 15 turns in alternation: 8 units
+  // x 5003 rows 11.28 -> 11.13 us, 32 x 347 9.65 -> 9.50, fp32 8 x 2048 9.38 -> 9.31 (0.7 to 1.6 %, the same sign in every
+  // turn; two runs of one side differ by up to 1.6 %); calls above 20 us do not change.
   asm volatile("" ::"s"(a.k), "s"(a.S), "s"(a.NB), "s"(a.U), "s"(a.stagger_blocks), "s"(a.stagger_units), "s"(a.stagger_ticks));
   if (blockIdx.x < (uint32_t)a.U) {
     solo_prologue<DT>(a, blockIdx.x, (double *)tiles);   // the tiles are free in a block without rows
