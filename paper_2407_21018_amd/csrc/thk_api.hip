@@ -519,8 +519,8 @@ bool prune_single_launch(const thk_shape *s, const FusedPlan &fp) {
 // units of 4096 bf16 rows +5 % at 2.7 rounds, +1 % at 5, -2 % at 11, -2.5 % at 16, -4.4 % at 32,
 // -5 % at 43; units of 32768 rows +2 % at 5, +1 % at 11, -1.6 % at 21.
 // With the values that the score leaves in the memory-side cache (prunes of two query tiles and more) the line lies where
-// it did: 54 calls, one and two tiles +2 to +3 % at 4 to 6 rounds, 0 at 10 to 13, -2 to -3.4 % at 16 to 20, -4.5 % from 22 on;
-// four and eight tiles +1 to +5 % below 8, +-1 % at 15 to 19, -2 to +1 % at 22 to 28.
+// it did: 50 calls, one and two tiles +2 to +3 % at 4 to 6 rounds, 0 at 10 to 13, -2 to -3.4 % at 16 to 20, -4.5 % from 22 on;
+// four and eight tiles 0 to +6 % below 8, +-1 % at 15 to 19, -2 to +1 % at 22 to 28.
 // THK_VALUE_COMPACT = flat | burst overrides (burst only where the rows can be held).
 bool value_compact_in_bursts(const thk_shape *s, const FusedPlan &fp) {
   if (!fp.ok || fp.hold == 0) return false;
