@@ -5,6 +5,15 @@
 
 namespace thk {
 
+// threadIdx.x as a value the compiler cannot keep: whatever is computed from it (lane masks, LDS and list addresses) is computed
+// again where it is used, instead of waiting in registers beside the rows that the prune kernels hold.  k_prune_solo
+// with three tiles in registers: 168 -> 154 registers, 64 units x 36965 rows 181 -> 178 us, 64 x 26736 161 -> 157.
+__device__ __forceinline__ int tid_here() {
+  int t = threadIdx.x;
+  asm volatile("" : "+v"(t));
+  return t;
+}
+
 // ---------------------------------------------------------------------------
 // Column reduction of rows [s0, s1) of one [S, 128] unit by a 256-thread block:
 // sums of squares (P == 2) or of absolute values (P == 1) per channel, written
@@ -21,7 +30,7 @@ __device__ __forceinline__ void colsum_block(const u32x4 *__restrict__ base, int
                                              double *__restrict__ out, double (*red)[kD]) {
   using E = Elem<DT>;
   constexpr int VEC = E::VEC, LPR = kD / VEC, RPB = 256 / LPR, UNR = 8;
-  const int tid = threadIdx.x;
+  const int tid = tid_here();
   const int cl = tid % LPR, rg = tid / LPR;
   double dacc[VEC];
 #pragma unroll
@@ -64,7 +73,7 @@ __device__ __forceinline__ void colsum_block(const u32x4 *__restrict__ base, int
 
 // ---------------------------------------------------------------------------
 // sum over the G query heads of unit u of ||Q_obs,g[:, c]||_2 (Sec. 3.2, with the
-// observation window), for c = threadIdx.x < 128 (other threads return 0).
+// observation window), for c = tid_here() < 128 (other threads return 0).
 // The unit's heads hold G * S_obs contiguous rows of Q_obs; heads are taken
 // kQnHeads at a time, each thread squares (in fp64) the VEC channels it owns
 // over the rows of its row group, row groups are folded by shuffles inside a
@@ -78,7 +87,7 @@ __device__ __forceinline__ double unit_query_norm(const void *__restrict__ q_obs
                                                   int S_obs, double (*red)[NT / kWave][kD]) {
   using E = Elem<DT>;
   constexpr int VEC = E::VEC, LPR = kD / VEC, RG = NT / LPR, NW = NT / kWave, GC = kQnHeads;
-  const int tid = threadIdx.x, wave = tid / kWave, lane = tid % kWave;
+  const int tid = tid_here(), wave = tid / kWave, lane = tid % kWave;
   const int cl = tid % LPR, rg = tid / LPR;
   // unit u = (layer*batch, KV head) reads query heads u * G .. u * G + G - 1
   const u32x4 *qbase = (const u32x4 *)((const char *)q_obs + (size_t)u * G * S_obs * kD * E::EB);
@@ -193,7 +202,7 @@ __device__ __forceinline__ void block_query_norm(const void *__restrict__ q_obs,
                                                  double *__restrict__ qn_u, double *hn) {
   using E = Elem<DT>;
   constexpr int VEC = E::VEC, LPR = kD / VEC;
-  const int lane = threadIdx.x % kWave, w = threadIdx.x / kWave;
+  const int lane = tid_here() % kWave, w = tid_here() / kWave;
   const int cl = lane % LPR, rg = lane / LPR;
   const u32x4 *qbase = (const u32x4 *)((const char *)q_obs + (size_t)u * G * S_obs * kD * E::EB);
   double tot[VEC];
@@ -282,8 +291,8 @@ __device__ inline void select_wave(float s_lo, float s_hi, int T, int16_t *out, 
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ void select_block(const float *sc, int T, int16_t *out) {
   using u64 = unsigned long long;
-  if (threadIdx.x < kWave) {
-    const int lane = threadIdx.x;
+  if (tid_here() < kWave) {
+    const int lane = tid_here();
     auto key_of = [](float s) {
       const uint32_t b = __float_as_uint(s);
       return (b & 0x80000000u) ? ~b : (b | 0x80000000u);   // unsigned order == float order
@@ -372,8 +381,8 @@ __device__ __forceinline__ void compact_build_tab(int16_t *tab, const int16_t *u
   // 32 threads per row of the period, so that no entry needs a division by ld (three of them per
   // thread took 0.6 us in every block between the arrival of the list and the first store)
   const int period = 8 * ld;
-  const int row = threadIdx.x >> 5;
-  for (int t = threadIdx.x & 31; t < ld; t += 32) {
+  const int row = tid_here() >> 5;
+  for (int t = tid_here() & 31; t < ld; t += 32) {
     int i = row * ld + t + sh, back = 0;
     if (i >= period) { i -= period; back = 8 * Tile<DT>::ROW_ELEMS; }   // seen from the next 8-row block
     // BYTE offsets (at most 8 rows of 272 or 528 bytes: they fit 16 bits), so that a gather address
@@ -453,10 +462,117 @@ __device__ __forceinline__ void compact_emit_tile(const u32x4 *tile, const FlatO
   }
 }
 
+// Step 2 for blocks that hold several tiles per wave.  What a lane gathers is the same in every tile of a unit: chunk c_lo + lane + 64 i of the tile's output, i = 0, 1,
+// ...  Its table entries are fetched once (init) and kept, 16 bits each, so that the LDS reads of a tile
+// depend on nothing but the tile and are all in flight at once; with a table read in front of every chunk's gathers (compact_emit_tile) a
+// tile is a chain of two LDS trips per 64 chunks, 36 instructions where this takes 14.  The chunks go out through a buffer resource that ends with the tile's
+// last whole one, so that no lane is masked.  Whole prunes: 64 units x 26736 rows, T = 97, 157 -> 151 us, 56 x
+// 15051, T = 76, 80.2 -> 77.7, 80 x 29502, T = 34, 153.5 -> 148.5.  (k_compact_flat, whose tiles come one by one, gains nothing.)
+template <int DT>
+struct Emit {
+  using E = Elem<DT>;
+  using ET = typename E::Bits;
+  static constexpr int VEC = E::VEC, NW = VEC / 2;                               // words of a chunk's offsets
+  static constexpr int STEPS = kCompactTileRows * kD / VEC / kWave;              // of a tile of full-width rows
+  static constexpr int kNonTemporal = 2;
+  uint32_t off[STEPS][NW];   // byte offsets into the tile, two per word
+  int c_lo;                  // first whole chunk of a tile
+
+  __device__ __forceinline__ void init(const int16_t *tab, int sh, int ld, int lane) {
+    // chunk c lies in 8-row block pb = c / cpp of the tile, at chunk rc = c % cpp of the table's period
+    const int cpp = 8 * ld / VEC;
+    const int dq = kWave / cpp, dr = kWave - dq * cpp;   // uniform
+    c_lo = (sh + VEC - 1) / VEC;
+    int c = c_lo + lane;
+    int pb = (c >= cpp) + (c >= 2 * cpp) + (c >= 3 * cpp) + (c >= 4 * cpp);
+    int rc = c - pb * cpp;
+#pragma unroll
+    for (int i = 0; i < STEPS; ++i) {
+      if (c_lo + i * kWave < 4 * cpp) {
+        // (a lane past the tile's last chunk looks into the last 8-row block; what it finds is not stored)
+        const uint32_t blk = (uint32_t)min(pb, 3) * (uint32_t)(8 * Tile<DT>::ROW_ELEMS * sizeof(ET));
+        const uint32_t *te = (const uint32_t *)(tab + rc * VEC);
+#pragma unroll
+        for (int w = 0; w < NW; ++w) {
+          const uint32_t x = te[w];   // signed, but block + entry is not: a chunk that looks back is not in block 0
+          off[i][w] = ((x + blk) & 0xffffu) | ((x & 0xffff0000u) + (blk << 16));
+        }
+        rc += dr;
+        pb += dq;
+        if (rc >= cpp) { rc -= cpp; ++pb; }
+      }
+    }
+  }
+  __device__ __forceinline__ u32x4 gather(const char *tile, const uint32_t (&o)[NW]) const {
+    auto at = [&](uint32_t b) { return (uint32_t) * (const ET *)(tile + b); };
+    u32x4 w;
+    if constexpr (DT == THK_BF16) {
+      w.x = at(o[0] & 0xffffu) | (at(o[0] >> 16) << 16);
+      w.y = at(o[1] & 0xffffu) | (at(o[1] >> 16) << 16);
+      w.z = at(o[2] & 0xffffu) | (at(o[2] >> 16) << 16);
+      w.w = at(o[3] & 0xffffu) | (at(o[3] >> 16) << 16);
+    } else {
+      w.x = at(o[0] & 0xffffu); w.y = at(o[0] >> 16);
+      w.z = at(o[1] & 0xffffu); w.w = at(o[1] >> 16);
+    }
+    return w;
+  }
+  // One tile that is already in LDS: rows r0 .. r0 + nr of the unit (r0 a multiple of 32), ld elements each in the output.
+  __device__ __forceinline__ void tile(const u32x4 *t, const FlatOut<DT> &out, int64_t r0, int nr, int ld, const int16_t *tab,
+                                       int lane) const {
+    uint32_t zero = 0;
+    asm volatile("" : "+s"(zero));                     // the addresses are not kept from tile to tile: 8 registers a step
+    const char *b = (const char *)t + zero;
+    const int nq = nr * ld;                            // positions sh .. sh + nq, counted from the tile's first chunk
+    const int c_hi = (out.sh + nq) / VEC;              // whole chunks: c_lo <= c < c_hi
+    u32x4 *const o = out.o + r0 * ld / VEC;
+    const int whole = c_hi - c_lo;
+    const auto rsrc = __builtin_amdgcn_make_buffer_rsrc((void *)(o + c_lo), (short)0, max(whole, 0) * 16, 0x00027000);
+    auto put = [&](int i, const u32x4 &x) { __builtin_amdgcn_raw_buffer_store_b128(x, rsrc, (i * kWave + lane) * 16, 0, kNonTemporal); };
+#pragma unroll
+    for (int i = 0; i < STEPS; i += 2) {
+      if (i * kWave < whole) {   // uniform
+        const u32x4 x = gather(b, off[i]);
+        if ((i + 1) * kWave < whole) {
+          const u32x4 y = gather(b, off[i + 1]);
+          put(i, x);
+          put(i + 1, y);
+        } else {
+          put(i, x);
+        }
+      }
+    }
+    // positions outside the whole chunks: [sh, min(VEC c_lo, sh + nq)) and [max(VEC c_hi, VEC c_lo), sh + nq)
+    const int head_end = min(c_lo * VEC, out.sh + nq);
+    const int n_head = head_end - out.sh;
+    const int tail_beg = max(c_hi * VEC, head_end);
+    const int n_tail = out.sh + nq - tail_beg;
+    if (lane < n_head + n_tail) {                       // at most 2 (VEC - 1) lanes
+      const int period = 8 * ld;
+      const int p = lane < n_head ? out.sh + lane : tail_beg + (lane - n_head);
+      const int pb = p / period;
+      const int pe = p - pb * period;
+      ((ET *)o)[p] = *(const ET *)(b + pb * (8 * Tile<DT>::ROW_ELEMS * (int)sizeof(ET)) + tab[pe]);
+    }
+  }
+};
+
 // The padding chunk of every LDS row of a wave's tile, cleared (the source of the zeros above).
 template <int DT>
 __device__ __forceinline__ void tile_clear_padding(u32x4 *tile, int lane) {
   if (lane < kCompactTileRows) tile[lane * Tile<DT>::PITCH + Tile<DT>::CPR] = u32x4{0u, 0u, 0u, 0u};
+}
+
+// A tile's rows r0 .. r0 + nr (nr <= 32, <= 0: none) of the unit at `base` into registers, chunk j * 64 + lane in r[j]: through a
+// buffer resource that ends with them, so that what lies past the end comes as zeros (which add nothing to a column
+// sum) and moves nothing, without a clamp, a mask or a branch around a load.
+template <int DT, int NLD>
+__device__ __forceinline__ void request_tile(u32x4 (&r)[NLD], const char *base, int r0, int nr, int lane) {
+  constexpr int kRow = kD * Elem<DT>::EB, kNonTemporal = 2;
+  const auto rsrc = __builtin_amdgcn_make_buffer_rsrc((void *)(base + (size_t)(uint32_t)r0 * kRow), (short)0, max(nr, 0) * kRow, 0x00027000);
+#pragma unroll
+  for (int j = 0; j < NLD; ++j)
+    r[j] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rsrc, (j * kWave + lane) * 16, 0, kNonTemporal));
 }
 
 template <int DT>
@@ -466,7 +582,7 @@ __device__ __forceinline__ void compact_rows(const u32x4 *__restrict__ src, cons
   using E = Elem<DT>;
   constexpr int VEC = E::VEC, CPR = kD / VEC, TR = kCompactTileRows;
   constexpr int NLD = TR * CPR / kWave;   // 16-byte loads per lane per tile
-  const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
+  const int wave = tid_here() / kWave, lane = tid_here() % kWave;
   u32x4 *tile = tiles + wave * Tile<DT>::CHUNKS;
   if (ld != T) tile_clear_padding<DT>(tile, lane);
   for (int64_t r0 = s0 + (int64_t)wave * TR; r0 < s1; r0 += 4 * TR) {

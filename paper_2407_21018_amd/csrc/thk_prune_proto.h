@@ -85,7 +85,7 @@ __device__ inline void block_stores_done() {
 // of the list are summed by two thread groups (eight loads in flight each) and added, first
 // half first.  The result is valid in the threads of the first group.  xch: 128 doubles of LDS.
 __device__ __forceinline__ double merge_partials(const double *base, int n, double *xch) {
-  const int tid = threadIdx.x;
+  const int tid = tid_here();
   const int c = tid & (kD - 1), half = tid >> 7;
   const int b_mid = (n + 1) / 2;
   const int b0 = half ? b_mid : 0, b1 = half ? n : b_mid;
@@ -111,7 +111,7 @@ __device__ __forceinline__ double merge_partials(const double *base, int n, doub
 // per 64 bytes: clamping 24 loads cost more than the trips it saved).
 template <int UN>
 __device__ __forceinline__ double merge_partials_once(const double *base, int n, double *xch) {
-  const int tid = threadIdx.x;
+  const int tid = tid_here();
   const int c = tid & (kD - 1);
   const int half = __builtin_amdgcn_readfirstlane(tid >> 7);   // whole waves
   const int b_mid = (n + 1) / 2;
@@ -136,7 +136,7 @@ __device__ __forceinline__ double merge_partials_once(const double *base, int n,
 
 // One arrival: thread 0 bumps the counter; true in every thread of the block that makes it `full`.
 __device__ __forceinline__ bool arrive(int *counter, int full, int *s_flag) {
-  if (threadIdx.x == 0) *s_flag = (atomicAdd(counter, 1) == full - 1);
+  if (tid_here() == 0) *s_flag = (atomicAdd(counter, 1) == full - 1);
   __syncthreads();
   const bool last = *s_flag != 0;
   __syncthreads();   // everyone has read the flag before it is reused
@@ -158,7 +158,7 @@ __device__ inline unsigned long long pub_load_bits(const double *p) {
 // `writer` also stores both for the caller.
 __device__ __forceinline__ void score_and_select(const PruneFusedArgs &a, int64_t u, double qn_c, double kss,
                                                  float *s_sc, int16_t *s_idx, bool writer) {
-  const int tid = threadIdx.x;
+  const int tid = tid_here();
   if (a.given) {
     if (tid < a.T) s_idx[tid] = a.idx[(size_t)u * a.T + tid];
     __syncthreads();

@@ -54,7 +54,7 @@ constexpr int kInitPolls = 1 << 22;      // polls for the prologue's initialisat
 // lds: at least 5 * 128 doubles.
 template <int DT>
 __device__ __forceinline__ void solo_prologue(const PruneFusedArgs &a, int64_t u, double *lds) {
-  const int tid = threadIdx.x;
+  const int tid = tid_here();
   double *hn = lds, *qn_l = lds + 4 * kD;
   // test hook (THK_PRUNE_PROLOGUE_DELAY_US): a late prologue makes the row blocks arrive on
   // counters that are not initialised yet, the path that otherwise needs an unlucky schedule
@@ -95,8 +95,8 @@ __device__ __forceinline__ void solo_prologue(const PruneFusedArgs &a, int64_t u
 // running then and waits for nobody, so the word comes; if the looks run out all the same the
 // norm is NaN, and so is the score: no list is made of sums that lack their norms without a sign.
 __device__ __forceinline__ double query_norm_of(const PruneFusedArgs &a, int64_t u, unsigned long long w) {
-  if (threadIdx.x >= kD) return 0.0;
-  const double *p = a.qn + (size_t)u * kD + threadIdx.x;
+  if (tid_here() >= kD) return 0.0;
+  const double *p = a.qn + (size_t)u * kD + tid_here();
   for (int n = 0; (w & kNormValid) == 0 && n < a.norm_polls; ++n) {
     __builtin_amdgcn_s_sleep(2);
     w = pub_load_bits(p);
@@ -104,13 +104,13 @@ __device__ __forceinline__ double query_norm_of(const PruneFusedArgs &a, int64_t
   return (w & kNormValid) != 0 ? __longlong_as_double((long long)(w & ~kNormValid)) : __builtin_nan("");
 }
 __device__ __forceinline__ unsigned long long query_norm_word(const PruneFusedArgs &a, int64_t u) {
-  return threadIdx.x < kD ? pub_load_bits(a.qn + (size_t)u * kD + threadIdx.x) : 0ull;
+  return tid_here() < kD ? pub_load_bits(a.qn + (size_t)u * kD + tid_here()) : 0ull;
 }
 
 // One arrival on a tagged counter: true in every thread of the block that makes the count `full`.
 __device__ __forceinline__ bool arrive_tagged(unsigned long long *ctr, unsigned long long nonce, int full,
                                               int *s_flag) {
-  if (threadIdx.x == 0) {
+  if (tid_here() == 0) {
     unsigned long long old = atomicAdd(ctr, 1ull);
     if ((old >> 16) != nonce) {
       // earlier than the prologue's initialisation, whose store wipes what was just added
@@ -135,7 +135,7 @@ __device__ __forceinline__ bool arrive_tagged(unsigned long long *ctr, unsigned 
 // every thread if the whole list was there.
 __device__ __forceinline__ bool read_list_words(const PruneFusedArgs &a, int64_t u, int16_t *s_idx, int *s_flag,
                                                 int limit) {
-  const int tid = threadIdx.x;
+  const int tid = tid_here();
   if (tid < kWave) {
     const uint32_t *p = a.idx_pub + (size_t)u * kWave + tid;
     uint32_t w = __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -162,7 +162,7 @@ __device__ __forceinline__ bool read_list_words(const PruneFusedArgs &a, int64_t
 // sum is then valid in threads < 128.  s_part: 128 doubles of LDS.
 __device__ __forceinline__ bool read_group_sums(const PruneFusedArgs &a, int64_t u, double *s_part, int *s_flag,
                                                 int limit, double &kss) {
-  const int tid = threadIdx.x;
+  const int tid = tid_here();
   const double *gp = a.gpartial + (size_t)u * kMaxGroups * kD;
   const int n_grp = (a.NB + a.GS - 1) / a.GS;
   constexpr int HG = kMaxGroups / 2;
@@ -201,7 +201,7 @@ __device__ __forceinline__ bool read_group_sums(const PruneFusedArgs &a, int64_t
 template <int UN>
 __device__ __forceinline__ int solo_index_list(const PruneFusedArgs &a, int64_t u, int64_t item, double part,
                                                double *s_part, float *s_sc, int16_t *s_idx, int *s_flag) {
-  const int tid = threadIdx.x;
+  const int tid = tid_here();
   if (tid < kD) pub_store_f64(a.partial + (size_t)item * kD + tid, part);
   block_stores_done();
 
@@ -256,7 +256,7 @@ __device__ __forceinline__ int solo_index_list(const PruneFusedArgs &a, int64_t 
 // fetches it after all (true) and goes on as usual.
 __device__ __forceinline__ bool hand_over_rows(const PruneFusedArgs &a, int64_t u, int64_t item, double *s_part,
                                                float *s_sc, int16_t *s_idx, int *s_flag) {
-  const int tid = threadIdx.x;
+  const int tid = tid_here();
   if (tid == 0)
     __hip_atomic_store(a.undone + item, (unsigned char)1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   block_stores_done();
@@ -284,7 +284,7 @@ __device__ __forceinline__ bool hand_over_rows(const PruneFusedArgs &a, int64_t 
 // itself.  (Drawing the ticket after the finisher's own rows instead, behind a wait for the
 // acknowledgement of everything it had published, measured the same on every shape.)
 __device__ __forceinline__ int close_unit(const PruneFusedArgs &a, int64_t u, int *s_flag) {
-  if (threadIdx.x == 0) *s_flag = atomicAdd(a.gaveup + u * kCtrStep<int>, kFinisherDone);
+  if (tid_here() == 0) *s_flag = atomicAdd(a.gaveup + u * kCtrStep<int>, kFinisherDone);
   __syncthreads();
   const int n = *s_flag;
   __syncthreads();
@@ -324,13 +324,12 @@ void k_prune_solo(PruneFusedArgs a) {
   __shared__ float s_sc[kD];
   __shared__ int16_t s_idx[kD];
   __shared__ int s_flag;
-  const int tid = threadIdx.x, lane = tid % kWave;
+  const int tid = tid_here(), lane = tid % kWave;
   // A launch of this kernel is over in ten to a hundred microseconds and runs most of its code
   // once, so what it executes is kept SHORT: instructions come from memory at about 45 ns per
   // 64 bytes.  The wave index is uniform (row counts and their branches are scalar), rows are
   // numbered in 32 bits (a unit held on chip has fewer than 2^19), every load takes the same
-  // form -- a byte offset, clamped to the unit's last chunk, on the unit's base -- and only a
-  // ragged tile pays for its raggedness.  8 units x 5003 rows: first load issued after 0.6
+  // form and only a ragged tile pays for its raggedness.  8 units x 5003 rows: first load issued after 0.6
   // instead of 1.8 us.
   const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
   // What the block needs in front of its first loads, asked for at once: an argument loaded where it is
@@ -363,8 +362,15 @@ void k_prune_solo(PruneFusedArgs a) {
   }
 
   // ---- load: every chunk of the block's rows is in flight at once ----------------------------
+  // A block of 128 KB is one of many, and registers are short: its tiles go through buffer resources (request_tile).  Short
+  // calls of smaller blocks want their first load out early: one clamped byte offset per load, and ragged tiles are masked below
+  // (8 fp32 units x 2048 rows 9.23 us, with resources 9.42; 24 x 7629 19.4 / 19.8; 8 x 131072 83.6 / 81.7).
+  constexpr bool kRanged = NTW * E::EB == 8;
   u32x4 r[NTW][NLD];
-  {
+  if constexpr (kRanged) {
+#pragma unroll
+    for (int n = 0; n < NTW; ++n) request_tile<DT>(r[n], src, tile_row0(n), tile_rows(n, s1), lane);
+  } else {
     const uint32_t last = (uint32_t)S * CPR - 1;
 #pragma unroll
     for (int n = 0; n < NTW; ++n)
@@ -385,11 +391,13 @@ void k_prune_solo(PruneFusedArgs a) {
 #pragma unroll
   for (int nn = 0; nn < NTW; ++nn) {
     const int n = (nn + NRT) % NTW;          // LDS-bound tiles first: their registers free up early
-    const int nr = tile_rows(n, s1);
-    if (__builtin_expect(nr < TR, 0)) {      // rows past the block's end count nothing
+    if constexpr (!kRanged) {
+      const int nr = tile_rows(n, s1);
+      if (__builtin_expect(nr < TR, 0)) {    // rows past the block's end count nothing
 #pragma unroll
-      for (int j = 0; j < NLD; ++j)
-        if (j * kWave + lane >= nr * CPR) r[n][j] = u32x4{0u, 0u, 0u, 0u};
+        for (int j = 0; j < NLD; ++j)
+          if (j * kWave + lane >= nr * CPR) r[n][j] = u32x4{0u, 0u, 0u, 0u};
+      }
     }
     float facc[VEC];
 #pragma unroll
@@ -424,11 +432,18 @@ void k_prune_solo(PruneFusedArgs a) {
   const FlatOut<DT> dst((char *)a.kp + (size_t)u * a.kp_unit_rows * a.ld * E::EB);
   compact_build_tab<DT>(tab, s_idx, a.T, a.ld, dst.sh);
   __syncthreads();
+  // (one or two tiles per wave: keeping the gathers' offsets costs more than it saves, 128 units x 430 rows 12.1 -> 12.3 us)
+  [[maybe_unused]] Emit<DT> emit;
+  if constexpr (kRanged) emit.init(tab, dst.sh, a.ld, lane);
+  auto emit_tile = [&](const u32x4 *t, int r0, int nr) {
+    if constexpr (kRanged) emit.tile(t, dst, r0, nr, a.ld, tab, lane);
+    else compact_emit_tile<DT>(t, dst, r0, nr, a.ld, tab, lane);
+  };
   const int s1c = min(s1, (int)a.S_keep);
 #pragma unroll
   for (int n = NRT; n < NTW; ++n) {
     const int nr = tile_rows(n, s1c);
-    if (nr > 0) compact_emit_tile<DT>(wtile + (size_t)(n - NRT) * Tile<DT>::CHUNKS, dst, tile_row0(n), nr, a.ld, tab, lane);
+    if (nr > 0) emit_tile(wtile + (size_t)(n - NRT) * Tile<DT>::CHUNKS, tile_row0(n), nr);
   }
 #pragma unroll
   for (int n = 0; n < NRT; ++n) {
@@ -441,7 +456,7 @@ void k_prune_solo(PruneFusedArgs a) {
       __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
       __builtin_amdgcn_wave_barrier();
       __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-      compact_emit_tile<DT>(wtile, dst, tile_row0(n), nr, a.ld, tab, lane);
+      emit_tile(wtile, tile_row0(n), nr);
     }
   }
   if (n_gaveup > 0) {   // block-uniform
