@@ -566,13 +566,16 @@ __device__ __forceinline__ void tile_clear_padding(u32x4 *tile, int lane) {
 // A tile's rows r0 .. r0 + nr (nr <= 32, <= 0: none) of the unit at `base` into registers, chunk j * 64 + lane in r[j]: through a
 // buffer resource that ends with them, so that what lies past the end comes as zeros (which add nothing to a column
 // sum) and moves nothing, without a clamp, a mask or a branch around a load.
-template <int DT, int NLD>
-__device__ __forceinline__ void request_tile(u32x4 (&r)[NLD], const char *base, int r0, int nr, int lane) {
+// FLIGHT > 0: no more than that many of the wave's loads are in flight; `before`: how many it has issued.
+template <int DT, int FLIGHT, int NLD>
+__device__ __forceinline__ void request_tile(u32x4 (&r)[NLD], const char *base, int r0, int nr, int lane, int before) {
   constexpr int kRow = kD * Elem<DT>::EB, kNonTemporal = 2;
   const auto rsrc = __builtin_amdgcn_make_buffer_rsrc((void *)(base + (size_t)(uint32_t)r0 * kRow), (short)0, max(nr, 0) * kRow, 0x00027000);
 #pragma unroll
-  for (int j = 0; j < NLD; ++j)
+  for (int j = 0; j < NLD; ++j) {
+    if (FLIGHT > 0 && before + j >= FLIGHT && j % 2 == 0) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(FLIGHT - 2) : "memory");
     r[j] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rsrc, (j * kWave + lane) * 16, 0, kNonTemporal));
+  }
 }
 
 template <int DT>

@@ -51,6 +51,7 @@ struct PruneFusedArgs {
   int32_t prologue_delay;      // test hook: 64-cycle ticks the prologue block sleeps before it starts
   int32_t norm_delay;          // ... and between the arrival counters and the query norms
   int32_t norm_polls;          // looks for a query norm before a block goes on without
+  int32_t round_blocks;        // blocks that are resident at once
   int64_t U;                   // units of the call: blocks 0 .. U-1 are the prologue blocks, the row blocks follow
   int64_t S, RB;          // rows per unit, rows per block
   int64_t S_keep;         // rows [0, S_keep) of every unit are compacted

@@ -48,11 +48,12 @@ enum ListState { kGaveUp = 0, kHaveList = 1, kFinisher = 2 };
 constexpr int kFinisherDone = 1 << 24;   // the finisher's closing ticket on the give-up counter
 constexpr unsigned long long kNormValid = 1ull << 63;   // mark of a published query norm
 constexpr int kSurePolls = 1 << 20;      // polls for what is in place or a running block is about to publish
+constexpr int kAheadKB = 24;              // of the next round's rows that a waiting block fetches into the L2
 constexpr int kInitPolls = 1 << 22;      // polls for the prologue's initialisation (a block that was dispatched earlier)
 
 // ---- the prologue block --------------------------------------------------------------------
 // lds: at least 5 * 128 doubles.
-template <int DT>
+template <int DT, bool GRP>
 __device__ __forceinline__ void solo_prologue(const PruneFusedArgs &a, int64_t u, double *lds) {
   const int tid = tid_here();
   double *hn = lds, *qn_l = lds + 4 * kD;
@@ -67,11 +68,11 @@ __device__ __forceinline__ void solo_prologue(const PruneFusedArgs &a, int64_t u
     __hip_atomic_store(a.arrived + u * kCtrStep<int>, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
   if (tid < kD) pub_store_f64(a.qn + (size_t)u * kD + tid, 0.0);
-  if (a.GS > 0)
+  if constexpr (GRP)
     for (int i = tid; i < kMaxGroups * kD; i += 256) pub_store_f64(a.gpartial + (size_t)u * kMaxGroups * kD + i, 0.0);
   block_stores_done();
   // everything above has landed: the counters may now be found initialised
-  if (a.GS > 0) {
+  if constexpr (GRP) {
     const int n_grp = (a.NB + a.GS - 1) / a.GS;
     if (tid < n_grp)
       __hip_atomic_store(a.tctr_g + ((size_t)u * kMaxGroups + tid) * kCtrStep<unsigned long long>, a.nonce << 16,
@@ -157,56 +158,62 @@ __device__ __forceinline__ bool read_list_words(const PruneFusedArgs &a, int64_t
 }
 
 // Two-level form: the unit's column sums from its (at most 16) group vectors, added in group
-// order, polling at most `limit` times.  Thread (c, half) polls channel c of groups 8 half ..
-// 8 half + 7, all loads in flight at once.  True in every thread if all vectors were there; the
-// sum is then valid in threads < 128.  s_part: 128 doubles of LDS.
-__device__ __forceinline__ bool read_group_sums(const PruneFusedArgs &a, int64_t u, double *s_part, int *s_flag,
-                                                int limit, double &kss) {
+// order (the first eight, the others, the two sums), polling at most `limit` times.  Two waves poll, thread c channel c of all groups,
+// through a buffer resource that ends with the last group's vector, all loads in flight at once: a wave's loads return in order, and the
+// other two may have rows ahead in flight (rows_ahead; with four waves polling behind them 96 units x 54784 rows took 417 us instead
+// of 392).  True in every thread if all vectors were there; the sum is then valid in threads < 128.
+__device__ __forceinline__ bool read_group_sums(const PruneFusedArgs &a, int64_t u, int *s_flag, int limit, double &kss) {
   const int tid = tid_here();
-  const double *gp = a.gpartial + (size_t)u * kMaxGroups * kD;
   const int n_grp = (a.NB + a.GS - 1) / a.GS;
-  constexpr int HG = kMaxGroups / 2;
-  const int c = tid & (kD - 1), j0 = (tid >> 7) * HG;
-  unsigned long long w[HG];
-#pragma unroll
-  for (int j = 0; j < HG; ++j) w[j] = pub_load_bits(gp + (size_t)min(j0 + j, n_grp - 1) * kD + c);
-  bool ok;
-  for (int n = 0;; ++n) {
-    bool miss = false;
-#pragma unroll
-    for (int j = 0; j < HG; ++j) miss |= (w[j] & 1ull) == 0;
-    if (!__any(miss) || n >= limit) { ok = !miss; break; }
-    for (int t = a.poll_ticks; t > 0; t -= 4) __builtin_amdgcn_s_sleep(4);
-#pragma unroll
-    for (int j = 0; j < HG; ++j)
-      if ((w[j] & 1ull) == 0) w[j] = pub_load_bits(gp + (size_t)min(j0 + j, n_grp - 1) * kD + c);
-  }
   kss = 0.0;
-#pragma unroll
-  for (int j = 0; j < HG; ++j) kss += j0 + j < n_grp ? __longlong_as_double((long long)(w[j] & ~1ull)) : 0.0;
   if (tid == 0) *s_flag = 1;
   __syncthreads();
-  if (!ok) *s_flag = 0;      // any thread that ran out of polls
-  if (tid >= kD) s_part[c] = kss;
+  if (tid < kD) {
+    constexpr int kRow = kD * (int)sizeof(double), kDeviceScope = 16;   // sc1, as pub_load_bits
+    const auto rsrc = __builtin_amdgcn_make_buffer_rsrc((void *)(a.gpartial + (size_t)u * kMaxGroups * kD), (short)0, n_grp * kRow, 0x00027000);
+    auto look = [&](int j) {
+      return __builtin_bit_cast(unsigned long long, __builtin_amdgcn_raw_buffer_load_b64(rsrc, tid * (int)sizeof(double) + j * kRow, 0, kDeviceScope));
+    };
+    // all groups in flight at once; a wave looks again at all of them while one is missing (registers are short: three tiles are
+    // held beside these words)
+    unsigned long long w[kMaxGroups];
+    bool ok;
+    for (int n = 0;; ++n) {
+#pragma unroll
+      for (int j = 0; j < kMaxGroups; ++j) w[j] = look(j);
+      int there = 0;   // (what lies past the last group comes as 0)
+#pragma unroll
+      for (int j = 0; j < kMaxGroups; ++j) there += (int)((uint32_t)w[j] & 1u);
+      ok = there == n_grp;
+      if (__all(ok) || n >= limit) break;
+      for (int t = a.poll_ticks; t > 0; t -= 4) __builtin_amdgcn_s_sleep(4);
+      asm volatile("" ::: "memory");   // look again
+    }
+    double half[2] = {0.0, 0.0};
+#pragma unroll
+    for (int j = 0; j < kMaxGroups; ++j) half[j / (kMaxGroups / 2)] += __longlong_as_double((long long)(w[j] & ~1ull));
+    kss = half[0] + half[1];
+    if (!ok) *s_flag = 0;      // any thread that ran out of polls
+  }
   __syncthreads();
   const bool all_ok = *s_flag != 0;
-  if (tid < kD) kss += s_part[c];
-  __syncthreads();           // flag and s_part may be reused
+  __syncthreads();           // the flag may be reused
   return all_ok;
 }
 
 // A row block's way from its column sums (`part`: of channel tid, threads < 128) to the unit's index
 // list (s_idx).  item: u * NB + the block's number among the unit's row blocks.
-// UN: partial sums of other blocks in flight per thread while they are merged.
-template <int UN>
-__device__ __forceinline__ int solo_index_list(const PruneFusedArgs &a, int64_t u, int64_t item, double part,
-                                               double *s_part, float *s_sc, int16_t *s_idx, int *s_flag) {
+// UN: partial sums of other blocks in flight per thread while they are merged.  ahead(w): called by blocks that have arrived and now wait, to
+// put idle time to use with waves w .. 3.
+template <int UN, bool GRP, class Ahead>
+__device__ __forceinline__ int solo_index_list(const PruneFusedArgs &a, int64_t u, int64_t item, double part, double *s_part,
+                                               float *s_sc, int16_t *s_idx, int *s_flag, Ahead &&ahead) {
   const int tid = tid_here();
   if (tid < kD) pub_store_f64(a.partial + (size_t)item * kD + tid, part);
   block_stores_done();
 
   const double *src = a.partial + (size_t)u * a.NB * kD;
-  if (a.GS > 0) {
+  if constexpr (GRP) {
     // Two levels: the last block of a group of a.GS consecutive blocks merges the group's sums
     // into one vector and publishes it; EVERY block of the unit then reads the (at most 16)
     // group vectors, adds them in group order and makes the index list for itself -- the same
@@ -227,9 +234,11 @@ __device__ __forceinline__ int solo_index_list(const PruneFusedArgs &a, int64_t 
       if (tid < kD) pub_store_marked(gp + (size_t)g * kD + tid, gs);
       block_stores_done();
       finisher = arrive(a.arrived + u * kCtrStep<int>, n_grp, s_flag);
+    } else {
+      ahead(2);
     }
     double kss;
-    if (!read_group_sums(a, u, s_part, s_flag, finisher ? kSurePolls : a.spin_limit, kss)) return kGaveUp;
+    if (!read_group_sums(a, u, s_flag, finisher ? kSurePolls : a.spin_limit, kss)) return kGaveUp;
     score_and_select(a, u, query_norm_of(a, u, qn_w), kss, s_sc, s_idx, finisher);
     return finisher ? kFinisher : kHaveList;
   }
@@ -246,7 +255,8 @@ __device__ __forceinline__ int solo_index_list(const PruneFusedArgs &a, int64_t 
     }
     return kFinisher;
   }
-  // ---- wait (bounded) for the unit's index list
+  // ---- wait (bounded) for the unit's index list; wave 0 polls
+  ahead(1);
   return read_list_words(a, u, s_idx, s_flag, a.spin_limit) ? kHaveList : kGaveUp;
 }
 
@@ -254,6 +264,7 @@ __device__ __forceinline__ int solo_index_list(const PruneFusedArgs &a, int64_t 
 // sure the flag has landed, and draws a ticket.  A ticket drawn after the finisher's closing one
 // means that the finisher will not look again -- and that the list is in place: the block then
 // fetches it after all (true) and goes on as usual.
+template <bool GRP>
 __device__ __forceinline__ bool hand_over_rows(const PruneFusedArgs &a, int64_t u, int64_t item, double *s_part,
                                                float *s_sc, int16_t *s_idx, int *s_flag) {
   const int tid = tid_here();
@@ -265,10 +276,10 @@ __device__ __forceinline__ bool hand_over_rows(const PruneFusedArgs &a, int64_t 
   const bool late = *s_flag != 0;
   __syncthreads();
   if (!late) return false;
-  if (a.GS > 0) {
+  if constexpr (GRP) {
     const unsigned long long qn_w = query_norm_word(a, u);
     double kss;
-    read_group_sums(a, u, s_part, s_flag, kSurePolls, kss);
+    read_group_sums(a, u, s_flag, kSurePolls, kss);
     score_and_select(a, u, query_norm_of(a, u, qn_w), kss, s_sc, s_idx, false);
   } else {
     read_list_words(a, u, s_idx, s_flag, kSurePolls);
@@ -309,7 +320,9 @@ __device__ __forceinline__ void serve_gaveup(const PruneFusedArgs &a, int64_t u,
 // The row blocks keep their rows (NTW tiles of 32 rows per wave, RB = 128 * NTW rows) on chip
 // from the column sums until the index list arrives: the first NTW - NLT tiles of a wave in
 // registers, the last NLT in the wave's LDS tiles -- exactly as k_prune_onepass does.
-template <int DT, int NTW, int NLT>
+// GRP: units of more than 64 blocks, whose sums travel in two levels (kernels of their own: the registers of one form are not
+// those of the other, and a short launch fetches less code).  LONG: more blocks than are resident at once.
+template <int DT, int NTW, int NLT, bool GRP, bool LONG>
 __global__ __launch_bounds__(256, Elem<DT>::EB == 4 ? 2 : (NTW - NLT) * 16 * Elem<DT>::EB <= 32 ? 4 : 3)
 void k_prune_solo(PruneFusedArgs a) {
   using E = Elem<DT>;
@@ -338,7 +351,7 @@ void k_prune_solo(PruneFusedArgs a) {
   // turn; two runs of one side differ by up to 1.6 %); calls above 20 us do not change.
   asm volatile("" ::"s"(a.k), "s"(a.S), "s"(a.NB), "s"(a.U), "s"(a.stagger_blocks), "s"(a.stagger_units), "s"(a.stagger_ticks));
   if (blockIdx.x < (uint32_t)a.U) {
-    solo_prologue<DT>(a, blockIdx.x, (double *)tiles);   // the tiles are free in a block without rows
+    solo_prologue<DT, GRP>(a, blockIdx.x, (double *)tiles);   // the tiles are free in a block without rows
     return;
   }
   const uint32_t item = blockIdx.x - (uint32_t)a.U;
@@ -362,14 +375,15 @@ void k_prune_solo(PruneFusedArgs a) {
   }
 
   // ---- load: every chunk of the block's rows is in flight at once ----------------------------
-  // A block of 128 KB is one of many, and registers are short: its tiles go through buffer resources (request_tile).  Short
-  // calls of smaller blocks want their first load out early: one clamped byte offset per load, and ragged tiles are masked below
-  // (8 fp32 units x 2048 rows 9.23 us, with resources 9.42; 24 x 7629 19.4 / 19.8; 8 x 131072 83.6 / 81.7).
-  constexpr bool kRanged = NTW * E::EB == 8;
+  // Blocks of a long launch load their tiles through buffer resources (request_tile), at most 8 KB of a wave in flight: all four tiles at
+  // once only fill the queues that the blocks' exchange of sums has to pass as well (64 units x 26736 rows 150.6 -> 148.1 us,
+  // 8 x 131072 83.6 -> 81.7; 16 KB no gain, 4 KB a loss).  A launch of one round wants all of it as early as it can: one
+  // clamped byte offset per load, and ragged tiles are masked below (32 x 10000 rows 20.2 us, as above 20.7; 24 x 7629 19.4 / 20.0).
+  constexpr bool kKeepOffsets = NTW * E::EB == 8;   // blocks of 128 KB
   u32x4 r[NTW][NLD];
-  if constexpr (kRanged) {
+  if constexpr (LONG) {
 #pragma unroll
-    for (int n = 0; n < NTW; ++n) request_tile<DT>(r[n], src, tile_row0(n), tile_rows(n, s1), lane);
+    for (int n = 0; n < NTW; ++n) request_tile<DT, 8>(r[n], src, tile_row0(n), tile_rows(n, s1), lane, n * NLD);
   } else {
     const uint32_t last = (uint32_t)S * CPR - 1;
 #pragma unroll
@@ -391,7 +405,7 @@ void k_prune_solo(PruneFusedArgs a) {
 #pragma unroll
   for (int nn = 0; nn < NTW; ++nn) {
     const int n = (nn + NRT) % NTW;          // LDS-bound tiles first: their registers free up early
-    if constexpr (!kRanged) {
+    if constexpr (!LONG) {
       const int nr = tile_rows(n, s1);
       if (__builtin_expect(nr < TR, 0)) {    // rows past the block's end count nothing
 #pragma unroll
@@ -421,9 +435,32 @@ void k_prune_solo(PruneFusedArgs a) {
   __syncthreads();
   const double part = tid < kD ? ((red[0][tid] + red[1][tid]) + red[2][tid]) + red[3][tid] : 0.0;
 
-  int st = solo_index_list<kHeld == 0 ? 24 : kHeld <= 32 ? 16 : 8>(a, u, item, part, s_part, s_sc, s_idx, &s_flag);
+  // What a block does between its arrival and the list is wait, 5 to 10 us, and the blocks of a round wait at about the same
+  // time, while the memory idles.  In that time it fetches the first rows of the block that will take its place, one round of
+  // resident blocks further on, without a hint against caching: workgroup i runs on XCD i % 8, a round is a multiple of 8, so the rows
+  // are in that XCD's L2 when they are wanted.  24 KB: 96 blocks an XCD x 24 KB of 4 MB L2 (16: half of the gain, 48: less than 32, 96: a loss).  What
+  // arrives is dropped into 1 KB of LDS that nobody reads.  Whole calls, without / with: 64 units x 26736 rows, T = 97, 147 -> 137 us, 80 x
+  // 29502, T = 34, 146 -> 139, 56 x 15051 76.7 -> 73.5, 64 x 36965 171 -> 165, 8 x 131072 80.4 -> 77.
+  [[maybe_unused]] auto rows_ahead = [&](int w0) {
+    if constexpr (LONG) {
+      __shared__ __attribute__((aligned(16))) u32x4 s_drop[kWave];
+      const uint32_t next = item + (uint32_t)a.round_blocks;
+      if (wave < w0 || next >= (uint32_t)a.U * (uint32_t)a.NB) return;
+      const uint32_t un = next / (uint32_t)a.NB;
+      const int per = kAheadKB / (4 - w0);
+      const uint32_t last = (uint32_t)S * CPR - 1, c0 = (next - un * (uint32_t)a.NB) * (128 * NTW * CPR) + (uint32_t)((wave - w0) * per * kWave + lane);
+      const char *srcn = (const char *)a.k + (size_t)un * S * (kD * E::EB);
+#pragma unroll 4
+      for (int i = 0; i < per; ++i)
+        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(srcn + min(c0 + (uint32_t)(i * kWave), last) * 16u),
+                                         (__attribute__((address_space(3))) void *)s_drop, 16, 0, 0);
+    }
+  };
+  int st = solo_index_list<kHeld == 0 ? 24 : kHeld <= 32 ? 16 : 8, GRP>(a, u, item, part, s_part, s_sc, s_idx, &s_flag, rows_ahead);
+  // (the rows ahead have landed before anything else happens to this block's LDS, whose end they must not outlive)
+  if constexpr (LONG) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   if (st == kGaveUp) {
-    if (!hand_over_rows(a, u, item, s_part, s_sc, s_idx, &s_flag)) return;
+    if (!hand_over_rows<GRP>(a, u, item, s_part, s_sc, s_idx, &s_flag)) return;
     st = kHaveList;
   }
   const int n_gaveup = st == kFinisher ? close_unit(a, u, &s_flag) : 0;
@@ -434,9 +471,9 @@ void k_prune_solo(PruneFusedArgs a) {
   __syncthreads();
   // (one or two tiles per wave: keeping the gathers' offsets costs more than it saves, 128 units x 430 rows 12.1 -> 12.3 us)
   [[maybe_unused]] Emit<DT> emit;
-  if constexpr (kRanged) emit.init(tab, dst.sh, a.ld, lane);
+  if constexpr (kKeepOffsets) emit.init(tab, dst.sh, a.ld, lane);
   auto emit_tile = [&](const u32x4 *t, int r0, int nr) {
-    if constexpr (kRanged) emit.tile(t, dst, r0, nr, a.ld, tab, lane);
+    if constexpr (kKeepOffsets) emit.tile(t, dst, r0, nr, a.ld, tab, lane);
     else compact_emit_tile<DT>(t, dst, r0, nr, a.ld, tab, lane);
   };
   const int s1c = min(s1, (int)a.S_keep);
@@ -518,6 +555,7 @@ hipError_t launch_prune_solo(int dtype, const void *q_obs, const void *k, float 
   a.idx_pub = (uint32_t *)w;         w += (size_t)U * kWave * sizeof(uint32_t);
   a.undone = (unsigned char *)w;
   a.nonce = next_nonce48();
+  a.round_blocks = kCUs * (dtype == THK_BF16 ? 3 : 2);
   // at most 500 us, in 64-cycle ticks at about 2.4 GHz
   a.prologue_delay = (int32_t)(std::min(std::max(env_switches().prologue_delay_us, 0L), 500L) * 2400 / 64);
   a.norm_delay = (int32_t)(std::min(std::max(env_switches().norm_delay_us, 0L), 500L) * 2400 / 64);
@@ -549,23 +587,30 @@ hipError_t launch_prune_solo(int dtype, const void *q_obs, const void *k, float 
       a.stagger_ticks = std::max((int32_t)(ns * 2.4 / 64.0), 1);   // 2.4 GHz, s_sleep counts 64-cycle ticks
     }
   }
+  const bool grp = a.GS > 0, lng = U * NB > a.round_blocks;
   const void *fn = nullptr;
+  auto pick = [&](const void *short1, const void *short2, const void *long1, const void *long2) {
+    fn = lng ? (grp ? long2 : long1) : (grp ? short2 : short1);
+  };
+#define THK_SOLO(DT, NTW, GRP, LONG) (const void *)k_prune_solo<DT, NTW, 1, GRP, LONG>
+  // (blocks of fewer rows than are held are taken for calls of one round only)
   if (dtype == THK_BF16) {
     switch (hold) {
-      case 1: fn = (const void *)k_prune_solo<THK_BF16, 1, 1>; break;
-      case 2: fn = (const void *)k_prune_solo<THK_BF16, 2, 1>; break;
-      case 4: fn = (const void *)k_prune_solo<THK_BF16, 4, 1>; break;
+      case 1: pick(THK_SOLO(THK_BF16, 1, false, false), THK_SOLO(THK_BF16, 1, true, false), THK_SOLO(THK_BF16, 1, false, false), THK_SOLO(THK_BF16, 1, true, false)); break;
+      case 2: pick(THK_SOLO(THK_BF16, 2, false, false), THK_SOLO(THK_BF16, 2, true, false), THK_SOLO(THK_BF16, 2, false, false), THK_SOLO(THK_BF16, 2, true, false)); break;
+      case 4: pick(THK_SOLO(THK_BF16, 4, false, false), THK_SOLO(THK_BF16, 4, true, false), THK_SOLO(THK_BF16, 4, false, true), THK_SOLO(THK_BF16, 4, true, true)); break;
     }
   } else {
     switch (hold) {
-      case 1: fn = (const void *)k_prune_solo<THK_F32, 1, 1>; break;
-      case 2: fn = (const void *)k_prune_solo<THK_F32, 2, 1>; break;
+      case 1: pick(THK_SOLO(THK_F32, 1, false, false), THK_SOLO(THK_F32, 1, true, false), THK_SOLO(THK_F32, 1, false, false), THK_SOLO(THK_F32, 1, true, false)); break;
+      case 2: pick(THK_SOLO(THK_F32, 2, false, false), THK_SOLO(THK_F32, 2, true, false), THK_SOLO(THK_F32, 2, false, true), THK_SOLO(THK_F32, 2, true, true)); break;
     }
   }
+#undef THK_SOLO
   if (fn == nullptr || RB != 128 * hold || U * ((int64_t)NB + 1) > 2147483647LL) return hipErrorInvalidValue;
   const size_t lds = 2048 + 4 * compact_tile_bytes(eb);
-  static DynLds set[2][5];
-  hipError_t e = ensure_dyn_lds(fn, lds, set[dtype == THK_BF16 ? 1 : 0][hold]);
+  static DynLds set[2][5][2][2];
+  hipError_t e = ensure_dyn_lds(fn, lds, set[dtype == THK_BF16 ? 1 : 0][hold][grp][lng]);
   if (e != hipSuccess) return e;
   void *kargs[] = {(void *)&a};
   e = launch_main_kernel(fn, dim3((unsigned)(U * (NB + 1))), dim3(256), kargs, lds, st);
