@@ -4,7 +4,6 @@
 
 namespace thk {
 
-constexpr int kMaxSplitDev = 4096;   // largest n_split the API accepts
 static_assert(kFuseMaxSplit == kDecodeFuseMaxSplit, "the host and the kernels must agree on the fused merge's reach");
 
 hipError_t decode_launch_bf16_g1(const DecodeArgs &, int, hipStream_t);
@@ -23,73 +22,77 @@ hipError_t decode_kv_launch_f32_g4(const DecodeArgs &, int, hipStream_t);
 hipError_t decode_mq_launch(const DecodeArgs &, hipStream_t);
 
 // Merge of the per-split states: m = max m_i, l = sum l_i 2^(m_i - m),
-// acc = sum acc_i 2^(m_i - m), out = acc / l.  One block of 128 * PG threads per query head:
-// thread (c, g) owns channel c and the g-th contiguous share of the splits.  The (m_i, l_i)
-// pairs are read once per block, turned into weights kept in LDS, and the acc_i[c] loads of
-// eight splits are in flight together; the PG shares are then added in share order, so the
-// result does not depend on timing.  PG = 4 when there are many splits (few heads, long S).
-template <int DT, int PG>
-__global__ __launch_bounds__(128 * PG) void k_decode_merge(const float *__restrict__ ws,
-                                                           void *__restrict__ out, int n_split) {
+// acc = sum acc_i 2^(m_i - m), out = acc / l.  One block of NW wavefronts per query head: wave w takes the
+// pieces 16 w .. 16 w + 15 of every 16 NW, a lane two channels of them, lane i also piece i's maximum and sum,
+// whose weight reaches the other lanes through v_readlane.  Latency bounds it: the maxima, the sums and the
+// accumulators of a wave's 16 pieces are one trip to memory, absent pieces read 0 past the end of the buffer
+// and weigh nothing, and the waves' states meet in LDS once, in wave order (the result does not depend on timing).
+// Before, a block asked for the maxima, then for eight accumulators at a time, and for those past a multiple of eight
+// one by one.  Whole calls, us, before / now: 4 units x 8 heads x 8000 rows (63 pieces) 11.6 / 9.5, fp32 8 x 9000 (29)
+// 15.6 / 13.4, 8 x 4 heads x 131072 (64) 64.2 / 63.3, 64 x 4 heads x 32768 (16) 123.4 / 122.0, 64 x 8 heads x 8191, pruned
+// values (8) 30.3 / 29.8.
+template <int DT, int NW>
+__global__ __launch_bounds__(64 * NW) void k_decode_merge(const float *__restrict__ ws,
+                                                          void *__restrict__ out, int n_split) {
   using E = Elem<DT>;
-  constexpr int NW = 2 * PG;   // wavefronts per block
-  __shared__ float wgt[kMaxSplitDev];
-  __shared__ float red[NW];
-  __shared__ float part_l[PG], part_a[PG][kD];
-  const int tid = threadIdx.x, c = tid & (kD - 1), g = tid >> 7;
-  const int lane = tid % kWave, wave = tid / kWave;
+  typedef float f32x2 __attribute__((ext_vector_type(2)));
+  constexpr int kRecB = (kD + 2) * 4, P = 16;
+  __shared__ f32x2 part_ml[NW], part_a[NW][kWave];
+  const int lane = threadIdx.x % kWave, wave = uniform(threadIdx.x / kWave);
   const size_t bn = blockIdx.x;
-  const float *rec0 = ws + bn * n_split * (kD + 2);
-  float mloc = -INFINITY;
-  for (int i = tid; i < n_split; i += 128 * PG) mloc = fmaxf(mloc, rec0[(size_t)i * (kD + 2)]);
-  mloc = wave_max(mloc);
-  if (lane == 0) red[wave] = mloc;
-  __syncthreads();
-  float M = red[0];
+  const auto rsrc = __builtin_amdgcn_make_buffer_rsrc((void *)uniform_ptr((const char *)(ws + bn * n_split * (kD + 2))),
+                                                      (short)0, n_split * kRecB, kBufferWord3);
+  auto load2 = [&](int off) { return __builtin_bit_cast(f32x2, __builtin_amdgcn_raw_buffer_load_b64(rsrc, off, 0, 0)); };
+  auto weight = [](float m, float M) { return m == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m - M); };
+  float M = -INFINITY, L = 0.f, A0 = 0.f, A1 = 0.f;
+  for (int i0 = wave * P; i0 < n_split; i0 += NW * P) {
+    const f32x2 ml = load2((i0 + min(lane, P)) * kRecB);   // lanes from P on hold a piece that is not this wave's
+    f32x2 av[P];
 #pragma unroll
-  for (int w = 1; w < NW; ++w) M = fmaxf(M, red[w]);
-  for (int i = tid; i < n_split; i += 128 * PG) {
-    const float mi = rec0[(size_t)i * (kD + 2)];
-    wgt[i] = mi == -INFINITY ? 0.f : exp2f(mi - M);
-  }
-  __syncthreads();
-  const int per = (n_split + PG - 1) / PG;
-  const int i0 = g * per, i1 = min(n_split, i0 + per);
-  float Lsum = 0.f, A = 0.f;
-  int i = i0;
-  for (; i + 8 <= i1; i += 8) {
-    float lv[8], av[8];
+    for (int i = 0; i < P; ++i) av[i] = load2((i0 + i) * kRecB + 8 + lane * 8);
+    const float m = lane < P && i0 + lane < n_split ? ml[0] : -INFINITY;
+    const float M_new = fmaxf(M, wave_max(m));
+    const float wgt = weight(m, M_new), keep = weight(M, M_new);
+    M = M_new;
+    L = fmaf(L, keep, wave_sum(lane < P ? ml[1] * wgt : 0.f));
+    A0 *= keep;
+    A1 *= keep;
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      const float *rec = rec0 + (size_t)(i + j) * (kD + 2);
-      lv[j] = rec[1];
-      av[j] = rec[2 + c];
-    }
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      Lsum = fmaf(lv[j], wgt[i + j], Lsum);
-      A = fmaf(av[j], wgt[i + j], A);
+    for (int i = 0; i < P; ++i) {
+      const float wi = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(wgt), i));
+      A0 = fmaf(av[i][0], wi, A0);
+      A1 = fmaf(av[i][1], wi, A1);
     }
   }
-  for (; i < i1; ++i) {
-    const float *rec = rec0 + (size_t)i * (kD + 2);
-    Lsum = fmaf(rec[1], wgt[i], Lsum);
-    A = fmaf(rec[2 + c], wgt[i], A);
-  }
-  if constexpr (PG > 1) {
-    part_a[g][c] = A;
-    if (c == 0) part_l[g] = Lsum;
+  if constexpr (NW > 1) {
+    part_a[wave][lane] = f32x2{A0, A1};
+    if (lane == 0) part_ml[wave] = f32x2{M, L};
     __syncthreads();
-    if (g != 0) return;
-    A = part_a[0][c];
-    Lsum = part_l[0];
+    if (wave != 0) return;
+    f32x2 ml[NW], av[NW];
 #pragma unroll
-    for (int k = 1; k < PG; ++k) {
-      A += part_a[k][c];
-      Lsum += part_l[k];
+    for (int w = 0; w < NW; ++w) { ml[w] = part_ml[w]; av[w] = part_a[w][lane]; }
+#pragma unroll
+    for (int w = 0; w < NW; ++w) M = fmaxf(M, ml[w][0]);
+    L = A0 = A1 = 0.f;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+      const float wi = weight(ml[w][0], M);
+      L = fmaf(ml[w][1], wi, L);
+      A0 = fmaf(av[w][0], wi, A0);
+      A1 = fmaf(av[w][1], wi, A1);
     }
   }
-  E::store1(out, bn * kD + c, A / Lsum);
+  E::store2(out, bn * kD + 2 * lane, A0 / L, A1 / L);
+}
+
+template <int DT>
+static void launch_decode_merge(const DecodeArgs &a, hipStream_t st) {
+  const dim3 heads((unsigned)(a.units / a.N_kv * a.N_q));
+  // one trip up to 128 pieces; fewer waves have less to say to each other
+  if (a.n_split <= 16) hipLaunchKernelGGL((k_decode_merge<DT, 1>), heads, dim3(64), 0, st, a.ws, a.out, a.n_split);
+  else if (a.n_split <= 64) hipLaunchKernelGGL((k_decode_merge<DT, 4>), heads, dim3(256), 0, st, a.ws, a.out, a.n_split);
+  else hipLaunchKernelGGL((k_decode_merge<DT, 8>), heads, dim3(512), 0, st, a.ws, a.out, a.n_split);
 }
 
 hipError_t launch_decode(const DecodeArgs &a, hipStream_t st) {
@@ -116,15 +119,8 @@ hipError_t launch_decode(const DecodeArgs &a, hipStream_t st) {
                 : gt == 2 ? decode_launch_f32_g2(a, groups, st) : decode_launch_f32_g1(a, groups, st);
   if (e != hipSuccess) return e;
   if (a.n_split > 1 && a.arrive == nullptr) {
-    const int64_t heads = a.units / a.N_kv * a.N_q;
-    const bool wide = a.n_split >= 32;   // many splits: four thread groups share them
-    if (a.dtype == THK_BF16) {
-      if (wide) hipLaunchKernelGGL((k_decode_merge<THK_BF16, 4>), dim3((unsigned)heads), dim3(512), 0, st, a.ws, a.out, a.n_split);
-      else hipLaunchKernelGGL((k_decode_merge<THK_BF16, 1>), dim3((unsigned)heads), dim3(128), 0, st, a.ws, a.out, a.n_split);
-    } else {
-      if (wide) hipLaunchKernelGGL((k_decode_merge<THK_F32, 4>), dim3((unsigned)heads), dim3(512), 0, st, a.ws, a.out, a.n_split);
-      else hipLaunchKernelGGL((k_decode_merge<THK_F32, 1>), dim3((unsigned)heads), dim3(128), 0, st, a.ws, a.out, a.n_split);
-    }
+    if (a.dtype == THK_BF16) launch_decode_merge<THK_BF16>(a, st);
+    else launch_decode_merge<THK_F32>(a, st);
     e = hipGetLastError();
   }
   return e;

@@ -52,3 +52,27 @@ def test_decode_tile_edges(dtype, G, T, T_v, tail, decode_merge):
             ref = O.decode_attn(as_numpy(q), h(kp, S), idx_np.reshape(B, N_kv, T), h(v, S), dtype, *tails)
         err = attn_rel_err(out, ref.reshape(-1, D)).max()
         assert err <= ATTN_TOL[dtype], f"S={S} n_split={n_split}: {err}"
+
+
+# the merge launch: a wave takes 16 pieces at a time, one, four or eight waves a head; 130 pieces are a second turn of
+# the first wave's, and 70 pieces of 64 rows leave most of 130 without rows
+@pytest.mark.parametrize("n_split", [2, 15, 16, 17, 33, 63, 64, 65, 128, 130, 300])
+@pytest.mark.parametrize("dtype,G,T", [("bf16", 4, 64), ("f32", 1, 51)])
+def test_decode_merge_launch_piece_counts(dtype, G, T, n_split, thk_env):
+    thk_env.setenv("THK_DECODE_MERGE", "kernel")
+    B, N_kv = 1, 2
+    for S in (64 * min(n_split, 140), 4450):
+        g = torch.Generator(device="cuda"); g.manual_seed(S + n_split)
+        rnd = lambda *shape: torch.randn(*shape, generator=g, device="cuda").to(TDT[dtype])
+        idx_np = _kept(np.random.default_rng(n_split), N_kv, T)
+        q, kp, v = 4 * rnd(B, N_kv * G, D), rnd(N_kv, S, T), rnd(N_kv, S, D)
+        shape = thk.make_shape(1, B, N_kv * G, N_kv, D, S, 1, T, 0, DT[dtype], n_split)
+        out = torch.empty(N_kv * G, D, dtype=q.dtype, device="cuda")
+        ws = ws_tensor(thk.thk_workspace_bytes(shape, thk.THK_OP_DECODE))
+        ws.fill_(255)   # NaN where a piece leaves no record, and behind the last one
+        thk.thk_decode_attn(shape, q, kp, torch.from_numpy(idx_np).cuda(), v, None, None, 0, 0, out, ws)
+        torch.cuda.synchronize()
+        h = lambda y: as_numpy(y).reshape(B, N_kv, S, y.shape[-1])
+        ref = O.decode_attn(as_numpy(q), h(kp), idx_np.reshape(B, N_kv, T), h(v), dtype)
+        err = attn_rel_err(out, ref.reshape(-1, D)).max()
+        assert err <= ATTN_TOL[dtype], f"S={S} n_split={n_split}: {err}"
