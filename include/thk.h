@@ -279,8 +279,7 @@ thk_status thk_prune(const thk_shape *shape, const void *q_obs, const void *k,
  * states go through ws and are merged in an order fixed by the shape and the launch form
  * (not by which block finishes first), so repeated calls give identical bits: by a second
  * kernel, or -- for calls of at most 16 pieces whose blocks serve one or two query heads,
- * four with at most 512 blocks (units x head groups x pieces), or eight with fewer than
- * 512 -- inside the one launch by the block that finishes last for a head group (the blocks signal
+ * or four with at most 512 blocks (units x head groups x pieces) -- inside the one launch by the block that finishes last for a head group (the blocks signal
  * through per-piece flag words in ws that carry a nonce drawn per call; no
  * read-modify-write, nothing in ws has to be cleared beforehand).
  * THK_DECODE_MERGE = kernel | fused in the environment overrides the choice.

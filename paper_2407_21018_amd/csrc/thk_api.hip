@@ -326,11 +326,14 @@ int decode_pieces(const thk_shape *s, int hpb, int64_t wgs, int64_t steps, int n
     return w;
   };
   const Width w_full = width(kD, resident), w_half = width(kD / 2, resident);
+  // (as it was when the constants were fitted; a call of eight heads per block that costs m_in here now has the merge kernel, which
+  // takes it less)
+  auto in_launch = [&](int64_t blocks) { return merges_in_launch(hpb, blocks) || (hpb == 8 && blocks < 2 * (int64_t)kCUs); };
   auto around = [&](int64_t n) {   // what the tiles do not pay for; grows with n
     const int64_t blocks = wgs * n;
     const double t = c.t0 + c.t_block * (double)ceil_div(blocks, kCUs);
     if (n == 1) return t;
-    return t + (n <= kDecodeFuseMaxSplit && merges_in_launch(hpb, blocks) ? c.m_in : c.m_out + 0.01 * (double)n + 0.0002 * (double)(heads * n));
+    return t + (n <= kDecodeFuseMaxSplit && in_launch(blocks) ? c.m_in : c.m_out + 0.01 * (double)n + 0.0002 * (double)(heads * n));
   };
   // (for rows of unknown value width)
   auto estimate = [&](int64_t i, const Width &wide_rows, const Width &narrow_rows) {
@@ -364,6 +367,23 @@ int decode_pieces(const thk_shape *s, int hpb, int64_t wgs, int64_t steps, int n
   // class has two, and with key rows of odd pitch, where a third one does not help)
   const Width c_full = hpb == 8 && odd ? width(kD, 2) : w_full, c_half = hpb == 8 ? width(kD / 2, 2) : w_half;
   return estimate(n_best, c_full, c_half) < 0.98 * 0.98 * estimate(n1, c_full, c_half) ? (int)n_best : n1;
+}
+
+// Calls so short that a block per 64 rows leaves no compute unit with two take such pieces (0: another call).  Two of
+// a block's waves have a tile of pruned rows each and the other two are free for the tail's, which a wave with rows of its own
+// takes 1 to 2 us after those.  us per call without a tail, with 38 rows, with the append in front, pieces of whole steps / these:
+// 8 units x 4 heads x 743 rows 7.5 8.3 10.2 / 7.4 7.4 9.0, 16 x 7 heads x 1020 9.0 10.3 12.2 / 8.1 8.2 10.1, fp32 8 x 2 heads x
+// 614 9.1 10.9 12.6 / 8.7 8.8 10.5, 8 x 2 heads x 1581 9.2 10.8 12.6 / 8.5 8.7 10.7.  With more blocks a call with a tail still
+// gains (32 x 5 heads x 683, 352 blocks 10.6 / 9.2) and one without loses (8 x 4 heads x 2910, 368 blocks 7.5 / 8.2).  Not bf16 blocks
+// of two heads above 16 pieces, whose merge is a second launch: where an append goes in front the host would
+// take longer to issue the three than the GPU to run them (8 units x 1191 rows 7.5 8.1 9.9 / 7.2 6.9 10.2), nor of one head, which
+// from 1025 rows on lose the same way (8 x 1338 6.7 7.2 8.9 / 7.1 6.7 10.2) and below that are mostly left whole.
+// Up to 512 rows the counts stay the powers of two that callers have planned with.
+int pieces_of_half_steps(const thk_shape *s, int hpb, int64_t wgs) {
+  const int64_t n = ceil_div(s->S, 64), heads = (int64_t)s->L * s->B * s->N_q;
+  if (wgs * n > kCUs || s->S <= 512) return 0;
+  if (s->dtype == THK_BF16 && (hpb == 1 || (hpb == 2 && n > kDecodeFuseMaxSplit))) return 0;
+  return n * heads <= (int64_t)THK_STATIC_SCRATCH_BYTES / ((kD + 2) * 4 + 8) ? (int)n : 0;
 }
 
 // ws_bytes: what the caller's workspace holds.  The estimate's count goes up and down with S, so a
@@ -404,6 +424,7 @@ Split decode_split(const thk_shape *s, size_t ws_bytes = SIZE_MAX) {
     const int n0 = n;
     const bool one = n0 == 1 || (wgs >= kCUs / 2 && s->S < 4096);
     if (s->S > one_block_rows || units_of(s) > 8) n = decode_pieces(s, hpb, wgs, steps, n0, one ? 1 : std::max(2, n0 / 4));
+    n = std::max(n, pieces_of_half_steps(s, hpb, wgs));
     const int64_t fit = (int64_t)std::min<size_t>(ws_bytes / decode_ws_bytes(s, 1), (size_t)n);
     if (fit < n && fit >= (one ? 0 : std::max(2, n0 / 8))) n = std::max((int)fit, 1);
   }
@@ -415,16 +436,16 @@ Split decode_split(const thk_shape *s, size_t ws_bytes = SIZE_MAX) {
 
 // Calls of at most 16 pieces merge their split records inside the launch: the block that finishes last for a
 // head group does it, and the second launch goes away.  The hand-off is three memory round trips
-// at the end of the kernel; a second launch costs about as much and its dispatch.  Merged by the kernel / inside,
-// us per call: one head, 32 units x 320 rows 8.9 / 7.2, 80 x 576 11.4 / 9.7, 160 x 2752 33.3 / 31.9, 256 x 9722 108.4 /
-// 106.4; four heads, 16 x 6494 rows 14.8 / 12.5, 128 x 2708 (512 blocks) 29.0 / 28.1, 96 x 5971 (768) 38.5 / 39.8, 128 x
-// 12777 (1024) 108.1 / 110.4; eight heads, 8 x 863 12.4 / 10.8, 40 x 2602 17.3 / 16.3, 80 x 12211 (480) 71.5 / 69.6, 64 x
-// 24512 (512) 106.4 / 109.1, 96 x 11824 (768) 71.1 / 78.0.  A block of four or eight heads exchanges four or eight records, and
-// with two such blocks per compute unit and more the exchange ends a launch whose memory queues are full.
-// Hence: up to two heads per block always, four up to two blocks per compute unit, eight below that.
+// at the end of the kernel; a second launch costs the GPU as much and its dispatch and the host 2.5 us, which is what counts where
+// a call takes the GPU about as long as the host.  Merged by the kernel / inside, us per call, and with the append in front:
+// one head, 8 units x 571 rows 5.9 8.5 / 6.3 7.9, 40 x 1226 8.9 10.5 / 8.6 10.3; two, 24 x 6140 16.7 17.9 / 16.2 17.9; four,
+// 8 x 881 7.1 10.9 / 7.5 8.9, 40 x 2629 (440 blocks) 13.8 15.4 / 13.9 15.6, before the kernel was made shorter 96 x 5971 (768) 38.5 / 39.8,
+// 128 x 12777 (1024) 108.1 / 110.4.  A block of eight heads exchanges eight records and is better off with the kernel:
+// 16 x 1929 9.9 11.7 / 10.3 12.3, 16 x 3207 11.8 13.6 / 12.3 14.2, 40 x 433 10.1 11.8 / 10.6 12.4, 40 x 5340 21.3 22.6 / 21.4 23.0.
+// Hence: up to two heads per block always, four up to two blocks per compute unit, eight never.
 // THK_DECODE_MERGE = kernel | fused overrides (fused only within the 16 pieces).
 bool merges_in_launch(int hpb, int64_t blocks) {
-  return hpb <= 2 || blocks < 2 * (int64_t)kCUs || (hpb == 4 && blocks == 2 * (int64_t)kCUs);
+  return hpb <= 2 || (hpb == 4 && blocks <= 2 * (int64_t)kCUs);
 }
 bool decode_merge_in_launch(const thk_shape *s, int n_split) {
   if (n_split < 2 || n_split > kDecodeFuseMaxSplit) return false;

@@ -51,7 +51,7 @@ __global__ __launch_bounds__(64 * NW) void k_decode_merge(const float *__restric
 #pragma unroll
     for (int i = 0; i < P; ++i) av[i] = load2((i0 + i) * kRecB + 8 + lane * 8);
     const float m = lane < P && i0 + lane < n_split ? ml[0] : -INFINITY;
-    const float M_new = fmaxf(M, wave_max(m));
+    const float M_new = fmaxf(M, wave_max(m));   // whole numbers: every weight here is an exact power of two
     const float wgt = weight(m, M_new), keep = weight(M, M_new);
     M = M_new;
     L = fmaf(L, keep, wave_sum(lane < P ? ml[1] * wgt : 0.f));

@@ -547,7 +547,10 @@ __device__ __forceinline__ void block_merge_store(const float *mrg, int wstride,
       ml[w] = *(const f32x2 *)rec;
       av[w] = *(const f32x2 *)(rec + 2 + 2 * lane);
     }
-    const float M = fmaxf(fmaxf(ml[0][0], ml[1][0]), fmaxf(ml[2][0], ml[3][0]));
+    // (a whole number at or above the maxima: what a record is weighed by against others, here and in k_decode_merge, is an
+    // exact power of two, and a wave's state is the only one with a rounded weight, in however many pieces; mean error against
+    // 64 bits of 11 fp32 calls of up to 33 pieces 1.32e-7 with the maximum itself, 1.26e-7 so)
+    const float M = ceilf(fmaxf(fmaxf(ml[0][0], ml[1][0]), fmaxf(ml[2][0], ml[3][0])));
     float Lsum = 0.f, A0 = 0.f, A1 = 0.f;
 #pragma unroll
     for (int w = 0; w < 4; ++w) {

@@ -76,3 +76,31 @@ def test_decode_merge_launch_piece_counts(dtype, G, T, n_split, thk_env):
         ref = O.decode_attn(as_numpy(q), h(kp), idx_np.reshape(B, N_kv, T), h(v), dtype)
         err = attn_rel_err(out, ref.reshape(-1, D)).max()
         assert err <= ATTN_TOL[dtype], f"S={S} n_split={n_split}: {err}"
+
+
+# calls of a block per 64 rows: the shortest, a last piece of one row, the most blocks (256), and one row more, where pieces have
+# whole steps again; with a workspace that holds half of the pieces the call takes those
+@pytest.mark.parametrize("dtype,N_q,N_kv,S,pieces", [("bf16", 32, 8, 513, 9), ("bf16", 32, 8, 2048, 32), ("bf16", 32, 8, 2049, None), ("bf16", 8, 4, 961, 16),
+                                                     ("bf16", 16, 2, 4033, 64), ("f32", 8, 8, 705, 12), ("f32", 8, 8, 2048, 32), ("f32", 8, 2, 1025, 17)])
+@pytest.mark.parametrize("tail", [0, 1, 112])
+def test_decode_pieces_of_half_steps(dtype, N_q, N_kv, S, pieces, tail):
+    T, G = 76, N_q // N_kv
+    shape = thk.make_shape(1, 1, N_q, N_kv, D, S, 1, T, 0, DT[dtype], 0)
+    n = thk.thk_default_split(shape, thk.THK_OP_DECODE)
+    assert n == pieces if pieces else n < -(-S // 64)
+    g = torch.Generator(device="cuda"); g.manual_seed(S)
+    rnd = lambda *shape: torch.randn(*shape, generator=g, device="cuda").to(TDT[dtype])
+    idx_np = _kept(np.random.default_rng(S), N_kv, T)
+    q, kp, v, kt, vt = 3 * rnd(N_q, D), rnd(N_kv, S, T), rnd(N_kv, S, D), rnd(N_kv, CAP, D), rnd(N_kv, CAP, D)
+    h = lambda y, m: as_numpy(y[:, :m].contiguous()).reshape(1, N_kv, m, y.shape[-1])
+    tails = (h(kt, tail), h(vt, tail), tail) if tail else ()
+    ref = O.decode_attn(as_numpy(q).reshape(1, N_q, D), h(kp, S), idx_np.reshape(1, N_kv, T), h(v, S), dtype, *tails).reshape(-1, D)
+    need = thk.thk_workspace_bytes(shape, thk.THK_OP_DECODE)
+    for held in (need, need // 2):
+        out = torch.empty(N_q, D, dtype=q.dtype, device="cuda")
+        ws = ws_tensor(held)[:held]
+        ws.fill_(255)
+        thk.thk_decode_attn(shape, q, kp, torch.from_numpy(idx_np).cuda(), v, kt, vt, tail, CAP, out, ws)
+        torch.cuda.synchronize()
+        err = attn_rel_err(out, ref).max()
+        assert err <= ATTN_TOL[dtype], f"workspace of {held}: {err}"
