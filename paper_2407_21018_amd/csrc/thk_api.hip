@@ -948,7 +948,7 @@ static thk_status score_value_common(const thk_shape *s, const void *q_obs, cons
   if (grid > kMaxGrid) return THK_ERR_SHAPE;
   if (ws == nullptr || !aligned16(ws) || ws_bytes < bytes(s, sp.n)) return THK_ERR_WORKSPACE;
   if (failed(launch_value_score(s->dtype, q_obs, k, v, (float *)ws, score_v, idx, s->T, units_of(s), s->S, G, s->S_obs,
-                         causal, sp.n, sp.rows, (hipStream_t)stream)))
+                         causal, sp.n, sp.rows, next_nonce(), (hipStream_t)stream)))
     return THK_ERR_HIP;
   return THK_OK;
 }

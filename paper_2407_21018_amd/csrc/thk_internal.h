@@ -268,9 +268,9 @@ int value_attn_qt(int G, int S_obs);   // query tiles of 32 rows carried by one 
 // ... and by a block of the 8-wave kernel (bf16, four tiles or more) in a call that fills the chip
 int value_wide_tiles(int G, int S_obs);
 size_t value_part_bytes(int64_t U, int G, int S_obs, int n_split);
-// idx (may be null): the Top_T of every unit's score
+// idx (may be null): the Top_T of every unit's score; nonce: 64 bits drawn per call, never 0
 hipError_t launch_value_score(int dtype, const void *q_obs, const void *k, const void *v, float *part,
                               float *score, int16_t *idx, int T, int64_t U, int64_t S, int G, int S_obs, int causal,
-                              int n_split, int64_t rows_per_split, hipStream_t st);
+                              int n_split, int64_t rows_per_split, unsigned long long nonce, hipStream_t st);
 
 }  // namespace thk

@@ -607,16 +607,38 @@ __global__ __launch_bounds__(64 * QT) void k_value_attn_f32(ValueAttnArgs a) {
 
 // Merge the partial records of one 32-row query tile of one unit and normalise.  A block of
 // 256 threads covers DQ = 256 / PG value channels: thread (d, pg) sums the records p = pg,
-// pg + PG, ... for channel d; the PG groups meet in LDS and are added in group order.  A unit
-// with a single tile gets its score here (each thread holds all of its rows); otherwise the
-// squared outputs go to sq[u][row][d] for k_value_norms.  PG = 2 for few records, 8 for many.
-// With idx (PG = 2 and a single tile: the block has the unit's whole score) the unit's Top_T follows here
-// instead of in a launch of its own: 40 units x 384 rows 25.0 -> 23.2 us.
+// pg + PG, ... for channel d; the PG groups meet in LDS and are added in group order.  PG = 2 for few records, 8 for many.
+// A unit with a single tile gets its score here (each thread holds all of its rows).  With several, a thread has the squares
+// of its tile's part of every head: it stores the sum over the heads that lie inside the tile and the parts of the head that
+// began before the tile and of the one that goes on behind it (kTileSums doubles a channel), and the block of the unit that
+// finishes last adds the tiles up, in their order, and takes the roots.  (Squares used to go to a launch of their own: 64 units x 4
+// tiles merge 8.2 and norms 7.4 us and the gap between them.)  Hand-off as in the decode kernels: sums and flags go to the
+// device's coherence point, a flag is a word per block that holds the call's nonce, each is acknowledged before the next
+// is issued, so the block whose flag comes last finds all of them set; blocks within a round trip of each other may both, and
+// store the same bits.  The finishing block clears the flags for a replay of the launch.
+// With idx the block that has a unit's whole score (a single tile and PG = 2, or several tiles) selects its Top_T, too: 40
+// units x 384 rows 25.0 -> 23.2 us.
+constexpr int kTileSums = 3;   // inside, began before, goes on behind
+struct ValueMergeArgs {
+  const float *part;
+  double *sums;                  // [U][nt][kTileSums][kD]
+  unsigned long long *flags;     // [U][blocks of a unit]
+  unsigned long long nonce;
+  float *score;
+  int16_t *idx;
+  int32_t T, G, S_obs, n_part, nqt, nt;
+};
+__device__ __forceinline__ double load_device(const double *p) {
+  return __longlong_as_double((long long)__hip_atomic_load((const unsigned long long *)p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+}
+__device__ __forceinline__ void store_device(double *p, double v) {
+  __hip_atomic_store((unsigned long long *)p, (unsigned long long)__double_as_longlong(v), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
 template <int PG>
-__global__ __launch_bounds__(256) void k_value_merge(const float *part, float *sq, float *score, int16_t *idx, int T, int G,
-                                                     int S_obs, int n_part, int nqt, int nt) {
+__global__ __launch_bounds__(256, 2) void k_value_merge(ValueMergeArgs a) {
   constexpr int DQ = 256 / PG, NDB = kD / DQ;   // channels per block, blocks per (unit, tile)
-  extern __shared__ float wts[];   // [n_part][32] merge weights, then [PG - 1][DQ][33] for the groups
+  extern __shared__ __attribute__((aligned(16))) float wts[];   // [n_part][32] merge weights, then [PG - 1][DQ][33] for the groups
+  const int nqt = a.nqt, nt = a.nt, n_part = a.n_part, S_obs = a.S_obs;
   int64_t bid = blockIdx.x;
   const int db = (int)(bid % NDB);
   bid /= NDB;
@@ -624,32 +646,38 @@ __global__ __launch_bounds__(256) void k_value_merge(const float *part, float *s
   const int t = (int)(bid % nt);
   const int dl = threadIdx.x % DQ, pg = threadIdx.x / DQ;
   const int d = db * DQ + dl;
-  const int rows_q = G * S_obs;
-  const float *pu = part + (size_t)u * n_part * nqt * kRec;
+  const int rows_q = a.G * S_obs;
+  const float *pu = a.part + (size_t)u * n_part * nqt * kRec;
+  // the first record's outputs are asked for in front of the weights; PG = 2: each further one's in front of the sums of the one before
+  float4 x[8];
+  auto fetch = [&](float4 (&to)[8], int p) {
+    const float4 *src = (const float4 *)(pu + ((size_t)min(p, n_part - 1) * nqt + t) * kRec + d * 32);
+#pragma unroll
+    for (int q4 = 0; q4 < 8; ++q4) to[q4] = src[q4];
+  };
+  fetch(x, pg);
   // weights of the records, row q = tid % 32, records tid / 32, + 8, ... per thread (one thread per row
-  // walked all of them before: 128 records took 60 us)
+  // walked all of them before: 128 records took 60 us); PG = 2: at most eight records, one per thread
   __shared__ float red_m[8][32], red_l[8][32], s_sc[kD];
-  if (n_part == 1) {   // short calls: one record, its weight is 1 over its sum
-    if (threadIdx.x < 32) {
-      const float L = pu[(size_t)t * kRec + 32 * kD + 32 + threadIdx.x];
-      wts[threadIdx.x] = L > 0.f ? 1.f / L : 0.f;
-    }
-  } else {
+  {
     const int q = threadIdx.x & 31, rg = threadIdx.x >> 5;
     const float *rec = pu + (size_t)t * kRec + 32 * kD + q;
-    float M = kNegBig;
-    for (int p = rg; p < n_part; p += 8) M = fmaxf(M, rec[(size_t)p * nqt * kRec]);
+    const size_t step = (size_t)nqt * kRec;
+    const float m0 = rec[min(rg, n_part - 1) * step], l0 = rec[min(rg, n_part - 1) * step + 32];   // a repeated record is no larger
+    float M = m0;
+    if constexpr (PG > 2)
+      for (int p = rg + 8; p < n_part; p += 8) M = fmaxf(M, rec[p * step]);
     red_m[rg][q] = M;
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < 8; ++i) M = fmaxf(M, red_m[i][q]);
-    float L = 0.f;
-    for (int p = rg; p < n_part; p += 8) {
-      const float *r = rec + (size_t)p * nqt * kRec;
-      const float wv = __builtin_amdgcn_exp2f(r[0] - M);
-      wts[p * 32 + q] = wv;
-      L += wv * r[32];
-    }
+    float w0 = rg < n_part ? __builtin_amdgcn_exp2f(m0 - M) : 0.f, L = rg < n_part ? w0 * l0 : 0.f;
+    if constexpr (PG > 2)
+      for (int p = rg + 8; p < n_part; p += 8) {
+        const float wv = __builtin_amdgcn_exp2f(rec[p * step] - M);
+        wts[p * 32 + q] = wv;
+        L += wv * rec[p * step + 32];
+      }
     red_l[rg][q] = L;
     __syncthreads();
     L = red_l[0][q];
@@ -657,22 +685,41 @@ __global__ __launch_bounds__(256) void k_value_merge(const float *part, float *s
     for (int i = 1; i < 8; ++i) L += red_l[i][q];
     const float inv = L > 0.f ? 1.f / L : 0.f;
     // normalised before the records are added: a single record's sums may be near the end of the range
-    for (int p = rg; p < n_part; p += 8) wts[p * 32 + q] *= inv;
+    if (rg < n_part) wts[rg * 32 + q] = w0 * inv;
+    if constexpr (PG > 2)
+      for (int p = rg + 8; p < n_part; p += 8) wts[p * 32 + q] *= inv;
   }
   __syncthreads();
   float acc[32];
 #pragma unroll
   for (int q = 0; q < 32; ++q) acc[q] = 0.f;
-  for (int p = pg; p < n_part; p += PG) {
-    const float4 *src = (const float4 *)(pu + ((size_t)p * nqt + t) * kRec + d * 32);
+  auto add = [&](const float4 (&from)[8], int p) {
     const float *wp = wts + p * 32;
 #pragma unroll
     for (int q4 = 0; q4 < 8; ++q4) {
-      const float4 x = src[q4];
-      acc[q4 * 4 + 0] += wp[q4 * 4 + 0] * x.x;
-      acc[q4 * 4 + 1] += wp[q4 * 4 + 1] * x.y;
-      acc[q4 * 4 + 2] += wp[q4 * 4 + 2] * x.z;
-      acc[q4 * 4 + 3] += wp[q4 * 4 + 3] * x.w;
+      const float4 w4 = *(const float4 *)(wp + q4 * 4);
+      acc[q4 * 4 + 0] += w4.x * from[q4].x;
+      acc[q4 * 4 + 1] += w4.y * from[q4].y;
+      acc[q4 * 4 + 2] += w4.z * from[q4].z;
+      acc[q4 * 4 + 3] += w4.w * from[q4].w;
+    }
+  };
+  if constexpr (PG > 2) {
+#pragma unroll 1
+    for (int p = pg; p < n_part; p += PG) {
+      if (p != pg) fetch(x, p);
+      add(x, p);
+    }
+  } else {
+    float4 y[8];
+#pragma unroll 1
+    for (int p = pg; p < n_part; p += 2 * PG) {
+      if (p + PG < n_part) fetch(y, p + PG);
+      add(x, p);
+      if (p + PG < n_part) {
+        if (p + 2 * PG < n_part) fetch(x, p + 2 * PG);
+        add(y, p + PG);
+      }
     }
   }
   __syncthreads();               // the weights are no longer read
@@ -682,73 +729,94 @@ __global__ __launch_bounds__(256) void k_value_merge(const float *part, float *s
     for (int q = 0; q < 32; ++q) xch[((pg - 1) * DQ + dl) * 33 + q] = acc[q];
   }
   __syncthreads();
-  if (pg > 0 && idx == nullptr) return;
   if (pg == 0) {
-#pragma unroll
+#pragma unroll 1
     for (int g2 = 1; g2 < PG; ++g2)
 #pragma unroll
       for (int q = 0; q < 32; ++q) acc[q] += xch[((g2 - 1) * DQ + dl) * 33 + q];
-    if (nt == 1) {
-      double ss = 0.0, total = 0.0;
+    // squares in fp64, head by head: pos = rows of the head that came before this one
+    double ss = 0.0, inside = 0.0, before = 0.0;
+    int pos = (t * 32) % S_obs;
+    bool mid = pos != 0;   // the head began before the tile
 #pragma unroll
-      for (int q = 0; q < 32; ++q) {
-        if (q < rows_q) {
-          ss += (double)acc[q] * (double)acc[q];
-          if ((q + 1) % S_obs == 0) {   // last window row of a head
-            total += sqrt(ss);
-            ss = 0.0;
-          }
+    for (int q = 0; q < 32; ++q) {
+      if (t * 32 + q < rows_q) {
+        ss += (double)acc[q] * (double)acc[q];
+        if (++pos == S_obs) {   // last window row of a head
+          if (mid) before = ss;
+          else inside += sqrt(ss);
+          mid = false;
+          ss = 0.0;
+          pos = 0;
         }
       }
-      score[(size_t)u * kD + d] = (float)total;
-      s_sc[d] = (float)total;
+    }
+    if (nt == 1) {
+      a.score[(size_t)u * kD + d] = (float)inside;
+      s_sc[d] = (float)inside;
     } else {
-      float *dst = sq + ((size_t)u * nt + t) * 32 * kD;
-#pragma unroll
-      for (int q = 0; q < 32; ++q) dst[q * kD + d] = acc[q] * acc[q];
+      double *dst = a.sums + ((size_t)u * nt + t) * (kTileSums * kD) + d;
+      store_device(dst, inside);
+      store_device(dst + kD, mid ? ss : before);   // (a head that fills the tile and goes on has all of it here)
+      store_device(dst + 2 * kD, mid ? 0.0 : ss);
     }
   }
-  if (idx == nullptr) return;
-  __syncthreads();
-  if (threadIdx.x < kWave) select_wave(s_sc[threadIdx.x], s_sc[threadIdx.x + kWave], T, idx + (size_t)u * T, threadIdx.x);
-}
-
-// Column norms per query head from the squared outputs.  1024 threads = 128 channels x 8 head
-// groups: thread (d, hg) sums the squares of heads hg, hg + 8, ... (eight rows in flight), takes
-// the roots, and the groups are added in group order.
-// With idx the unit's Top_T follows in the same block.
-__global__ __launch_bounds__(1024) void k_value_norms(const float *sq, float *score, int16_t *idx, int T, int G,
-                                                      int S_obs, int nt) {
-  __shared__ double tot[8][kD];
-  __shared__ float s_sc[kD];
-  const int64_t u = blockIdx.x;
-  const int d = threadIdx.x & (kD - 1), hg = threadIdx.x >> 7;
-  const float *src = sq + (size_t)u * nt * 32 * kD + d;
-  double total = 0.0;
-  for (int g = hg; g < G; g += 8) {
-    const float *hs = src + (size_t)g * S_obs * kD;
-    double ss = 0.0;
-    for (int i0 = 0; i0 < S_obs; i0 += 8) {
-      float x[8];
-#pragma unroll
-      for (int j = 0; j < 8; ++j) x[j] = hs[(size_t)min(i0 + j, S_obs - 1) * kD];
-#pragma unroll
-      for (int j = 0; j < 8; ++j) ss += (i0 + j < S_obs) ? (double)x[j] : 0.0;
+  if (nt > 1) {
+    __shared__ int s_last;
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this wave's sums are acknowledged
+    __syncthreads();                                   // ... and every wave's
+    const int nf = nt * NDB;
+    unsigned long long *flags = a.flags + (size_t)u * nf;
+    if (threadIdx.x < kWave) {
+      if (threadIdx.x == 0) __hip_atomic_store(flags + t * NDB + db, a.nonce, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the flag is out before the flags are read
+      bool all = true;
+      for (int i = threadIdx.x; i < nf; i += kWave)
+        all = all && __hip_atomic_load(flags + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == a.nonce;
+      all = __all(all);
+      if (threadIdx.x == 0) s_last = all ? 1 : 0;
     }
-    total += sqrt(ss);
-  }
-  tot[hg][d] = total;
-  __syncthreads();
-  if (hg == 0) {
-    double t = tot[0][d];
+    __syncthreads();
+    if (s_last == 0) return;
+    if (threadIdx.x < kD) {
+      const double *src = a.sums + (size_t)u * nt * (kTileSums * kD) + threadIdx.x;
+      double total = 0.0, open = 0.0;   // open: squares so far of a head that goes on
+      int pos = 0;                      // its rows so far
+      // sums that cannot be there are not asked for; those of eight tiles are in flight together
+      constexpr int NB = 8;
+      for (int t0 = 0; t0 < nt; t0 += NB) {
+        double v[NB][kTileSums];
+        int at = pos;
 #pragma unroll
-    for (int g2 = 1; g2 < 8; ++g2) t += tot[g2][d];
-    score[(size_t)u * kD + d] = (float)t;
-    s_sc[d] = (float)t;
+        for (int i = 0; i < NB; ++i) {
+          const double *tile = src + (size_t)(t0 + i) * (kTileSums * kD);
+          const int end = at + 32;
+          const bool here = t0 + i < nt;
+          v[i][0] = here && end >= S_obs ? load_device(tile) : 0.0;
+          v[i][1] = here && at != 0 ? load_device(tile + kD) : 0.0;
+          at = end % S_obs;
+          v[i][2] = here && at != 0 && (at < 32 || end == 32) ? load_device(tile + 2 * kD) : 0.0;
+        }
+#pragma unroll
+        for (int i = 0; i < NB; ++i) {
+          open += v[i][1];
+          const bool ends = pos + 32 >= S_obs;   // the open head, if there is one, ends here
+          if (ends && pos != 0) total += sqrt(open);
+          total += v[i][0];
+          open = ends || pos == 0 ? v[i][2] : open;
+          pos = (pos + 32) % S_obs;
+        }
+      }
+      s_sc[threadIdx.x] = (float)total;
+      a.score[(size_t)u * kD + threadIdx.x] = (float)total;
+    }
+    for (int i = threadIdx.x; i < nf; i += 256) __hip_atomic_store(flags + i, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
-  if (idx == nullptr) return;
+  if (a.idx == nullptr) return;
+  __shared__ int16_t s_list[kD];
   __syncthreads();
-  if (threadIdx.x < kWave) select_wave(s_sc[threadIdx.x], s_sc[threadIdx.x + kWave], T, idx + (size_t)u * T, threadIdx.x);
+  select_block(s_sc, a.T, s_list);   // (not select_wave, whose 28 unrolled steps take such a launch longer to fetch than to run)
+  if ((int)threadIdx.x < a.T) a.idx[(size_t)u * a.T + threadIdx.x] = s_list[threadIdx.x];
 }
 
 }  // namespace
@@ -768,13 +836,15 @@ size_t value_part_bytes(int64_t U, int G, int S_obs, int n_split) {
   const int QT = value_attn_qt(G, S_obs);
   const int nqt = (G * S_obs + 31) / 32;
   const int n_qblk = (nqt + QT - 1) / QT;
-  const size_t sq = nqt > 1 ? (size_t)U * nqt * 32 * kD * sizeof(float) : 0;
-  return (size_t)U * n_split * n_qblk * QT * kRec * sizeof(float) + sq;
+  // several tiles: room for a tile's squared outputs, of which the merge uses what its sums and flags take
+  const size_t sums = nqt > 1 ? (size_t)U * nqt * 32 * kD * sizeof(float) : 0;
+  static_assert(32 * kD * sizeof(float) >= kTileSums * kD * sizeof(double) + 4 * sizeof(unsigned long long), "sums and flags of a tile");
+  return (size_t)U * n_split * n_qblk * QT * kRec * sizeof(float) + sums;
 }
 
 hipError_t launch_value_score(int dtype, const void *q_obs, const void *k, const void *v, float *part,
                               float *score, int16_t *idx, int T, int64_t U, int64_t S, int G, int S_obs, int causal,
-                              int n_split, int64_t rows_per_split, hipStream_t st) {
+                              int n_split, int64_t rows_per_split, unsigned long long nonce, hipStream_t st) {
   clear_stale_hip_error();
   const int QT = value_attn_qt(G, S_obs);
   const int nqt_real = (G * S_obs + 31) / 32;
@@ -817,7 +887,6 @@ hipError_t launch_value_score(int dtype, const void *q_obs, const void *k, const
   if (e != hipSuccess) return e;
   const int n_part = n_split;
   const int nqt = a.n_qblk * QB;
-  float *sq = part + (size_t)U * n_part * nqt * kRec;   // behind the partial records
   // few records: 2 groups x 128 channels per block; many: 8 groups x 32 channels, 4 blocks
   const int PG = n_part > 8 ? 8 : 2;
   const int DQ = 256 / PG;
@@ -825,17 +894,17 @@ hipError_t launch_value_score(int dtype, const void *q_obs, const void *k, const
   const size_t xch = (size_t)(PG - 1) * DQ * 33 * sizeof(float);
   if (lds < xch) lds = xch;
   const dim3 mg((unsigned)(U * nqt_real * (kD / DQ)));
-  const bool select_here = PG == 2 && nqt_real == 1;
-  int16_t *const midx = select_here ? idx : nullptr;
-  if (PG == 8)
-    hipLaunchKernelGGL(k_value_merge<8>, mg, dim3(256), lds, st, part, sq, score, midx, T, G, S_obs, n_part, nqt, nqt_real);
-  else
-    hipLaunchKernelGGL(k_value_merge<2>, mg, dim3(256), lds, st, part, sq, score, midx, T, G, S_obs, n_part, nqt, nqt_real);
+  const bool select_here = idx != nullptr && (PG == 2 || nqt_real > 1);
+  ValueMergeArgs m;
+  m.part = part; m.score = score; m.idx = select_here ? idx : nullptr; m.nonce = nonce;
+  m.T = T; m.G = G; m.S_obs = S_obs; m.n_part = n_part; m.nqt = nqt; m.nt = nqt_real;
+  m.sums = (double *)(part + (size_t)U * n_part * nqt * kRec);   // behind the partial records, then the flags
+  m.flags = (unsigned long long *)(m.sums + (size_t)U * nqt_real * kTileSums * kD);
+  if (PG == 8) hipLaunchKernelGGL(k_value_merge<8>, mg, dim3(256), lds, st, m);
+  else hipLaunchKernelGGL(k_value_merge<2>, mg, dim3(256), lds, st, m);
   e = hipGetLastError();
-  if (e != hipSuccess || select_here) return e;
-  if (nqt_real == 1) return idx != nullptr ? launch_select(score, idx, U, T, st) : hipSuccess;
-  hipLaunchKernelGGL(k_value_norms, dim3((unsigned)U), dim3(1024), 0, st, sq, score, idx, T, G, S_obs, nqt_real);
-  return hipGetLastError();
+  if (e != hipSuccess || select_here || idx == nullptr) return e;
+  return launch_select(score, idx, U, T, st);
 }
 
 }  // namespace thk

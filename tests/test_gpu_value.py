@@ -460,3 +460,54 @@ def test_value_score_of_extreme_values(G, S, n_split, rising, log2_v, dtype):
     got = gpu_score_value(shape, q_obs, k, v, 0).cpu().numpy().astype(np.float64)
     want = O.score_value(as_numpy(q_obs), as_numpy(k), as_numpy(v), dtype, 0).reshape(2, D)
     check_score(got, want, None, G, 8, f"G={G} S={S} 2^{log2_v}", dtype)
+
+
+# heads that begin, end and go on inside, at and across the 32-row tiles of the merge: window lengths around the tile, one tile to
+# many (17 heads of 33 rows: 18 tiles, 72 blocks a unit where the pieces are many, more flags than a wave has lanes)
+@pytest.mark.parametrize("n_split", [1, 3, 9])
+@pytest.mark.parametrize("dtype,G,S_obs", [("bf16", 5, 7), ("bf16", 3, 31), ("bf16", 4, 32), ("bf16", 17, 33), ("bf16", 3, 64), ("bf16", 2, 100), ("bf16", 1, 129),
+                                           ("f32", 33, 1), ("f32", 3, 40), ("f32", 2, 96)])
+def test_value_score_heads_across_merge_tiles(dtype, G, S_obs, n_split):
+    N_kv, S, T = 2, 128 * 9 - 3, 50
+    g = torch.Generator(device="cuda"); g.manual_seed(100 * G + S_obs)
+    rnd = lambda *shape: torch.randn(*shape, generator=g, device="cuda").to(TDT[dtype])
+    q, k, v = 2 * rnd(1, 1, N_kv * G, S_obs, 128), rnd(1, 1, N_kv, S, 128), rnd(1, 1, N_kv, S, 128)
+    shape = thk.make_shape(1, 1, N_kv * G, N_kv, 128, S, S_obs, T, 0, DT[dtype], n_split)
+    score = torch.empty(N_kv, 128, device="cuda")
+    idx = torch.empty(N_kv, T, dtype=torch.int16, device="cuda")
+    kept = torch.empty(N_kv, S, T, dtype=v.dtype, device="cuda")
+    ws = ws_tensor(thk.thk_workspace_bytes(shape, thk.THK_OP_PRUNE_VALUE))
+    ref = O.score_value(as_numpy(q), as_numpy(k), as_numpy(v), dtype, causal=True).reshape(N_kv, 128)
+    for _ in range(2):   # the second call finds what the first one left in the workspace
+        score.zero_()
+        thk.thk_prune_value(shape, q, k, v, 1, score, idx, kept, ws)
+        torch.cuda.synchronize()
+        assert np.abs(score.cpu().numpy() / ref - 1).max() <= SCORE_V_TOL
+        sel = (-score.cpu().numpy()).argsort(axis=1, kind="stable")[:, :T]
+        assert (np.sort(sel, axis=1) == idx.cpu().numpy()).all()
+
+
+def test_value_prune_replays_from_a_graph():
+    """Several merge tiles and several pieces a unit: the block that finishes a unit clears the flags it was elected by."""
+    N_kv, G, S_obs, S, T = 6, 3, 40, 1149, 50
+    g = torch.Generator(device="cuda"); g.manual_seed(9)
+    rnd = lambda *shape: torch.randn(*shape, generator=g, device="cuda").to(torch.bfloat16)
+    q, k, v = 2 * rnd(1, 1, N_kv * G, S_obs, 128), rnd(1, 1, N_kv, S, 128), rnd(1, 1, N_kv, S, 128)
+    shape = thk.make_shape(1, 1, N_kv * G, N_kv, 128, S, S_obs, T, 0, thk.THK_BF16, 0)
+    score, idx = torch.empty(N_kv, 128, device="cuda"), torch.empty(N_kv, T, dtype=torch.int16, device="cuda")
+    kept = torch.empty(N_kv, S, T, dtype=v.dtype, device="cuda")
+    ws = ws_tensor(thk.thk_workspace_bytes(shape, thk.THK_OP_PRUNE_VALUE))
+    path = lambda: thk.thk_prune_value(shape, q, k, v, 1, score, idx, kept, ws)
+    path()
+    torch.cuda.synchronize()
+    want = [t.clone() for t in (score, idx, kept)]
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        path()
+    for _ in range(4):
+        for t in (score, idx, kept):
+            t.zero_()
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert all(torch.equal(a, b) for a, b in zip((score, idx, kept), want))
