@@ -73,6 +73,26 @@ __device__ __forceinline__ void softmax_exp(f32x16 &s, float scale_log2, float m
 #pragma unroll
   for (int r = 0; r < 16; ++r) s[r] = __builtin_amdgcn_exp2f(fmaf(s[r], scale_log2, -m_run));
 }
+// The probabilities of a sub-tile as two bf16 terms each, a pair per conversion instruction (one by one they take twice as
+// many, and this kernel's time goes with its instructions), and their sum.
+__device__ __forceinline__ void split_weights(const f32x16 &s, bf16x8 (&ph)[2], bf16x8 (&pl)[2], float &l_run) {
+  typedef float f32x2 __attribute__((ext_vector_type(2)));
+  float sum[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int r = 0; r < 16; r += 2) {
+    const f32x2 p = {s[r], s[r + 1]};
+    const bf16x2 hi = __builtin_convertvector(p, bf16x2);
+    const uint32_t b = __builtin_bit_cast(uint32_t, hi);
+    const f32x2 rest = {p[0] - __uint_as_float(b << 16), p[1] - __uint_as_float(b & 0xffff0000u)};
+    const bf16x2 lo = __builtin_convertvector(rest, bf16x2);
+    ph[r >> 3][r & 7] = hi[0];
+    ph[r >> 3][(r & 7) + 1] = hi[1];
+    pl[r >> 3][r & 7] = lo[0];
+    pl[r >> 3][(r & 7) + 1] = lo[1];
+    sum[r / 4] += p[0] + p[1];
+  }
+  l_run += (sum[0] + sum[1]) + (sum[2] + sum[3]);
+}
 __device__ __forceinline__ void softmax_step(f32x16 &s, int64_t kb, int h, int64_t lim, int64_t lim_min,
                                              float scale_log2, float &m_run, float &l_run, f32x16 (&o)[4]) {
   softmax_max(s, kb, h, lim, lim_min, scale_log2, m_run, l_run, o);
@@ -243,13 +263,7 @@ __global__ __launch_bounds__(256, 2) void k_value_attn_bf16(ValueAttnArgs a) {
       // |p - hi - lo| <= 2^-18 p, so the matrix product loses nothing that fp32 arithmetic keeps.
       // The row sum takes the fp32 values.
       bf16x8 ph[2], pl[2];
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const __bf16 hi = (__bf16)s[r];
-        ph[r >> 3][r & 7] = hi;
-        pl[r >> 3][r & 7] = (__bf16)(s[r] - (float)hi);
-        l_run += s[r];
-      }
+      split_weights(s, ph, pl, l_run);
 #pragma unroll
       for (int dt = 0; dt < 4; ++dt) {
 #pragma unroll
@@ -436,13 +450,7 @@ __global__ __launch_bounds__(512, 2) void k_value_attn_wide(ValueAttnArgs a) {
   auto values = [&](f32x16 &s, const unsigned char *vb, int t) {
     // two bf16 terms per probability (see k_value_attn_bf16)
     bf16x8 ph[2], pl[2];
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const __bf16 hi = (__bf16)s[r];
-      ph[r >> 3][r & 7] = hi;
-      pl[r >> 3][r & 7] = (__bf16)(s[r] - (float)hi);
-      l_run += s[r];
-    }
+    split_weights(s, ph, pl, l_run);
 #pragma unroll
     for (int k2 = 0; k2 < 2; ++k2)
 #pragma unroll
