@@ -552,16 +552,58 @@ bool value_compact_in_bursts(const thk_shape *s, const FusedPlan &fp) {
   return units_of(s) * (int64_t)fp.NB >= 16 * resident;
 }
 
-// Split of the S axis for the value score: pieces are whole 128-row chunks of at least 512
-// rows (fp32: 128), enough of them for one resident set of blocks (two per compute unit: 74 KB of LDS
-// each; more pieces only add merge work -- one layer of config 2: 65 us with 8 pieces per
-// unit, 54-55 us with 2-4), and few enough that the merge kernel's weight table (at most 256
-// pieces) fits.
+// Split of the S axis for the value score: pieces are whole 128-row chunks, few enough that the merge kernel's weight table (at
+// most 256 pieces) fits.  The count starts from one resident set of blocks (two per compute unit: 74 KB of LDS each) in pieces of at
+// least 512 rows (fp32: 128) and is the estimate's where that is surely better (value_pieces).
 Split value_cut(const thk_shape *s, int n) {
   int64_t rows = ceil_div(s->S, n);
   rows = ceil_div(rows, 128) * 128;
   return {(int)ceil_div(s->S, rows), rows};   // empty pieces dropped
 }
+// The number of pieces (no fewer than least) with the least estimated time of a value prune, if that is at least 4 % below the
+// estimate for n0.  In us, chunk = 128 rows, R = blocks resident on a compute unit, l of them on the fullest one:
+//     launches and copy  +  the longer of  all rows at the memory rate  and  the sum over rounds of R blocks of
+//     t0 + chunks of a piece * max(t_own, l t_shared)  +  records (t_rec each, 1.4 where the merge has more than eight)
+// t_own: a chunk of a block by itself; t_shared: what each resident block adds.  Fitted per kernel (32-row query tiles a block
+// carries) to 160 random bf16 and 110 fp32 shapes at up to ten piece counts each, within 4.4 %; the count taken costs 0.9 and
+// 1.0 % more than the best one on average, n0 5.9 and 7.6 %.  What it knows that n0 does not: short calls are as long as a piece, and
+// 128-row pieces use idle compute units (16 units x 311 rows 18.8 -> 16.0 us, 8 x 8 heads x 897 29.8 -> 26.8); the records of
+// many query tiles (16 units x 8 heads x 7007 rows 14 pieces 64.0, 8 53.6); fp32 blocks of one wave are four to a compute
+// unit (24 units x 17810 rows 20 pieces 214, 70 178).
+int value_pieces(const thk_shape *s, int nqt, int QT, int n0, int least) {
+  struct Cost { double base, copy, t0, t_own, t_shared, rate, t_rec, t_piece; int resident; };
+  static constexpr Cost b1 = {12.7, 4.52, 2.27, 1.59, 1.59, 7.46, 0.0039, 0.164, 2}, b2 = {12.7, 4.52, 3.50, 2.03, 1.48, 6.85, 0.0039, 0.164, 2},
+                        b4 = {12.7, 4.52, 6.02, 2.43, 2.43, 5.90, 0.0039, 0.164, 1}, f1 = {14.5, 5.38, 0.57, 17.2, 5.14, 5.48, 0.0003, 0.149, 4},
+                        f2 = {14.5, 5.38, 2.11, 16.9, 13.1, 6.0, 0.0003, 0.149, 4}, f4 = {14.5, 5.38, 5.72, 15.5, 15.8, 6.0, 0.0003, 0.149, 2};
+  const bool f32 = s->dtype == THK_F32;
+  const Cost &c = f32 ? (QT == 1 ? f1 : QT == 2 ? f2 : f4) : (QT == 1 ? b1 : QT == 2 ? b2 : b4);
+  const int64_t U = units_of(s);
+  const double mb = (double)U * (double)s->S * 2.0 * kD * elem_bytes(s->dtype) / 1e6;   // keys and values
+  const double base = c.base + 0.75 * mb / c.copy, stream = mb / c.rate;
+  const int wide = !f32 && QT == 4 ? value_wide_tiles(s->N_q / s->N_kv, s->S_obs) : 0;
+  auto cost = [&](int64_t n, int64_t chunks) {
+    int tiles = QT;
+    if (wide == 8 && U * n * ceil_div(nqt, 8) >= kCUs) tiles = 8;   // (as the launch chooses)
+    const double twice = tiles == 8 ? 2.0 : 1.0;
+    const int64_t blocks = U * n * ceil_div(nqt, tiles), per_cu = ceil_div(blocks, kCUs), full = per_cu / c.resident, rest = per_cu % c.resident;
+    auto round = [&](int64_t l) { return c.t0 + (double)chunks * twice * std::max(c.t_own, (double)l * c.t_shared); };
+    const double t = (double)full * round(c.resident) + (rest > 0 ? round(rest) : 0.0);
+    return base + std::max(t, stream) + (double)(U * n * ceil_div(nqt, tiles) * tiles) * c.t_rec + (n > 8 ? 1.4 : 0.0) + (double)n * c.t_piece;
+  };
+  // a last piece of less than 48 rows is not worth a block
+  const int64_t top = std::min<int64_t>({256, std::max<int64_t>((s->S + 80) / 128, 1), 6 * (int64_t)n0});
+  double best = 0.96 * cost(n0, ceil_div(ceil_div(s->S, n0), 128));
+  int64_t n_best = n0, k_last = 0;
+  for (int64_t i = least; i <= top; ++i) {
+    const int64_t k = ceil_div(ceil_div(s->S, i), 128);
+    if (k == k_last) continue;   // the same pieces, some of them empty
+    k_last = k;
+    const double t = cost(ceil_div(s->S, 128 * k), k);
+    if (t < best) { best = t; n_best = i; }
+  }
+  return (int)n_best;
+}
+
 // least (may be null): the fewest pieces a call with a smaller workspace is cut into
 // instead, never more for a shorter S than what any longer one reports (as in decode_split; half of
 // the count that is independent of rounds, for the runs are whole 128-row chunks).
@@ -596,6 +638,7 @@ Split value_split(const thk_shape *s, int *least = nullptr) {
       floor_n = (int)std::min<int64_t>(cap, std::max<int64_t>(kCUs / b1, 1));   // the most that one round holds
     }
     floor_n = std::max(std::min(floor_n, 256) / 2, 1);
+    n = value_pieces(s, nqt, QT, std::min(n, 256), floor_n);
   }
   if (n > 256) n = 256;
   if (least != nullptr) *least = floor_n;

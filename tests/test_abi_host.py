@@ -318,6 +318,23 @@ def test_default_decode_split_balances_rounds_and_stays_within_the_static_scratc
                         assert thk.thk_workspace_bytes(s, thk.THK_OP_DECODE) <= 8 << 20
 
 
+def test_default_value_split_by_estimate():
+    """Short calls take 128-row pieces while compute units are idle, many query tiles few pieces, fp32 blocks of one wave
+    four to a compute unit; a last piece of a few rows is none."""
+    def split(B, N_q, N_kv, S, S_obs, dtype=thk.THK_BF16):
+        return thk.thk_default_split(thk.make_shape(1, B, N_q, N_kv, 128, S, S_obs, 64, 0, dtype, 0), thk.THK_OP_SCORE_VALUE)
+    assert split(2, 8, 8, 311, 8) == 3                        # 16 units x 3 blocks: 18.8 us with one, 16.0
+    assert split(1, 8, 8, 300, 32) == 2                       # 44 rows behind the second chunk
+    assert 4 <= split(1, 64, 8, 897, 32) <= 7                 # 8 units x 8 query tiles: 29.8 us with two, 26.8
+    assert 7 <= split(2, 64, 8, 7007, 32) <= 9                # 16 units x 8 tiles: 64.0 us with 14, 53.6
+    assert split(8, 32, 8, 32768, 32) == 4                    # one block per compute unit
+    assert split(3, 32, 8, 17810, 8, thk.THK_F32) >= 28       # 24 units: 214 us with 20, 178 with 70
+    for S in range(1, 1200, 37):
+        for dtype in (thk.THK_BF16, thk.THK_F32):
+            n = split(1, 32, 8, S, min(S, 32), dtype)
+            assert 1 <= n <= max(1, (S + 80) // 128)
+
+
 def _shorter_lengths(S_max):
     return [s for s in sorted({1, 64, 128, 300, 321, 500, 769, 1000, 1024, 1025, 1815, 2047, 2048, 2176, 2816, 3264, 4032, 4160,
                                4928, 5000, 8000, 8064, 12345, 16257, 30000, 32768} | {S_max - d for d in (1, 63, 64, 65, 128, 640)})
