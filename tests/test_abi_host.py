@@ -330,9 +330,8 @@ def test_default_value_split_by_estimate():
     assert split(8, 32, 8, 32768, 32) == 4                    # one block per compute unit
     assert split(3, 32, 8, 17810, 8, thk.THK_F32) >= 28       # 24 units: 214 us with 20, 178 with 70
     for S in range(1, 1200, 37):
-        for dtype in (thk.THK_BF16, thk.THK_F32):
-            n = split(1, 32, 8, S, min(S, 32), dtype)
-            assert 1 <= n <= max(1, (S + 80) // 128)
+        assert 1 <= split(1, 32, 8, S, min(S, 32)) <= max(1, (S + 80) // 128)
+        assert 1 <= split(1, 32, 8, S, min(S, 32), thk.THK_F32) <= -(-S // 128)
 
 
 def _shorter_lengths(S_max):
