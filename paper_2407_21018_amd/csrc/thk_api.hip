@@ -373,16 +373,24 @@ int decode_pieces(const thk_shape *s, int hpb, int64_t wgs, int64_t steps, int n
 // a block's waves have a tile of pruned rows each and the other two are free for the tail's, which a wave with rows of its own
 // takes 1 to 2 us after those.  us per call without a tail, with 38 rows, with the append in front, pieces of whole steps / these:
 // 8 units x 4 heads x 743 rows 7.5 8.3 10.2 / 7.4 7.4 9.0, 16 x 7 heads x 1020 9.0 10.3 12.2 / 8.1 8.2 10.1, fp32 8 x 2 heads x
-// 614 9.1 10.9 12.6 / 8.7 8.8 10.5, 8 x 2 heads x 1581 9.2 10.8 12.6 / 8.5 8.7 10.7.  With more blocks a call with a tail still
-// gains (32 x 5 heads x 683, 352 blocks 10.6 / 9.2) and one without loses (8 x 4 heads x 2910, 368 blocks 7.5 / 8.2).  Not bf16 blocks
-// of two heads above 16 pieces, whose merge is a second launch: where an append goes in front the host would
-// take longer to issue the three than the GPU to run them (8 units x 1191 rows 7.5 8.1 9.9 / 7.2 6.9 10.2), nor of one head, which
-// from 1025 rows on lose the same way (8 x 1338 6.7 7.2 8.9 / 7.1 6.7 10.2) and below that are mostly left whole.
-// Up to 512 rows the counts stay the powers of two that callers have planned with.
-int pieces_of_half_steps(const thk_shape *s, int hpb, int64_t wgs) {
+// 614 9.1 10.9 12.6 / 8.7 8.8 10.5, 8 x 2 heads x 1581 9.2 10.8 12.6 / 8.5 8.7 10.7, 40 x 4 heads x 227 9.9 13.0 14.6 / 9.3 9.6 11.5.
+// With more blocks a call with a tail still
+// gains (32 x 5 heads x 683, 352 blocks 10.6 / 9.2) and one without loses (8 x 4 heads x 2910, 368 blocks 7.5 / 8.2).  In bf16
+//   * not up to 256 rows, below which one block without a merge is shorter (16 x 4 heads x 182 6.2 7.4 9.0 / 7.1 7.1 8.8);
+//   * blocks of one or two heads not above 16 pieces, whose merge is a second launch: with an append in front the host
+//     takes longer to issue the three than the GPU to run them (8 units x 2 heads x 1191 rows 7.5 8.1 9.9 / 7.2 6.9 10.2);
+//   * calls of at most 16 pieces that have no tail, and blocks of at most four heads: their merge, inside the launch, grows by what the
+//     shorter pieces save (8 x 4 heads x 947 7.2 / 7.6, 16 x 391 6.3 / 6.5).  A count is planned and reported as if there was a tail.
+// Up to 512 rows of eight units the counts stay the powers of two that callers have planned with, and so do those of one-head
+// blocks of eight units.
+int pieces_of_half_steps(const thk_shape *s, int hpb, int64_t wgs, bool tail) {
   const int64_t n = ceil_div(s->S, 64), heads = (int64_t)s->L * s->B * s->N_q;
-  if (wgs * n > kCUs || s->S <= 512) return 0;
-  if (s->dtype == THK_BF16 && (hpb == 1 || (hpb == 2 && n > kDecodeFuseMaxSplit))) return 0;
+  const bool eight = units_of(s) <= 8;
+  if (wgs * n > kCUs || s->S <= (eight ? 512 : s->dtype == THK_BF16 ? 256 : 128)) return 0;
+  if (s->dtype == THK_BF16) {
+    if (hpb <= 2 && (n > kDecodeFuseMaxSplit || (hpb == 1 && eight))) return 0;
+    if (hpb <= 4 && n <= kDecodeFuseMaxSplit && !tail) return 0;
+  }
   return n * heads <= (int64_t)THK_STATIC_SCRATCH_BYTES / ((kD + 2) * 4 + 8) ? (int)n : 0;
 }
 
@@ -395,7 +403,7 @@ int pieces_of_half_steps(const thk_shape *s, int hpb, int64_t wgs) {
 // which needs no workspace, is taken only where n0 is 1 and by calls of at least 128 blocks per piece
 // under 4096 rows (beyond, the estimate wants it of calls of over 500 blocks, to save 2-4 %): those
 // are served with any workspace.
-Split decode_split(const thk_shape *s, size_t ws_bytes = SIZE_MAX) {
+Split decode_split(const thk_shape *s, size_t ws_bytes = SIZE_MAX, bool tail = true) {
   int n = s->n_split;
   const int G = s->N_q / s->N_kv;
   const int64_t wgs = units_of(s) * ceil_div(G, decode_heads_per_block(s));
@@ -424,7 +432,7 @@ Split decode_split(const thk_shape *s, size_t ws_bytes = SIZE_MAX) {
     const int n0 = n;
     const bool one = n0 == 1 || (wgs >= kCUs / 2 && s->S < 4096);
     if (s->S > one_block_rows || units_of(s) > 8) n = decode_pieces(s, hpb, wgs, steps, n0, one ? 1 : std::max(2, n0 / 4));
-    n = std::max(n, pieces_of_half_steps(s, hpb, wgs));
+    n = std::max(n, pieces_of_half_steps(s, hpb, wgs, tail));
     const int64_t fit = (int64_t)std::min<size_t>(ws_bytes / decode_ws_bytes(s, 1), (size_t)n);
     if (fit < n && fit >= (one ? 0 : std::max(2, n0 / 8))) n = std::max((int)fit, 1);
   }
@@ -1057,7 +1065,7 @@ static thk_status decode_common(const thk_shape *s, const void *q, const void *k
       (s_tail > 0 && (!aligned16(k_tail) || (v_tail != nullptr && !aligned16(v_tail)))))
     return THK_ERR_ALIGN;
   const bool ws_usable = ws != nullptr && aligned16(ws);
-  const Split sp = split != nullptr ? *split : decode_split(s, ws_usable ? ws_bytes : 0);
+  const Split sp = split != nullptr ? *split : decode_split(s, ws_usable ? ws_bytes : 0, s_tail > 0);
   const int G = s->N_q / s->N_kv;
   if (units_of(s) * ceil_div(G, decode_heads_per_block(s)) * sp.n > kMaxGrid) return THK_ERR_SHAPE;
   if (sp.n > 1 && (!ws_usable || ws_bytes < decode_ws_bytes(s, sp.n))) return THK_ERR_WORKSPACE;
@@ -1144,7 +1152,7 @@ thk_status thk_decode_attn_static(const thk_shape *s, const void *q, const void 
   thk_status st = check_shape(s, false);
   if (st != THK_OK) return st;
   // the size check comes before anything touches the device
-  const Split sp = decode_split(s);
+  const Split sp = decode_split(s, SIZE_MAX, s_tail > 0);
   if (sp.n > 1 && decode_ws_bytes(s, sp.n) > (size_t)THK_STATIC_SCRATCH_BYTES) return THK_ERR_SCRATCH;
   void *ws = nullptr;
   st = static_scratch(&ws);
