@@ -374,8 +374,10 @@ int decode_pieces(const thk_shape *s, int hpb, int64_t wgs, int64_t steps, int n
 // takes 1 to 2 us after those.  us per call without a tail, with 38 rows, with the append in front, pieces of whole steps / these:
 // 8 units x 4 heads x 743 rows 7.5 8.3 10.2 / 7.4 7.4 9.0, 16 x 7 heads x 1020 9.0 10.3 12.2 / 8.1 8.2 10.1, fp32 8 x 2 heads x
 // 614 9.1 10.9 12.6 / 8.7 8.8 10.5, 8 x 2 heads x 1581 9.2 10.8 12.6 / 8.5 8.7 10.7, 40 x 4 heads x 227 9.9 13.0 14.6 / 9.3 9.6 11.5.
-// With more blocks a call with a tail still
-// gains (32 x 5 heads x 683, 352 blocks 10.6 / 9.2) and one without loses (8 x 4 heads x 2910, 368 blocks 7.5 / 8.2).  In bf16
+// With a tail, blocks of eight heads and fp32 ones of the narrow staging class go on up to 1.75 blocks per compute unit (24 x 8 heads x
+// 779 10.5 / 9.3, 8 x 7 heads x 2989 11.1 / 9.4, fp32 16 x 4 heads x 1227 12.5 / 11.6, 8 x 2779 12.3 / 9.7); bf16 blocks of four heads do not gain
+// (32 x 785 8.7 / 9.1, 24 x 694 8.3 / 8.1), wide fp32 ones lose (24 x 4 heads x 936, T = 100 15.2 / 20.8), nor does a call without a
+// tail gain (8 x 4 heads x 2910 7.5 / 8.2). In bf16
 //   * not up to 256 rows, below which one block without a merge is shorter (16 x 4 heads x 182 6.2 7.4 9.0 / 7.1 7.1 8.8);
 //   * blocks of one or two heads not above 16 pieces, whose merge is a second launch: with an append in front the host
 //     takes longer to issue the three than the GPU to run them (8 units x 2 heads x 1191 rows 7.5 8.1 9.9 / 7.2 6.9 10.2);
@@ -386,7 +388,9 @@ int decode_pieces(const thk_shape *s, int hpb, int64_t wgs, int64_t steps, int n
 int pieces_of_half_steps(const thk_shape *s, int hpb, int64_t wgs, bool tail) {
   const int64_t n = ceil_div(s->S, 64), heads = (int64_t)s->L * s->B * s->N_q;
   const bool eight = units_of(s) <= 8;
-  if (wgs * n > kCUs || s->S <= (eight ? 512 : s->dtype == THK_BF16 ? 256 : 128)) return 0;
+  const bool more = tail && (s->dtype == THK_F32 ? ld_of(s) <= 79 : hpb == 8);
+  const int64_t most = more ? kCUs * 7 / 4 : kCUs;
+  if (wgs * n > most || s->S <= (eight ? 512 : s->dtype == THK_BF16 ? 256 : 128)) return 0;
   if (s->dtype == THK_BF16) {
     if (hpb <= 2 && (n > kDecodeFuseMaxSplit || (hpb == 1 && eight))) return 0;
     if (hpb <= 4 && n <= kDecodeFuseMaxSplit && !tail) return 0;
