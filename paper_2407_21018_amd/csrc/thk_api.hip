@@ -610,7 +610,9 @@ int value_pieces(const thk_shape *s, int nqt, int QT, int n0, int least) {
     const int64_t k = ceil_div(ceil_div(s->S, i), 128);
     if (k == k_last) continue;   // the same pieces, some of them empty
     k_last = k;
-    const double t = cost(ceil_div(s->S, 128 * k), k);
+    const int64_t n = ceil_div(s->S, 128 * k);   // what i whole-chunk pieces leave
+    if (n < least) continue;
+    const double t = cost(n, k);
     if (t < best) { best = t; n_best = i; }
   }
   return (int)n_best;

@@ -75,7 +75,7 @@ __device__ __forceinline__ void softmax_exp(f32x16 &s, float scale_log2, float m
   for (int r = 0; r < 16; ++r) s[r] = __builtin_amdgcn_exp2f(fmaf(s[r], scale_log2, -m_run));
 }
 // The probabilities of a sub-tile as two bf16 terms each, a pair per conversion instruction (one by one they take twice as
-// many, and this kernel's time goes with its instructions), and their sum.
+// many: value prunes of 64 units x 4 heads x 32768 rows 367.6 / 360.9 us, 32 x 8 heads x 13696 216.4 / 211.4), and their sum.
 __device__ __forceinline__ void split_weights(const f32x16 &s, bf16x8 (&ph)[2], bf16x8 (&pl)[2], float &l_run) {
   typedef float f32x2 __attribute__((ext_vector_type(2)));
   float sum[4] = {0.f, 0.f, 0.f, 0.f};
@@ -341,12 +341,10 @@ __global__ __launch_bounds__(256, 2) void k_value_attn_bf16(ValueAttnArgs a) {
 //     rows), of value row r at c ^ ((r & 3) << 2) (a transposing read takes 64 bytes of 4 rows);
 //   * the next sub-tile's logits are computed in front of this one's softmax, in straight-line code,
 //     so that matrix and vector instructions of one wave run side by side.
-// Neither the memory nor the matrix pipes bound it alone: 64 units x 32768 rows x 128 query rows take 221
-// us in a run with counters, 4.9 TB/s and 0.93 PFLOP/s of issued matrix work; the matrix pipes are
-// busy 43 % of the cycles, no bank conflicts, and the clock is 2.0 GHz (2.4 in the copy kernel of
-// the same run), so the same instructions also take a fifth longer under this load.  (Two phases per
-// sub-tile with waves 4 .. 7 half a step behind, so that one wave of a SIMD feeds the matrix pipe while
-// the other computes weights, measured the same.)
+// Matrix and vector instructions bound it, one after the other: of the 417000 cycles a compute unit is busy with 64 units x 32768
+// rows x 128 query rows a SIMD multiplies for 197000 and calculates for 204000, the LDS takes 16 %, without conflicts, and the clock is
+// 1.7 to 2.0 GHz (2.4 in the copy kernel of the same run).  Fewer instructions shorten it, fewer waits do not: operands read a
+// sub-tile ahead measured 2-3 % longer, a higher priority for one of a SIMD's two waves, or waves 4 .. 7 half a step behind, the same.
 // 64 units x 32768 rows, G = 4, S_obs = 32: 300 -> 277 us; 8 units x 131072 rows, S_obs = 64: 279 -> 237;
 // 32 units x 16384 rows, G = 8: 150 -> 131 us (score calls, before: the kernel above with QT = 4).
 constexpr int kWideRows = 128;                    // rows per chunk

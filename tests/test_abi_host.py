@@ -369,6 +369,21 @@ def test_workspace_of_the_longest_sequence_serves_every_shorter_one(B, N_q, N_kv
             assert call(s, (A, need)) == 6 and call(s, (A, need - 16)) == 5
 
 
+@pytest.mark.skipif(os.path.exists("/dev/kfd"), reason="accepted calls carry made-up addresses: host without a GPU only")
+@pytest.mark.parametrize("B,N_q,N_kv,S_obs,dtype", [(1, 4, 4, 32, thk.THK_BF16), (2, 8, 8, 8, thk.THK_BF16), (1, 8, 4, 32, thk.THK_BF16), (2, 64, 8, 32, thk.THK_BF16),
+                                                    (3, 32, 8, 64, thk.THK_BF16), (1, 4, 4, 32, thk.THK_F32), (2, 16, 8, 64, thk.THK_F32), (3, 32, 8, 64, thk.THK_F32)])
+def test_value_workspace_of_every_length_serves_the_shorter_ones(B, N_q, N_kv, S_obs, dtype):
+    """The estimate's piece count goes up and down with the length; a length's workspace still serves each shorter one."""
+    A = 1 << 20
+    mk = lambda S: thk.make_shape(1, B, N_q, N_kv, 128, S, min(S, S_obs), 64, 0, dtype, 0)
+    lengths = sorted(set(range(64, 2600, 97)) | {128 * n + d for n in (9, 17, 24, 40, 65, 97, 129, 160, 193, 256) for d in (-1, 0, 1, 20)})
+    least = None
+    for S in reversed(lengths):   # the smallest workspace that any length from S on reports
+        need = thk.thk_workspace_bytes(mk(S), thk.THK_OP_SCORE_VALUE)
+        least = need if least is None else min(least, need)
+        assert _status(thk.thk_score_value, mk(S), A, A, A, 1, A, (A, least), stream=0) == 6, (S, need, least)
+
+
 def test_plain_c_program_uses_the_boundary(tmp_path):
     """thk.h is a C header and libthk.so a C library: a gcc-built program with no C++ and no
     Python in it includes the one and links the other."""
