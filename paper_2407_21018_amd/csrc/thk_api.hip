@@ -586,7 +586,7 @@ int value_pieces(const thk_shape *s, int nqt, int QT, int n0, int least) {
   struct Cost { double base, copy, t0, t_own, t_shared, rate, t_rec, t_piece; int resident; };
   static constexpr Cost b1 = {12.7, 4.52, 2.27, 1.59, 1.59, 7.46, 0.0039, 0.164, 2}, b2 = {12.7, 4.52, 3.50, 2.03, 1.48, 6.85, 0.0039, 0.164, 2},
                         b4 = {12.7, 4.52, 6.02, 2.43, 2.43, 5.90, 0.0039, 0.164, 1}, f1 = {14.5, 5.38, 0.57, 17.2, 5.14, 5.48, 0.0003, 0.149, 4},
-                        f2 = {14.5, 5.38, 2.11, 16.9, 13.1, 6.0, 0.0003, 0.149, 4}, f4 = {14.5, 5.38, 5.72, 15.5, 15.8, 6.0, 0.0003, 0.149, 2};
+                        f2 = {11.4, 4.00, 4.25, 21.1, 9.79, 5.17, 0.0037, 0.143, 4}, f4 = {14.5, 5.38, 5.72, 15.5, 15.8, 6.0, 0.0003, 0.149, 2};
   const bool f32 = s->dtype == THK_F32;
   const Cost &c = f32 ? (QT == 1 ? f1 : QT == 2 ? f2 : f4) : (QT == 1 ? b1 : QT == 2 ? b2 : b4);
   const int64_t U = units_of(s);

@@ -528,7 +528,7 @@ constexpr int kKstF = 528;  // LDS bytes per key row (b128 reads of 16 rows: 64 
 constexpr int kVstF = 544;  // LDS bytes per value row (the two halves read rows 4 apart: 32 banks apart)
 
 template <int QT>
-__global__ __launch_bounds__(64 * QT, QT == 1 ? 1 : 2) void k_value_attn_f32(ValueAttnArgs a) {
+__global__ __launch_bounds__(64 * QT, QT == 4 ? 2 : 1) void k_value_attn_f32(ValueAttnArgs a) {
   __shared__ __attribute__((aligned(16))) unsigned char Ks[32 * kKstF];
   __shared__ __attribute__((aligned(16))) unsigned char Vs[32 * kVstF];
   constexpr int NT = 64 * QT;
@@ -578,27 +578,40 @@ __global__ __launch_bounds__(64 * QT, QT == 1 ? 1 : 2) void k_value_attn_f32(Val
   // 3062, S_obs = 64 193 / 136, 16 x 28441 275 / 205, 8 x 477 35.5 / 32.9
   constexpr int NP = 1024 / NT;
   u32x4 pk[NP], pv[NP];
-  constexpr int NA = QT == 2 ? NP / 2 : NP;   // keys asked for a tile ahead (two waves a block: registers for half of them)
-  auto fetch = [&](u32x4 (&to)[NP], const unsigned char *g, int64_t kb, auto first, auto end) {
+  // Blocks of two waves load a tile when they need it: ahead they measured longer wherever several share a compute unit (16 units x
+  // 12364 rows, S_obs = 64 147 / 172, 16 x 2 heads x 26432 249 / 299).
+  constexpr bool AHEAD = QT != 2;
+  auto fetch = [&](u32x4 (&to)[NP], const unsigned char *g, int64_t kb) {
     // (a tile is a flat run of bytes that ends with the unit: rows past the end read 0, and their weights are 0)
     const int bytes = __builtin_amdgcn_readfirstlane((int)(S - kb < 32 ? S - kb : 32) * (kD * 4));
     const auto rsrc = __builtin_amdgcn_make_buffer_rsrc((void *)(g + kb * (kD * 4)), (short)0, bytes, 0x00027000);
 #pragma unroll
-    for (int i = first; i < end; ++i)
+    for (int i = 0; i < NP; ++i)
       to[i] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rsrc, tid * 16 + i * (NT * 16), 0, 0));
   };
   auto commit = [&](unsigned char *lds, int pitch, const u32x4 (&from)[NP]) {
 #pragma unroll
     for (int i = 0; i < NP; ++i) *(u32x4 *)(lds + ((i * NT + tid) >> 5) * pitch + ((i * NT + tid) & 31) * 16) = from[i];
   };
-  const std::integral_constant<int, 0> i_0;
-  const std::integral_constant<int, NA> i_a;
-  const std::integral_constant<int, NP> i_p;
-  if (k0 < k1) fetch(pk, kg, k0, i_0, i_a);
+  auto stage = [&](int64_t kb) {   // both tensors' tile, a few pieces at a time
+#pragma unroll 4
+    for (int i = tid; i < 1024; i += NT) {
+      const int r = i >> 5, c = (i & 31) * 16;
+      int64_t gr = kb + r;
+      gr = gr < S ? gr : S - 1;   // rows past the end repeat the last one; their weights are zero
+      *(u32x4 *)(Ks + r * kKstF + c) = *(const u32x4 *)(kg + gr * (kD * 4) + c);
+      *(u32x4 *)(Vs + r * kVstF + c) = *(const u32x4 *)(vg + gr * (kD * 4) + c);
+    }
+  };
+  if (AHEAD && k0 < k1) fetch(pk, kg, k0);
   for (int64_t kb = k0; kb < k1; kb += 32) {
-    if constexpr (NA < NP) fetch(pk, kg, kb, i_a, i_p);
-    commit(Ks, kKstF, pk);
-    fetch(pv, vg, kb, i_0, i_p);
+    if constexpr (AHEAD) {
+      commit(Ks, kKstF, pk);
+      fetch(pv, vg, kb);
+    } else {
+      __syncthreads();   // the last tile is no longer read
+      stage(kb);
+    }
     __syncthreads();   // the keys are there, and the last tile's values are no longer read
     f32x16 s;
 #pragma unroll
@@ -612,9 +625,11 @@ __global__ __launch_bounds__(64 * QT, QT == 1 ? 1 : 2) void k_value_attn_f32(Val
       s = __builtin_amdgcn_mfma_f32_32x32x2f32(ka.w, qreg[jj].w, s, 0, 0, 0);
     }
     softmax_step(s, kb, h, lim, lim_min, a.scale_log2, m_run, l_run, o);
-    commit(Vs, kVstF, pv);
-    if (kb + 32 < k1) fetch(pk, kg, kb + 32, i_0, i_a);
-    __syncthreads();   // the values are there, and the keys are no longer read
+    if constexpr (AHEAD) {
+      commit(Vs, kVstF, pv);
+      if (kb + 32 < k1) fetch(pk, kg, kb + 32);
+      __syncthreads();   // the values are there, and the keys are no longer read
+    }
 #pragma unroll
     for (int r = 0; r < 16; ++r) l_run += s[r];
 #pragma unroll
