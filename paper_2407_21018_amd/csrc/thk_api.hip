@@ -577,7 +577,7 @@ Split value_cut(const thk_shape *s, int n) {
 //     launches and copy  +  the longer of  all rows at the memory rate  and  the sum over rounds of R blocks of
 //     t0 + chunks of a piece * max(t_own, l t_shared)  +  records (t_rec each, 1.4 where the merge has more than eight)
 // t_own: a chunk of a block by itself; t_shared: what each resident block adds.  Fitted per kernel (32-row query tiles a block
-// carries) to 160 random bf16 and 110 fp32 shapes at up to ten piece counts each, within 4.4 %; the count taken costs 0.9 and
+// carries; fp32 blocks of two are left out) to 160 random bf16 and 110 fp32 shapes at up to ten piece counts each, within 4.4 %; the count taken costs 0.9 and
 // 1.0 % more than the best one on average, n0 5.9 and 7.6 %.  What it knows that n0 does not: short calls are as long as a piece, and
 // 128-row pieces use idle compute units (16 units x 311 rows 18.8 -> 16.0 us, 8 x 8 heads x 897 29.8 -> 26.8); the records of
 // many query tiles (16 units x 8 heads x 7007 rows 14 pieces 64.0, 8 53.6); fp32 blocks of one wave are four to a compute
@@ -586,9 +586,9 @@ int value_pieces(const thk_shape *s, int nqt, int QT, int n0, int least) {
   struct Cost { double base, copy, t0, t_own, t_shared, rate, t_rec, t_piece; int resident; };
   static constexpr Cost b1 = {12.7, 4.52, 2.27, 1.59, 1.59, 7.46, 0.0039, 0.164, 2}, b2 = {12.7, 4.52, 3.50, 2.03, 1.48, 6.85, 0.0039, 0.164, 2},
                         b4 = {12.7, 4.52, 6.02, 2.43, 2.43, 5.90, 0.0039, 0.164, 1}, f1 = {14.5, 5.38, 0.57, 17.2, 5.14, 5.48, 0.0003, 0.149, 4},
-                        f2 = {11.4, 4.00, 4.25, 21.1, 9.79, 5.17, 0.0037, 0.143, 4}, f4 = {14.5, 5.38, 5.72, 15.5, 15.8, 6.0, 0.0003, 0.149, 2};
+                        f4 = {14.5, 5.38, 5.72, 15.5, 15.8, 6.0, 0.0003, 0.149, 2};
   const bool f32 = s->dtype == THK_F32;
-  const Cost &c = f32 ? (QT == 1 ? f1 : QT == 2 ? f2 : f4) : (QT == 1 ? b1 : QT == 2 ? b2 : b4);
+  const Cost &c = f32 ? (QT == 1 ? f1 : f4) : (QT == 1 ? b1 : QT == 2 ? b2 : b4);
   const int64_t U = units_of(s);
   const double mb = (double)U * (double)s->S * 2.0 * kD * elem_bytes(s->dtype) / 1e6;   // keys and values
   const double base = c.base + 0.75 * mb / c.copy, stream = mb / c.rate;
@@ -652,7 +652,9 @@ Split value_split(const thk_shape *s, int *least = nullptr) {
       floor_n = (int)std::min<int64_t>(cap, std::max<int64_t>(kCUs / b1, 1));   // the most that one round holds
     }
     floor_n = std::max(std::min(floor_n, 256) / 2, 1);
-    n = value_pieces(s, nqt, QT, std::min(n, 256), floor_n);
+    // (not fp32 blocks of two query tiles, whose times the estimate does not know well: 24 units x 7 heads x 7674 rows, S_obs = 8
+    // 126 us with the count there is, 150 with the estimate's)
+    if (s->dtype == THK_BF16 || QT != 2) n = value_pieces(s, nqt, QT, std::min(n, 256), floor_n);
   }
   if (n > 256) n = 256;
   if (least != nullptr) *least = floor_n;
