@@ -462,6 +462,25 @@ __device__ __forceinline__ void compact_emit_tile(const u32x4 *tile, const FlatO
   }
 }
 
+// Where a lane's chunks c, c + 64, ... of a tile's output lie: in 8-row block `block` of the tile, at chunk `entry` of the
+// table's period of cpp chunks.  A lane past the tile's last chunk (block > 3) stays inside the period, too: a tile of narrow rows (at most
+// 12 elements in bf16, 6 in fp32) has fewer than 64 chunks, and behind the period the table holds nothing.
+struct ChunkWalk {
+  int cpp, dq, dr, block, entry;
+  __host__ __device__ __forceinline__ ChunkWalk(int c, int chunks_per_period) : cpp(chunks_per_period) {
+    dq = kWave / cpp;
+    dr = kWave - dq * cpp;   // uniform, as dq
+    block = (c >= cpp) + (c >= 2 * cpp) + (c >= 3 * cpp) + (c >= 4 * cpp);
+    entry = c - block * cpp;
+    entry = entry < cpp ? entry : cpp - 1;
+  }
+  __host__ __device__ __forceinline__ void next() {
+    entry += dr;
+    block += dq;
+    if (entry >= cpp) { entry -= cpp; ++block; }
+  }
+};
+
 // Step 2 for blocks that hold several tiles per wave.  What a lane gathers is the same in every tile of a unit: chunk c_lo + lane + 64 i of the tile's output, i = 0, 1,
 // ...  Its table entries are fetched once (init) and kept, 16 bits each, so that the LDS reads of a tile
 // depend on nothing but the tile and are all in flight at once; with a table read in front of every chunk's gathers (compact_emit_tile) a
@@ -479,27 +498,20 @@ struct Emit {
   int c_lo;                  // first whole chunk of a tile
 
   __device__ __forceinline__ void init(const int16_t *tab, int sh, int ld, int lane) {
-    // chunk c lies in 8-row block pb = c / cpp of the tile, at chunk rc = c % cpp of the table's period
-    const int cpp = 8 * ld / VEC;
-    const int dq = kWave / cpp, dr = kWave - dq * cpp;   // uniform
     c_lo = (sh + VEC - 1) / VEC;
-    int c = c_lo + lane;
-    int pb = (c >= cpp) + (c >= 2 * cpp) + (c >= 3 * cpp) + (c >= 4 * cpp);
-    int rc = c - pb * cpp;
+    ChunkWalk at(c_lo + lane, 8 * ld / VEC);
 #pragma unroll
     for (int i = 0; i < STEPS; ++i) {
-      if (c_lo + i * kWave < 4 * cpp) {
+      if (c_lo + i * kWave < 4 * at.cpp) {
         // (a lane past the tile's last chunk looks into the last 8-row block; what it finds is not stored)
-        const uint32_t blk = (uint32_t)min(pb, 3) * (uint32_t)(8 * Tile<DT>::ROW_ELEMS * sizeof(ET));
-        const uint32_t *te = (const uint32_t *)(tab + rc * VEC);
+        const uint32_t blk = (uint32_t)min(at.block, 3) * (uint32_t)(8 * Tile<DT>::ROW_ELEMS * sizeof(ET));
+        const uint32_t *te = (const uint32_t *)(tab + at.entry * VEC);
 #pragma unroll
         for (int w = 0; w < NW; ++w) {
           const uint32_t x = te[w];   // signed, but block + entry is not: a chunk that looks back is not in block 0
           off[i][w] = ((x + blk) & 0xffffu) | ((x & 0xffff0000u) + (blk << 16));
         }
-        rc += dr;
-        pb += dq;
-        if (rc >= cpp) { rc -= cpp; ++pb; }
+        at.next();
       }
     }
   }

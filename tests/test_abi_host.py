@@ -470,3 +470,16 @@ def test_bench_stream_rejects_misuse():
     assert st(thk.THK_STREAM_READ, None, None, 1, 0) == 1                          # src missing
     assert st(thk.THK_STREAM_COPY, A, None, 1, 4) == 1 and st(thk.THK_STREAM_WRITE, None, None, 1, 4) == 1
     assert st(thk.THK_STREAM_READ, A + 8, None, 1, 0) == 4 and st(thk.THK_STREAM_COPY, A, A + 4, 1, 4) == 4
+
+
+def test_gather_table_is_read_inside_its_period(tmp_path):
+    """The offsets that the one-launch prune's blocks keep per lane (csrc/thk_prune_device.h), for every row pitch."""
+    import shutil
+    import subprocess
+    if shutil.which("hipcc") is None:
+        pytest.skip("needs the ROCm compiler")
+    exe = tmp_path / "chunk_walk_check"
+    subprocess.check_call(["hipcc", "--cuda-host-only", "-std=c++17", "-O1", "-I", os.path.join(ROOT, "include"), "-I",
+                           os.path.join(ROOT, "paper_2407_21018_amd", "csrc"), os.path.join(ROOT, "tests", "c", "chunk_walk_check.hip"), "-o", str(exe)])
+    out = subprocess.run([str(exe)], capture_output=True, text=True, timeout=120)
+    assert out.returncode == 0 and "chunk walk ok" in out.stdout, out.stdout + out.stderr
