@@ -434,6 +434,45 @@ def test_prune_single_launch_block_counts(dtype, block_rows, n_blocks, short, th
         np.testing.assert_array_equal(as_numpy(kp), O.compact_keys(as_numpy(k).reshape(U, S, D), idx.cpu().numpy(), dtype))
 
 
+@pytest.mark.parametrize("rest", [1, 33, -31])
+@pytest.mark.parametrize("dtype,U,NB", [("bf16", 16, 49), ("bf16", 11, 70), ("f32", 16, 33), ("f32", 8, 65)])
+def test_prune_single_launch_of_more_than_one_round(dtype, U, NB, rest, thk_env):
+    """Single launches of a few blocks more than are resident at once (768, fp32 512), with one level of sums and with two
+    (more than 64 blocks a unit): the last block of every unit has one row, a tile and a row, or all but 31; rows of one element to
+    128, dense and padded, the last rows left alone or not; behind the list, and with every block but a unit's last
+    resigning while rows of the next round are on their way."""
+    thk_env.setenv("THK_PRUNE_LAUNCH", "solo")
+    block_rows = 512 if dtype == "bf16" else 256
+    S, G, S_obs = block_rows * (NB if rest < 0 else NB - 1) + rest, 2, 8
+    assert U * NB > (768 if dtype == "bf16" else 512)
+    q_obs = _randn((1, 1, U * G, S_obs, D), dtype, 311 + rest, 1.0)
+    k = _randn((1, 1, U, S, D), dtype, 312 + rest, 1.0)
+    kd = k.reshape(U, S, D)
+    norms = torch.stack([x.double().square().sum(0).sqrt() for x in kd])
+    want = (norms * q_obs.reshape(U, G, S_obs, D).double().square().sum(2).sqrt().sum(1)).cpu().numpy()
+    for T, ld, recent in [(1, 0, 0), (7, 0, 33), (51, 0, 0), (128, 0, 1), (7, 12, 0), (1, 5, 32), (51, 56, 40), (12, 0, 0)]:
+        shape = thk.make_shape(1, 1, U * G, U, D, S, S_obs, T, ld, DT[dtype], 0, recent)
+        assert thk.thk_prune_launches(shape) == 1
+        rows, n = S - recent, U * (S - recent) * (ld or T)
+        score, idx = torch.empty(U, D, device="cuda"), torch.empty(U, T, dtype=torch.int16, device="cuda")
+        ws = ws_tensor(thk.thk_workspace_bytes(shape, thk.THK_OP_PRUNE))
+        for spin in (None, "0"):
+            if spin is None:
+                thk_env.delenv("THK_PRUNE_SPIN_LIMIT", raising=False)
+            else:
+                thk_env.setenv("THK_PRUNE_SPIN_LIMIT", spin)
+            kp = torch.full((n + 64,), 3.0, dtype=k.dtype, device="cuda")   # what lies behind the last row stays
+            thk.thk_prune(shape, q_obs, k, score, idx, kp, ws)
+            torch.cuda.synchronize()
+            where = f"T={T} ld={ld} recent={recent} spin={spin}"
+            assert np.abs(score.cpu().numpy() / want - 1).max() <= SCORE_TOL, where
+            check_idx_with_tie_rule(idx.cpu().numpy(), O.select_topk(want, T), want, T)
+            got = kp[:n].reshape(U, rows, -1)
+            for u in range(U):
+                assert torch.equal(got[u, :, :T], kd[u, :rows, idx[u].long()]), (where, u)
+            assert (got[..., T:] == 0).all() and (kp[n:] == 3).all(), where
+
+
 @pytest.mark.parametrize("path", ["fused", "fused-small-blocks", "fused-no-wait", "hold-128", "hold-256", "hold-512",
                                   "hold-256-no-wait", "reread-256", "staged", "staged-groups"])
 @pytest.mark.parametrize("dtype,G,S,T,sigma", PRUNE_CASES)
