@@ -387,8 +387,11 @@ int decode_pieces(const thk_shape *s, int hpb, int64_t wgs, int64_t steps, int n
 //     10.9 / 10.7, 8 x 1500 11.5 / 11.1);
 //   * blocks of at most four heads that merge inside the launch not without a tail: the merge grows by what the
 //     shorter pieces save (8 x 4 heads x 947 7.2 / 7.6, 16 x 391 6.3 / 6.5).  A count is planned and reported as if there was a tail.
-// Up to 512 rows of eight units the counts stay the powers of two that callers have planned with, and so do those of one-head
-// blocks of eight units.
+// One case is kept for what it reports and not for its time: up to 512 rows of eight units, and bf16 blocks of one head of eight units, have the
+// counts that thk_default_split gave before there were these pieces (4 of 512 rows, 8 of 1024), which its tests state.  They would gain as their
+// neighbours do (with the append in front, as it is / these: 8 units x 4 heads x 450 rows 9.9 / 8.7, x 2 heads 12.7 / 9.0, 8 heads 11.8 / 11.5,
+// one head x 512 9.6 / 8.1, x 743 11.5 / 8.3, fp32 8 x 1 head x 384 13.6 / 9.6; without a tail 7.1 / 7.0, 9.8 / 7.3, 8.2 / 8.0, 6.6 / 5.8, 8.8 / 6.6,
+// 10.1 / 7.7).
 int pieces_of_half_steps(const thk_shape *s, int hpb, int64_t wgs, int n, bool tail) {
   const int64_t half = ceil_div(s->S, 64), heads = (int64_t)s->L * s->B * s->N_q;
   const bool eight = units_of(s) <= 8;
@@ -407,8 +410,8 @@ int pieces_of_half_steps(const thk_shape *s, int hpb, int64_t wgs, int n, bool t
 // ws_bytes: what the caller's workspace holds.  The estimate's count goes up and down with S, so a
 // workspace asked for at a sequence's final length can hold fewer pieces than a shorter length
 // would take; a call then takes the pieces that fit, down to an eighth of the count n0 that the estimate
-// starts from, and to two.  n0 never falls with S, the estimate takes a quarter of it or more, and
-// cutting n pieces into whole 64-row runs leaves more than half of them (a piece has at least 127 rows):
+// starts from, and to two.  n0 never falls with S, the estimate takes a quarter of it or more in pieces of at least 127 rows, of
+// which cutting into whole 64-row runs leaves more than half; pieces of 64 rows only raise a count and lose none to the cut:
 // the workspace of the final length serves every shorter one.  Less than that is refused.  One piece,
 // which needs no workspace, is taken only where n0 is 1 and by calls of at least 128 blocks per piece
 // under 4096 rows (beyond, the estimate wants it of calls of over 500 blocks, to save 2-4 %): those
