@@ -264,8 +264,8 @@ int pieces_by_rounds(const thk_shape *s, int hpb, int64_t wgs, int64_t steps, in
 // A round's compute units hold q blocks each and some of them one more.  They move their rows at the least of what the memory
 // gives them (an equal share of 7.6 TB/s: 30 KB/us, more for the ones left over once the others are done), of what a compute
 // unit takes (c1 KB/us with one block, c2 with several), and of what waiting for its own loads lets a block take (k t_step).
-// t_block: what a block costs whatever its length; merge: nothing for one piece, m_in inside the launch, m_out + 0.01
-// per piece + 0.2 per thousand records by the merge kernel.  Rows whose pitch makes the kernels put words together (odd) and
+// t_block: what a block costs whatever its length; merge: nothing for one piece, m_in for a short one (cheap_merge), m_out + 0.01
+// per piece + 0.2 per thousand records for others.  Rows whose pitch makes the kernels put words together (odd) and
 // long ones that take the wide staging class (wide) slow t_step, c1 and c2 by a factor.  The width of
 // the value rows is not known here (the workspace must not depend on it), so the estimate is the mean of those of 128
 // and of 64 channels.
@@ -326,14 +326,16 @@ int decode_pieces(const thk_shape *s, int hpb, int64_t wgs, int64_t steps, int n
     return w;
   };
   const Width w_full = width(kD, resident), w_half = width(kD / 2, resident);
-  // (as it was when the constants were fitted; a call of eight heads per block that costs m_in here now has the merge kernel, which
-  // takes it less)
-  auto in_launch = [&](int64_t blocks) { return merges_in_launch(hpb, blocks) || (hpb == 8 && blocks < 2 * (int64_t)kCUs); };
+  // A merge of up to 16 pieces costs m_in, inside the launch or, for eight heads, in a launch whose blocks are one wave each; with
+  // two blocks per compute unit and more the launch is priced.  (With eight heads priced at m_out, as it is or at 2.6 or 3.0, 4 % of 3000
+  // random shapes take another count and those 118 to 127 are 1.2 to 1.3 % longer on average, 67 to 69 of them by 2 % and more, up to
+  // 16; 32 to 39 are shorter: 256 units x 8 heads x 1071 rows 1 piece 21.0 us, 2 23.9; 24 x 8 heads x 6975 10 16.2, 19 17.1.)
+  auto cheap_merge = [&](int64_t n, int64_t blocks) { return n <= kDecodeFuseMaxSplit && (merges_in_launch(hpb, blocks) || (hpb == 8 && blocks < 2 * (int64_t)kCUs)); };
   auto around = [&](int64_t n) {   // what the tiles do not pay for; grows with n
     const int64_t blocks = wgs * n;
     const double t = c.t0 + c.t_block * (double)ceil_div(blocks, kCUs);
     if (n == 1) return t;
-    return t + (n <= kDecodeFuseMaxSplit && in_launch(blocks) ? c.m_in : c.m_out + 0.01 * (double)n + 0.0002 * (double)(heads * n));
+    return t + (cheap_merge(n, blocks) ? c.m_in : c.m_out + 0.01 * (double)n + 0.0002 * (double)(heads * n));
   };
   // (for rows of unknown value width)
   auto estimate = [&](int64_t i, const Width &wide_rows, const Width &narrow_rows) {
