@@ -265,8 +265,8 @@ __device__ __forceinline__ int solo_index_list(const PruneFusedArgs &a, int64_t 
 // means that the finisher will not look again -- and that the list is in place: the block then
 // fetches it after all (true) and goes on as usual.
 template <bool GRP>
-__device__ __forceinline__ bool hand_over_rows(const PruneFusedArgs &a, int64_t u, int64_t item, double *s_part,
-                                               float *s_sc, int16_t *s_idx, int *s_flag) {
+__device__ __forceinline__ bool hand_over_rows(const PruneFusedArgs &a, int64_t u, int64_t item, float *s_sc, int16_t *s_idx,
+                                               int *s_flag) {
   const int tid = tid_here();
   if (tid == 0)
     __hip_atomic_store(a.undone + item, (unsigned char)1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -374,7 +374,7 @@ void k_prune_solo(PruneFusedArgs a) {
     for (; ticks >= 16; ticks -= 16) __builtin_amdgcn_s_sleep(16);
   }
 
-  // ---- load: every chunk of the block's rows is in flight at once ----------------------------
+  // ---- load: in a launch of one round every chunk of the block's rows is in flight at once ----
   // Blocks of a long launch load their tiles through buffer resources (request_tile), at most 8 KB of a wave in flight: all four tiles at
   // once only fill the queues that the blocks' exchange of sums has to pass as well (64 units x 26736 rows 150.6 -> 148.1 us,
   // 8 x 131072 83.6 -> 81.7; 16 KB no gain, 4 KB a loss).  A launch of one round wants all of it as early as it can: one
@@ -460,7 +460,7 @@ void k_prune_solo(PruneFusedArgs a) {
   // (the rows ahead have landed before anything else happens to this block's LDS, whose end they must not outlive)
   if constexpr (LONG) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   if (st == kGaveUp) {
-    if (!hand_over_rows<GRP>(a, u, item, s_part, s_sc, s_idx, &s_flag)) return;
+    if (!hand_over_rows<GRP>(a, u, item, s_sc, s_idx, &s_flag)) return;
     st = kHaveList;
   }
   const int n_gaveup = st == kFinisher ? close_unit(a, u, &s_flag) : 0;
