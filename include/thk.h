@@ -280,10 +280,12 @@ thk_status thk_prune(const thk_shape *shape, const void *q_obs, const void *k,
  * states go through ws and are merged in an order fixed by the shape and the launch form
  * (not by which block finishes first), so repeated calls give identical bits: by a second
  * kernel, or -- for calls of at most 16 pieces whose blocks serve one or two query heads,
- * or four with at most 512 blocks (units x head groups x pieces) -- inside the one launch by the block that finishes last for a head group (the blocks signal
- * through per-piece flag words in ws that carry a nonce drawn per call; no
- * read-modify-write, nothing in ws has to be cleared beforehand).
- * THK_DECODE_MERGE = kernel | fused in the environment overrides the choice.
+ * or four with at most 512 blocks (units x head groups x pieces) -- inside the one launch by
+ * the block that finishes last for a head group (the blocks signal through per-piece flag
+ * words in ws that carry a nonce drawn per call; no read-modify-write, nothing in ws has to be
+ * cleared beforehand).
+ * THK_DECODE_MERGE = kernel | fused in the environment overrides the choice (calls whose
+ * blocks serve eight heads always have the second kernel).
  * bf16 caches with N_q / N_kv >= 3 run the two products on the matrix cores, here and in
  * thk_decode_attn_kv: four or eight query heads share every key and value byte a block
  * reads (accumulation in fp32; elements of a padded row past T are masked, whatever they

@@ -466,16 +466,16 @@ Split decode_split(const thk_shape *s, size_t ws_bytes = SIZE_MAX, bool tail = t
 // 128 x 12777 (1024) 108.1 / 110.4.  A block of eight heads exchanges eight records and is better off with the kernel:
 // 16 x 1929 9.9 11.7 / 10.3 12.3, 16 x 3207 11.8 13.6 / 12.3 14.2, 40 x 433 10.1 11.8 / 10.6 12.4, 40 x 5340 21.3 22.6 / 21.4 23.0.
 // Hence: up to two heads per block always, four up to two blocks per compute unit, eight never.
-// THK_DECODE_MERGE = kernel | fused overrides (fused only within the 16 pieces).
+// THK_DECODE_MERGE = kernel | fused overrides (fused only within the 16 pieces and the four heads).
 bool merges_in_launch(int hpb, int64_t blocks) {
   return hpb <= 2 || (hpb == 4 && blocks <= 2 * (int64_t)kCUs);
 }
 bool decode_merge_in_launch(const thk_shape *s, int n_split) {
   if (n_split < 2 || n_split > kDecodeFuseMaxSplit) return false;
+  const int hpb = decode_heads_per_block(s);
   const char sw = env_switches().decode_merge;
-  if (sw == 'k') return false;
-  if (sw == 'f') return true;
-  return merges_in_launch(decode_heads_per_block(s), decode_groups(s) * n_split);
+  if (hpb > 4 || sw == 'k') return false;
+  return sw == 'f' || merges_in_launch(hpb, decode_groups(s) * n_split);
 }
 
 // Units per group in the staged form of thk_prune (three launches per group).

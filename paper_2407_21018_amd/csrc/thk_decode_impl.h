@@ -527,7 +527,7 @@ __device__ __forceinline__ void block_merge_store(const float *mrg, int wstride,
                                                   int64_t bn0, int sp, int heads, int64_t grp, int *s_last) {
   using E = Elem<DT>;
   typedef float f32x2 __attribute__((ext_vector_type(2)));
-  const bool fused = a.arrive != nullptr;
+  const bool fused = GT <= 4 && a.arrive != nullptr;   // (blocks of eight heads have a launch for it: merges_in_launch)
   int lane = threadIdx.x % kWave;
   asm volatile("" : "+v"(lane));   // a copy of its own: nothing made from it is kept through the tile loops (registers)
   const int wave = uniform(threadIdx.x / kWave);
@@ -595,39 +595,31 @@ __device__ __forceinline__ void block_merge_store(const float *mrg, int wstride,
   __syncthreads();
   if (*s_last == 0) return;
   // Again a head per wave, two channels per lane; lane i also holds piece i's maximum and sum, whose
-  // weight reaches the others through v_readlane.  One trip to memory for all of a wave's heads: the loads go
+  // weight reaches the others through v_readlane.  One trip to memory for all of it: the loads go
   // through a buffer resource that ends with the last piece, so that those of absent pieces return 0
   // (little code matters here as much as few trips).
   constexpr int kRecB = (kD + 2) * 4, kDeviceScope = 16;   // bytes from piece to piece; sc1, the scope of the stores
-  constexpr int NG = (GT + 3) / 4;                         // heads per wave
-  f32x2 ml[NG], av[NG][kFuseMaxSplit];
-#pragma unroll
-  for (int j = 0; j < NG; ++j) {
-    const int g = min(4 * j + wave, heads - 1);
-    const auto rsrc = __builtin_amdgcn_make_buffer_rsrc((void *)uniform_ptr((const char *)(a.ws + (size_t)(bn0 + g) * a.n_split * (kD + 2))),
+  if (wave < heads) {
+    const auto rsrc = __builtin_amdgcn_make_buffer_rsrc((void *)uniform_ptr((const char *)(a.ws + (size_t)(bn0 + wave) * a.n_split * (kD + 2))),
                                                         (short)0, a.n_split * kRecB, kBufferWord3);
     auto load2 = [&](int off) {
       return __builtin_bit_cast(f32x2, __builtin_amdgcn_raw_buffer_load_b64(rsrc, off, 0, kDeviceScope));
     };
-    ml[j] = load2(lane * kRecB);
+    const f32x2 ml = load2(lane * kRecB);
+    f32x2 av[kFuseMaxSplit];
 #pragma unroll
-    for (int i = 0; i < kFuseMaxSplit; ++i) av[j][i] = load2(i * kRecB + 8 + lane * 8);
-  }
-#pragma unroll
-  for (int j = 0; j < NG; ++j) {
-    const int g = 4 * j + wave;
-    if (g >= heads) break;
-    const float m = lane < a.n_split ? ml[j][0] : -INFINITY;
+    for (int i = 0; i < kFuseMaxSplit; ++i) av[i] = load2(i * kRecB + 8 + lane * 8);
+    const float m = lane < a.n_split ? ml[0] : -INFINITY;
     const float wgt = weight(m, wave_max(m));
-    const float Lsum = wave_sum(ml[j][1] * wgt);
+    const float Lsum = wave_sum(ml[1] * wgt);
     float A0 = 0.f, A1 = 0.f;
 #pragma unroll
     for (int i = 0; i < kFuseMaxSplit; ++i) {
       const float wi = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(wgt), i));
-      A0 = fmaf(av[j][i][0], wi, A0);
-      A1 = fmaf(av[j][i][1], wi, A1);
+      A0 = fmaf(av[i][0], wi, A0);
+      A1 = fmaf(av[i][1], wi, A1);
     }
-    store_out((size_t)(bn0 + g), A0, A1, Lsum);
+    store_out((size_t)(bn0 + wave), A0, A1, Lsum);
   }
   if ((int)threadIdx.x < a.n_split)
     __hip_atomic_store(flags + threadIdx.x, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);

@@ -137,7 +137,7 @@ struct EnvSwitches {
   long norm_delay_us;     // THK_PRUNE_NORM_DELAY_US (the same, in front of the query norms), <= 0 = none
   long norm_polls;        // THK_PRUNE_NORM_POLLS (test hook: looks for the query norms), < 0 = unset
   char decode_merge;      // first letter of THK_DECODE_MERGE ('k'ernel: a second launch merges the split
-                          // records, 'f'used: the last block of a head group merges), 0 = unset
+                          // records, 'f'used: the last block of a head group merges where it can), 0 = unset
   char value_compact;     // first letter of THK_VALUE_COMPACT ('f'lat: the plain compaction kernel,
                           // 'b'urst: the one-pass prune kernels with the list given), 0 = unset
 };
