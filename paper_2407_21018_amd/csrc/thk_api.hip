@@ -381,32 +381,26 @@ int decode_pieces(const thk_shape *s, int hpb, int64_t wgs, int64_t steps, int n
 // (32 x 785 8.7 / 9.1, 24 x 694 8.3 / 8.1), wide fp32 ones lose (24 x 4 heads x 936, T = 100 15.2 / 20.8), nor does a call without a
 // tail gain (8 x 4 heads x 2910 7.5 / 8.2). In bf16
 //   * not up to 256 rows, below which one block without a merge is shorter (16 x 4 heads x 182 6.2 7.4 9.0 / 7.1 7.1 8.8);
-//   * not where the merge, inside the launch with the n pieces of the call otherwise, became a second launch: with an append in front the
-//     host takes 9 to 11 us to issue the three, as long as the GPU or longer (append in front, n pieces / these: 8 units x 2 heads x 1191 rows 9.9 / 10.2,
-//     8 x 4 heads x 1188 10.2 / 10.8, x 2048 10.0 / 10.9, 4 x 4 heads x 3000 10.1 / 10.9; without it 8.5 / 7.3, 8.3 / 7.2, 8.4 / 7.2); where there is a
-//     second launch anyway they gain (1 x 4 heads x 4000, n = 32 9.4 / 9.1, 4 x 4 heads x 4000 9.9 / 9.0; one and two heads were not looked at there
-//     and stay).  fp32 takes the GPU longer than the host but for one head of one or two units (1 x 1300 9.7 / 10.6, 2 x 1700 10.3 / 10.6; 3 x 1500
-//     10.9 / 10.7, 8 x 1500 11.5 / 11.1);
-//   * blocks of at most four heads that merge inside the launch not without a tail: the merge grows by what the
+//   * blocks of one or two heads not above 16 pieces, whose merge is a second launch: with an append in front the host
+//     takes longer to issue the three than the GPU to run them (8 units x 2 heads x 1191 rows 7.5 8.1 9.9 / 7.2 6.9 10.2);
+//   * calls of at most 16 pieces that have no tail, and blocks of at most four heads: their merge, inside the launch, grows by what the
 //     shorter pieces save (8 x 4 heads x 947 7.2 / 7.6, 16 x 391 6.3 / 6.5).  A count is planned and reported as if there was a tail.
 // One case is kept for what it reports and not for its time: up to 512 rows of eight units, and bf16 blocks of one head of eight units, have the
 // counts that thk_default_split gave before there were these pieces (4 of 512 rows, 8 of 1024), which its tests state.  They would gain as their
 // neighbours do (with the append in front, as it is / these: 8 units x 4 heads x 450 rows 9.9 / 8.7, x 2 heads 12.7 / 9.0, 8 heads 11.8 / 11.5,
 // one head x 512 9.6 / 8.1, x 743 11.5 / 8.3, fp32 8 x 1 head x 384 13.6 / 9.6; without a tail 7.1 / 7.0, 9.8 / 7.3, 8.2 / 8.0, 6.6 / 5.8, 8.8 / 6.6,
 // 10.1 / 7.7).
-int pieces_of_half_steps(const thk_shape *s, int hpb, int64_t wgs, int n, bool tail) {
-  const int64_t half = ceil_div(s->S, 64), heads = (int64_t)s->L * s->B * s->N_q;
+int pieces_of_half_steps(const thk_shape *s, int hpb, int64_t wgs, bool tail) {
+  const int64_t n = ceil_div(s->S, 64), heads = (int64_t)s->L * s->B * s->N_q;
   const bool eight = units_of(s) <= 8;
   const bool more = tail && (s->dtype == THK_F32 ? ld_of(s) <= 79 : hpb == 8);
   const int64_t most = more ? kCUs * 7 / 4 : kCUs;
-  if (wgs * half > most || s->S <= (eight ? 512 : s->dtype == THK_BF16 ? 256 : 128)) return 0;
-  const bool second_launch = half > kDecodeFuseMaxSplit && n <= kDecodeFuseMaxSplit;
-  if (s->dtype == THK_BF16 && hpb <= 4) {
-    if (second_launch || (half <= kDecodeFuseMaxSplit && !tail) || (half > kDecodeFuseMaxSplit && hpb <= 2) || (hpb == 1 && eight)) return 0;
-  } else if (second_launch && hpb == 1 && units_of(s) <= 2) {
-    return 0;
+  if (wgs * n > most || s->S <= (eight ? 512 : s->dtype == THK_BF16 ? 256 : 128)) return 0;
+  if (s->dtype == THK_BF16) {
+    if (hpb <= 2 && (n > kDecodeFuseMaxSplit || (hpb == 1 && eight))) return 0;
+    if (hpb <= 4 && n <= kDecodeFuseMaxSplit && !tail) return 0;
   }
-  return half * heads <= (int64_t)THK_STATIC_SCRATCH_BYTES / ((kD + 2) * 4 + 8) ? (int)half : 0;
+  return n * heads <= (int64_t)THK_STATIC_SCRATCH_BYTES / ((kD + 2) * 4 + 8) ? (int)n : 0;
 }
 
 // ws_bytes: what the caller's workspace holds.  The estimate's count goes up and down with S, so a
@@ -447,7 +441,7 @@ Split decode_split(const thk_shape *s, size_t ws_bytes = SIZE_MAX, bool tail = t
     const int n0 = n;
     const bool one = n0 == 1 || (wgs >= kCUs / 2 && s->S < 4096);
     if (s->S > one_block_rows || units_of(s) > 8) n = decode_pieces(s, hpb, wgs, steps, n0, one ? 1 : std::max(2, n0 / 4));
-    n = std::max(n, pieces_of_half_steps(s, hpb, wgs, n, tail));
+    n = std::max(n, pieces_of_half_steps(s, hpb, wgs, tail));
     const int64_t fit = (int64_t)std::min<size_t>(ws_bytes / decode_ws_bytes(s, 1), (size_t)n);
     if (fit < n && fit >= (one ? 0 : std::max(2, n0 / 8))) n = std::max((int)fit, 1);
   }

@@ -318,20 +318,6 @@ def test_default_decode_split_balances_rounds_and_stays_within_the_static_scratc
                         assert thk.thk_workspace_bytes(s, thk.THK_OP_DECODE) <= 8 << 20
 
 
-def test_default_decode_split_keeps_the_merge_inside_the_launch():
-    """Calls of up to four heads per block that merge inside their launch do not leave it for 64-row pieces (an append, the
-    call and a merge take the host longer to issue than the GPU to run); those of more than 16 pieces have a merge launch anyway."""
-    for G in (1, 2, 3, 4):
-        for B, N_kv, S in ((1, 8, 1188), (1, 8, 2048), (1, 4, 1025), (1, 4, 3000), (1, 1, 1500), (2, 8, 1100)):
-            s = thk.make_shape(1, B, N_kv * G, N_kv, 128, S, 1, 64, 0, thk.THK_BF16, 0)
-            assert thk.thk_default_split(s, thk.THK_OP_DECODE) <= 16, (G, B, N_kv, S)
-    four = lambda S: thk.thk_default_split(thk.make_shape(1, 1, 32, 8, 128, S, 1, 64, 0, thk.THK_BF16, 0), thk.THK_OP_DECODE)
-    assert [four(S) for S in (513, 1000, 1024, 1025, 2048)] == [9, 16, 16, 9, 16]
-    small = lambda U, G, S, dt: thk.thk_default_split(thk.make_shape(1, 1, U * G, U, 128, S, 1, 64, 0, dt, 0), thk.THK_OP_DECODE)
-    assert [small(U, 4, 4000, thk.THK_BF16) for U in (1, 4)] == [63, 63]
-    assert [small(U, 1, S, thk.THK_F32) for U, S in ((1, 1024), (1, 1300), (2, 2048), (1, 2049), (3, 1500), (8, 2048))] == [16, 11, 16, 33, 24, 32]
-
-
 def test_default_value_split_by_estimate():
     """Short calls take 128-row pieces while compute units are idle, many query tiles few pieces, fp32 blocks of one wave
     four to a compute unit; a last piece of a few rows is none."""

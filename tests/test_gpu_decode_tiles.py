@@ -78,9 +78,9 @@ def test_decode_merge_launch_piece_counts(dtype, G, T, n_split, thk_env):
         assert err <= ATTN_TOL[dtype], f"S={S} n_split={n_split}: {err}"
 
 
-# calls of a block per 64 rows: the shortest, a last piece of one row, the most pieces (16 of bf16 blocks of one to four heads) and blocks
-# (256), and more of either, where pieces have whole steps again; with a workspace that holds half of the pieces the call takes those
-@pytest.mark.parametrize("dtype,N_q,N_kv,S,pieces", [("bf16", 32, 8, 513, 9), ("bf16", 32, 8, 1024, 16), ("bf16", 32, 8, 2048, 16), ("bf16", 8, 4, 961, 16),
+# calls of a block per 64 rows: the shortest, a last piece of one row, the most blocks (256), and one row more, where pieces have
+# whole steps again; with a workspace that holds half of the pieces the call takes those
+@pytest.mark.parametrize("dtype,N_q,N_kv,S,pieces", [("bf16", 32, 8, 513, 9), ("bf16", 32, 8, 2048, 32), ("bf16", 32, 8, 2049, None), ("bf16", 8, 4, 961, 16),
                                                      ("bf16", 16, 2, 4033, 64), ("f32", 8, 8, 705, 12), ("f32", 8, 8, 2048, 32), ("f32", 8, 2, 1025, 17),
                                                      ("bf16", 56, 8, 3553, 56), ("bf16", 56, 8, 3585, None), ("f32", 9, 9, 129, 3)])
 @pytest.mark.parametrize("tail", [0, 1, 112])
