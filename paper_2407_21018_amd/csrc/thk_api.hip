@@ -382,7 +382,12 @@ int decode_pieces(const thk_shape *s, int hpb, int64_t wgs, int64_t steps, int n
 // tail gain (8 x 4 heads x 2910 7.5 / 8.2). In bf16
 //   * not up to 256 rows, below which one block without a merge is shorter (16 x 4 heads x 182 6.2 7.4 9.0 / 7.1 7.1 8.8);
 //   * blocks of one or two heads not above 16 pieces, whose merge is a second launch: with an append in front the host
-//     takes longer to issue the three than the GPU to run them (8 units x 2 heads x 1191 rows 7.5 8.1 9.9 / 7.2 6.9 10.2);
+//     takes longer to issue the three than the GPU to run them (8 units x 2 heads x 1191 rows 7.5 8.1 9.9 / 7.2 6.9 10.2).  Blocks of four heads
+//     do go on: their calls of 1025 to 2048 rows of eight units, 4096 of four and fewer, merged in the launch with whole steps and gain more
+//     (8 x 4 heads x 1188 7.8 8.5 / 7.3 7.3, x 2048 7.4 8.3 / 6.9 7.2, 4 x 4 x 3000 8.1 8.4 / 6.9 7.2), so the host decides with the append in
+//     front: it issues the three in 9.0 us in most processes and in 10.9 in others (three and two of five, medians), which is what they
+//     take then: 8 x 4 heads x 1188 9.7 / 9.1 or 10.9, 4 x 4 x 3000 9.9 / 9.1 or 10.9, 1 x 4 x 1188 9.4 / 9.0 or 10.7, 1 x 4 x 1500 8.8 / 9.0 or
+//     10.7, fp32 1 x 1 head x 1300 10.2 / 8.9 or 10.8;
 //   * calls of at most 16 pieces that have no tail, and blocks of at most four heads: their merge, inside the launch, grows by what the
 //     shorter pieces save (8 x 4 heads x 947 7.2 / 7.6, 16 x 391 6.3 / 6.5).  A count is planned and reported as if there was a tail.
 // One case is kept for what it reports and not for its time: up to 512 rows of eight units, and bf16 blocks of one head of eight units, have the
