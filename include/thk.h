@@ -129,7 +129,8 @@ int32_t thk_keep_count(int32_t D, double lambda);
 size_t thk_workspace_bytes(const thk_shape *shape, int32_t op);
 
 /* The n_split the library would use for `op` when shape->n_split == 0 (THK_OP_DECODE: for a call
- * with rows in the tail; short bf16 calls without any may take fewer, longer pieces). */
+ * with rows in the tail; short calls without any, of either element type, may take fewer, longer
+ * pieces). */
 int32_t thk_default_split(const thk_shape *shape, int32_t op);
 
 /* How thk_prune would run `shape`: 2 = one launch that keeps the rows on chip between the

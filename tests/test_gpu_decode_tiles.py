@@ -78,11 +78,12 @@ def test_decode_merge_launch_piece_counts(dtype, G, T, n_split, thk_env):
         assert err <= ATTN_TOL[dtype], f"S={S} n_split={n_split}: {err}"
 
 
-# calls of a block per 64 rows: the shortest, a last piece of one row, the most blocks (256), and one row more, where pieces have
-# whole steps again; with a workspace that holds half of the pieces the call takes those
+# calls of a block per 64 rows: the shortest, a last piece of one row, the most blocks (256; of eight heads and of fp32 in narrow rows 448,
+# which only calls with a tail take), and one row more, where pieces have whole steps again; with a workspace that holds half of the
+# pieces the call takes those
 @pytest.mark.parametrize("dtype,N_q,N_kv,S,pieces", [("bf16", 32, 8, 513, 9), ("bf16", 32, 8, 2048, 32), ("bf16", 32, 8, 2049, None), ("bf16", 8, 4, 961, 16),
                                                      ("bf16", 16, 2, 4033, 64), ("f32", 8, 8, 705, 12), ("f32", 8, 8, 2048, 32), ("f32", 8, 2, 1025, 17),
-                                                     ("bf16", 56, 8, 3553, 56), ("bf16", 56, 8, 3585, None), ("f32", 9, 9, 129, 3)])
+                                                     ("bf16", 56, 8, 3553, 56), ("bf16", 56, 8, 3585, None), ("f32", 9, 9, 129, 3), ("f32", 8, 8, 2779, 44), ("f32", 8, 8, 3585, None)])
 @pytest.mark.parametrize("tail", [0, 1, 112])
 def test_decode_pieces_of_half_steps(dtype, N_q, N_kv, S, pieces, tail):
     T, G = 76, N_q // N_kv
