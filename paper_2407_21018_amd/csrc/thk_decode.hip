@@ -27,6 +27,7 @@ hipError_t decode_mq_launch(const DecodeArgs &, hipStream_t);
 // whose weight reaches the other lanes through v_readlane.  Latency bounds it: the maxima, the sums and the
 // accumulators of a wave's 16 pieces are one trip to memory, absent pieces read 0 past the end of the buffer
 // and weigh nothing, and the waves' states meet in LDS once, in wave order (the result does not depend on timing).
+// (A weight below 2^-126 is 0, as in the tiles, where the library's exp2 kept a denormal.)
 // Before, a block asked for the maxima, then for eight accumulators at a time, and for those past a multiple of eight
 // one by one.  Whole calls, us, before / now: 4 units x 8 heads x 8000 rows (63 pieces) 11.6 / 9.5, fp32 8 x 9000 (29)
 // 15.6 / 13.4, 8 x 4 heads x 131072 (64) 64.2 / 63.3, 64 x 4 heads x 32768 (16) 123.4 / 122.0, 64 x 8 heads x 8191, pruned
