@@ -341,10 +341,13 @@ __global__ __launch_bounds__(256, 2) void k_value_attn_bf16(ValueAttnArgs a) {
 //     rows), of value row r at c ^ ((r & 3) << 2) (a transposing read takes 64 bytes of 4 rows);
 //   * the next sub-tile's logits are computed in front of this one's softmax, in straight-line code,
 //     so that matrix and vector instructions of one wave run side by side.
-// Matrix and vector instructions bound it, one after the other: of the 417000 cycles a compute unit is busy with 64 units x 32768
-// rows x 128 query rows a SIMD multiplies for 197000 and calculates for 204000, the LDS takes 16 %, without conflicts, and the clock is
-// 1.7 to 2.0 GHz (2.4 in the copy kernel of the same run).  Fewer instructions shorten it, fewer waits do not: operands read a
-// sub-tile ahead measured 2-3 % longer, a higher priority for one of a SIMD's two waves, or waves 4 .. 7 half a step behind, the same.
+// Two thirds of its time are instructions: of the 417000 cycles a compute unit is busy with 64 units x 32768 rows x 128 query rows a SIMD
+// multiplies for 197000 (6144 products) and issues 40500 vector instructions, 6.6 a product.  A loop of such a mix, two waves a SIMD
+// (a product of 32 cycles, six multiply-adds of 2.7, an exponential of 9.8), takes 44.6 cycles a product, for about 14 cycles of vector
+// instructions run beside one: 274000.  The other third is waiting, for operands from LDS and at a chunk's barriers; the LDS
+// is in use for 16 %, without conflicts.  206 GFLOP issued at 0.91 PFLOP/s, where a large product sustains 1.2 on this card; the clock
+// is 1.7 to 2.0 GHz (2.4 in the copy kernel of the same run).  Operands read a sub-tile ahead measured 2-3 %
+// longer, a higher priority for one of a SIMD's two waves, or waves 4 .. 7 half a step behind, the same.
 // 64 units x 32768 rows, G = 4, S_obs = 32: 300 -> 277 us; 8 units x 131072 rows, S_obs = 64: 279 -> 237;
 // 32 units x 16384 rows, G = 8: 150 -> 131 us (score calls, before: the kernel above with QT = 4).
 constexpr int kWideRows = 128;                    // rows per chunk
