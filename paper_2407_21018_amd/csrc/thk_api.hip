@@ -390,7 +390,7 @@ int decode_pieces(const thk_shape *s, int hpb, int64_t wgs, int64_t steps, int n
 //     10.7, fp32 1 x 1 head x 1300 10.2 / 8.9 or 10.8;
 //   * calls of at most 16 pieces that have no tail, and blocks of at most four heads: their merge, inside the launch, grows by what the
 //     shorter pieces save (8 x 4 heads x 947 7.2 / 7.6, 16 x 391 6.3 / 6.5).  A count is planned and reported as if there was a tail.
-// One case is kept for what it reports and not for its time: up to 512 rows of eight units, and bf16 blocks of one head of eight units, have the
+// One case is kept for what it reports and not for its time: up to 512 rows of eight units, and in bf16 blocks of one head of eight units, have the
 // counts that thk_default_split gave before there were these pieces (4 of 512 rows, 8 of 1024), which its tests state.  They would gain as their
 // neighbours do (with the append in front, as it is / these: 8 units x 4 heads x 450 rows 9.9 / 8.7, x 2 heads 12.7 / 9.0, 8 heads 11.8 / 11.5,
 // one head x 512 9.6 / 8.1, x 743 11.5 / 8.3, fp32 8 x 1 head x 384 13.6 / 9.6; without a tail 7.1 / 7.0, 9.8 / 7.3, 8.2 / 8.0, 6.6 / 5.8, 8.8 / 6.6,
@@ -588,7 +588,10 @@ Split value_cut(const thk_shape *s, int n) {
 //     t0 + chunks of a piece * max(t_own, l t_shared)  +  records (t_rec each, 1.4 where the merge has more than eight)
 // t_own: a chunk of a block by itself; t_shared: what each resident block adds.  Fitted per kernel (32-row query tiles a block
 // carries; fp32 blocks of two are left out) to 160 random bf16 and 110 fp32 shapes at up to ten piece counts each, within 4.4 %; the count taken costs 0.9 and
-// 1.0 % more than the best one on average, n0 5.9 and 7.6 %.  What it knows that n0 does not: short calls are as long as a piece, and
+// 1.0 % more than the best one on average, n0 5.9 and 7.6 %.  The margin is no larger than the fit's error, so what decides is the trial: 110
+// random value prunes of other shapes, with all that changed beside the counts, bf16 of one, two, more query tiles 1.15, 1.13, 1.10 times as
+// fast, fp32 of one or four tiles a block 1.43, of two (not planned here) 1.05; the least 0.995 and 0.998.  Host time of a plan
+// (thk_prune_value makes two) 0.0-0.2 us before, 0.1-0.3 and up to 0.7 (131072 rows) with it.  What it knows that n0 does not: short calls are as long as a piece, and
 // 128-row pieces use idle compute units (16 units x 311 rows 18.8 -> 16.0 us, 8 x 8 heads x 897 29.8 -> 26.8); the records of
 // many query tiles (16 units x 8 heads x 7007 rows 14 pieces 64.0, 8 53.6); fp32 blocks of one wave are four to a compute
 // unit (24 units x 17810 rows 20 pieces 214, 70 178).
