@@ -75,6 +75,7 @@ def prune_launch(request, thk_env):
 @pytest.fixture(params=["kernel", "fused"])
 def decode_merge(request, thk_env):
     """Both ways of merging the split records of a decode call with at most 16 pieces: a second
-    launch, or the last block of every head group inside the one launch."""
+    launch, or the last block of every head group inside the one launch (blocks of up to four
+    heads; those of eight have the second launch either way)."""
     thk_env.setenv("THK_DECODE_MERGE", request.param)
     return request.param
